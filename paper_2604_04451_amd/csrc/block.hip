@@ -5,6 +5,7 @@
 
 #include "chorus_ops.h"
 #include "common.h"
+#include "gemm.h"
 
 namespace chorus {
 namespace {
@@ -57,6 +58,7 @@ struct BlockWs {
   uint16_t* kc;     // [H, LtPad, dh]
   uint16_t* vct;    // [D, LtPad]
   size_t bytes;
+  GemmParts ffn_parts;  // what the second FFN product may use for slices of K: h and ao, and everything behind the FFN hidden
 };
 
 inline long pad_rows(long L) { return (long)align_up((size_t)L, 256); }
@@ -88,6 +90,7 @@ BlockWs carve(const chorus_block_shape& sh, long Ls, void* base) {
   w.kc = take(LtPad * D);
   w.vct = take(LtPad * D);
   w.bytes = off;
+  w.ffn_parts = GemmParts{w.h, a0, p + a0 + ffn_bytes, w.bytes - a0 - ffn_bytes};
   return w;
 }
 
@@ -265,7 +268,8 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   {
     ProfScope p(CHORUS_PROF_GEMM, s);
     CHK(chorus_gemm_bf16(b.h, w->w_1, Ls, F, D, CHORUS_EPI_GELU_BF16, b.ffn, w->b_1, nullptr, nullptr, 1.f, stream));
-    CHK(chorus_gemm_bf16(b.ffn, w->w_2, Ls, D, F, CHORUS_EPI_RESID, x, w->b_2, row(tab, 5), row(t_mod, 5), 1.f, stream));
+    CHK(gemm_bf16_parts(b.ffn, w->w_2, Ls, D, F, CHORUS_EPI_RESID, x, w->b_2, row(tab, 5), row(t_mod, 5), 1.f, b.ffn_parts,
+                        stream));
   }
   return CHORUS_OK;
 }

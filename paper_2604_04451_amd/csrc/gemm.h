@@ -1,0 +1,23 @@
+// The GEMM as the library's own callers use it: chorus_gemm_bf16 with optional scratch, with which a gated-residual
+// product that would leave most compute units idle is cut into slices of K.
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+namespace chorus {
+
+// Two pieces of scratch (16-byte aligned device memory, either may be empty), used only by the kernels of the call.
+// Every slice but the last puts its fp32 [M, N] result there: the first one into `first`, the others into `rest`.
+struct GemmParts {
+  void* first;
+  size_t first_bytes;
+  void* rest;
+  size_t rest_bytes;
+};
+
+// chorus_gemm_bf16 with scratch; the number of slices depends on the sizes given here and on nothing else
+int32_t gemm_bf16_parts(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, int32_t epilogue, void* out,
+                        const float* bias, const float* gate0, const float* gate1, float scale, const GemmParts& parts,
+                        void* stream);
+
+}  // namespace chorus

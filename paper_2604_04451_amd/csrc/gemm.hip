@@ -9,11 +9,17 @@
 // column operand, so lane l of a 32x32 accumulator holds ONE output row m = l%32 and the 16
 // output columns n = 4*(l/32) + 8*g + e (register 4g+e): four consecutive columns per
 // register group, which the epilogue moves as one 8-byte (bf16) or 16-byte (fp32) access.
+#include <cmath>
+
 #include "chorus_ops.h"
 #include "common.h"
+#include "gemm.h"
 
 namespace chorus {
 namespace {
+
+// s_waitcnt operand that waits for at most n vector memory operations in flight and for nothing else
+constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 
 constexpr int BK = 64;
 constexpr int LS = BK + 8;  // LDS row stride in elements
@@ -33,6 +39,15 @@ struct EpiArgs {
   const float* gate0;
   const float* gate1;
   float scale;
+};
+
+// where the slices of K but the last leave their [M, N] results
+struct PartPtrs {
+  float* first;
+  float* rest;
+  __device__ __forceinline__ float* of(int slice, long M, int N) const {
+    return slice == 0 ? first : rest + (size_t)(slice - 1) * M * N;
+  }
 };
 
 
@@ -320,7 +335,11 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const uint16_t* __res
 // a new home, at the price of several hundred accumulator moves per k-step.
 // ---------------------------------------------------------------------------
 
-// WB = 16 x 16 blocks along each side of a wave's quadrant: 8 (256 x 256 tiles) or 4 (128 x 128 tiles).
+// WB = 16 x 16 blocks along each side of a wave's quadrant: 8 (256 x 256 tiles), 4 (128 x 128) or 2 (64 x 64).
+// NST = stages in LDS: a step's loads are issued NST - 1 half-steps and more before its barrier. Two stages leave room for
+// two 128 x 128 workgroups on a compute unit, which then hide each other's waits; a launch with fewer tiles than units has
+// no second workgroup there, and three stages (96 KB) take its place: 1200 x 1536 x 8960 113 -> 72 us. Four or five
+// stages measured the same (73, 71 us): from three on the unit's L1, not the distance, sets the rate.
 //
 // bf16 (optionally GELU) epilogue of the 16x16 layout: 32 output rows at a time go through a private LDS region as
 // [32][16 WB] bf16 (row stride 16 WB + 8), then leave as full row segments of the quadrant (256 or 128 bytes).
@@ -456,10 +475,25 @@ __device__ __forceinline__ void gemm16_finish(f32x4 (&acc)[8][8], const EpiArgs&
   }
 }
 
-template <int EPI, int WB>
+// waits until at most min(steps, MOST) k-steps of this wave's loads (NS each) are in flight; steps is uniform
+template <int MOST, int NS>
+__device__ __forceinline__ void wait_steps(int steps) {
+  if constexpr (MOST <= 0) {
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+  } else {
+    if (steps >= MOST)
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(MOST * NS));
+    else
+      wait_steps<MOST - 1, NS>(steps);
+  }
+}
+
+template <int EPI, int WB, int NST>
 __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
-                                                          long M, int N, int K, EpiArgs ep, int tiles_m, int tiles_n) {
-  static_assert(WB == 8 || WB == 4, "quadrants of 8 x 8 or 4 x 4 blocks");
+                                                          long M, int N, int K, EpiArgs ep, PartPtrs parts, int tiles_m,
+                                                          int tiles_n) {
+  static_assert(WB == 8 || WB == 4 || WB == 2, "quadrants of 8 x 8, 4 x 4 or 2 x 2 blocks");
+  static_assert(NST >= 2 && NST <= 8 && 2 * WB * (NST - 1) < 64, "the loads in flight must fit the wait counter");
   constexpr int BM = 32 * WB, BN = 32 * WB;
   constexpr int WT = 16 * WB;  // rows and columns of a wave's quadrant
   constexpr int GM = 8;
@@ -467,8 +501,16 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[];
   uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
 
+  // The grid holds gridDim.x / ntiles slices of K of as many steps as can be (never none: the host asks for no more
+  // slices than steps), all tiles of a slice together. The last slice runs the epilogue, the others leave their plain fp32 result in `parts`; without a
+  // split there is one slice.
   const int ntiles = tiles_m * tiles_n;
-  const int tile = xcd_remap(blockIdx.x, ntiles);
+  const int nslices = gridDim.x / ntiles, slice = blockIdx.x / ntiles;
+  const int tile = xcd_remap(blockIdx.x - slice * ntiles, ntiles);
+  const int k_first = slice * (K / BK) / nslices;
+  const int KTN = (slice + 1) * (K / BK) / nslices - k_first;
+  A += (long)k_first * BK;
+  W += (long)k_first * BK;
   const int per_group = GM * tiles_n;
   const int group = tile / per_group;
   const int first_m = group * GM;
@@ -565,9 +607,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
   // the wave index is kept in a scalar register so that the LDS address of a load costs no vector instruction.
   constexpr int NS = 2 * WB;              // slots of a half-step = fragments of a half-step = loads of a k-step
   constexpr int MPS = WB / 2;             // MFMAs of a slot
-  constexpr int kReadSlots = 3 * WB / 2;  // 12 of 16 (6 of 8)
-  const int KTN = K / BK;
-  auto clampk = [&](int k) { return k < KTN ? k : KTN - 1; };  // past the end: re-fetch the last tile into an idle stage
+  constexpr int kReadSlots = 3 * WB / 2;  // 12 of 16 (6 of 8, 3 of 4)
   // reads of slot f: one fragment, two in the first NS - kReadSlots slots (which = 0: the first, 1: the second)
   auto read_of_slot = [&](const uint16_t* stg, int h, int set, int f, int which) {
     constexpr int kDouble = NS - kReadSlots;
@@ -576,23 +616,30 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
     else if (f < kReadSlots && which == 0)
       read_frag(stg, h, set, frag_order(f + kDouble));
   };
-  issue(0, 0, 0, NS);
-  issue(clampk(1), 1, 0, NS);
-  // vmcnt(NS): the first step's pieces are in LDS, the second step's may be in flight
-  if constexpr (WB == 8)
-    __builtin_amdgcn_s_waitcnt(0x4F70);
+  // With two stages the loads of a step past the end fetch the last tile again into an idle stage (no branch in the
+  // loop); with more stages there would be several such steps, so they are left out.
+  constexpr bool kClamp = NST == 2;
+#pragma unroll
+  for (int j = 0; j < NST; ++j)
+    if (kClamp || j < KTN) issue(j < KTN ? j : KTN - 1, j, 0, NS);
+  // the first step's pieces are in LDS, the later ones may be in flight
+  if (kClamp || KTN >= NST)
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 1) * NS));
   else
-    __builtin_amdgcn_s_waitcnt(0x0F78);
+    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
   lds_barrier();
   __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
   for (int f = 0; f < NS; ++f) read_frag(smem, 0, 0, frag_order(f));
   __builtin_amdgcn_sched_barrier(0);
 
+  int stage = 0;
   for (int kt = 0; kt < KTN; ++kt) {
-    const uint16_t* st = smem + (kt & 1) * STAGE;
-    const uint16_t* stn = smem + ((kt + 1) & 1) * STAGE;
-    const int k2 = clampk(kt + 2);
+    const int next = stage + 1 < NST ? stage + 1 : 0;
+    const uint16_t* st = smem + stage * STAGE;
+    const uint16_t* stn = smem + next * STAGE;
+    const bool more = kt + NST < KTN;
+    const int k2 = more ? kt + NST : KTN - 1;
     // ---- half-step 0: WB^2 MFMAs and the fragment reads of half-step 1
 #pragma unroll
     for (int f = 0; f < NS; ++f) {
@@ -600,61 +647,72 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
       __builtin_amdgcn_sched_barrier(0);
       read_of_slot(st, 1, 1, f, 0);
       __builtin_amdgcn_sched_barrier(0);
-      mfmas(0, MPS * f + 1, MPS * f + 2);
+      if constexpr (MPS > 1) mfmas(0, MPS * f + 1, MPS * f + 2);
       __builtin_amdgcn_sched_barrier(0);
       read_of_slot(st, 1, 1, f, 1);
       __builtin_amdgcn_sched_barrier(0);
       mfmas(0, MPS * f + 2, MPS * f + MPS);
       __builtin_amdgcn_sched_barrier(0);
     }
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's pieces of step kt+1 are in LDS
-    lds_barrier();                       // every wave has all its fragments of this stage in registers
+    // this wave's pieces of step kt + 1 are in LDS: the steps requested behind it, at most up to the last one, may be in flight
+    wait_steps<NST - 2, NS>(KTN - 2 - kt);
+    lds_barrier();  // every wave has all its fragments of this stage in registers
     __builtin_amdgcn_sched_barrier(0);
-    // ---- half-step 1: WB^2 MFMAs, the next step's first-half fragments, the loads of step kt+2 into the stage just freed
+    // ---- half-step 1: WB^2 MFMAs, the next step's first-half fragments, the loads of step kt + NST into the stage just freed
 #pragma unroll
     for (int f = 0; f < NS; ++f) {
       mfmas(1, MPS * f, MPS * f + 1);
       __builtin_amdgcn_sched_barrier(0);
       read_of_slot(stn, 0, 0, f, 0);
       __builtin_amdgcn_sched_barrier(0);
-      mfmas(1, MPS * f + 1, MPS * f + 2);
+      if constexpr (MPS > 1) mfmas(1, MPS * f + 1, MPS * f + 2);
       __builtin_amdgcn_sched_barrier(0);
       read_of_slot(stn, 0, 0, f, 1);
       __builtin_amdgcn_sched_barrier(0);
-      mfmas(1, MPS * f + 2, MPS * f + MPS - 1);  // (none for the small tile)
+      mfmas(1, MPS * f + 2, MPS * f + MPS - 1);  // (none for the small tiles)
       __builtin_amdgcn_sched_barrier(0);
-      issue(k2, kt & 1, f, f + 1);
+      if (kClamp || more) issue(k2, stage, f, f + 1);
       __builtin_amdgcn_sched_barrier(0);
       if constexpr (MPS > 2) mfmas(1, MPS * f + MPS - 1, MPS * f + MPS);
       __builtin_amdgcn_sched_barrier(0);
     }
+    stage = next;
   }
 
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the look-ahead loads of the last step have landed
+  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // no direct load may land in the staging regions of the epilogue
   // The compiler does not know the assembly above for MFMAs and so keeps no distance between the last of them and the
   // first instruction that reads an accumulator: cover the longest such distance explicitly. The wait is tied to the
   // accumulators of the last four MFMAs (operands of the statement), so that no copy or spill of one of them can be
   // placed in front of it; every other accumulator was written at least four MFMAs earlier.
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15"
-               : "+a"(acc[WB - 1][WB - 1]), "+a"(acc[WB - 1][WB - 2]), "+a"(acc[WB - 1][WB - 3]), "+a"(acc[WB - 1][WB - 4]));
+               : "+a"(acc[WB - 1][WB - 1]), "+a"(acc[WB - 1][WB - 2]), "+a"(acc[WB > 2 ? WB - 1 : 0][WB > 2 ? WB - 3 : 1]),
+                 "+a"(acc[WB > 2 ? WB - 1 : 0][WB > 2 ? WB - 4 : 0]));
   lds_barrier();  // the staging regions of the epilogue overlay the operand stages
+  if constexpr (EPI == CHORUS_EPI_RESID) {
+    if (slice + 1 < nslices) {
+      const EpiArgs plain{parts.of(slice, M, N), nullptr, nullptr, nullptr, 1.f};
+      gemm16_finish<CHORUS_EPI_F32, WB>(acc, plain, smem_raw, wave, wm, wn, m0, n0, M, N, lane);
+      return;
+    }
+  }
   gemm16_finish<EPI, WB>(acc, ep, smem_raw, wave, wm, wn, m0, n0, M, N, lane);
 }
 
-template <int WB>
-int32_t launch_gemm_w16(const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, EpiArgs ep, hipStream_t s) {
-  constexpr int T = 32 * WB;  // tile side: 256 or 128
+template <int WB, int NST>
+int32_t launch_gemm_w16(const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, EpiArgs ep, hipStream_t s,
+                        int slices, const PartPtrs& parts) {
+  constexpr int T = 32 * WB;  // tile side: 256, 128 or 64
   long tm = (M + T - 1) / T;
   int tn = (N + T - 1) / T;
-  if (tm * tn > 0x7fffffffL) return CHORUS_E_SHAPE;
-  dim3 grid((unsigned)(tm * tn)), block(256);
-  const size_t smem = 2 * (T + T) * BK * sizeof(uint16_t);  // 128 KB (64 KB)
+  if (tm * tn * slices > 0x7fffffffL) return CHORUS_E_SHAPE;
+  dim3 grid((unsigned)(tm * tn * slices)), block(256);
+  const size_t smem = NST * (T + T) * BK * sizeof(uint16_t);
 #define GEMM_W16(E)                                                                             \
   {                                                                                             \
-    auto kern = gemm_w16_kernel<E, WB>;                                                         \
+    auto kern = gemm_w16_kernel<E, WB, NST>;                                                         \
     static DynLdsOnce once;                                                                     \
     CHK_STATUS(once.ensure(reinterpret_cast<const void*>(kern), (int)smem));                    \
-    hipLaunchKernelGGL(kern, grid, block, smem, s, A, W, M, N, K, ep, (int)tm, tn);             \
+    hipLaunchKernelGGL(kern, grid, block, smem, s, A, W, M, N, K, ep, parts, (int)tm, tn);  \
   }
   switch (epi) {
     case CHORUS_EPI_BF16: GEMM_W16(CHORUS_EPI_BF16); break;
@@ -664,6 +722,42 @@ int32_t launch_gemm_w16(const uint16_t* A, const uint16_t* W, long M, int N, int
     default: return CHORUS_E_ARG;
   }
 #undef GEMM_W16
+  CHORUS_LAUNCH_CHECK();
+  return CHORUS_OK;
+}
+
+// What the last slice of K left out: out[m][n] += gate[n] scale sum_s part_s[m][n], P parts in ascending order (the bias
+// went in with the last slice).
+template <int P>
+__global__ __launch_bounds__(256) void gemm_add_parts_kernel(PartPtrs parts, long M, int N, EpiArgs ep) {
+  const long n4 = N / 4, i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= M * n4) return;
+  const int n = (int)(i % n4) * 4;
+  f32x4 p[P];
+#pragma unroll
+  for (int k = 0; k < P; ++k) p[k] = *reinterpret_cast<const f32x4*>(parts.of(k, M, N) + i * 4);
+  f32x4* o = reinterpret_cast<f32x4*>(reinterpret_cast<float*>(ep.out) + i * 4);
+  const f32x4 cur = *o;
+  f32x4 gate = {1.f, 1.f, 1.f, 1.f};
+  if (ep.gate0 || ep.gate1) {
+    gate = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (ep.gate0) gate += *reinterpret_cast<const f32x4*>(ep.gate0 + n);
+    if (ep.gate1) gate += *reinterpret_cast<const f32x4*>(ep.gate1 + n);
+  }
+  gate *= ep.scale;
+#pragma unroll
+  for (int k = 1; k < P; ++k) p[0] += p[k];
+  *o = cur + gate * p[0];
+}
+
+int32_t launch_add_parts(const PartPtrs& parts, int slices, long M, int N, const EpiArgs& ep, hipStream_t s) {
+  const dim3 grid((unsigned)((M * (N / 4) + 255) / 256));
+  switch (slices) {
+    case 2: hipLaunchKernelGGL(gemm_add_parts_kernel<1>, grid, dim3(256), 0, s, parts, M, N, ep); break;
+    case 3: hipLaunchKernelGGL(gemm_add_parts_kernel<2>, grid, dim3(256), 0, s, parts, M, N, ep); break;
+    case 4: hipLaunchKernelGGL(gemm_add_parts_kernel<3>, grid, dim3(256), 0, s, parts, M, N, ep); break;
+    default: return CHORUS_E_ARG;
+  }
   CHORUS_LAUNCH_CHECK();
   return CHORUS_OK;
 }
@@ -688,7 +782,137 @@ int32_t launch_gemm(const uint16_t* A, const uint16_t* W, long M, int N, int K, 
   return CHORUS_OK;
 }
 
+// ---------------------------------------------------------------------------
+// Which tile, and in how many slices of K. The estimated time of each direct-to-LDS kernel in microseconds, from fits
+// to measurements on this chip with activations in the last-level cache and weights cold, as a request finds them
+// (K from 64 to 13824, N from 64 to 15360, M from 64 to 32760; figures in brackets: K = 1536 / K = 8960 where N = 1536).
+// What bounds a launch that does not fill the chip is the rate at which ONE compute unit gets operands: its L1 holds
+// 256 lines in flight, 32 KB, so a unit takes in about 60 KB per microsecond whatever the kernel does, and the launch
+// that spreads the same problem over more units wins: smaller tiles, or slices of K.
+//   256 x 256  one workgroup per unit, rounds of 256; a partly filled round is up to a quarter faster [39 / 190 us]
+//   128 x 128  two stages, two workgroups per unit: one round of up to 256 tiles [21 / 115], then rounds of 512 [27 / 145]
+//   128 x 128  three stages, one workgroup per unit: up to 256 tiles [17 / 75]
+//   64 x 64    four stages, two workgroups per unit: up to 256 tiles [9.7 / 40], growing with the tiles beyond
+// ---------------------------------------------------------------------------
+enum Tile { kTile256, kTile128, kTile128Deep, kTile64, kTiles };
+constexpr int kTileSide[kTiles] = {256, 128, 128, 64};
+constexpr int kMaxSlices = 4;  // more slices than this were never the fastest
+
+double tile_time(int tile, long m, int N, int K, int epi, int slices) {
+  const long side = kTileSide[tile];
+  const double steps = (double)((K / BK + slices - 1) / slices);
+  const double w = (double)(((m + side - 1) / side) * ((N + side - 1) / side) * slices);
+  const bool f32_out = slices == 1 && (epi == CHORUS_EPI_F32 || epi == CHORUS_EPI_RESID);
+  switch (tile) {
+    case kTile256: {
+      const double full = (f32_out ? 14.0 : epi == CHORUS_EPI_GELU_BF16 ? 4.0 : 2.0) + 1.65 * steps;
+      const double rounds = floor(w / 256.0), fill = w / 256.0 - rounds;
+      return full * (rounds + (fill > 0.0 ? 0.76 + 0.24 * fill * fill : 0.0));
+    }
+    case kTile128: {
+      const double one = (f32_out ? 5.0 : 2.0) + 0.74 * steps, round512 = (f32_out ? 4.5 : 0.5) + 1.005 * steps;
+      if (w <= 256.0) return one;
+      if (w <= 512.0) return one + (w - 256.0) / 256.0 * fmax(round512 - one, 0.0);
+      return ceil(w / 512.0) * round512;
+    }
+    case kTile128Deep:
+      return w <= 256.0 ? (f32_out ? 5.0 : 4.0) + 0.5 * steps : INFINITY;
+    default:
+      return (w <= 256.0 ? 1.0 : 1.25 + 0.66 * (w - 256.0) / 256.0) * (3.5 + 0.255 * steps);
+  }
+}
+
+constexpr GemmParts kNoParts{nullptr, 0, nullptr, 0};
+
+struct GemmPlan {
+  int tile;
+  int slices;
+  double time;
+};
+
+// The fastest tile by the estimates. With scratch a gated-residual product may also be cut into slices of K: every slice
+// but the last writes its fp32 result and a second launch adds them (about 6 TB/s from the caches, and the launch itself).
+// Measured where N = 1536, K = 8960, slices against the best whole tile: 128 rows 17 / 40 us, 480 rows 31 / 39, 1200
+// rows 51 / 67; from about 1700 rows a whole tile fills the chip.
+GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
+  GemmPlan best{kTile256, 1, INFINITY};
+  for (int t = 0; t < kTiles; ++t) {
+    const double v = tile_time(t, m, N, K, epi, 1);
+    if (v < best.time) best = GemmPlan{t, 1, v};
+  }
+  if (epi != CHORUS_EPI_RESID || !parts.first || !aligned16(parts.first) || !aligned16(parts.rest)) return best;
+  const double whole = best.time;
+  const size_t one = (size_t)m * (size_t)N * sizeof(float);
+  if (one > parts.first_bytes) return best;
+  for (int sl = 2; sl <= kMaxSlices && sl <= K / BK; ++sl) {
+    if (sl > 2 && (!parts.rest || (size_t)(sl - 2) * one > parts.rest_bytes)) break;
+    const double add = 3.0 + (double)(2 * sl) * 4.0 * (double)m * N / 6.0e6;
+    for (int t = 0; t < kTiles; ++t) {
+      const double v = tile_time(t, m, N, K, epi, sl) + add;
+      if (v < 0.95 * whole && v < best.time) best = GemmPlan{t, sl, v};
+    }
+  }
+  return best;
+}
+
+int32_t launch_tile(int tile, const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, const EpiArgs& ep,
+                    hipStream_t s, int slices = 1, const PartPtrs& parts = PartPtrs{nullptr, nullptr}) {
+  switch (tile) {
+    case kTile256: return launch_gemm_w16<8, 2>(A, W, M, N, K, epi, ep, s, slices, parts);
+    case kTile128: return launch_gemm_w16<4, 2>(A, W, M, N, K, epi, ep, s, slices, parts);
+    case kTile128Deep: return launch_gemm_w16<4, 3>(A, W, M, N, K, epi, ep, s, slices, parts);
+    default: return launch_gemm_w16<2, 4>(A, W, M, N, K, epi, ep, s, slices, parts);
+  }
+}
+
+int32_t launch_plan(const GemmPlan& p, const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, const EpiArgs& ep,
+                    const GemmParts& parts, hipStream_t s) {
+  const PartPtrs pp{static_cast<float*>(parts.first), static_cast<float*>(parts.rest)};
+  CHK_STATUS(launch_tile(p.tile, A, W, M, N, K, epi, ep, s, p.slices, pp));
+  return p.slices > 1 ? launch_add_parts(pp, p.slices, M, N, ep, s) : CHORUS_OK;
+}
+
+int32_t check_gemm(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, const void* out, const float* bias,
+                   const float* gate0, const float* gate1) {
+  if (M < 0 || N <= 0 || K <= 0) return CHORUS_E_ARG;
+  if (M == 0) return CHORUS_OK;
+  if (!A || !W || !out) return CHORUS_E_ARG;
+  if (K % BK || N % 8) return CHORUS_E_SHAPE;
+  if (!aligned16(A) || !aligned16(W) || !aligned16(out) || !aligned16(bias) || !aligned16(gate0) || !aligned16(gate1))
+    return CHORUS_E_ARG;
+  return CHORUS_OK;
+}
+
 }  // namespace
+
+int32_t gemm_bf16_parts(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, int32_t epilogue, void* out,
+                        const float* bias, const float* gate0, const float* gate1, float scale, const GemmParts& parts,
+                        void* stream) {
+  CHK_STATUS(check_gemm(A, W, M, N, K, out, bias, gate0, gate1));
+  if (M == 0) return CHORUS_OK;
+  if (epilogue < CHORUS_EPI_BF16 || epilogue > CHORUS_EPI_RESID) return CHORUS_E_ARG;
+  const EpiArgs ep{out, bias, gate0, gate1, scale};
+  hipStream_t s = (hipStream_t)stream;
+  const GemmPlan whole = plan_gemm((long)M, N, K, epilogue, parts);
+  // A last round of 256 x 256 tiles that fills a small part of the chip costs most of a whole round. The rows can be cut
+  // instead: the row tiles that make up whole rounds go to the 256 x 256 kernel, the rows left over to whichever
+  // kernel suits that many rows, in a second launch behind the first. Taken when the estimate is better by 5 %.
+  const long tiles_n256 = (N + 255) / 256, tiles256 = ((M + 255) / 256) * tiles_n256;
+  const long head_rows = tiles256 > 256 ? (tiles256 / 256 * 256 / tiles_n256) * 256 : 0;
+  if (head_rows > 0 && head_rows < M) {
+    const long rest = (long)M - head_rows;
+    const GemmPlan tail = plan_gemm(rest, N, K, epilogue, kNoParts);
+    if (tile_time(kTile256, head_rows, N, K, epilogue, 1) + tail.time < 0.95 * whole.time) {
+      CHK_STATUS(launch_tile(kTile256, A, W, head_rows, N, K, epilogue, ep, s));
+      const size_t out_elt = (epilogue == CHORUS_EPI_F32 || epilogue == CHORUS_EPI_RESID) ? 4 : 2;
+      EpiArgs ep_rest = ep;
+      ep_rest.out = static_cast<uint8_t*>(out) + (size_t)head_rows * (size_t)N * out_elt;
+      return launch_plan(tail, A + (size_t)head_rows * (size_t)K, W, rest, N, K, epilogue, ep_rest, kNoParts, s);
+    }
+  }
+  return launch_plan(whole, A, W, (long)M, N, K, epilogue, ep, parts, s);
+}
+
 }  // namespace chorus
 
 using namespace chorus;
@@ -696,70 +920,20 @@ using namespace chorus;
 extern "C" int32_t chorus_gemm_bf16_kernel(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K,
                                            int32_t epilogue, void* out, const float* bias, const float* gate0,
                                            const float* gate1, float scale, int32_t kernel, void* stream) {
-  if (M < 0 || N <= 0 || K <= 0) return CHORUS_E_ARG;
   if (kernel < 0 || kernel > 4) return CHORUS_E_ARG;
+  if (kernel == 0) return gemm_bf16_parts(A, W, M, N, K, epilogue, out, bias, gate0, gate1, scale, kNoParts, stream);
+  CHK_STATUS(check_gemm(A, W, M, N, K, out, bias, gate0, gate1));
   if (M == 0) return CHORUS_OK;
-  if (!A || !W || !out) return CHORUS_E_ARG;
-  if (K % BK || N % 8) return CHORUS_E_SHAPE;
-  if (!aligned16(A) || !aligned16(W) || !aligned16(out) || !aligned16(bias) || !aligned16(gate0) || !aligned16(gate1))
-    return CHORUS_E_ARG;
   EpiArgs ep{out, bias, gate0, gate1, scale};
   hipStream_t s = (hipStream_t)stream;
   if (kernel == 1) return launch_gemm<128, 64, 64, 32>(A, W, (long)M, N, K, epilogue, ep, s);
   if (kernel == 2) return launch_gemm<256, 128, 128, 64>(A, W, (long)M, N, K, epilogue, ep, s);
-  if (kernel == 3) return launch_gemm_w16<8>(A, W, (long)M, N, K, epilogue, ep, s);
-  if (kernel == 4) return launch_gemm_w16<4>(A, W, (long)M, N, K, epilogue, ep, s);
-  // Automatic choice: the estimated time of each tile shape, in microseconds, from fits to measurements on this chip
-  // at K = 1536 and K = 8960, M from 48 to 32760 and N = 1536, 4608 and 8960 (a constant for prologue and epilogue
-  // plus a cost per element of K). The 256 x 256 and 256 x 128 tiles run one workgroup per compute unit, so they go in
-  // rounds of 256 workgroups (the figures are those of a full round: a round that fills few units runs faster, and
-  // there a smaller tile is chosen anyway). The 128 x 128 and 128 x 64 tiles keep several workgroups per unit in
-  // flight, so their time grows with the tile count past the first 256.
-  const double k = (double)K;
-  const long tiles_n256 = (N + 255) / 256;
-  const bool f32_out = epilogue == CHORUS_EPI_F32 || epilogue == CHORUS_EPI_RESID;
-  auto t256 = [&](long m) { return (double)((((m + 255) / 256) * tiles_n256 + 255) / 256) * (2.0 + 0.0265 * k); };
-  auto t128 = [&](long m) { return (double)((((m + 255) / 256) * ((N + 127) / 128) + 255) / 256) * (9.0 + 0.0177 * k); };
-  auto t128sq = [&](long m) {  // two workgroups per unit: up to 256 tiles one each, then rounds of 512
-    const long tiles = ((m + 127) / 128) * ((N + 127) / 128);
-    const double one = (f32_out ? 6.0 : -2.0) + 0.0099 * k, round512 = (f32_out ? 9.0 : 1.0) + 0.0162 * k;
-    if (tiles <= 256) return one;
-    if (tiles <= 512) return one + (double)(tiles - 256) / 256.0 * (round512 - one);
-    return (double)((tiles + 511) / 512) * round512;
-  };
-  auto t64 = [&](long m) {
-    const long small_tiles = ((m + 127) / 128) * ((N + 63) / 64);
-    return (5.6 + 0.0084 * k) + (small_tiles > 256 ? (double)(small_tiles - 256) / 256.0 * (0.8 + 0.0057 * k) : 0.0);
-  };
-  auto t_best = [&](long m) { return fmin(fmin(t256(m), t128(m)), fmin(t128sq(m), t64(m))); };
-  auto launch_best = [&](const uint16_t* a, long m, const EpiArgs& e) {
-    const double a256 = t256(m), a128 = t128(m), a128sq = t128sq(m), a64 = t64(m), best = t_best(m);
-    if (a256 <= best) return launch_gemm_w16<8>(a, W, m, N, K, epilogue, e, s);
-    if (a128sq <= best) return launch_gemm_w16<4>(a, W, m, N, K, epilogue, e, s);
-    if (a128 <= a64) return launch_gemm<256, 128, 128, 64>(a, W, m, N, K, epilogue, e, s);
-    return launch_gemm<128, 64, 64, 32>(a, W, m, N, K, epilogue, e, s);
-  };
-  // A last round of 256 x 256 tiles that fills a small part of the chip costs a whole round. The rows can be cut
-  // instead: the row tiles that make up whole rounds go to the 256 x 256 kernel, the rows left over to whichever
-  // kernel suits that many rows, in a second launch behind the first. Taken when the estimate is better by 5 %.
-  const long tiles256 = ((M + 255) / 256) * tiles_n256;
-  const long head_rows = tiles256 > 256 ? (tiles256 / 256 * 256 / tiles_n256) * 256 : 0;
-  if (head_rows > 0 && head_rows < M) {
-    const long rest = (long)M - head_rows;
-    if (t256(head_rows) + t_best(rest) < 0.95 * t_best((long)M)) {
-      const int32_t rc = launch_gemm_w16<8>(A, W, head_rows, N, K, epilogue, ep, s);
-      if (rc != CHORUS_OK) return rc;
-      const size_t out_elt = (epilogue == CHORUS_EPI_F32 || epilogue == CHORUS_EPI_RESID) ? 4 : 2;
-      EpiArgs ep_rest = ep;
-      ep_rest.out = static_cast<uint8_t*>(out) + (size_t)head_rows * (size_t)N * out_elt;
-      return launch_best(A + (size_t)head_rows * (size_t)K, rest, ep_rest);
-    }
-  }
-  return launch_best(A, (long)M, ep);
+  if (kernel == 3) return launch_tile(kTile256, A, W, (long)M, N, K, epilogue, ep, s);
+  return launch_tile(kTile128, A, W, (long)M, N, K, epilogue, ep, s);
 }
 
 extern "C" int32_t chorus_gemm_bf16(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K,
                                     int32_t epilogue, void* out, const float* bias, const float* gate0,
                                     const float* gate1, float scale, void* stream) {
-  return chorus_gemm_bf16_kernel(A, W, M, N, K, epilogue, out, bias, gate0, gate1, scale, 0, stream);
+  return gemm_bf16_parts(A, W, M, N, K, epilogue, out, bias, gate0, gate1, scale, kNoParts, stream);
 }
