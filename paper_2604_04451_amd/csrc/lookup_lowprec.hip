@@ -17,37 +17,55 @@
 namespace chorus {
 namespace {
 
-constexpr int kWaves = 4;             // waves per workgroup of the scan, one row per wave at a time
-constexpr int kMaxScanBlocks = 4096;
-constexpr size_t kHeaderBytes = 256;  // |q|^2
+constexpr int kWaves = 4;            // waves per workgroup of the scan and of the re-rank
+constexpr int kMaxBlocks = 1024;     // workgroups of either: four on every compute unit; beyond that a wave takes several rows
+constexpr int kMaxScanBlocks = 4096; // the workspace is laid out for this many
 
-inline long scan_blocks(long N) {
+inline long lp_blocks(long N) {
   long g = (N + kWaves - 1) / kWaves;
-  return g < kMaxScanBlocks ? g : kMaxScanBlocks;
+  return g < kMaxBlocks ? g : kMaxBlocks;
 }
 
-struct RerankPartial;
+// Where the re-rank's workgroups leave what they found; the first workgroup of the scan resets it. A line each: when
+// every row is a candidate a thousand workgroups arrive, and atomics on one line are served one at a time (10 ns).
+constexpr int kSlots = 64;
+struct alignas(128) LpSlot {
+  unsigned long long best;  // best exact r with its row (pack_best), 0 = none
+  int32_t count;            // rows re-scored
+};
 struct LpWs {
   float* qnorm2;
-  float* partial_max;      // [scan_blocks]
-  RerankPartial* rerank;   // [scan_blocks]
+  LpSlot* slots;           // [kSlots]
+  float* partial_max;      // [lp_blocks]
   float* scores;           // [N] approximate r_j = <q, c^_j> / |c^_j|
   size_t bytes;
 };
+static_assert(kSlots * sizeof(LpSlot) <= (size_t)kMaxScanBlocks * 16, "the slots' place in the workspace");
 LpWs carve_lp(long N, void* base) {
   const BytePtr p(base);
   LpWs w;
   size_t off = 0;
   w.qnorm2 = (float*)(p + off);
-  off += kHeaderBytes;
+  off += 256;
   w.partial_max = (float*)(p + off);
   off += align_up((size_t)kMaxScanBlocks * sizeof(float), 256);
-  w.rerank = (RerankPartial*)(p + off);
+  w.slots = (LpSlot*)(p + off);
   off += (size_t)kMaxScanBlocks * 16;
   w.scores = (float*)(p + off);
   off += align_up((size_t)(N > 0 ? N : 1) * sizeof(float), 256);
   w.bytes = off;
   return w;
+}
+
+// r > -inf and its row as one integer that orders by r and, between equal r (0 and -0 are equal), by the lower row
+__device__ __forceinline__ unsigned long long pack_best(float r, uint32_t row) {
+  const uint32_t u = __float_as_uint(r + 0.0f);
+  const uint32_t ord = (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  return ((unsigned long long)ord << 32) | (uint32_t)~row;
+}
+__device__ __forceinline__ float unpack_r(unsigned long long k) {
+  const uint32_t ord = (uint32_t)(k >> 32);
+  return __uint_as_float((ord & 0x80000000u) ? (ord & 0x7fffffffu) : ~ord);
 }
 
 // ---- decoding 16 bytes of a row into floats ------------------------------------------------
@@ -121,58 +139,93 @@ __global__ __launch_bounds__(256) void lowprec_store_kernel(const float* __restr
 }
 
 // ---- scan of the low-precision rows -------------------------------------------------------------
+// One 16-byte chunk of codes against its query values: dot += <f, q>, cc += <f, f>, four elements at a time in
+// ascending order (the order of additions depends on d only, so equal rows score equal)
 template <int FMT>
+__device__ __forceinline__ void add_chunk(const u32x4& v, const float4* q, float& dot, float& cc) {
+  constexpr int E = Codes<FMT>::kPer16;
+  float f[E];
+  Codes<FMT>::decode(v, f);
+#pragma unroll
+  for (int e4 = 0; e4 < E / 4; ++e4) {
+    dot += f[4 * e4] * q[e4].x + f[4 * e4 + 1] * q[e4].y + f[4 * e4 + 2] * q[e4].z + f[4 * e4 + 3] * q[e4].w;
+    cc += f[4 * e4] * f[4 * e4] + f[4 * e4 + 1] * f[4 * e4 + 1] + f[4 * e4 + 2] * f[4 * e4 + 2] + f[4 * e4 + 3] * f[4 * e4 + 3];
+  }
+}
+
+// One wave per row at a time. NC > 0: a row has at most 64 NC chunks of 16 bytes, and a lane keeps the query values of
+// its NC chunks (64 registers at d = 4096) for all its rows and has the next row's chunks in flight while it sums this
+// one. Read again for every row, the fp32 query is four times the bytes of an FP8 row, all through the L1, which is
+// what bound this kernel: 16384 x 4096 FP8 (67 MB) 23.8 us that way. NC = 0: any d, the query is read for every row.
+template <int FMT, int NC>
 __global__ __launch_bounds__(kWaves * 64) void lowprec_scan_kernel(const void* __restrict__ cache_lp,
                                                                    const float* __restrict__ query, long N, int d,
                                                                    float* __restrict__ scores,
                                                                    float* __restrict__ partial_max,
-                                                                   float* __restrict__ qnorm2) {
+                                                                   float* __restrict__ qnorm2, LpSlot* __restrict__ slots) {
   constexpr int E = Codes<FMT>::kPer16;
-  constexpr int U = 4;  // 16-byte loads in flight per lane
   __shared__ float sv[kWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n16 = d / E;  // 16-byte chunks per row
   const long row_bytes = (long)d * (16 / E);
+  const uint8_t* base = reinterpret_cast<const uint8_t*>(cache_lp);
   float best = -INFINITY;
   const long stride = (long)gridDim.x * kWaves;
-  for (long row = (long)blockIdx.x * kWaves + wave; row < N; row += stride) {
-    const u32x4* c16 = reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(cache_lp) + row * row_bytes);
-    float dot = 0.f, cc = 0.f;
-    int i = lane;
-    for (; i + (U - 1) * 64 < n16; i += U * 64) {
-      u32x4 v[U];
+  long row = (long)blockIdx.x * kWaves + wave;
+  auto finish = [&](long r, float dot, float cc) {
+    const float v = row_ratio(wave_sum(dot), wave_sum(cc));
+    if (lane == 0) scores[r] = v;
+    best = fmaxf(best, v);
+  };
+  if constexpr (NC > 0) {
+    float4 q[NC][E / 4];
+    u32x4 v[2][NC];
+    auto fetch = [&](u32x4 (&dst)[NC], long r) {
+      const u32x4* c16 = reinterpret_cast<const u32x4*>(base + r * row_bytes);
 #pragma unroll
-      for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(&c16[i + u * 64]);
+      for (int c = 0; c < NC; ++c)
+        dst[c] = __builtin_nontemporal_load(&c16[lane + 64 * c < n16 ? lane + 64 * c : n16 - 1]);
+    };
+    auto sum = [&](const u32x4 (&src)[NC], long r) {
+      float dot = 0.f, cc = 0.f;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        float f[E];
-        Codes<FMT>::decode(v[u], f);
-        const float4* q4 = reinterpret_cast<const float4*>(query + (long)(i + u * 64) * E);
+      for (int c = 0; c < NC; ++c) {
+        const u32x4 w = lane + 64 * c < n16 ? src[c] : u32x4{0u, 0u, 0u, 0u};  // code 0 is 0.0 in both formats
+        add_chunk<FMT>(w, q[c], dot, cc);
+      }
+      finish(r, dot, cc);
+    };
+    if (row < N) fetch(v[0], row);
 #pragma unroll
-        for (int e4 = 0; e4 < E / 4; ++e4) {
-          const float4 q = q4[e4];
-          dot += f[4 * e4] * q.x + f[4 * e4 + 1] * q.y + f[4 * e4 + 2] * q.z + f[4 * e4 + 3] * q.w;
-          cc += f[4 * e4] * f[4 * e4] + f[4 * e4 + 1] * f[4 * e4 + 1] + f[4 * e4 + 2] * f[4 * e4 + 2] + f[4 * e4 + 3] * f[4 * e4 + 3];
-        }
+    for (int c = 0; c < NC; ++c)
+#pragma unroll
+      for (int e = 0; e < E / 4; ++e)
+        q[c][e] = reinterpret_cast<const float4*>(query)[(lane + 64 * c < n16 ? lane + 64 * c : n16 - 1) * (E / 4) + e];
+    for (; row < N; row += 2 * stride) {  // two rows a turn: the buffers are named, not indexed
+      if (row + stride < N) fetch(v[1], row + stride);
+      sum(v[0], row);
+      if (row + stride < N) {
+        if (row + 2 * stride < N) fetch(v[0], row + 2 * stride);
+        sum(v[1], row + stride);
       }
     }
-    for (; i < n16; i += 64) {
-      const u32x4 v = __builtin_nontemporal_load(&c16[i]);
-      float f[E];
-      Codes<FMT>::decode(v, f);
-      const float4* q4 = reinterpret_cast<const float4*>(query + (long)i * E);
+  } else {
+    for (; row < N; row += stride) {
+      const u32x4* c16 = reinterpret_cast<const u32x4*>(base + row * row_bytes);
+      constexpr int U = 4;  // 16-byte loads in flight per lane
+      float dot = 0.f, cc = 0.f;
+      int i = lane;
+      for (; i + (U - 1) * 64 < n16; i += U * 64) {
+        u32x4 v[U];
 #pragma unroll
-      for (int e4 = 0; e4 < E / 4; ++e4) {
-        const float4 q = q4[e4];
-        dot += f[4 * e4] * q.x + f[4 * e4 + 1] * q.y + f[4 * e4 + 2] * q.z + f[4 * e4 + 3] * q.w;
-        cc += f[4 * e4] * f[4 * e4] + f[4 * e4 + 1] * f[4 * e4 + 1] + f[4 * e4 + 2] * f[4 * e4 + 2] + f[4 * e4 + 3] * f[4 * e4 + 3];
+        for (int u = 0; u < U; ++u) v[u] = __builtin_nontemporal_load(&c16[i + u * 64]);
+#pragma unroll
+        for (int u = 0; u < U; ++u) add_chunk<FMT>(v[u], reinterpret_cast<const float4*>(query + (long)(i + u * 64) * E), dot, cc);
       }
+      for (; i < n16; i += 64)
+        add_chunk<FMT>(__builtin_nontemporal_load(&c16[i]), reinterpret_cast<const float4*>(query + (long)i * E), dot, cc);
+      finish(row, dot, cc);
     }
-    dot = wave_sum(dot);
-    cc = wave_sum(cc);
-    const float r = row_ratio(dot, cc);
-    if (lane == 0) scores[row] = r;
-    best = fmaxf(best, r);
   }
   if (blockIdx.x == 0 && wave == 0) {  // |q|^2 exactly as the fp32 lookup sums it
     float qq = 0.f;
@@ -192,6 +245,9 @@ __global__ __launch_bounds__(kWaves * 64) void lowprec_scan_kernel(const void* _
     }
     qq = wave_sum(qq);
     if (lane == 0) *qnorm2 = qq;
+    static_assert(kSlots == 64, "one slot per lane");
+    slots[lane].best = 0;
+    slots[lane].count = 0;
   }
   if (lane == 0) sv[wave] = best;
   __syncthreads();
@@ -204,49 +260,55 @@ __global__ __launch_bounds__(kWaves * 64) void lowprec_scan_kernel(const void* _
 
 // ---- candidates and exact re-rank ---------------------------------------------------------------
 // threshold = best approximate r - margin * |q| (r = cosine * |q|); every row at or above it is re-scored from its
-// fp32 row by a whole wave with the fp32 lookup's own row pass. The launch has the scan's shape (one wave per row at
-// a time), so even when every row is a candidate (FP8 on a query far from every entry) the re-rank costs one fp32
-// scan, spread over the chip; usually a single wave has work. Each wave first reduces the scan's partial maxima
-// itself (at most 4096 floats, L2-resident).
-struct RerankPartial {
-  float r;
-  int32_t idx;
-  int32_t count;
-  int32_t pad;
-};
-static_assert(sizeof(RerankPartial) == 16, "workspace carving assumes 16 bytes per partial");
-
+// fp32 row by a whole wave with the fp32 lookup's own row pass. A wave owns a run of consecutive rows and looks at the
+// scores of 64 of them at once; the rows are spread over the whole chip, so even when every row is a candidate (FP8 on
+// a query far from every entry) the re-rank costs one fp32 scan. Each workgroup reduces the scan's partial maxima
+// itself (at most 1024, four per thread). Usually a handful of waves have a row at all, so the winners meet in atomic
+// maxima in memory. (With every wave of 4096 workgroups reducing 4096 maxima, and a partial
+// result per workgroup, the re-rank of one row among 16384 took 35.9 us and its final reduction 7.5.)
 __global__ __launch_bounds__(kWaves * 64) void lowprec_rerank_kernel(const float* __restrict__ cache_emb,
                                                                      const float* __restrict__ query, long N, int d,
                                                                      const float* __restrict__ scores,
                                                                      const float* __restrict__ partial_max, int nparts,
                                                                      const float* __restrict__ qnorm2, float margin,
-                                                                     RerankPartial* __restrict__ partial) {
+                                                                     LpSlot* __restrict__ slots) {
+  __shared__ float sm[kWaves];
   __shared__ float sv[kWaves];
   __shared__ int32_t si[kWaves];
   __shared__ int32_t sc[kWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float mx = -INFINITY;
-  for (int j = lane; j < nparts; j += 64) mx = fmaxf(mx, partial_max[j]);
-  mx = wave_max(mx);
+  const long nwaves = (long)gridDim.x * kWaves, w_id = (long)blockIdx.x * kWaves + wave;
+  const long first = w_id * N / nwaves, end = (w_id + 1) * N / nwaves;
+  float own = first + lane < end ? scores[first + lane] : -INFINITY;  // in flight beside the maxima
   const float nq = sqrtf(*qnorm2);
+  float mx = -INFINITY;
+  for (int j = threadIdx.x; j < nparts; j += kWaves * 64) mx = fmaxf(mx, partial_max[j]);
+  mx = wave_max(mx);
+  if (lane == 0) sm[wave] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) mx = fmaxf(mx, sm[w]);
   // no finite score (all rows zero) or a zero query: every exact score is -inf as well, nothing is re-scored
   const float thr = nq > 0.f ? mx - margin * nq : -INFINITY;
   const float4* q4 = reinterpret_cast<const float4*>(query);
   const int n4 = d >> 2;
   float best = -INFINITY;
   int32_t bi = 0x7fffffff, count = 0;
-  const long stride = (long)gridDim.x * kWaves;
   if (thr > -INFINITY) {
-    for (long row = (long)blockIdx.x * kWaves + wave; row < N; row += stride) {
-      if (!(scores[row] >= thr)) continue;  // one address per wave: uniform
-      float dot, cc, qq;
-      fp32_row_products(reinterpret_cast<const float4*>(cache_emb + row * (long)d), q4, n4, lane, dot, cc, qq);
-      const float r = row_ratio(dot, cc);
-      ++count;
-      if (r > best) {  // rows ascend within a wave
-        best = r;
-        bi = (int32_t)row;
+    for (long r0 = first; r0 < end; r0 += 64) {
+      if (r0 != first) own = r0 + lane < end ? scores[r0 + lane] : -INFINITY;
+      unsigned long long todo = __ballot(own >= thr);
+      count += __popcll(todo);
+      while (todo) {  // ascending rows
+        const long row = r0 + __builtin_ctzll(todo);
+        todo &= todo - 1;
+        float dot, cc, qq;
+        fp32_row_products(reinterpret_cast<const float4*>(cache_emb + row * (long)d), q4, n4, lane, dot, cc, qq);
+        const float r = row_ratio(dot, cc);
+        if (r > best) {
+          best = r;
+          bi = (int32_t)row;
+        }
       }
     }
   }
@@ -265,75 +327,53 @@ __global__ __launch_bounds__(kWaves * 64) void lowprec_rerank_kernel(const float
       }
       count += sc[w];
     }
-    RerankPartial p;
-    p.r = best;
-    p.idx = bi;
-    p.count = count;
-    p.pad = 0;
-    partial[blockIdx.x] = p;
+    LpSlot& slot = slots[blockIdx.x % kSlots];
+    if (count > 0) atomicAdd(&slot.count, count);
+    if (best > -INFINITY) atomicMax(&slot.best, pack_best(best, (uint32_t)bi));
   }
 }
 
-// Single workgroup: the best exact r among the workgroup partials (lowest index among equal ones), the number of
-// re-scored rows, then the division by |q| and the threshold test, as in the fp32 lookup.
-__global__ __launch_bounds__(256) void lowprec_final_kernel(const RerankPartial* __restrict__ partial, int nparts,
-                                                            const float* __restrict__ qnorm2, long N, float tau,
-                                                            chorus_lookup_result* __restrict__ out,
-                                                            int32_t* __restrict__ n_rescored) {
-  __shared__ float sv[4];
-  __shared__ int32_t si[4];
-  __shared__ int32_t sc[4];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  float best = -INFINITY;
-  int32_t bi = 0x7fffffff, count = 0;
-  for (int j = threadIdx.x; j < nparts; j += 256) {
-    const RerankPartial p = partial[j];
-    count += p.count;
-    if (p.r > best || (p.r == best && p.idx < bi)) {
-      best = p.r;
-      bi = p.idx;
-    }
-  }
+// One wave: the best of the slots, the division by |q| and the threshold test, as in the fp32 lookup.
+__global__ __launch_bounds__(64) void lowprec_final_kernel(const LpSlot* __restrict__ slots, const float* __restrict__ qnorm2,
+                                                           long N, float tau, chorus_lookup_result* __restrict__ out,
+                                                           int32_t* __restrict__ n_rescored) {
+  unsigned long long key = N > 0 ? slots[threadIdx.x].best : 0;
+  int32_t count = N > 0 ? slots[threadIdx.x].count : 0;
+  const float nq = N > 0 ? sqrtf(*qnorm2) : 0.f;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    const float ob = __shfl_xor(best, o, 64);
-    const int32_t oi = __shfl_xor(bi, o, 64);
+    const unsigned long long other = __shfl_xor(key, o, 64);
+    key = other > key ? other : key;
     count += __shfl_xor(count, o, 64);
-    if (ob > best || (ob == best && oi < bi)) {
-      best = ob;
-      bi = oi;
-    }
   }
-  if (lane == 0) {
-    sv[wave] = best;
-    si[wave] = bi;
-    sc[wave] = count;
+  if (threadIdx.x != 0) return;
+  chorus_lookup_result r;
+  if (N <= 0) {
+    r.index = -1;
+    r.score = -INFINITY;
+    r.hit = 0;
+  } else {
+    const float best = key ? unpack_r(key) : -INFINITY;
+    float mm = (nq > 0.f && best > -INFINITY) ? best / nq : -INFINITY;
+    if (!(mm == mm)) mm = -INFINITY;
+    r.index = mm == -INFINITY ? 0 : (int32_t)~(uint32_t)key;
+    r.score = mm;
+    r.hit = mm >= tau ? 1 : 0;
   }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w) {
-      if (sv[w] > best || (sv[w] == best && si[w] < bi)) {
-        best = sv[w];
-        bi = si[w];
-      }
-      count += sc[w];
-    }
-    chorus_lookup_result r;
-    if (N <= 0) {
-      r.index = -1;
-      r.score = -INFINITY;
-      r.hit = 0;
-    } else {
-      const float nq = sqrtf(*qnorm2);
-      float mm = (nq > 0.f && best > -INFINITY) ? best / nq : -INFINITY;
-      if (!(mm == mm)) mm = -INFINITY;
-      r.index = (bi == 0x7fffffff || mm == -INFINITY) ? 0 : bi;
-      r.score = mm;
-      r.hit = mm >= tau ? 1 : 0;
-    }
-    *out = r;
-    if (n_rescored) *n_rescored = count;
-  }
+  *out = r;
+  if (n_rescored) *n_rescored = count;
+}
+
+template <int FMT>
+void launch_lp_scan(const void* cache_lp, const float* query, long N, int d, const LpWs& w, unsigned grid, hipStream_t s) {
+  const int nc = (d / Codes<FMT>::kPer16 + 63) / 64, most = 64 / Codes<FMT>::kPer16;  // 64 query values per lane
+#define LP_SCAN(NC) \
+  hipLaunchKernelGGL((lowprec_scan_kernel<FMT, NC>), dim3(grid), dim3(kWaves * 64), 0, s, cache_lp, query, N, d, w.scores, w.partial_max, w.qnorm2, w.slots)
+  if (nc > most) LP_SCAN(0);
+  else if (nc > most / 2) LP_SCAN(64 / Codes<FMT>::kPer16);
+  else if (nc > most / 4) LP_SCAN(32 / Codes<FMT>::kPer16);
+  else LP_SCAN(16 / Codes<FMT>::kPer16);
+#undef LP_SCAN
 }
 
 inline double lowprec_margin(int format, int d) {
@@ -387,23 +427,18 @@ int32_t chorus_cache_lookup_lowprec(const float* cache_emb, const void* cache_lp
   if (!ws || ws_bytes < chorus_cache_lookup_lowprec_workspace_bytes(N)) return CHORUS_E_WORKSPACE;
   LpWs w = carve_lp((long)N, ws);
   hipStream_t s = (hipStream_t)stream;
-  int nparts = 0;
   if (N > 0) {
-    nparts = (int)scan_blocks((long)N);
+    const unsigned grid = (unsigned)lp_blocks((long)N);
     if (format == CHORUS_LP_BF16)
-      hipLaunchKernelGGL(lowprec_scan_kernel<CHORUS_LP_BF16>, dim3((unsigned)nparts), dim3(kWaves * 64), 0, s, cache_lp, query,
-                         (long)N, d, w.scores, w.partial_max, w.qnorm2);
+      launch_lp_scan<CHORUS_LP_BF16>(cache_lp, query, (long)N, d, w, grid, s);
     else
-      hipLaunchKernelGGL(lowprec_scan_kernel<CHORUS_LP_FP8>, dim3((unsigned)nparts), dim3(kWaves * 64), 0, s, cache_lp, query,
-                         (long)N, d, w.scores, w.partial_max, w.qnorm2);
+      launch_lp_scan<CHORUS_LP_FP8>(cache_lp, query, (long)N, d, w, grid, s);
+    CHORUS_LAUNCH_CHECK();
+    hipLaunchKernelGGL(lowprec_rerank_kernel, dim3(grid), dim3(kWaves * 64), 0, s, cache_emb, query, (long)N, d, w.scores,
+                       w.partial_max, (int)grid, w.qnorm2, (float)lowprec_margin(format, d), w.slots);
     CHORUS_LAUNCH_CHECK();
   }
-  if (N > 0) {
-    hipLaunchKernelGGL(lowprec_rerank_kernel, dim3((unsigned)nparts), dim3(kWaves * 64), 0, s, cache_emb, query, (long)N, d,
-                       w.scores, w.partial_max, nparts, w.qnorm2, (float)lowprec_margin(format, d), w.rerank);
-    CHORUS_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(lowprec_final_kernel, dim3(1), dim3(256), 0, s, w.rerank, nparts, w.qnorm2, (long)N, tau, out, n_rescored);
+  hipLaunchKernelGGL(lowprec_final_kernel, dim3(1), dim3(64), 0, s, w.slots, w.qnorm2, (long)N, tau, out, n_rescored);
   CHORUS_LAUNCH_CHECK();
   return CHORUS_OK;
 }

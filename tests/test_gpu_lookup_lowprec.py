@@ -98,3 +98,21 @@ def test_lowprec_lookup_near_duplicates_and_edges(fmt, code):
     out, nn = B.chorus_cache_lookup_lowprec(torch.empty(0, 64, device=DEV), torch.empty(0, 64, dtype=torch.uint8 if fmt == "fp8" else torch.int16, device=DEV),
                                             code, dev_f32(q), 0.75)
     assert P.lookup_result(out) == (-1, -math.inf, False) and int(nn.cpu()[0]) == 0
+
+
+@pytest.mark.parametrize("fmt,code", FMTS)
+@pytest.mark.parametrize("N,d", [(1, 16), (5, 512), (4097, 1024), (9001, 1040), (4100, 2064), (4099, 4096), (4103, 4112), (8200, 48)])
+def test_lowprec_lookup_rows_per_wave(N, d, fmt, code):
+    """Rows in registers (all chunk counts, partly filled ones) and the wide fallback, waves with one, several and no
+    rows: the result words equal the fp32 lookup's for a query near a row that occurs twice and for one far from all."""
+    print(f"[case] lowprec rows per wave N={N} d={d} {fmt}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + d)
+    cache = torch.randn(N, d, device=DEV, generator=g)
+    near = N // 2
+    cache[N - 1] = cache[near]
+    lp = B.chorus_cache_lowprec_store(cache, code)
+    for q in (cache[near] + 0.2 * torch.randn(d, device=DEV, generator=g), torch.randn(d, device=DEV, generator=g), -cache[0]):
+        got, n = B.chorus_cache_lookup_lowprec(cache, lp, code, q, 0.75)
+        ref = B.chorus_cache_lookup(cache, q, 0.75)
+        assert torch.equal(got, ref), (P.lookup_result(got), P.lookup_result(ref))
+        assert 1 <= int(n.cpu()[0]) <= N
