@@ -24,8 +24,10 @@ inline BatchPlan plan_batch(long N, int d) {
   BatchPlan p;
   p.tiles = (int)((N + kBR - 1) / kBR);
   const int nchunks = (d + kBK - 1) / kBK;
-  // enough workgroups to put four on each of 256 CUs; partial sums of the slices are added in a fixed order afterwards
-  int want = p.tiles > 0 ? (1024 + p.tiles - 1) / p.tiles : 1;
+  // As many workgroups as fit the chip at once, four on each of 256 CUs, and no more: a few beyond that are a second round
+  // (20000 x 4096, 32 queries: 1252 workgroups 130 us the call, 939 108). Partial sums of the slices are added in a fixed order
+  // afterwards.
+  int want = p.tiles > 0 ? 1024 / p.tiles : 1;
   if (want < 1) want = 1;
   if (want > nchunks) want = nchunks;
   if (want > 16) want = 16;  // every slice writes and re-reads its own partial sums
@@ -40,11 +42,12 @@ __global__ __launch_bounds__(256) void lookup_batch_scores_kernel(const float* _
                                                                   const float* __restrict__ queries,
                                                                   float* __restrict__ part_dot,
                                                                   float* __restrict__ part_cc, long N, int d, int Q,
-                                                                  int chunks_per_slice) {
+                                                                  int chunks_per_slice, uint32_t* __restrict__ done) {
   constexpr int QP = 16 * QB;
   __shared__ __attribute__((aligned(16))) float sA[kBR * kLS];
   __shared__ __attribute__((aligned(16))) float sB[QP * kLS];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  if (done && blockIdx.x == 0 && blockIdx.y == 0 && tid < QP) done[tid] = 0;  // arrivals of the selection's workgroups
   const long row0 = (long)blockIdx.x * kBR;
   const long Npad = (long)gridDim.x * kBR;
   const int ks = blockIdx.y;
@@ -167,11 +170,217 @@ __device__ __forceinline__ void sum_slices(const float* __restrict__ part_dot, c
   }
 }
 
-constexpr int kWaveK = 64;  // up to this k the selection runs without a barrier per position
+constexpr int kWaveK = 64;  // up to this k a list is one key per lane
 
-// Final scores of all queries: score[q][j] = (partial dots summed in slice order) / (|c_j| |q|), -inf for zero norms
-// and NaN. Grid (row blocks of 1024, queries): spread over the chip, because one workgroup per query would pull its
-// KS slices (half a megabyte at 4096 entries) through a single compute unit.
+// ---- keys: a score and its row as one integer, larger = better (higher score, then lower row); 0 = no entry ----
+__device__ __forceinline__ uint64_t make_key(float score, uint32_t row) {
+  const uint32_t u = __float_as_uint(score + 0.0f);  // 0 and -0 are equal
+  return ((uint64_t)((u & 0x80000000u) ? ~u : (u | 0x80000000u)) << 32) | (uint32_t)~row;
+}
+__device__ __forceinline__ float key_score(uint64_t k) {
+  const uint32_t ord = (uint32_t)(k >> 32);
+  return k == 0 ? -INFINITY : __uint_as_float((ord & 0x80000000u) ? (ord & 0x7fffffffu) : ~ord);
+}
+__device__ __forceinline__ int key_row(uint64_t k) { return k == 0 ? -1 : (int)~(uint32_t)k; }
+
+template <int CTRL>
+__device__ __forceinline__ uint64_t max_dpp(uint64_t k) {
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (uint32_t)k, CTRL, 0xf, 0xf, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (uint32_t)(k >> 32), CTRL, 0xf, 0xf, false);
+  const uint64_t o = ((uint64_t)hi << 32) | lo;
+  return o > k ? o : k;
+}
+// largest key of the wave, in every lane: four steps inside rows of 16 lanes (quad permutes, half-row and row mirror),
+// then the register-file swaps
+__device__ __forceinline__ uint64_t wave_max_key(uint64_t k) {
+  k = max_dpp<0xB1>(k);
+  k = max_dpp<0x4E>(k);
+  k = max_dpp<0x141>(k);
+  k = max_dpp<0x140>(k);
+  {
+    const uint64_t o = ((uint64_t)__float_as_uint(swap_rows16(__uint_as_float((uint32_t)(k >> 32)))) << 32) |
+                       __float_as_uint(swap_rows16(__uint_as_float((uint32_t)k)));
+    k = o > k ? o : k;
+  }
+  const uint64_t o = ((uint64_t)__float_as_uint(swap_halves(__uint_as_float((uint32_t)(k >> 32)))) << 32) |
+                     __float_as_uint(swap_halves(__uint_as_float((uint32_t)k)));
+  return o > k ? o : k;
+}
+
+// The k <= 64 largest of the wave's keys (four per lane, all different but for 0), best first, one per lane (0 behind the
+// last). Few: a lane keeps its four sorted and offers its best, a round per position is one wave-wide maximum (about 400
+// clocks). More than kRounds: a bitonic sort of all 256, whose cost does not depend on k (about 3000).
+constexpr int kRounds = 8;
+__device__ __forceinline__ uint64_t shfl_key(uint64_t k, int from) {
+  return ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(k >> 32), from, 64) << 32) | (uint32_t)__shfl((int)(uint32_t)k, from, 64);
+}
+__device__ __forceinline__ uint64_t wave_topk(uint64_t (&key)[4], int k, int lane) {
+  auto order = [&](int i, int j, bool down) {  // down: the larger one to i
+    const bool swap = (key[i] < key[j]) == down;
+    const uint64_t a = swap ? key[j] : key[i], b = swap ? key[i] : key[j];
+    key[i] = a;
+    key[j] = b;
+  };
+  uint64_t mine = 0;
+  if (k <= kRounds) {
+    order(0, 1, true);
+    order(2, 3, true);
+    order(0, 2, true);
+    order(1, 3, true);
+    order(1, 2, true);
+    for (int r = 0; r < k; ++r) {
+      const uint64_t best = wave_max_key(key[0]);
+      if (best == 0) break;
+      if (lane == r) mine = best;
+      if (key[0] == best) {
+        key[0] = key[1];
+        key[1] = key[2];
+        key[2] = key[3];
+        key[3] = 0;
+      }
+    }
+    return mine;
+  }
+  // element i = 4 * lane + u; runs of `size` are sorted in alternating directions, the last one downwards
+  order(0, 1, true);
+  order(2, 3, false);
+  for (int size = 4; size <= 256; size *= 2) {
+    const bool down = ((4 * lane) & size) == 0;
+    for (int dist = size / 2; dist >= 4; dist /= 2) {
+      const int other = lane ^ (dist / 4);
+      const bool keep_max = (((4 * lane) & dist) == 0) == down;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint64_t o = shfl_key(key[u], other);
+        key[u] = (o > key[u]) == keep_max ? o : key[u];
+      }
+    }
+    order(0, 2, down);
+    order(1, 3, down);
+    order(0, 1, down);
+    order(2, 3, down);
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const uint64_t o = shfl_key(key[u], lane >> 2);
+    if ((lane & 3) == u) mine = o;
+  }
+  return lane < k ? mine : 0;
+}
+
+// Final scores and selection for k <= 64: score[q][j] = (partial dots summed in slice order) / (|c_j| |q|), -inf for zero
+// norms and NaN. Grid (row blocks of 1024, queries): spread over the chip, because one workgroup per query would pull its
+// KS slices (half a megabyte at 4096 entries) through a single compute unit. A wave keeps its 256 scores in registers and
+// lists the k best of them; the last workgroup of a query to arrive merges the lists. Lists and arrivals are
+// agent-scope atomics, as the workgroups of a query run on different XCDs, whose L2s are not coherent otherwise. With
+// the scores written out and one workgroup per query selecting from them (two launches): 23 us at 4096 x 32 queries,
+// k = 8, in this kernel 16; 20000 entries, 48 queries, k = 50 the whole call 538 -> 123 us.
+__global__ __launch_bounds__(256) void lookup_batch_select_kernel(const float* __restrict__ part_dot,
+                                                                  const float* __restrict__ part_cc,
+                                                                  const float* __restrict__ queries, uint64_t* lists,
+                                                                  uint32_t* done, long N, long Npad, int d, int QP, int KS,
+                                                                  int k, float tau, int32_t* __restrict__ out_idx,
+                                                                  float* __restrict__ out_score,
+                                                                  int32_t* __restrict__ out_hit) {
+  constexpr int R = 4;
+  __shared__ float sq[4];
+  __shared__ uint64_t sl[4][kWaveK];
+  __shared__ uint32_t s_arrived;
+  const int q = blockIdx.y, nb = gridDim.x;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const long j0 = (long)blockIdx.x * (256 * R) + tid;
+  float dot[R], cc[R];
+#pragma unroll
+  for (int u = 0; u < R; ++u) dot[u] = cc[u] = 0.f;
+  float qq = 0.f;
+  const f32x4* q4 = reinterpret_cast<const f32x4*>(queries + (long)q * d);
+  for (int i = tid; i < (d >> 2); i += 256) {
+    const f32x4 v = q4[i];
+    qq += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
+  }
+  sum_slices<R, 8, R, 256>(part_dot, part_cc, KS, QP, q, Npad, j0, N, dot, cc);
+  qq = wave_sum(qq);
+  if (lane == 0) sq[wave] = qq;
+  __syncthreads();
+  const float qn = sqrtf(sq[0] + sq[1] + sq[2] + sq[3]);
+  uint64_t key[4];
+#pragma unroll
+  for (int u = 0; u < R; ++u) {
+    const long j = j0 + 256L * u;
+    const float den = sqrtf(cc[u]) * qn;
+    float v = den > 0.f ? dot[u] / den : -INFINITY;
+    if (!(v == v)) v = -INFINITY;
+    key[u] = j < N ? make_key(v, (uint32_t)j) : 0;
+  }
+  // Every wave lists the k best of its 256 entries; with several row blocks the lists of a query meet in memory, one per
+  // wave while the last workgroup can take them all in one go, else one per workgroup.
+  uint64_t own = wave_topk(key, k, lane);
+  const bool per_wave = (long)nb * 4 * k <= 256;
+  if (nb > 1 && !per_wave) {
+    if (lane < k) sl[wave][lane] = own;
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) key[w] = lane < k ? sl[w][lane] : 0;
+      own = wave_topk(key, k, lane);
+    }
+  }
+  const long total = (long)nb * (per_wave ? 4 : 1) * k;
+  uint64_t* all = lists + (long)q * total;
+  if (nb > 1) {
+    const long at = per_wave ? (long)blockIdx.x * 4 + wave : (long)blockIdx.x;
+    if (lane < k && (per_wave || wave == 0))
+      __hip_atomic_store(&all[at * k + lane], own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    if (tid == 0) s_arrived = __hip_atomic_fetch_add(&done[q], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (s_arrived != (uint32_t)nb - 1) return;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  } else {
+    if (lane < k) sl[wave][lane] = own;
+    __syncthreads();
+  }
+  uint64_t best = 0;  // wave 0, lane r: the r-th best
+  if (nb == 1 || total <= 256) {  // four keys per lane are all there are
+    if (wave != 0) return;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (nb == 1)
+        key[u] = lane < k ? sl[u][lane] : 0;
+      else
+        key[u] = 64 * u + lane < total ? __hip_atomic_load(&all[64 * u + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    }
+    best = wave_topk(key, k, lane);
+  } else {
+    // every wave merges its share of the lists into its own k best, 192 new keys at a time beside the 64 it may hold
+    uint64_t run = 0;
+    for (long i0 = (long)wave * 192; i0 < total; i0 += 4 * 192) {
+      key[0] = run;
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        const long i = i0 + 64 * u + lane;
+        key[u + 1] = i < total ? __hip_atomic_load(&all[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+      }
+      run = wave_topk(key, k, lane);
+    }
+    if (lane < k) sl[wave][lane] = run;
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) key[w] = lane < k ? sl[w][lane] : 0;
+      best = wave_topk(key, k, lane);
+    }
+  }
+  if (wave == 0 && lane < k) {
+    const float sc = key_score(best);
+    out_idx[(long)q * k + lane] = key_row(best);
+    out_score[(long)q * k + lane] = sc;
+    if (lane == 0) out_hit[q] = (best != 0 && sc >= tau) ? 1 : 0;
+  }
+}
+
+// Final scores alone, for k > 64
 __global__ __launch_bounds__(256) void lookup_batch_final_kernel(const float* __restrict__ part_dot,
                                                                  const float* __restrict__ part_cc,
                                                                  const float* __restrict__ queries,
@@ -205,7 +414,7 @@ __global__ __launch_bounds__(256) void lookup_batch_final_kernel(const float* __
   }
 }
 
-// One workgroup per query: k rounds over its final scores, each picking the best entry that comes after the
+// k > 64, or an empty cache. One workgroup per query: k rounds over its final scores, each picking the best entry that comes after the
 // previous winner in the order (score descending, index ascending). REG: the scores of a thread live in registers
 // (N <= 8 * 1024), else they are re-read from `scores`.
 template <bool REG>
@@ -215,8 +424,6 @@ __global__ __launch_bounds__(1024) void lookup_topk_kernel(const float* __restri
   constexpr int R = 8;
   __shared__ float sv[2][16];
   __shared__ int si[2][16];  // N < 2^31 entries per call
-  __shared__ float cv[16][kWaveK];  // small k: the kWaveK best of every wave, best first
-  __shared__ int ci[16][kWaveK];
   const int q = blockIdx.x;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const float* sc = scores + (long)q * Npad;
@@ -227,82 +434,6 @@ __global__ __launch_bounds__(1024) void lookup_topk_kernel(const float* __restri
     mine[u] = (REG && j < N) ? sc[j] : -INFINITY;
   }
   unsigned taken = 0;  // REG: bit u set = this thread's entry u has been output
-  if (k <= kWaveK) {
-    // Small k without a workgroup barrier per position: every wave first lists the k best of ITS entries (rounds of
-    // in-wave exchanges only), then the first wave merges the 16 sorted lists. The k best overall are among them.
-    float ps_w = INFINITY;
-    int pj_w = -1;
-    for (int r = 0; r < k; ++r) {
-      float best = -INFINITY;
-      int bi = -1;
-      if (REG) {
-#pragma unroll
-        for (int u = 0; u < R; ++u) {
-          const int j = tid + 1024 * u;
-          if (j < N && !(taken & (1u << u)) && (bi < 0 || mine[u] > best)) {
-            best = mine[u];
-            bi = j;
-          }
-        }
-      } else {
-        for (long j = tid; j < N; j += 1024) {
-          const float v = sc[j];
-          const bool eligible = r == 0 || v < ps_w || (v == ps_w && j > pj_w);
-          if (eligible && (bi < 0 || v > best)) {
-            best = v;
-            bi = (int)j;
-          }
-        }
-      }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        const float ob = __shfl_xor(best, o, 64);
-        const int oi = __shfl_xor(bi, o, 64);
-        if (oi >= 0 && (bi < 0 || ob > best || (ob == best && oi < bi))) {
-          best = ob;
-          bi = oi;
-        }
-      }
-      if (lane == 0) {
-        cv[wave][r] = best;
-        ci[wave][r] = bi;
-      }
-      ps_w = best;
-      pj_w = bi;
-      if (REG && bi >= 0 && (bi & 1023) == tid) taken |= 1u << (unsigned)(bi >> 10);
-      if (bi < 0) {  // this wave's entries are used up: the rest of its list is empty
-        for (int rr = r + 1 + lane; rr < k; rr += 64) ci[wave][rr] = -1;
-        break;
-      }
-    }
-    __syncthreads();
-    if (wave == 0) {
-      int head = 0;  // lanes 0..15: position in the list of wave `lane`
-      for (int r = 0; r < k; ++r) {
-        int i = (lane < 16 && head < k) ? ci[lane][head] : -1;
-        float b = i >= 0 ? cv[lane][head] : -INFINITY;
-        const int mine_i = i;
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) {
-          const float ob = __shfl_xor(b, o, 64);
-          const int oi = __shfl_xor(i, o, 64);
-          if (oi >= 0 && (i < 0 || ob > b || (ob == b && oi < i))) {
-            b = ob;
-            i = oi;
-          }
-        }
-        b = __shfl(b, 0, 64);
-        i = __shfl(i, 0, 64);
-        if (lane == 0) {
-          out_idx[(long)q * k + r] = i;
-          out_score[(long)q * k + r] = i >= 0 ? b : -INFINITY;
-          if (r == 0) out_hit[q] = (i >= 0 && b >= tau) ? 1 : 0;
-        }
-        if (i >= 0 && mine_i == i) ++head;  // the winner's list moves on
-      }
-    }
-    return;
-  }
   float ps = INFINITY;
   int pj = -1;
   for (int r = 0; r < k; ++r) {
@@ -429,20 +560,31 @@ int32_t chorus_cache_lookup_batch(const float* cache_emb, int64_t N, int32_t d, 
     const int QP = Qc > 16 ? 32 : 16;
     BatchWs w = carve_batch((long)N, d, Q > 32 ? 32 : Q, ws);
     const float* qs = queries + (long)q0 * d;
+    const long Npad = (long)p.tiles * kBR;
+    const long nb = (N + 1023) / 1024;  // row blocks of the selection
+    const bool lists_fit = k <= kWaveK;
+    // the waves' lists take the place of the scores (128 bytes a row against at most 64 a row of a block), the arrival
+    // counts stand behind them; a single row block needs neither
+    uint64_t* lists = reinterpret_cast<uint64_t*>(w.scores);
+    uint32_t* done = lists_fit && nb > 1 ? reinterpret_cast<uint32_t*>(lists + nb * 4 * 32 * kWaveK) : nullptr;
     if (N > 0) {
-      dim3 grid((unsigned)p.tiles, (unsigned)p.KS);
+      const dim3 grid((unsigned)p.tiles, (unsigned)p.KS);
       if (QP == 32)
         hipLaunchKernelGGL(lookup_batch_scores_kernel<2>, grid, dim3(256), 0, s, cache_emb, qs, w.part_dot, w.part_cc,
-                           (long)N, d, Qc, p.chunks_per_slice);
+                           (long)N, d, Qc, p.chunks_per_slice, done);
       else
         hipLaunchKernelGGL(lookup_batch_scores_kernel<1>, grid, dim3(256), 0, s, cache_emb, qs, w.part_dot, w.part_cc,
-                           (long)N, d, Qc, p.chunks_per_slice);
+                           (long)N, d, Qc, p.chunks_per_slice, done);
       CHORUS_LAUNCH_CHECK();
-    }
-    const long Npad = (long)p.tiles * kBR;
-    if (N > 0) {
-      hipLaunchKernelGGL(lookup_batch_final_kernel, dim3((unsigned)((N + 1023) / 1024), (unsigned)Qc), dim3(256), 0, s,
-                         w.part_dot, w.part_cc, qs, w.scores, (long)N, Npad, d, QP, p.KS);
+      if (lists_fit) {
+        hipLaunchKernelGGL(lookup_batch_select_kernel, dim3((unsigned)nb, (unsigned)Qc), dim3(256), 0, s, w.part_dot, w.part_cc,
+                           qs, lists, done, (long)N, Npad, d, QP, p.KS, k, tau, out_index + (long)q0 * k,
+                           out_score + (long)q0 * k, out_hit + q0);
+        CHORUS_LAUNCH_CHECK();
+        continue;
+      }
+      hipLaunchKernelGGL(lookup_batch_final_kernel, dim3((unsigned)nb, (unsigned)Qc), dim3(256), 0, s, w.part_dot, w.part_cc,
+                         qs, w.scores, (long)N, Npad, d, QP, p.KS);
       CHORUS_LAUNCH_CHECK();
     }
     if (N <= 8 * 1024)

@@ -273,3 +273,31 @@ def test_lookup_batch_shapes(N, d, Q, k):
     queries = np.stack([synth.cache_query(cache, seed=1, near=(N // 3 + 17 * t) % N if t % 4 else None, trial=t)
                         for t in range(Q)])
     _check_topk(cache, queries, 0.75, k)
+
+
+@pytest.mark.parametrize("N,k", [(1024, 8), (1025, 9), (2049, 64), (2100, 1), (9000, 8), (9000, 9), (9000, 64), (9000, 65), (70001, 3)])
+def test_lookup_batch_selection(N, k):
+    """The selection's own edges: one and several row blocks, lists per wave and per workgroup, rounds (k <= 8) and the
+    sort, lists and the pass with scores (k > 64); many equal scores, rows of zero norm and scores of either sign."""
+    print(f"[case] lookup_batch selection N={N} k={k}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + k)
+    d = 64
+    base = torch.randn(97, d, device=DEV, generator=g)
+    cache = base[torch.randint(0, 97, (N,), device=DEV, generator=g)].contiguous()  # a hundred different scores, ties by index
+    cache[::13] = torch.randn(len(cache[::13]), d, device=DEV, generator=g)
+    cache[5] = 0.0
+    queries = torch.cat([torch.randn(2, d, device=DEV, generator=g), base[3:4], torch.zeros(1, d, device=DEV)])
+    idx, sc, hit = P.chorus_cache_lookup_batch(cache, queries, 0.75, k)
+
+    s64 = (queries.double() @ cache.double().T) / cache.double().norm(dim=1) / queries.double().norm(dim=1, keepdim=True)
+    for q in range(3):
+        order = torch.argsort(torch.nan_to_num(s64[q], nan=-9.0), descending=True, stable=True).cpu()
+        got_i, got_s = idx[q].cpu().long(), sc[q].double().cpu()
+        assert len(set(got_i.tolist())) == min(k, N)
+        want = torch.nan_to_num(s64[q], nan=-math.inf).cpu()
+        assert (got_s - want[order[:k]]).abs().max() < 1e-6          # position by position
+        assert (got_s - want[got_i]).abs().max() < 1e-6              # and each score is its row's
+        equal = got_s[1:] == got_s[:-1]
+        assert bool((got_i[1:][equal] > got_i[:-1][equal]).all())    # equal scores by index
+        assert int(hit[q]) == int(got_s[0] >= 0.75)
+    assert idx[3].tolist() == list(range(k)) and bool(torch.isneginf(sc[3]).all()) and int(hit[3]) == 0
