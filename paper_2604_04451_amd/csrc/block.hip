@@ -6,6 +6,7 @@
 #include "chorus_ops.h"
 #include "common.h"
 #include "gemm.h"
+#include "norms.h"
 
 namespace chorus {
 namespace {
@@ -170,8 +171,9 @@ int32_t project_text_kv(const chorus_block_shape& sh, const chorus_block_weights
   }
   {
     ProfScope p(CHORUS_PROF_NORM, s);
-    CHK(chorus_qk_norm_rope(tkv, 2L * D, w->g_ck, kc, Lt, LtPad, H, dh, nullptr, sh.gT, sh.gH, sh.gW, 0, 1.0f, stream));
-    CHK(chorus_v_transpose(tkv + D, 2L * D, vct, Lt, LtPad, D, stream));
+    if (!w->g_ck || !aligned16(w->g_ck)) return CHORUS_E_ARG;
+    CHK(attn_prepare(nullptr, tkv, tkv + D, 2L * D, nullptr, w->g_ck, nullptr, kc, vct, Lt, LtPad, H, dh, nullptr, sh.gH, sh.gW, 0,
+                     1.0f, stream));
   }
   return CHORUS_OK;
 }
@@ -214,10 +216,9 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   const bool q_prescaled = CHORUS_ATTENTION_LONG_KEYS(Ls, Lpad);
   {
     ProfScope p(CHORUS_PROF_NORM, s);
-    CHK(chorus_qk_norm_rope(b.qkv, 3L * D, w->g_q, b.qh, Ls, Lpad, H, dh, token_idx, sh.gT, sh.gH, sh.gW, 1,
-                            q_prescaled ? CHORUS_ATTENTION_Q_PRESCALE(dh) : 1.0f, stream));
-    CHK(chorus_qk_norm_rope(b.qkv + D, 3L * D, w->g_k, b.kh, Ls, Lpad, H, dh, token_idx, sh.gT, sh.gH, sh.gW, 1, 1.0f, stream));
-    CHK(chorus_v_transpose(b.qkv + 2 * D, 3L * D, b.vt, Ls, Lpad, D, stream));
+    if (!w->g_q || !w->g_k || !aligned16(w->g_q) || !aligned16(w->g_k)) return CHORUS_E_ARG;
+    CHK(attn_prepare(b.qkv, b.qkv + D, b.qkv + 2 * D, 3L * D, w->g_q, w->g_k, b.qh, b.kh, b.vt, Ls, Lpad, H, dh, token_idx, sh.gH,
+                     sh.gW, 1, q_prescaled ? CHORUS_ATTENTION_Q_PRESCALE(dh) : 1.0f, stream));
   }
   // 4. self-attention over exactly the Ls rows, output projection, gated residual
   {

@@ -4,6 +4,7 @@
 //  - V transpose into the key-contiguous layout the attention kernel reads
 #include "chorus_ops.h"
 #include "common.h"
+#include "norms.h"
 
 namespace chorus {
 namespace {
@@ -101,58 +102,38 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
   }
 }
 
-// One wave per token row (rows >= L up to Lpad are written as zeros). Lanes own
-// 8-element chunks; chunk c covers dims [8c, 8c+8) of the D-wide row, inside one head.
-// NCH > 0: D == 512 * NCH and the row lives in registers: its loads are issued first, the rotation
-// angles are computed while they are in flight, and the row is read from HBM once. NCH == 0: any D % 8 == 0,
-// the row is read again (from cache) for the second pass.
+// Rotation angles of one token into the wave's LDS rows (cos, sin): they depend on the pair index inside a head only,
+// dh / 2 <= 64 of them.
+__device__ __forceinline__ void rope_angles(float* s_cos, float* s_sin, long n, int dh, int gH, int gW, int lane) {
+  const int pw = (int)(n % gW), phh = (int)((n / gW) % gH), pt = (int)(n / ((long)gW * gH));
+  const int s6 = dh / 6;
+  const int g0 = dh - 4 * s6, g1 = 2 * s6;
+  if (lane < dh / 2) {
+    const int d = 2 * lane;
+    int off, g, pos;
+    if (d < g0) { off = 0; g = g0; pos = pt; }
+    else if (d < g0 + g1) { off = g0; g = g1; pos = phh; }
+    else { off = g0 + g1; g = g1; pos = pw; }
+    const float expo = -(float)(d - off) / (float)g;     // -2p/g
+    const float freq = exp2f(expo * 13.287712379549449f);  // 10000^expo
+    float sn, cs;
+    sincosf((float)pos * freq, &sn, &cs);
+    s_cos[lane] = cs;
+    s_sin[lane] = sn;
+  }
+  __builtin_amdgcn_wave_barrier();
+}
+
+// One wave, one token row: RMSNorm over the full width, gain, optional rotation, head-major store. Lanes own 8-element
+// chunks; chunk c covers dims [8c, 8c+8) of the D-wide row, inside one head. NCH > 0: D == 512 * NCH and the row lives
+// in registers (rv, loaded by the caller ahead of the angles). NCH == 0: any D % 8 == 0, the row is read again (from
+// cache) for the second pass.
 template <int NCH>
-__global__ __launch_bounds__(256) void qk_norm_rope_kernel(const uint16_t* __restrict__ in, long ld,
-                                                           const float* __restrict__ gain, uint16_t* __restrict__ out,
-                                                           long L, long Lpad, int H, int dh,
-                                                           const int* __restrict__ token_idx, int gH, int gW,
-                                                           int rope, float out_scale) {
-  __shared__ float s_cos[4][64];
-  __shared__ float s_sin[4][64];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long row = (long)blockIdx.x * 4 + wave;
-  if (row >= Lpad) return;
-  const int D = H * dh;
+__device__ __forceinline__ void norm_rope_row(const uint16_t* __restrict__ r, const u32x4 (&rv)[NCH > 0 ? NCH : 1],
+                                              const float* __restrict__ gain, uint16_t* __restrict__ out, long row, long Lpad,
+                                              int D, int dh, int rope, const float* s_cos, const float* s_sin, float out_scale,
+                                              int lane) {
   const int nchunk = D >> 3;
-  if (row >= L) {
-    for (int c = lane; c < nchunk; c += 64) {
-      int head = (c * 8) / dh, d0 = (c * 8) % dh;
-      *reinterpret_cast<uint4*>(out + ((long)head * Lpad + row) * dh + d0) = make_uint4(0, 0, 0, 0);
-    }
-    return;
-  }
-  const uint16_t* r = in + row * ld;
-  u32x4 rv[NCH > 0 ? NCH : 1];
-  if (NCH > 0) {
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) rv[i] = *reinterpret_cast<const u32x4*>(r + (lane + 64 * i) * 8);
-  }
-  if (rope) {
-    // rotation angles depend on the pair index inside a head only: dh/2 <= 64 of them
-    long n = token_idx ? (long)token_idx[row] : row;
-    int pw = (int)(n % gW), phh = (int)((n / gW) % gH), pt = (int)(n / ((long)gW * gH));
-    const int s6 = dh / 6;
-    const int g0 = dh - 4 * s6, g1 = 2 * s6;
-    if (lane < dh / 2) {
-      int d = 2 * lane;
-      int off, g, pos;
-      if (d < g0) { off = 0; g = g0; pos = pt; }
-      else if (d < g0 + g1) { off = g0; g = g1; pos = phh; }
-      else { off = g0 + g1; g = g1; pos = pw; }
-      float expo = -(float)(d - off) / (float)g;           // -2p/g
-      float freq = exp2f(expo * 13.287712379549449f);       // 10000^expo
-      float sn, cs;
-      sincosf((float)pos * freq, &sn, &cs);
-      s_cos[wave][lane] = cs;
-      s_sin[wave][lane] = sn;
-    }
-    __builtin_amdgcn_wave_barrier();
-  }
   // pass 1: mean of squares
   float ss = 0.f;
   if (NCH > 0) {
@@ -194,7 +175,7 @@ __global__ __launch_bounds__(256) void qk_norm_rope_kernel(const uint16_t* __res
       float a = __uint_as_float(w[k] << 16) * rstd * gv[2 * k];
       float b = __uint_as_float(w[k] & 0xffff0000u) * rstd * gv[2 * k + 1];
       if (rope) {
-        float cs = s_cos[wave][(d0 >> 1) + k], sn = s_sin[wave][(d0 >> 1) + k];
+        float cs = s_cos[(d0 >> 1) + k], sn = s_sin[(d0 >> 1) + k];
         float ra = a * cs - b * sn, rb = a * sn + b * cs;
         a = ra;
         b = rb;
@@ -205,15 +186,52 @@ __global__ __launch_bounds__(256) void qk_norm_rope_kernel(const uint16_t* __res
   }
 }
 
+template <int NCH>
+__device__ __forceinline__ void load_row(u32x4 (&rv)[NCH > 0 ? NCH : 1], const uint16_t* __restrict__ r, int lane) {
+  if (NCH > 0) {
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) rv[i] = *reinterpret_cast<const u32x4*>(r + (lane + 64 * i) * 8);
+  }
+}
+
+__device__ __forceinline__ void zero_row(uint16_t* __restrict__ out, long row, long Lpad, int D, int dh, int lane) {
+  for (int c = lane; c < (D >> 3); c += 64) {
+    const int head = (c * 8) / dh, d0 = (c * 8) % dh;
+    *reinterpret_cast<uint4*>(out + ((long)head * Lpad + row) * dh + d0) = make_uint4(0, 0, 0, 0);
+  }
+}
+
+// One wave per token row (rows >= L up to Lpad are written as zeros). The row's loads are issued first, the rotation
+// angles are computed while they are in flight, and the row is read from HBM once (NCH > 0).
+template <int NCH>
+__global__ __launch_bounds__(256) void qk_norm_rope_kernel(const uint16_t* __restrict__ in, long ld,
+                                                           const float* __restrict__ gain, uint16_t* __restrict__ out,
+                                                           long L, long Lpad, int H, int dh,
+                                                           const int* __restrict__ token_idx, int gH, int gW,
+                                                           int rope, float out_scale) {
+  __shared__ float s_cos[4][64];
+  __shared__ float s_sin[4][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const long row = (long)blockIdx.x * 4 + wave;
+  if (row >= Lpad) return;
+  const int D = H * dh;
+  if (row >= L) {
+    zero_row(out, row, Lpad, D, dh, lane);
+    return;
+  }
+  const uint16_t* r = in + row * ld;
+  u32x4 rv[NCH > 0 ? NCH : 1];
+  load_row<NCH>(rv, r, lane);
+  if (rope) rope_angles(s_cos[wave], s_sin[wave], token_idx ? (long)token_idx[row] : row, dh, gH, gW, lane);
+  norm_rope_row<NCH>(r, rv, gain, out, row, Lpad, D, dh, rope, s_cos[wave], s_sin[wave], out_scale, lane);
+}
+
 // Tile transpose: in[token][dim] -> out[dim][pos], 64 tokens x 64 dims per workgroup.
 // Inside every group of 16 tokens the output position p = 8c + 4u + i holds token
 // 8u + 4c + i: that is the order in which a lane of the attention kernel holds its
 // probabilities after the QK^T MFMA, so its V operand is one 16-byte read.
-__global__ __launch_bounds__(256) void v_transpose_kernel(const uint16_t* __restrict__ in, long ld,
-                                                          uint16_t* __restrict__ out, long L, long Lpad) {
-  __shared__ uint16_t tile[64][64 + 2];
-  const long t0 = (long)blockIdx.x * 64;
-  const int d0 = blockIdx.y * 64;
+__device__ __forceinline__ void transpose_tile(uint16_t (&tile)[64][64 + 2], const uint16_t* __restrict__ in, long ld,
+                                               uint16_t* __restrict__ out, long L, long Lpad, long t0, int d0) {
   for (int q = threadIdx.x; q < 512; q += 256) {
     int tok = q >> 3, ch = q & 7;
     uint4 u = make_uint4(0, 0, 0, 0);
@@ -242,7 +260,72 @@ __global__ __launch_bounds__(256) void v_transpose_kernel(const uint16_t* __rest
   }
 }
 
+__global__ __launch_bounds__(256) void v_transpose_kernel(const uint16_t* __restrict__ in, long ld,
+                                                          uint16_t* __restrict__ out, long L, long Lpad) {
+  __shared__ uint16_t tile[64][64 + 2];
+  transpose_tile(tile, in, ld, out, L, Lpad, (long)blockIdx.x * 64, blockIdx.y * 64);
+}
+
+// What stands between a projection and attention, in one launch: the first row_blocks workgroups normalise (and rotate)
+// four tokens each, a wave the query row, if there is one, and the key row of a token, whose rotation angles are computed
+// once; the others transpose a tile of V. HBM-bound where the sequence is long; where it is short each of the launches
+// that this replaces took longer to start than to run (128 tokens of width 256: 3.6 + 3.6 + 2.8 us and two gaps).
+template <int NCH>
+__global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
+                                                           const uint16_t* __restrict__ v, long ld,
+                                                           const float* __restrict__ gain_q, const float* __restrict__ gain_k,
+                                                           uint16_t* __restrict__ qh, uint16_t* __restrict__ kh,
+                                                           uint16_t* __restrict__ vt, long L, long Lpad, int H, int dh,
+                                                           const int* __restrict__ token_idx, int gH, int gW, int rope,
+                                                           float q_scale, int row_blocks, int v_tiles) {
+  __shared__ union {
+    struct {
+      float cos[4][64], sin[4][64];
+    } rot;
+    uint16_t tile[64][64 + 2];
+  } sm;
+  if ((int)blockIdx.x >= row_blocks) {
+    const int b = blockIdx.x - row_blocks;
+    transpose_tile(sm.tile, v, ld, vt, L, Lpad, (long)(b % v_tiles) * 64, b / v_tiles * 64);
+    return;
+  }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, D = H * dh;
+  const long row = (long)blockIdx.x * 4 + wave;
+  if (row >= Lpad) return;
+  if (row >= L) {
+    if (q) zero_row(qh, row, Lpad, D, dh, lane);
+    zero_row(kh, row, Lpad, D, dh, lane);
+    return;
+  }
+  u32x4 rq[NCH > 0 ? NCH : 1], rk[NCH > 0 ? NCH : 1];
+  if (q) load_row<NCH>(rq, q + row * ld, lane);
+  load_row<NCH>(rk, k + row * ld, lane);
+  if (rope) rope_angles(sm.rot.cos[wave], sm.rot.sin[wave], token_idx ? (long)token_idx[row] : row, dh, gH, gW, lane);
+  if (q)
+    norm_rope_row<NCH>(q + row * ld, rq, gain_q, qh, row, Lpad, D, dh, rope, sm.rot.cos[wave], sm.rot.sin[wave], q_scale, lane);
+  norm_rope_row<NCH>(k + row * ld, rk, gain_k, kh, row, Lpad, D, dh, rope, sm.rot.cos[wave], sm.rot.sin[wave], 1.0f, lane);
+}
+
 }  // namespace
+
+int32_t attn_prepare(const uint16_t* q, const uint16_t* k, const uint16_t* v, long ld, const float* gain_q, const float* gain_k,
+                     uint16_t* qh, uint16_t* kh, uint16_t* vt, long L, long Lpad, int H, int dh, const int32_t* token_idx, int gH,
+                     int gW, int rope, float q_scale, void* stream) {
+  const int D = H * dh;
+  const long row_blocks = (Lpad + 3) / 4, v_tiles = Lpad / 64, blocks = row_blocks + v_tiles * (D / 64);
+  if (blocks > 0x7fffffffL) return CHORUS_E_SHAPE;
+#define PREPARE(NCH)                                                                                                       \
+  hipLaunchKernelGGL(attn_prepare_kernel<NCH>, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, q, k, v, ld, gain_q, \
+                     gain_k, qh, kh, vt, L, Lpad, H, dh, token_idx, gH, gW, rope, q_scale, (int)row_blocks, (int)v_tiles)
+  if (D == 1536) PREPARE(3);
+  else if (D == 5120) PREPARE(10);
+  else if (D == 512) PREPARE(1);
+  else PREPARE(0);
+#undef PREPARE
+  CHORUS_LAUNCH_CHECK();
+  return CHORUS_OK;
+}
+
 }  // namespace chorus
 
 using namespace chorus;

@@ -66,3 +66,45 @@ def test_block_ffn_in_slices(Ls, Lt, F):
     check(outs[0], ref, "x", max_abs=np.abs(ref).max() * 2 ** -6, rel_l2=1e-2)
     _, rel = errs(outs[0] - inp["x"], ref - inp["x"])
     assert rel <= 2e-2
+
+
+@pytest.mark.parametrize("D,H,Lt", [(256, 4, 1), (256, 4, 65), (512, 8, 63), (512, 4, 64), (1536, 12, 130), (320, 5, 17)])
+def test_text_kv_equals_the_single_operations(D, H, Lt):
+    """Keys and values prepared in one launch against the three calls that it stands for, bit for bit (rows and tiles at
+    their edges, padding rows included)."""
+    print(f"[case] text kv D={D} H={H} Lt={Lt}", flush=True)
+    dh, g = D // H, torch.Generator(device=DEV).manual_seed(Lt)
+    rnd = lambda *s: torch.randn(*s, device=DEV, generator=g)  # noqa: E731
+    t = {n: torch.zeros(1, device=DEV) for n in B._W_FIELDS}
+    t.update(w_ckv=(rnd(2 * D, D) * 0.05).bfloat16(), b_ckv=rnd(2 * D), g_ck=rnd(D))
+    w = B.DeviceBlock(t, B.BlockWeights(**{n: t[n].data_ptr() for n in B._W_FIELDS}))
+    ctx, pad = rnd(Lt, D).bfloat16(), -(-Lt // 64) * 64
+    kv = B.chorus_text_kv_project(P.make_block_shape(D, H, dh, 64, Lt, (1, 1, 1)), w, ctx)
+    proj = torch.empty(Lt, 2 * D, dtype=torch.bfloat16, device=DEV)
+    B.chorus_gemm_bf16(ctx, t["w_ckv"], B.EPI_BF16, proj, t["b_ckv"])
+    k = torch.empty(H, pad, dh, dtype=torch.bfloat16, device=DEV)
+    vt = torch.empty(D, pad, dtype=torch.bfloat16, device=DEV)
+    B.chorus_qk_norm_rope(proj, 0, t["g_ck"], k, Lt, H, dh, None, (1, 1, 1), False)
+    B.chorus_v_transpose(proj, D, vt, Lt)
+    half = kv.numel() // 2
+    assert torch.equal(kv[:k.numel() * 2], k.view(torch.uint8).flatten())
+    assert torch.equal(kv[half:half + vt.numel() * 2], vt.view(torch.uint8).flatten())
+
+
+@pytest.mark.parametrize("D,H,Ls", [(256, 4, 1), (512, 4, 67), (1536, 12, 300), (320, 5, 250)])
+def test_block_queries_and_keys_rotate_alike(D, H, Ls):
+    """Self-attention alone (the other branches' output weights are zero) on a scattered selection: queries and keys of a
+    token share one set of rotation angles, against the oracle."""
+    print(f"[case] block rotation D={D} H={H} Ls={Ls}", flush=True)
+    bs = dataclasses.replace(synth.SHAPES["c1"], D=D, H=H, dh=D // H, F=64, Lt=8, grid=(6, 8, 8), latent_std=1.0)
+    w = synth.stress_block_weights(bs, 4)
+    for n in ("w_co", "b_co", "w_2", "b_2"):
+        w[n] = np.zeros_like(w[n])
+    inp = synth.block_inputs(bs, 4, L=Ls)
+    idx = np.sort(synth.stream(4, "rot.idx").permutation(bs.L)[:Ls]).astype(np.int32)
+    x = dev_f32(inp["x"])
+    P.chorus_dit_block_step(P.make_block_shape(bs.D, bs.H, bs.dh, bs.F, bs.Lt, bs.grid), P.upload_block_weights(w), x, Ls,
+                            torch.from_numpy(idx).to(DEV), dev_bf16(inp["text_ctx"]), dev_f32(inp["t_mod"]), None, 1.0)
+    ref = O.dit_block(inp["x"], w, bs, inp["text_ctx"], inp["t_mod"], token_idx=idx)
+    _, rel = errs(host(x) - inp["x"], ref - inp["x"])
+    assert rel <= 2e-2, rel
