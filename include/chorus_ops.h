@@ -84,8 +84,9 @@ int32_t chorus_v_transpose(const uint16_t* in, int64_t ld, uint16_t* out, int64_
  *   col_scale dev [Lk] fp32, 16-byte aligned, or NULL
  * dh in {64,128}; LkPad % 64 == 0, LkPad >= Lk >= 1; rows/cols beyond Lq/Lk are padding
  * (finite values).
- * variant: 0 = the default choice (128-key tiles on 16x16x32 MFMAs when
- * CHORUS_ATTENTION_LONG_KEYS(Lk, LkPad): LkPad % 128 == 0 and Lk >= 512; else 64-key tiles on 32x32x16 MFMAs);
+ * variant: 0 = the default choice (128-key tiles on 16x16x32 MFMAs when CHORUS_ATTENTION_LONG_KEYS(Lk, LkPad):
+ * LkPad % 128 == 0 and Lk >= 512, and on shorter keys padded to 128 where they are the faster; else 64-key tiles on
+ * 32x32x16 MFMAs);
  * 3 = 64-key tiles; 5 = 128-key tiles on
  * 16x16x32 MFMAs; 6 = as 5 for a Q that holds the queries already multiplied by log2(e) / sqrt(dh)
  * (CHORUS_ATTENTION_Q_PRESCALE(dh), applied in fp32 by the producer before its rounding to bf16): the same

@@ -3,9 +3,9 @@
 // Used for the block's 3-D self-attention (g = 1) and for the text cross-attention
 // with TGAA key amplification (Eq. 2: scaling key j by gamma_k scales logit column j).
 // Two kernels of one design: attention_pp_kernel on v_mfma_f32_32x32x16_bf16 (64-key
-// tiles: key sequences shorter than 512 or padded to 64), described first, and
-// attention_pp16_kernel on v_mfma_f32_16x16x32_bf16 (128-key tiles: self-attention and
-// the text cross-attention from 512 keys on), whose differences are described in front of it.
+// tiles: keys padded to 64 only, and many queries on few keys), described first, and
+// attention_pp16_kernel on v_mfma_f32_16x16x32_bf16 (128-key tiles: the rest, see
+// attention_wide_tiles), whose differences are described in front of it.
 // Both take the optional per-key logit factor.
 //
 // Work split: a workgroup of 8 waves owns 256 query rows of one head (32 per wave, held in
@@ -24,6 +24,7 @@
 // The running maximum is only refreshed when a tile exceeds it by more than 8
 // (in log2 units), which keeps exp2 arguments <= 8 and makes the accumulator
 // rescale rare; the final division by the row sum makes the result exact either way.
+#include "attention.h"
 #include "chorus_ops.h"
 #include "common.h"
 
@@ -309,6 +310,8 @@ __global__ __launch_bounds__(512, 2) void attention_pp_kernel(
 // cross-attention) a kernel name of their own, so that a kernel profile lists self- and cross-attention separately.
 // KIND 2 multiplies the logit of key j by col_scale[j] (TGAA's key amplification, Eq. 2, applied to the logit): the
 // S^T accumulators then start at zero and one multiply-add per logit applies the factor and, with PRE, the reference.
+// The factors of a tile come through LDS like its keys: read from memory where they are used, in pairs for want of
+// registers, they cost four memory latencies per tile (480 x 512 24.3 -> 15.5 us, 13104 x 512 73.6 -> 69.2).
 template <int DH, bool PRE, int RB, int KIND>
 __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ Vt,
@@ -329,6 +332,7 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   extern __shared__ __attribute__((aligned(16))) uint8_t smem_raw[];
   uint16_t* smk = reinterpret_cast<uint16_t*>(smem_raw);   // [2][KTL][KS]
   uint16_t* smv = smk + 2 * KTL * KS;                      // [2][DH][VS]
+  float* smc = reinterpret_cast<float*>(smv + 2 * DH * VS);  // [2][KTL]: the key factors of two tiles (CS)
 
   // this launch covers the tiles tile_base .. tile_base + gridDim.x - 1 of the H * n_qtiles of its tile size
   const int tile_id = tile_base + xcd_remap(blockIdx.x, gridDim.x);
@@ -399,6 +403,17 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
       *reinterpret_cast<u32x4*>(&smv[(buf * DH + row) * VS + ch * 8]) = rv[i];
     }
   };
+  // Key factors of a tile: a thread of the first two waves fetches one with the tile before and stores it in its MFMA
+  // phase, one barrier ahead of the softmax phase that reads it (the other group, half an iteration behind, then still
+  // reads the other buffer). Keys past the end get 1.
+  float rc = 1.f;
+  auto load_c = [&](int kt) {
+    const int key = kt * KTL + tid;
+    if (tid < KTL) rc = key < (int)Lk ? col_scale[key] : 1.0f;
+  };
+  auto store_c = [&](int buf) {
+    if (tid < KTL) smc[buf * KTL + tid] = rc;
+  };
   // LDS row of the K tile that fragment row lane % 16 of block kb stands for
   const int krow0 = 16 * (lq >> 3) + (lq & 7);
   f32x4 s[KB][RB];
@@ -421,13 +436,22 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
     }
   };
 
-  // prologue: K(0), V(0), K(1) into LDS; K(2), V(1) into the prefetch registers
-  load_k(0);
-  load_v(0);
-  store_k(0);
-  store_v(0);
-  if (ntiles > 1) {
-    load_k(1);
+  // prologue: K(0), V(0), K(1) into LDS, all requested before the first is stored
+  {
+    load_k(0);
+    load_v(0);
+    if constexpr (CS) load_c(0);
+    u32x4 r0[K_LD];
+#pragma unroll
+    for (int i = 0; i < K_LD; ++i) r0[i] = rk[i];
+    load_k(ntiles > 1 ? 1 : 0);
+#pragma unroll
+    for (int i = 0; i < K_LD; ++i) {
+      const int id = tid + NT * i, row = id / (DH / 8), ch = id % (DH / 8);
+      *reinterpret_cast<u32x4*>(&smk[row * KS + ch * 8]) = r0[i];
+    }
+    store_v(0);
+    if constexpr (CS) store_c(0);
     store_k(1);
   }
 #pragma unroll
@@ -443,20 +467,10 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
     // ================= VALU phase: softmax of tile j =================
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (CS) {
-      // the column factors of this tile are fetched and applied before the prefetch is issued: loads return in order,
-      // and the 32 registers they take are free again when the prefetch needs its own
-      const int key0 = j * KTL + 16 * (g >> 1) + 4 * (g & 1);
-      const int lk = (int)Lk;
+      const float* cfs = smc + (j & 1) * KTL + 16 * (g >> 1) + 4 * (g & 1);
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) {
-        const int key = key0 + 32 * (kb >> 1) + 8 * (kb & 1);
-        f32x4 cf;
-        if (key + 3 < lk) {
-          cf = *reinterpret_cast<const f32x4*>(col_scale + key);
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) cf[i] = key + i < lk ? col_scale[key + i] : 1.0f;
-        }
+        const f32x4 cf = *reinterpret_cast<const f32x4*>(cfs + 32 * (kb >> 1) + 8 * (kb & 1));
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -464,6 +478,7 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
             s[kb][rb][i] = PRE ? __builtin_fmaf(s[kb][rb][i], cf[i], -m_run[rb]) : s[kb][rb][i] * cf[i];
         if (kb % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // two factors in flight at a time: there are no registers for eight
       }
+      load_c(j + 1 < ntiles ? j + 1 : ntiles - 1);
       __builtin_amdgcn_sched_barrier(0);
     }
     // the global prefetch of the tiles that the next MFMA phase stores: K(j+2), V(j+1) (past the end the last tile again)
@@ -559,6 +574,7 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
     __builtin_amdgcn_s_setprio(1);
     store_k(j & 1);
     store_v((j + 1) & 1);
+    if constexpr (CS) store_c((j + 1) & 1);
     {
       const int vb = j & 1;
 #pragma unroll
@@ -619,7 +635,7 @@ template <int DH, bool PRE, int RB, int KIND>
 int32_t launch_attn_pp16_tiles(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* cs,
                                long Lq, long Lk, long LqPad, long LkPad, int H, long nqt, long tile_base, long ntile,
                                hipStream_t s) {
-  size_t smem = 2 * ((size_t)128 * (DH + 16) + (size_t)DH * (128 + 16)) * sizeof(uint16_t);
+  size_t smem = 2 * ((size_t)128 * (DH + 16) + (size_t)DH * (128 + 16)) * sizeof(uint16_t) + (KIND == 2 ? 2 * 128 * sizeof(float) : 0);
   auto kern = attention_pp16_kernel<DH, PRE, RB, KIND>;
   static DynLdsOnce once;  // the raised dynamic-LDS limit is a per-device property of the kernel
   CHK_STATUS(once.ensure(reinterpret_cast<const void*>(kern), (int)smem));
@@ -630,7 +646,8 @@ int32_t launch_attn_pp16_tiles(const uint16_t* Q, const uint16_t* K, const uint1
   return CHORUS_OK;
 }
 
-// 256 query rows per workgroup. One workgroup fits a CU, so a launch runs in rounds of as many workgroups as the device
+// Launches of at most half as many 256-row tiles as CUs run as workgroups of 128 rows throughout (1200 tokens, 12 heads:
+// 36.2 -> 24.8 us). Else 256 query rows per workgroup. One workgroup fits a CU, so a launch runs in rounds of as many workgroups as the device
 // has CUs. When the last round would be at most half full, its tiles run as workgroups of 128 rows instead (one block
 // of 16 rows per wave: the same K / V stream for half the arithmetic, 0.63-0.67 of a full workgroup's time), twice as
 // many of them, in a second launch behind the first: the partly filled round then takes two thirds of a full one.
@@ -643,6 +660,8 @@ int32_t launch_attn_pp16_kind(const uint16_t* Q, const uint16_t* K, const uint16
   int dev = 0, cus = 0;
   CHORUS_HIP(hipGetDevice(&dev));
   CHORUS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  if (2 * tiles <= cus)
+    return launch_attn_pp16_tiles<DH, PRE, 1, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, 2 * nqt, 0, 2 * tiles, s);
   const long tail = cus > 0 ? tiles % cus : 0;
   if (tiles > cus && tail > 0 && 2 * tail <= cus) {
     CHK_STATUS((launch_attn_pp16_tiles<DH, PRE, 2, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, nqt, 0, tiles - tail, s)));
@@ -677,6 +696,24 @@ int32_t launch_attn_pp(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt,
 }
 
 }  // namespace
+
+// Measured with 12 heads of 128 (microseconds, 64-key kernel / 128-key kernel; f: with the key factor):
+//   half tiles     480 x 480 20.4 / 13.7, 1200 x 77 12.6 / 9.6, 128 x 128 9.7 / 8.9: the 64-key kernel has no half tile
+//   f, any launch  3271 x 77 16.8 / 15.9, 13104 x 226 61.6 / 52.0: the factors come from LDS
+//   full tiles     13104 x 480 71.4 / 66.7, 13104 x 226 50.7 / 49.5, but 13104 x 128 40.3 / 41.4, 32760 x 16 69.8 / 84.9 (half of
+//                  the one tile is padding), and, where one round does not fill the chip, 3271 x 256 16.8 / 17.6
+bool attention_wide_tiles(long Lq, long Lk, long LkPad, int H, bool factor) {
+  if (LkPad % 128) return false;
+  if (Lk >= 512) return true;
+  if (Lk <= 64) return false;
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return false;
+  const long tiles = (Lq + 255) / 256 * H;
+  if (factor || 2 * tiles <= cus) return true;
+  return Lk > 128 && tiles > cus;
+}
+
 }  // namespace chorus
 
 using namespace chorus;
@@ -695,8 +732,7 @@ extern "C" int32_t chorus_attention(const uint16_t* Q, const uint16_t* K, const 
   if (!aligned16(Q) || !aligned16(K) || !aligned16(Vt) || !aligned16(O) || !aligned16(col_scale)) return CHORUS_E_ARG;
   hipStream_t s = (hipStream_t)stream;
   const bool cs = col_scale != nullptr;
-  // 128-key tiles on the 16x16x32 kernel when the keys are long enough and the padding allows
-  if (variant == 0) variant = CHORUS_ATTENTION_LONG_KEYS(Lk, LkPad) ? 5 : 3;
+  if (variant == 0) variant = attention_wide_tiles((long)Lq, (long)Lk, (long)LkPad, H, cs) ? 5 : 3;
   if (variant == 5 || variant == 6) {
     if (LkPad % 128) return CHORUS_E_SHAPE;
     if (variant == 6)
