@@ -11,38 +11,62 @@
 namespace chorus {
 namespace {
 
+// Feature i of [cos(t w), sin(t w)]
+__device__ __forceinline__ float sinusoid(float t, int i, int half) {
+  const int j = i < half ? i : i - half;
+  const float a = t * exp2f(-(float)j / (float)half * 13.287712379549449f);  // w = 10000^(-j/half)
+  float sn, cs;
+  sincosf(a, &sn, &cs);
+  return i < half ? cs : sn;
+}
+
+constexpr int kFeatureLds = 8192;  // more features than this (32 KB of LDS) are made in a launch of their own
+
 __global__ __launch_bounds__(256) void sinusoid_kernel(float t, int half, float* __restrict__ f) {
   const int i = blockIdx.x * 256 + threadIdx.x;
-  if (i >= half) return;
-  const float w = exp2f(-(float)i / (float)half * 13.287712379549449f);  // 10000^(-i/half)
-  float sn, cs;
-  sincosf(t * w, &sn, &cs);
-  f[i] = cs;
-  f[half + i] = sn;
+  if (i < 2 * half) f[i] = sinusoid(t, i, half);
 }
 
 // out[n] = sum_k W[n][k] act(x[k]) + b[n]; ACT: silu on the input vector. One wave per row n; K % 8 == 0.
-// out2 (optional) receives the same values (the two head rows).
-template <bool SILU_IN>
-__global__ __launch_bounds__(256) void gemv_bf16w_kernel(const uint16_t* __restrict__ W, const float* __restrict__ x,
+// out2 (optional) receives the same values (the two head rows). FEATURES: x is the sinusoidal features of t (K of them),
+// made by every workgroup for itself in LDS: one sine per thread instead of a launch in front of this one (4.8 us).
+template <bool SILU_IN, bool FEATURES>
+__global__ __launch_bounds__(256) void gemv_bf16w_kernel(const uint16_t* __restrict__ W, const float* __restrict__ x_in,
                                                          const float* __restrict__ b, float* __restrict__ out,
-                                                         float* __restrict__ out2, int N, int K) {
+                                                         float* __restrict__ out2, int N, int K, float t) {
+  extern __shared__ __attribute__((aligned(16))) float s_f[];  // [K] (FEATURES)
+  if constexpr (FEATURES) {
+    for (int i = threadIdx.x; i < K; i += 256) s_f[i] = sinusoid(t, i, K / 2);
+    __syncthreads();
+  }
+  const float* x = FEATURES ? s_f : x_in;
   const int lane = threadIdx.x & 63;
   const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (n >= N) return;
   const uint16_t* w = W + (long)n * K;
   float acc = 0.f;
-  for (int k = lane * 8; k < K; k += 64 * 8) {
-    const u32x4 u = *reinterpret_cast<const u32x4*>(w + k);
-    const f32x4 x0 = *reinterpret_cast<const f32x4*>(x + k);
-    const f32x4 x1 = *reinterpret_cast<const f32x4*>(x + k + 4);
-    float xv[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+  constexpr int U = 4;  // weight loads in flight per lane: they are what this kernel waits for
+  for (int k0 = lane * 8; k0 < K; k0 += U * 64 * 8) {
+    u32x4 u[U];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      float v = xv[j];
-      if (SILU_IN) v = v / (1.0f + __expf(-v));
-      const float wv = __uint_as_float((j & 1) ? (u[j >> 1] & 0xffff0000u) : (u[j >> 1] << 16));
-      acc = __builtin_fmaf(wv, v, acc);
+    for (int c = 0; c < U; ++c) {
+      const int k = k0 + c * 512;
+      u[c] = *reinterpret_cast<const u32x4*>(w + (k < K ? k : k0));
+    }
+#pragma unroll
+    for (int c = 0; c < U; ++c) {
+      const int k = k0 + c * 512;
+      if (k >= K) break;
+      const f32x4 x0 = *reinterpret_cast<const f32x4*>(x + k);
+      const f32x4 x1 = *reinterpret_cast<const f32x4*>(x + k + 4);
+      const float xv[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        float v = xv[j];
+        if (SILU_IN) v = v / (1.0f + __expf(-v));
+        const float wv = __uint_as_float((j & 1) ? (u[c][j >> 1] & 0xffff0000u) : (u[c][j >> 1] << 16));
+        acc = __builtin_fmaf(wv, v, acc);
+      }
     }
   }
   acc = wave_sum(acc);
@@ -76,18 +100,22 @@ int32_t chorus_time_mod(float t, int32_t freq_dim, int32_t D, const chorus_time_
   hipStream_t s = (hipStream_t)stream;
   float* f = (float*)ws;
   float* h = (float*)((uint8_t*)ws + align_up((size_t)freq_dim * 4, 256));
-  const int half = freq_dim / 2;
-  hipLaunchKernelGGL(sinusoid_kernel, dim3((unsigned)((half + 255) / 256)), dim3(256), 0, s, t, half, f);
-  CHORUS_LAUNCH_CHECK();
   // h = W1 f + b1;  e = W2 silu(h) + b2 -> both head rows;  t_mod = Wp silu(e) + bp
-  hipLaunchKernelGGL(gemv_bf16w_kernel<false>, dim3((unsigned)((D + 3) / 4)), dim3(256), 0, s, w->w_t1, f, w->b_t1, h,
-                     (float*)nullptr, D, freq_dim);
+  if (freq_dim <= kFeatureLds) {
+    hipLaunchKernelGGL((gemv_bf16w_kernel<false, true>), dim3((unsigned)((D + 3) / 4)), dim3(256), (size_t)freq_dim * 4, s, w->w_t1,
+                       (const float*)nullptr, w->b_t1, h, (float*)nullptr, D, freq_dim, t);
+  } else {
+    hipLaunchKernelGGL(sinusoid_kernel, dim3((unsigned)((freq_dim + 255) / 256)), dim3(256), 0, s, t, freq_dim / 2, f);
+    CHORUS_LAUNCH_CHECK();
+    hipLaunchKernelGGL((gemv_bf16w_kernel<false, false>), dim3((unsigned)((D + 3) / 4)), dim3(256), 0, s, w->w_t1, f, w->b_t1, h,
+                       (float*)nullptr, D, freq_dim, 0.f);
+  }
   CHORUS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(gemv_bf16w_kernel<true>, dim3((unsigned)((D + 3) / 4)), dim3(256), 0, s, w->w_t2, h, w->b_t2, t_head,
-                     t_head + D, D, D);
+  hipLaunchKernelGGL((gemv_bf16w_kernel<true, false>), dim3((unsigned)((D + 3) / 4)), dim3(256), 0, s, w->w_t2, h, w->b_t2,
+                     t_head, t_head + D, D, D, 0.f);
   CHORUS_LAUNCH_CHECK();
-  hipLaunchKernelGGL(gemv_bf16w_kernel<true>, dim3((unsigned)((6 * D + 3) / 4)), dim3(256), 0, s, w->w_tp, t_head, w->b_tp,
-                     t_mod, (float*)nullptr, 6 * D, D);
+  hipLaunchKernelGGL((gemv_bf16w_kernel<true, false>), dim3((unsigned)((6 * D + 3) / 4)), dim3(256), 0, s, w->w_tp, t_head,
+                     w->b_tp, t_mod, (float*)nullptr, 6 * D, D, 0.f);
   CHORUS_LAUNCH_CHECK();
   return CHORUS_OK;
 }
