@@ -133,3 +133,18 @@ def test_mask_pipeline_full_shape(name, Hp, Wp):
     np.testing.assert_array_equal(host(idx)[:Ls], O.region_compact(o_see.reshape(-1)))
     print(f"[info] base {o_base.mean():.3f} edit {o_edit.mean():.3f} see {o_see.mean():.3f} of the grid", flush=True)
     assert 0 < o_base.sum() < o_edit.sum() < o_see.sum() < o_see.size
+
+
+@pytest.mark.parametrize("L", [1, 3, 4, 1023, 1024, 1025, 4097, 75600, 81919, 81920, 81921, 300001])
+@pytest.mark.parametrize("offset", [0, 1, 4])
+def test_compact_tiles(L, offset):
+    """One launch up to 81920 sites, three beyond; masks on and off a 16- and a 4-byte boundary, any non-zero byte set."""
+    print(f"[case] compact L={L} offset={offset}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(L + offset)
+    buf = torch.randint(0, 3, (L + offset,), device="cuda", generator=g, dtype=torch.uint8) * 127
+    for mask in (buf[offset:], torch.zeros_like(buf)[offset:], torch.ones_like(buf)[offset:]):
+        idx = torch.full((L + 1,), -7, dtype=torch.int32, device="cuda")
+        idx, count = P.chorus_region_compact(mask, idx)
+        want = mask.nonzero()[:, 0].to(torch.int32)
+        n = int(count.cpu()[0])
+        assert n == want.numel() and torch.equal(idx[:n], want) and bool((idx[n:] == -7).all())
