@@ -1,14 +1,14 @@
-// bf16 MFMA GEMM with fused epilogues: C = epi(A W^T + bias), A [M,K], W [N,K],
-// both K-contiguous, fp32 accumulation with v_mfma_f32_32x32x16_bf16.
+// bf16 MFMA GEMM with fused epilogues: C = epi(A W^T + bias), A [M,K], W [N,K], both K-contiguous, fp32 accumulation.
 //
-// Workgroup = 4 waves, tile BM x BN x 64. Each k-step the A and W tiles go
-// global -> registers -> LDS (rows padded to 72 elements so the 16-byte operand
-// reads of 16 consecutive lanes fall in distinct banks) while the MFMAs of the
-// previous tile run. A wave owns a WM x WN sub-tile as (WM/32) x (WN/32) 32x32
-// accumulators. The W fragment is the MFMA's row operand and the activation fragment its
-// column operand, so lane l of a 32x32 accumulator holds ONE output row m = l%32 and the 16
-// output columns n = 4*(l/32) + 8*g + e (register 4g+e): four consecutive columns per
-// register group, which the epilogue moves as one 8-byte (bf16) or 16-byte (fp32) access.
+// Two families. `gemm_w16_kernel` (below) copies its tiles straight from global memory to LDS, four tile shapes, and is
+// what a product is run on; which shape, and whether K is cut into slices, is decided by `plan_gemm` at the end of the file.
+// `gemm_bf16_kernel` is the register-staged one, kept because it can be asked for by name (kernels 1 and 2): workgroup =
+// 4 waves, tile BM x BN x 64; each k-step the A and W tiles go global -> registers -> LDS (rows padded to 72 elements so
+// the 16-byte operand reads of 16 consecutive lanes fall in distinct banks) while the MFMAs (32x32x16) of the previous
+// tile run. A wave owns a WM x WN sub-tile as (WM/32) x (WN/32) 32x32 accumulators. The W fragment is the MFMA's row
+// operand and the activation fragment its column operand, so lane l of a 32x32 accumulator holds ONE output row m = l%32
+// and the 16 output columns n = 4*(l/32) + 8*g + e (register 4g+e): four consecutive columns per register group, which
+// the epilogue moves as one 8-byte (bf16) or 16-byte (fp32) access.
 #include <cmath>
 
 #include "chorus_ops.h"
@@ -335,36 +335,37 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const uint16_t* __res
 // a new home, at the price of several hundred accumulator moves per k-step.
 // ---------------------------------------------------------------------------
 
-// WB = 16 x 16 blocks along each side of a wave's quadrant: 8 (256 x 256 tiles), 4 (128 x 128) or 2 (64 x 64).
+// WBM, WBN = 16 x 16 blocks along the rows (M) and columns (N) of a wave's quadrant: 8, 8 (256 x 256 tiles), 4, 4 (128 x
+// 128), 2, 2 (64 x 64) or 4, 8 (128 x 256).
 // NST = stages in LDS: a step's loads are issued NST - 1 half-steps and more before its barrier. Two stages leave room for
 // two 128 x 128 workgroups on a compute unit, which then hide each other's waits; a launch with fewer tiles than units has
 // no second workgroup there, and three stages (96 KB) take its place: 1200 x 1536 x 8960 113 -> 72 us. Four or five
 // stages measured the same (73, 71 us): from three on the unit's L1, not the distance, sets the rate.
 //
 // bf16 (optionally GELU) epilogue of the 16x16 layout: 32 output rows at a time go through a private LDS region as
-// [32][16 WB] bf16 (row stride 16 WB + 8), then leave as full row segments of the quadrant (256 or 128 bytes).
-template <int WB> constexpr int e16_bf_stride() { return 16 * WB + 8; }
-template <int WB> constexpr int e16_bf_wave() { return 32 * e16_bf_stride<WB>(); }  // elements per wave
-template <int EPI, int WB>
+// [32][16 WBN] bf16 (row stride 16 WBN + 8), then leave as full row segments of the quadrant (256, 128 or 64 bytes).
+template <int WBN> constexpr int e16_bf_stride() { return 16 * WBN + 8; }
+template <int WBN> constexpr int e16_bf_wave() { return 32 * e16_bf_stride<WBN>(); }  // elements per wave
+template <int EPI, int WBM, int WBN>
 __device__ __forceinline__ void gemm16_epilogue_bf16(const f32x4 (&acc)[8][8], const EpiArgs& ep, uint16_t* cw, long m_wave0,
                                                      int n_wave0, long M, int N, int lane) {
-  constexpr int E16_BF_STRIDE = e16_bf_stride<WB>();
-  constexpr int LPR = 2 * WB, RPI = 64 / LPR;  // read-back: LPR lanes x 16 bytes per row, RPI rows per instruction
+  constexpr int E16_BF_STRIDE = e16_bf_stride<WBN>();
+  constexpr int LPR = 2 * WBN, RPI = 64 / LPR;  // read-back: LPR lanes x 16 bytes per row, RPI rows per instruction
   const int lj = lane & 15, lg = lane >> 4;
   const int rrow = lane / LPR, rcol = (lane % LPR) * 8;
-  float4 bias[WB];
+  float4 bias[WBN];
 #pragma unroll
-  for (int nb = 0; nb < WB; ++nb) {
+  for (int nb = 0; nb < WBN; ++nb) {
     const int n = n_wave0 + 16 * nb + 4 * lg;
     bias[nb] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (ep.bias && n < N) bias[nb] = *reinterpret_cast<const float4*>(ep.bias + n);
   }
 #pragma unroll
-  for (int mp = 0; mp < WB / 2; ++mp) {  // pairs of 16-row blocks
+  for (int mp = 0; mp < WBM / 2; ++mp) {  // pairs of 16-row blocks
 #pragma unroll
     for (int mh = 0; mh < 2; ++mh)
 #pragma unroll
-      for (int nb = 0; nb < WB; ++nb) {
+      for (int nb = 0; nb < WBN; ++nb) {
         const f32x4& a = acc[nb][2 * mp + mh];
         float v0 = a[0] + bias[nb].x, v1 = a[1] + bias[nb].y, v2 = a[2] + bias[nb].z, v3 = a[3] + bias[nb].w;
         if (EPI == CHORUS_EPI_GELU_BF16) {
@@ -392,15 +393,15 @@ __device__ __forceinline__ void gemm16_epilogue_bf16(const f32x4 (&acc)[8][8], c
 }
 
 // fp32 gated-residual epilogue of the 16x16 layout: 16 output rows at a time through a private LDS region as
-// [16][16 WB] fp32 (row stride 16 WB + 4), read back with 4 WB lanes per row; the residual rows are requested before the
+// [16][16 WBN] fp32 (row stride 16 WBN + 4), read back with 4 WBN lanes per row; the residual rows are requested before the
 // LDS round trip. out[m][n] += gate[n] * scale * (acc + bias[n]).
-template <int WB> constexpr int e16_f32_stride() { return 16 * WB + 4; }
-template <int WB> constexpr int e16_f32_wave() { return 16 * e16_f32_stride<WB>(); }  // floats per wave
-template <int WB>
+template <int WBN> constexpr int e16_f32_stride() { return 16 * WBN + 4; }
+template <int WBN> constexpr int e16_f32_wave() { return 16 * e16_f32_stride<WBN>(); }  // floats per wave
+template <int WBM, int WBN>
 __device__ __forceinline__ void gemm16_epilogue_resid(const f32x4 (&acc)[8][8], const EpiArgs& ep, float* cw, long m_wave0,
                                                       int n_wave0, long M, int N, int lane) {
-  constexpr int E16_F32_STRIDE = e16_f32_stride<WB>();
-  constexpr int LPR = 4 * WB, RPI = 64 / LPR;  // read-back: LPR lanes x 16 bytes per row, RPI rows per instruction
+  constexpr int E16_F32_STRIDE = e16_f32_stride<WBN>();
+  constexpr int LPR = 4 * WBN, RPI = 64 / LPR;  // read-back: LPR lanes x 16 bytes per row, RPI rows per instruction
   const int lj = lane & 15, lg = lane >> 4;
   const int rrow = lane / LPR, rcol = (lane % LPR) * 4;
   const int n = n_wave0 + rcol;
@@ -418,10 +419,10 @@ __device__ __forceinline__ void gemm16_epilogue_resid(const f32x4 (&acc)[8][8], 
   float* out = reinterpret_cast<float*>(ep.out);
   // The residual rows of block mb + 1 are requested before the results of block mb are stored: memory operations
   // retire in order, so a load issued behind a block's stores could only be consumed once those stores had drained.
-  f32x4 cur[2][WB];
-  auto fetch = [&](int mb, f32x4 (&dst)[WB]) {
+  f32x4 cur[2][WBN];
+  auto fetch = [&](int mb, f32x4 (&dst)[WBN]) {
 #pragma unroll
-    for (int it = 0; it < WB; ++it) {
+    for (int it = 0; it < WBN; ++it) {
       long m = m_wave0 + 16 * mb + RPI * it + rrow;
       if (m > M - 1) m = M - 1;  // rows past the end read the last row (never stored)
       dst[it] = *reinterpret_cast<const f32x4*>(out + m * N + (n_ok ? n : 0));
@@ -429,14 +430,14 @@ __device__ __forceinline__ void gemm16_epilogue_resid(const f32x4 (&acc)[8][8], 
   };
   fetch(0, cur[0]);
 #pragma unroll
-  for (int mb = 0; mb < WB; ++mb) {
+  for (int mb = 0; mb < WBM; ++mb) {
 #pragma unroll
-    for (int nb = 0; nb < WB; ++nb) *reinterpret_cast<f32x4*>(cw + lj * E16_F32_STRIDE + 16 * nb + 4 * lg) = acc[nb][mb];
+    for (int nb = 0; nb < WBN; ++nb) *reinterpret_cast<f32x4*>(cw + lj * E16_F32_STRIDE + 16 * nb + 4 * lg) = acc[nb][mb];
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    if (mb + 1 < WB) fetch(mb + 1, cur[(mb + 1) & 1]);
+    if (mb + 1 < WBM) fetch(mb + 1, cur[(mb + 1) & 1]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int it = 0; it < WB; ++it) {
+    for (int it = 0; it < WBN; ++it) {
       const f32x4 v = *reinterpret_cast<const f32x4*>(cw + (RPI * it + rrow) * E16_F32_STRIDE + rcol);
       const long m = m_wave0 + 16 * mb + RPI * it + rrow;
       if (n_ok && m < M) *reinterpret_cast<f32x4*>(out + m * N + n) = cur[mb & 1][it] + gate * (v + bias);
@@ -446,29 +447,30 @@ __device__ __forceinline__ void gemm16_epilogue_resid(const f32x4 (&acc)[8][8], 
   }
 }
 
-// Epilogue of the 4-wave 16x16 kernels: wave (wm, wn) holds rows m0 + 16 WB wm .. + 16 WB, columns n0 + 16 WB wn .. + 16 WB.
-template <int EPI, int WB>
+// Epilogue of the 4-wave 16x16 kernels: wave (wm, wn) holds rows m0 + 16 WBM wm .. + 16 WBM, columns
+// n0 + 16 WBN wn .. + 16 WBN.
+template <int EPI, int WBM, int WBN>
 __device__ __forceinline__ void gemm16_finish(f32x4 (&acc)[8][8], const EpiArgs& ep, uint8_t* smem_raw, int wave, int wm, int wn,
                                               long m0, int n0, long M, int N, int lane) {
-  constexpr int WT = 16 * WB;  // rows and columns of a wave's quadrant
+  constexpr int WTM = 16 * WBM, WTN = 16 * WBN;  // rows and columns of a wave's quadrant
   uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
   const int lj = lane & 15, lg = lane >> 4;
   if constexpr (EPI == CHORUS_EPI_BF16 || EPI == CHORUS_EPI_GELU_BF16) {
-    gemm16_epilogue_bf16<EPI, WB>(acc, ep, smem + wave * e16_bf_wave<WB>(), m0 + wm * WT, n0 + wn * WT, M, N, lane);
+    gemm16_epilogue_bf16<EPI, WBM, WBN>(acc, ep, smem + wave * e16_bf_wave<WBN>(), m0 + wm * WTM, n0 + wn * WTN, M, N, lane);
   } else if constexpr (EPI == CHORUS_EPI_RESID) {
-    gemm16_epilogue_resid<WB>(acc, ep, reinterpret_cast<float*>(smem_raw) + wave * e16_f32_wave<WB>(), m0 + wm * WT, n0 + wn * WT, M,
-                              N, lane);
+    gemm16_epilogue_resid<WBM, WBN>(acc, ep, reinterpret_cast<float*>(smem_raw) + wave * e16_f32_wave<WBN>(), m0 + wm * WTM,
+                                    n0 + wn * WTN, M, N, lane);
   } else {
     // plain fp32: a lane stores its four consecutive columns of every block
 #pragma unroll
-    for (int nb = 0; nb < WB; ++nb) {
-      const int n = n0 + wn * WT + 16 * nb + 4 * lg;
+    for (int nb = 0; nb < WBN; ++nb) {
+      const int n = n0 + wn * WTN + 16 * nb + 4 * lg;
       if (n >= N) continue;
       f32x4 bias = {0.f, 0.f, 0.f, 0.f};
       if (ep.bias) bias = *reinterpret_cast<const f32x4*>(ep.bias + n);
 #pragma unroll
-      for (int mb = 0; mb < WB; ++mb) {
-        const long m = m0 + wm * WT + 16 * mb + lj;
+      for (int mb = 0; mb < WBM; ++mb) {
+        const long m = m0 + wm * WTM + 16 * mb + lj;
         if (m < M) *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(ep.out) + m * N + n) = acc[nb][mb] + bias;
       }
     }
@@ -488,22 +490,25 @@ __device__ __forceinline__ void wait_steps(int steps) {
   }
 }
 
-template <int EPI, int WB, int NST>
+// The 128 x 256 shape takes three quarters of the operand bytes per product of 128 x 128 tiles: for products of 257 to
+// 512 such tiles with a long K, which run two to a unit, half as many wide ones finish earlier (N = 1536, K = 8960: 3271
+// rows 124 -> 115 us, 5000 rows 136 -> 130; N = 5120, K = 13824, 1200 rows: 202 -> 181).
+template <int EPI, int WBM, int WBN, int NST>
 __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
                                                           long M, int N, int K, EpiArgs ep, PartPtrs parts, int tiles_m,
                                                           int tiles_n) {
-  static_assert(WB == 8 || WB == 4 || WB == 2, "quadrants of 8 x 8, 4 x 4 or 2 x 2 blocks");
-  static_assert(NST >= 2 && NST <= 8 && 2 * WB * (NST - 1) < 64, "the loads in flight must fit the wait counter");
-  constexpr int BM = 32 * WB, BN = 32 * WB;
-  constexpr int WT = 16 * WB;  // rows and columns of a wave's quadrant
+  static_assert((WBM == 8 || WBM == 4 || WBM == 2) && (WBN == WBM || (WBM == 4 && WBN == 8)), "quadrants of 8 x 8, 4 x 4, 2 x 2 or 4 x 8 blocks");
+  static_assert(NST >= 2 && NST <= 8 && (WBM + WBN) * (NST - 1) < 64, "the loads in flight must fit the wait counter");
+  constexpr int BM = 32 * WBM, BN = 32 * WBN;
+  constexpr int WTM = 16 * WBM, WTN = 16 * WBN;  // rows and columns of a wave's quadrant
   constexpr int GM = 8;
   constexpr int STAGE = (BM + BN) * BK;  // elements per stage
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[];
   uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
 
-  // The grid holds gridDim.x / ntiles slices of K of as many steps as can be (never none: the host asks for no more
-  // slices than steps), all tiles of a slice together. The last slice runs the epilogue, the others leave their plain fp32 result in `parts`; without a
-  // split there is one slice.
+  // The grid holds gridDim.x / ntiles slices of K, their steps shared out as evenly as can be (never none: the host asks
+  // for no more slices than steps), all tiles of a slice together. The last slice runs the epilogue, the others leave
+  // their plain fp32 result in `parts`; without a split there is one slice.
   const int ntiles = tiles_m * tiles_n;
   const int nslices = gridDim.x / ntiles, slice = blockIdx.x / ntiles;
   const int tile = xcd_remap(blockIdx.x - slice * ntiles, ntiles);
@@ -530,34 +535,40 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
   const int wm = wave >> 1, wn = wave & 1;
   const int lj = lane & 15, lg = lane >> 4;
 
-  // ---- loader: wave w, slot i (0..WB-1) covers tile rows 8*(WB w+i) .. +8 of A and of W; lane -> (row, position)
+  // ---- loader: wave w, slot i covers tile rows 8*(WBM w+i) .. +8 of A and 8*(WBN w+i) .. +8 of W; lane -> (row, position)
   const int lr = lane >> 3, lp = lane & 7;
   // (the arrays that the lambdas below capture have the large tile's size for either tile: a bound that depends on
   // the template parameter loses the kernel's host-side stub)
   const uint16_t* ga[8];
   const uint16_t* gb[8];
 #pragma unroll
-  for (int i = 0; i < WB; ++i) {
-    const int r = 8 * (WB * wave + i) + lr;
+  for (int i = 0; i < WBM; ++i) {
+    const int r = 8 * (WBM * wave + i) + lr;
     const int ch = lp ^ ((r >> 1) & 7);  // global chunk that belongs at position lp
     long ra = m0 + r;
     if (ra > M - 1) ra = M - 1;
+    ga[i] = A + ra * (long)K + ch * 8;
+  }
+#pragma unroll
+  for (int i = 0; i < WBN; ++i) {
+    const int r = 8 * (WBN * wave + i) + lr;
+    const int ch = lp ^ ((r >> 1) & 7);
     int rb = n0 + r;
     if (rb > N - 1) rb = N - 1;
-    ga[i] = A + ra * (long)K + ch * 8;
     gb[i] = W + (long)rb * K + ch * 8;
   }
-  auto issue = [&](int kt, int stage, int t0, int t1) {  // loads t0 .. t1-1 of the 2 WB per k-step (even: A rows, odd: W rows)
+  // loads t0 .. t1-1 of the WBM + WBN per k-step (A and W rows in turn, in a rectangular tile the A rows first)
+  auto issue = [&](int kt, int stage, int t0, int t1) {
     uint16_t* sa = smem + stage * STAGE;
     uint16_t* sb = sa + BM * BK;
 #pragma unroll
     for (int t = t0; t < t1; ++t) {
-      const int i = t >> 1;
-      const int rows0 = 8 * (WB * wave + i);
-      if (t & 1)
-        __builtin_amdgcn_global_load_lds(gb[i] + (long)kt * BK, sb + rows0 * BK, 16, 0, 0);
+      const bool of_w = WBM == WBN ? (t & 1) != 0 : t >= WBM;
+      const int i = WBM == WBN ? t >> 1 : (of_w ? t - WBM : t);
+      if (of_w)
+        __builtin_amdgcn_global_load_lds(gb[i] + (long)kt * BK, sb + 8 * (WBN * wave + i) * BK, 16, 0, 0);
       else
-        __builtin_amdgcn_global_load_lds(ga[i] + (long)kt * BK, sa + rows0 * BK, 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(ga[i] + (long)kt * BK, sa + 8 * (WBM * wave + i) * BK, 16, 0, 0);
     }
   };
 
@@ -566,37 +577,37 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
   int koff[2];
 #pragma unroll
   for (int h = 0; h < 2; ++h) koff[h] = ((4 * h + lg) ^ sw) * 8;
-  const int a_row0 = (wm * WT + lj) * BK;
-  const int b_row0 = BM * BK + (wn * WT + lj) * BK;
+  const int a_row0 = (wm * WTM + lj) * BK;
+  const int b_row0 = BM * BK + (wn * WTN + lj) * BK;
 
-  f32x4 acc[8][8];  // [n block][m block]; the WB x WB corner is used
+  f32x4 acc[8][8];  // [n block][m block]; the WBN x WBM corner is used
 #pragma unroll
-  for (int nb = 0; nb < WB; ++nb)
+  for (int nb = 0; nb < WBN; ++nb)
 #pragma unroll
-    for (int mb = 0; mb < WB; ++mb) acc[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int mb = 0; mb < WBM; ++mb) acc[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   bf16x8 af[2][8], bfr[2][8];
-  // fragment f of a half-step: 0 .. WB-1 the activation blocks (m), WB .. 2 WB-1 the weight blocks (n)
+  // fragment f of a half-step: 0 .. WBM-1 the activation blocks (m), then the WBN weight blocks (n)
   auto read_frag = [&](const uint16_t* st, int h, int set, int f) {
-    if (f < WB)
+    if (f < WBM)
       af[set][f] = *reinterpret_cast<const bf16x8*>(st + a_row0 + f * 16 * BK + koff[h]);
     else
-      bfr[set][f - WB] = *reinterpret_cast<const bf16x8*>(st + b_row0 + (f - WB) * 16 * BK + koff[h]);
+      bfr[set][f - WBM] = *reinterpret_cast<const bf16x8*>(st + b_row0 + (f - WBM) * 16 * BK + koff[h]);
   };
-  // MFMAs g0 .. g1-1 of the WB * WB of a half-step, weight block major: g = WB nb + mb. In place on the accumulator
+  // MFMAs g0 .. g1-1 of the WBM * WBN of a half-step, weight block major: g = WBM nb + mb. In place on the accumulator
   // registers (left to itself the register allocator gives every result a new home and pays with hundreds of
   // accumulator moves per k-step); being volatile they also keep their place between the loads written around them.
   auto mfmas = [&](int set, int g0, int g1) {
 #pragma unroll
     for (int g = g0; g < g1; ++g)
-      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[g / WB][g % WB]) : "v"(bfr[set][g / WB]), "v"(af[set][g % WB]));
+      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc[g / WBM][g % WBM]) : "v"(bfr[set][g / WBM]), "v"(af[set][g % WBM]));
   };
   // order in which the fragments of a half-step are fetched: what its first MFMAs need comes first (the first weight
   // block, the activation blocks, the other weight blocks)
-  auto frag_order = [](int i) { return i == 0 ? WB : (i <= WB ? i - 1 : i); };
+  auto frag_order = [](int i) { return i == 0 ? WBM : (i <= WBM ? i - 1 : i); };
 
-  // Schedule of one k-step (2 WB^2 MFMAs a wave in 4 WB slots of WB / 2: 128 MFMAs in 32 slots of four for the large
-  // tile). The barrier sits between the two half-steps. In the
+  // Schedule of one k-step (square tiles, WB = WBM = WBN: 2 WB^2 MFMAs a wave in 4 WB slots of WB / 2, 128 MFMAs in 32
+  // slots of four for the large tile). The barrier sits between the two half-steps. In the
   // first half a wave fetches its fragments of the second half (same stage); at the barrier every wave holds all its
   // fragments of the current stage in registers and its own pieces of the next stage, requested a whole half-step
   // earlier, have landed. Behind it the stage just consumed is free: the second half issues the loads of the step after
@@ -605,9 +616,12 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
   // wave per SIMD nothing else feeds the matrix pipe while this wave issues something that is not an MFMA, so reads and
   // loads stand one at a time between single MFMAs, where they issue in the shadow of the MFMA in front of them, and
   // the wave index is kept in a scalar register so that the LDS address of a load costs no vector instruction.
-  constexpr int NS = 2 * WB;              // slots of a half-step = fragments of a half-step = loads of a k-step
-  constexpr int MPS = WB / 2;             // MFMAs of a slot
-  constexpr int kReadSlots = 3 * WB / 2;  // 12 of 16 (6 of 8, 3 of 4)
+  // A rectangular tile has no whole number of MFMAs per slot: its reads stand behind MFMAs spread evenly over the first
+  // three quarters of a half, its loads over all of it.
+  constexpr int NS = WBM + WBN;            // slots of a half-step = fragments of a half-step = loads of a k-step
+  constexpr int G = WBM * WBN;             // MFMAs of a half-step
+  constexpr int MPS = WBM / 2;             // MFMAs of a slot
+  constexpr int kReadSlots = 3 * WBM / 2;  // 12 of 16 (6 of 8, 3 of 4)
   // reads of slot f: one fragment, two in the first NS - kReadSlots slots (which = 0: the first, 1: the second)
   auto read_of_slot = [&](const uint16_t* stg, int h, int set, int f, int which) {
     constexpr int kDouble = NS - kReadSlots;
@@ -640,7 +654,8 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
     const uint16_t* stn = smem + next * STAGE;
     const bool more = kt + NST < KTN;
     const int k2 = more ? kt + NST : KTN - 1;
-    // ---- half-step 0: WB^2 MFMAs and the fragment reads of half-step 1
+    // ---- half-step 0: its MFMAs and the fragment reads of half-step 1
+    if constexpr (WBM == WBN) {
 #pragma unroll
     for (int f = 0; f < NS; ++f) {
       mfmas(0, MPS * f, MPS * f + 1);
@@ -654,11 +669,23 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
       mfmas(0, MPS * f + 2, MPS * f + MPS);
       __builtin_amdgcn_sched_barrier(0);
     }
+    } else {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        mfmas(0, g, g + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+          if (i * 3 * G / (4 * NS) == g) read_frag(st, 1, 1, frag_order(i));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
     // this wave's pieces of step kt + 1 are in LDS: the steps requested behind it, at most up to the last one, may be in flight
     wait_steps<NST - 2, NS>(KTN - 2 - kt);
     lds_barrier();  // every wave has all its fragments of this stage in registers
     __builtin_amdgcn_sched_barrier(0);
-    // ---- half-step 1: WB^2 MFMAs, the next step's first-half fragments, the loads of step kt + NST into the stage just freed
+    // ---- half-step 1: its MFMAs, the next step's first-half fragments, the loads of step kt + NST into the stage just freed
+    if constexpr (WBM == WBN) {
 #pragma unroll
     for (int f = 0; f < NS; ++f) {
       mfmas(1, MPS * f, MPS * f + 1);
@@ -676,6 +703,21 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
       if constexpr (MPS > 2) mfmas(1, MPS * f + MPS - 1, MPS * f + MPS);
       __builtin_amdgcn_sched_barrier(0);
     }
+    } else {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        mfmas(1, g, g + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+          if (i * 3 * G / (4 * NS) == g) read_frag(stn, 0, 0, frag_order(i));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+          if ((2 * i + 1) * G / (2 * NS) == g && (kClamp || more)) issue(k2, stage, i, i + 1);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
     stage = next;
   }
 
@@ -685,34 +727,34 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
   // accumulators of the last four MFMAs (operands of the statement), so that no copy or spill of one of them can be
   // placed in front of it; every other accumulator was written at least four MFMAs earlier.
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15"
-               : "+a"(acc[WB - 1][WB - 1]), "+a"(acc[WB - 1][WB - 2]), "+a"(acc[WB > 2 ? WB - 1 : 0][WB > 2 ? WB - 3 : 1]),
-                 "+a"(acc[WB > 2 ? WB - 1 : 0][WB > 2 ? WB - 4 : 0]));
+               : "+a"(acc[WBN - 1][WBM - 1]), "+a"(acc[WBN - 1][WBM - 2]), "+a"(acc[WBM > 2 ? WBN - 1 : 0][WBM > 2 ? WBM - 3 : 1]),
+                 "+a"(acc[WBM > 2 ? WBN - 1 : 0][WBM > 2 ? WBM - 4 : 0]));
   lds_barrier();  // the staging regions of the epilogue overlay the operand stages
   if constexpr (EPI == CHORUS_EPI_RESID) {
     if (slice + 1 < nslices) {
       const EpiArgs plain{parts.of(slice, M, N), nullptr, nullptr, nullptr, 1.f};
-      gemm16_finish<CHORUS_EPI_F32, WB>(acc, plain, smem_raw, wave, wm, wn, m0, n0, M, N, lane);
+      gemm16_finish<CHORUS_EPI_F32, WBM, WBN>(acc, plain, smem_raw, wave, wm, wn, m0, n0, M, N, lane);
       return;
     }
   }
-  gemm16_finish<EPI, WB>(acc, ep, smem_raw, wave, wm, wn, m0, n0, M, N, lane);
+  gemm16_finish<EPI, WBM, WBN>(acc, ep, smem_raw, wave, wm, wn, m0, n0, M, N, lane);
 }
 
-template <int WB, int NST>
+template <int WBM, int WBN, int NST>
 int32_t launch_gemm_w16(const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, EpiArgs ep, hipStream_t s,
                         int slices, const PartPtrs& parts) {
-  constexpr int T = 32 * WB;  // tile side: 256, 128 or 64
-  long tm = (M + T - 1) / T;
-  int tn = (N + T - 1) / T;
+  constexpr int BM = 32 * WBM, BN = 32 * WBN;
+  long tm = (M + BM - 1) / BM;
+  int tn = (N + BN - 1) / BN;
   if (tm * tn * slices > 0x7fffffffL) return CHORUS_E_SHAPE;
   dim3 grid((unsigned)(tm * tn * slices)), block(256);
-  const size_t smem = NST * (T + T) * BK * sizeof(uint16_t);
-#define GEMM_W16(E)                                                                             \
-  {                                                                                             \
-    auto kern = gemm_w16_kernel<E, WB, NST>;                                                         \
-    static DynLdsOnce once;                                                                     \
-    CHK_STATUS(once.ensure(reinterpret_cast<const void*>(kern), (int)smem));                    \
-    hipLaunchKernelGGL(kern, grid, block, smem, s, A, W, M, N, K, ep, parts, (int)tm, tn);  \
+  const size_t smem = NST * (BM + BN) * BK * sizeof(uint16_t);
+#define GEMM_W16(E)                                                                           \
+  {                                                                                           \
+    auto kern = gemm_w16_kernel<E, WBM, WBN, NST>;                                            \
+    static DynLdsOnce once;                                                                   \
+    CHK_STATUS(once.ensure(reinterpret_cast<const void*>(kern), (int)smem));                  \
+    hipLaunchKernelGGL(kern, grid, block, smem, s, A, W, M, N, K, ep, parts, (int)tm, tn);    \
   }
   switch (epi) {
     case CHORUS_EPI_BF16: GEMM_W16(CHORUS_EPI_BF16); break;
@@ -790,18 +832,20 @@ int32_t launch_gemm(const uint16_t* A, const uint16_t* W, long M, int N, int K, 
 // 256 lines in flight, 32 KB, so a unit takes in about 60 KB per microsecond whatever the kernel does, and the launch
 // that spreads the same problem over more units wins: smaller tiles, or slices of K.
 //   256 x 256  one workgroup per unit, rounds of 256; a partly filled round is up to a quarter faster [39 / 190 us]
+//   128 x 256  three stages, one workgroup per unit: up to 256 tiles [27 / 111 few, 34 / 130 all units busy]
 //   128 x 128  two stages, two workgroups per unit: one round of up to 256 tiles [21 / 115], then rounds of 512 [27 / 145]
-//   128 x 128  three stages, one workgroup per unit: up to 256 tiles [17 / 75]
+//   128 x 128  three stages, one workgroup per unit: up to 256 tiles [17 / 72 few, 21 / 83 all units busy]
 //   64 x 64    four stages, two workgroups per unit: up to 256 tiles [9.7 / 40], growing with the tiles beyond
 // ---------------------------------------------------------------------------
-enum Tile { kTile256, kTile128, kTile128Deep, kTile64, kTiles };
-constexpr int kTileSide[kTiles] = {256, 128, 128, 64};
+enum Tile { kTile256, kTileWide, kTile128, kTile128Deep, kTile64, kTiles };
+constexpr int kTileRows[kTiles] = {256, 128, 128, 128, 64};
+constexpr int kTileCols[kTiles] = {256, 256, 128, 128, 64};
 constexpr int kMaxSlices = 4;  // more slices than this were never the fastest
 
 double tile_time(int tile, long m, int N, int K, int epi, int slices) {
-  const long side = kTileSide[tile];
+  const long rows = kTileRows[tile], cols = kTileCols[tile];
   const double steps = (double)((K / BK + slices - 1) / slices);
-  const double w = (double)(((m + side - 1) / side) * ((N + side - 1) / side) * slices);
+  const double w = (double)(((m + rows - 1) / rows) * ((N + cols - 1) / cols) * slices);
   const bool f32_out = slices == 1 && (epi == CHORUS_EPI_F32 || epi == CHORUS_EPI_RESID);
   switch (tile) {
     case kTile256: {
@@ -809,14 +853,22 @@ double tile_time(int tile, long m, int N, int K, int epi, int slices) {
       const double rounds = floor(w / 256.0), fill = w / 256.0 - rounds;
       return full * (rounds + (fill > 0.0 ? 0.76 + 0.24 * fill * fill : 0.0));
     }
+    case kTileWide: {
+      if (w > 256.0) return INFINITY;
+      const double fill = w / 256.0;
+      return (f32_out ? 9.5 : epi == CHORUS_EPI_GELU_BF16 ? 10.0 : 7.0) + (0.72 + 0.13 * fill * fill * fill) * steps;
+    }
     case kTile128: {
       const double one = (f32_out ? 5.0 : 2.0) + 0.74 * steps, round512 = (f32_out ? 4.5 : 0.5) + 1.005 * steps;
       if (w <= 256.0) return one;
       if (w <= 512.0) return one + (w - 256.0) / 256.0 * fmax(round512 - one, 0.0);
       return ceil(w / 512.0) * round512;
     }
-    case kTile128Deep:
-      return w <= 256.0 ? (f32_out ? 5.0 : 4.0) + 0.5 * steps : INFINITY;
+    case kTile128Deep: {
+      if (w > 256.0) return INFINITY;
+      const double fill = w / 256.0;
+      return (f32_out ? 6.5 : 5.0) + (0.45 + 0.1 * fill * fill) * steps;
+    }
     default:
       return (w <= 256.0 ? 1.0 : 1.25 + 0.66 * (w - 256.0) / 256.0) * (3.5 + 0.255 * steps);
   }
@@ -833,7 +885,7 @@ struct GemmPlan {
 // The fastest tile by the estimates. With scratch a gated-residual product may also be cut into slices of K: every slice
 // but the last writes its fp32 result and a second launch adds them (about 6 TB/s from the caches, and the launch itself).
 // Measured where N = 1536, K = 8960, slices against the best whole tile: 128 rows 17 / 40 us, 480 rows 31 / 39, 1200
-// rows 51 / 67; from about 1700 rows a whole tile fills the chip.
+// rows 51 / 67, 2000 rows (two slices of 128 x 256 tiles) 74 / 77; from about 2300 rows a whole tile fills the chip.
 GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
   GemmPlan best{kTile256, 1, INFINITY};
   for (int t = 0; t < kTiles; ++t) {
@@ -858,10 +910,11 @@ GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
 int32_t launch_tile(int tile, const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, const EpiArgs& ep,
                     hipStream_t s, int slices = 1, const PartPtrs& parts = PartPtrs{nullptr, nullptr}) {
   switch (tile) {
-    case kTile256: return launch_gemm_w16<8, 2>(A, W, M, N, K, epi, ep, s, slices, parts);
-    case kTile128: return launch_gemm_w16<4, 2>(A, W, M, N, K, epi, ep, s, slices, parts);
-    case kTile128Deep: return launch_gemm_w16<4, 3>(A, W, M, N, K, epi, ep, s, slices, parts);
-    default: return launch_gemm_w16<2, 4>(A, W, M, N, K, epi, ep, s, slices, parts);
+    case kTile256: return launch_gemm_w16<8, 8, 2>(A, W, M, N, K, epi, ep, s, slices, parts);
+    case kTileWide: return launch_gemm_w16<4, 8, 3>(A, W, M, N, K, epi, ep, s, slices, parts);
+    case kTile128: return launch_gemm_w16<4, 4, 2>(A, W, M, N, K, epi, ep, s, slices, parts);
+    case kTile128Deep: return launch_gemm_w16<4, 4, 3>(A, W, M, N, K, epi, ep, s, slices, parts);
+    default: return launch_gemm_w16<2, 2, 4>(A, W, M, N, K, epi, ep, s, slices, parts);
   }
 }
 

@@ -1,5 +1,5 @@
 """GPU parity of the GEMM tiles and slices that the automatic choice takes for problems that do not fill the chip:
-64 x 64 tiles, 128 x 128 tiles with three stages, and the second FFN product of a block in slices of K."""
+64 x 64 tiles, 128 x 128 tiles with three stages, 128 x 256 tiles, and the second FFN product of a block in slices of K."""
 import dataclasses
 
 import numpy as np
@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,N,K", [
     (1, 8, 64), (63, 64, 128), (64, 72, 192), (65, 768, 256), (129, 256, 320), (480, 1536, 1536),   # 64 x 64, 1 to 24 steps
     (1000, 1536, 4096), (200, 3080, 1024), (1100, 2304, 64), (130, 13824, 512),                      # two per unit, or 128 x 128 deep
+    (1990, 4088, 4096), (1025, 7000, 8960),                                                          # 128 x 256
 ])
 def test_gemm_default_tiles(M, N, K):
     """Ragged rows and columns, fewer rows or columns than a tile, K of fewer steps than the kernels have stages."""
@@ -42,12 +43,12 @@ def test_gemm_default_tiles(M, N, K):
 
 
 @pytest.mark.parametrize("Ls,Lt,F", [(200, 16, 8960), (200, 128, 8960), (200, 512, 8960), (1, 16, 8960), (131, 77, 4160),
-                                     (384, 300, 13824)])
+                                     (384, 300, 13824), (2000, 16, 8960)])
 def test_block_ffn_in_slices(Ls, Lt, F):
     """The FFN of a narrow block with a long hidden row: its second product runs in two, three or four slices of K,
     by what the workspace holds behind the hidden rows (more with more text tokens); slices of unequal length."""
     print(f"[case] ffn slices Ls={Ls} Lt={Lt} F={F}", flush=True)
-    bs = dataclasses.replace(synth.SHAPES["c1"], F=F, Lt=Lt, grid=(6, 8, 8), latent_std=1.0, text_std=1.0)
+    bs = dataclasses.replace(synth.SHAPES["c1"], F=F, Lt=Lt, grid=(6, 8, 8) if Ls <= 384 else (8, 16, 16), latent_std=1.0, text_std=1.0)
     w = synth.stress_block_weights(bs, 3)
     for n in ("w_qkv", "w_cq"):  # the attention branches small: the FFN is what is compared
         w[n] = synth.round_bf16(w[n] * 0.25)
