@@ -267,9 +267,11 @@ __global__ __launch_bounds__(256) void v_transpose_kernel(const uint16_t* __rest
 }
 
 // What stands between a projection and attention, in one launch: the first row_blocks workgroups normalise (and rotate)
-// four tokens each, a wave the query row, if there is one, and the key row of a token, whose rotation angles are computed
-// once; the others transpose a tile of V. HBM-bound where the sequence is long; where it is short each of the launches
-// that this replaces took longer to start than to run (128 tokens of width 256: 3.6 + 3.6 + 2.8 us and two gaps).
+// the query rows, if there are any, or the key rows of four tokens, a wave a row and queries and keys in turn; the others
+// transpose a tile of V. HBM-bound where the sequence is long; where it is short each of the launches that this replaces
+// took longer to start than to run (128 tokens of width 256: 3.6 + 3.6 + 2.8 us and two gaps). A wave that did both rows
+// of a token, for one set of angles, held twice the registers (width 5120, 75600 tokens: 957 us against 897 of the three
+// launches) and was the longer chain where the chip is not filled (block of 128 tokens 69.7 us, now 68.9).
 template <int NCH>
 __global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                            const uint16_t* __restrict__ v, long ld,
@@ -290,20 +292,20 @@ __global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __res
     return;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, D = H * dh;
-  const long row = (long)blockIdx.x * 4 + wave;
+  const bool of_q = q && !(blockIdx.x & 1);
+  const long row = (long)(q ? blockIdx.x >> 1 : blockIdx.x) * 4 + wave;
   if (row >= Lpad) return;
+  uint16_t* out = of_q ? qh : kh;
   if (row >= L) {
-    if (q) zero_row(qh, row, Lpad, D, dh, lane);
-    zero_row(kh, row, Lpad, D, dh, lane);
+    zero_row(out, row, Lpad, D, dh, lane);
     return;
   }
-  u32x4 rq[NCH > 0 ? NCH : 1], rk[NCH > 0 ? NCH : 1];
-  if (q) load_row<NCH>(rq, q + row * ld, lane);
-  load_row<NCH>(rk, k + row * ld, lane);
+  const uint16_t* r = (of_q ? q : k) + row * ld;
+  u32x4 rv[NCH > 0 ? NCH : 1];
+  load_row<NCH>(rv, r, lane);
   if (rope) rope_angles(sm.rot.cos[wave], sm.rot.sin[wave], token_idx ? (long)token_idx[row] : row, dh, gH, gW, lane);
-  if (q)
-    norm_rope_row<NCH>(q + row * ld, rq, gain_q, qh, row, Lpad, D, dh, rope, sm.rot.cos[wave], sm.rot.sin[wave], q_scale, lane);
-  norm_rope_row<NCH>(k + row * ld, rk, gain_k, kh, row, Lpad, D, dh, rope, sm.rot.cos[wave], sm.rot.sin[wave], 1.0f, lane);
+  norm_rope_row<NCH>(r, rv, of_q ? gain_q : gain_k, out, row, Lpad, D, dh, rope, sm.rot.cos[wave], sm.rot.sin[wave],
+                     of_q ? q_scale : 1.0f, lane);
 }
 
 }  // namespace
@@ -312,7 +314,7 @@ int32_t attn_prepare(const uint16_t* q, const uint16_t* k, const uint16_t* v, lo
                      uint16_t* qh, uint16_t* kh, uint16_t* vt, long L, long Lpad, int H, int dh, const int32_t* token_idx, int gH,
                      int gW, int rope, float q_scale, void* stream) {
   const int D = H * dh;
-  const long row_blocks = (Lpad + 3) / 4, v_tiles = Lpad / 64, blocks = row_blocks + v_tiles * (D / 64);
+  const long row_blocks = (Lpad + 3) / 4 * (q ? 2 : 1), v_tiles = Lpad / 64, blocks = row_blocks + v_tiles * (D / 64);
   if (blocks > 0x7fffffffL) return CHORUS_E_SHAPE;
 #define PREPARE(NCH)                                                                                                       \
   hipLaunchKernelGGL(attn_prepare_kernel<NCH>, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, q, k, v, ld, gain_q, \
