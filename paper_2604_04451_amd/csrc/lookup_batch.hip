@@ -184,32 +184,32 @@ __device__ __forceinline__ float key_score(uint64_t k) {
 __device__ __forceinline__ int key_row(uint64_t k) { return k == 0 ? -1 : (int)~(uint32_t)k; }
 
 template <int CTRL>
-__device__ __forceinline__ uint64_t max_dpp(uint64_t k) {
-  const uint32_t lo = __builtin_amdgcn_update_dpp(0, (uint32_t)k, CTRL, 0xf, 0xf, false);
-  const uint32_t hi = __builtin_amdgcn_update_dpp(0, (uint32_t)(k >> 32), CTRL, 0xf, 0xf, false);
-  const uint64_t o = ((uint64_t)hi << 32) | lo;
+__device__ __forceinline__ uint32_t max_dpp(uint32_t k) {
+  const uint32_t o = __builtin_amdgcn_update_dpp(0, k, CTRL, 0xf, 0xf, false);
   return o > k ? o : k;
 }
-// largest key of the wave, in every lane: four steps inside rows of 16 lanes (quad permutes, half-row and row mirror),
+// largest value of the wave, in every lane: four steps inside rows of 16 lanes (quad permutes, half-row and row mirror),
 // then the register-file swaps
-__device__ __forceinline__ uint64_t wave_max_key(uint64_t k) {
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t k) {
   k = max_dpp<0xB1>(k);
   k = max_dpp<0x4E>(k);
   k = max_dpp<0x141>(k);
   k = max_dpp<0x140>(k);
-  {
-    const uint64_t o = ((uint64_t)__float_as_uint(swap_rows16(__uint_as_float((uint32_t)(k >> 32)))) << 32) |
-                       __float_as_uint(swap_rows16(__uint_as_float((uint32_t)k)));
-    k = o > k ? o : k;
-  }
-  const uint64_t o = ((uint64_t)__float_as_uint(swap_halves(__uint_as_float((uint32_t)(k >> 32)))) << 32) |
-                     __float_as_uint(swap_halves(__uint_as_float((uint32_t)k)));
+  uint32_t o = __float_as_uint(swap_rows16(__uint_as_float(k)));
+  k = o > k ? o : k;
+  o = __float_as_uint(swap_halves(__uint_as_float(k)));
   return o > k ? o : k;
+}
+// largest key: the largest upper half, then the largest lower half beside it (two chains of one instruction a step; the
+// comparison of whole keys takes five)
+__device__ __forceinline__ uint64_t wave_max_key(uint64_t k) {
+  const uint32_t hi = wave_max_u32((uint32_t)(k >> 32));
+  return ((uint64_t)hi << 32) | wave_max_u32((uint32_t)(k >> 32) == hi ? (uint32_t)k : 0);
 }
 
 // The k <= 64 largest of the wave's keys (four per lane, all different but for 0), best first, one per lane (0 behind the
-// last). Few: a lane keeps its four sorted and offers its best, a round per position is one wave-wide maximum (about 400
-// clocks). More than kRounds: a bitonic sort of all 256, whose cost does not depend on k (about 3000).
+// last). Few: a lane keeps its four sorted and offers its best, a round per position is one wave-wide maximum (two
+// chains of six 32-bit steps). More than kRounds: a bitonic sort of all 256, whose cost does not depend on k (about 3000).
 constexpr int kRounds = 8;
 __device__ __forceinline__ uint64_t shfl_key(uint64_t k, int from) {
   return ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(k >> 32), from, 64) << 32) | (uint32_t)__shfl((int)(uint32_t)k, from, 64);
@@ -274,7 +274,7 @@ __device__ __forceinline__ uint64_t wave_topk(uint64_t (&key)[4], int k, int lan
 // lists the k best of them; the last workgroup of a query to arrive merges the lists. Lists and arrivals are
 // agent-scope atomics, as the workgroups of a query run on different XCDs, whose L2s are not coherent otherwise. With
 // the scores written out and one workgroup per query selecting from them (two launches): 23 us at 4096 x 32 queries,
-// k = 8, in this kernel 16; 20000 entries, 48 queries, k = 50 the whole call 538 -> 123 us.
+// k = 8, in this kernel 11.6; 20000 entries, 48 queries, k = 50 the whole call 538 -> 109 us.
 __global__ __launch_bounds__(256) void lookup_batch_select_kernel(const float* __restrict__ part_dot,
                                                                   const float* __restrict__ part_cc,
                                                                   const float* __restrict__ queries, uint64_t* lists,
@@ -292,13 +292,21 @@ __global__ __launch_bounds__(256) void lookup_batch_select_kernel(const float* _
   float dot[R], cc[R];
 #pragma unroll
   for (int u = 0; u < R; ++u) dot[u] = cc[u] = 0.f;
-  float qq = 0.f;
+  // the first 4096 query values are requested ahead of the partial sums and added behind them
+  constexpr int QU = 4;
+  const int n4 = d >> 2;
   const f32x4* q4 = reinterpret_cast<const f32x4*>(queries + (long)q * d);
-  for (int i = tid; i < (d >> 2); i += 256) {
+  f32x4 qv[QU];
+#pragma unroll
+  for (int c = 0; c < QU; ++c) qv[c] = tid + 256 * c < n4 ? q4[tid + 256 * c] : f32x4{0.f, 0.f, 0.f, 0.f};
+  sum_slices<R, 8, R, 256>(part_dot, part_cc, KS, QP, q, Npad, j0, N, dot, cc);
+  float qq = 0.f;
+#pragma unroll
+  for (int c = 0; c < QU; ++c) qq += (qv[c][0] * qv[c][0] + qv[c][1] * qv[c][1]) + (qv[c][2] * qv[c][2] + qv[c][3] * qv[c][3]);
+  for (int i = tid + 256 * QU; i < n4; i += 256) {
     const f32x4 v = q4[i];
     qq += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
   }
-  sum_slices<R, 8, R, 256>(part_dot, part_cc, KS, QP, q, Npad, j0, N, dot, cc);
   qq = wave_sum(qq);
   if (lane == 0) sq[wave] = qq;
   __syncthreads();
@@ -331,9 +339,15 @@ __global__ __launch_bounds__(256) void lookup_batch_select_kernel(const float* _
     const long at = per_wave ? (long)blockIdx.x * 4 + wave : (long)blockIdx.x;
     if (lane < k && (per_wave || wave == 0))
       __hip_atomic_store(&all[at * k + lane], own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    // Every wave waits for its own stores, the barrier joins them, and one wave releases for the workgroup: the release
+    // writes the XCD's L2 back, and with one per wave that cost 4 us of 16 at 4096 entries and 32 queries (20000
+    // entries, 48 queries, k = 50: the call 123 -> 109 us); row blocks of 512, twice as many releases, were slower for it.
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
     __syncthreads();
-    if (tid == 0) s_arrived = __hip_atomic_fetch_add(&done[q], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (wave == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      if (lane == 0) s_arrived = __hip_atomic_fetch_add(&done[q], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     __syncthreads();
     if (s_arrived != (uint32_t)nb - 1) return;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
