@@ -312,12 +312,15 @@ __global__ __launch_bounds__(512, 2) void attention_pp_kernel(
 // S^T accumulators then start at zero and one multiply-add per logit applies the factor and, with PRE, the reference.
 // The factors of a tile come through LDS like its keys: read from memory where they are used, in pairs for want of
 // registers, they cost four memory latencies per tile (480 x 512 24.3 -> 15.5 us, 13104 x 512 73.6 -> 69.2).
+// KIND 3 and 4 are 1 and 2 for fewer than 512 keys: the row sums are taken by the vector pipe, in fp32 over the
+// probabilities before they are rounded, as attention_pp_kernel takes them. Over a few tiles that costs next to nothing, and a
+// call has the same denominator whichever of the two kernels runs it.
 template <int DH, bool PRE, int RB, int KIND>
 __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
     const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ Vt,
     uint16_t* __restrict__ O, const float* __restrict__ col_scale, long Lq, long Lk, long LqPad, long LkPad, int H,
     int n_qtiles, int tile_base, float scale_log2) {
-  constexpr bool CS = KIND == 2;
+  constexpr bool CS = KIND == 2 || KIND == 4, SUM32 = KIND >= 3;
   constexpr int NT = 512;
   constexpr int KTL = 128;
   constexpr int KS = DH + 16, VS = KTL + 16;  // padded LDS row strides (elements)
@@ -364,11 +367,13 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   // PRE: Q arrives multiplied by log2(e) / sqrt(dh) and the S^T accumulators start at minus the running reference, so
   // a logit leaves the MFMA as the exponent of its probability; the reference starts at 0 and the first tile sets it.
   float m_run[RB];
-  f32x4 lacc[RB];
+  f32x4 lacc[RB];   // row sums (a row's sum in every element), unless SUM32:
+  float l_run[RB];  // this lane's part of them
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
     m_run[rb] = PRE ? 0.f : -INFINITY;
     lacc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+    l_run[rb] = 0.f;
   }
   bf16x8 ones;
 #pragma unroll
@@ -532,6 +537,7 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
           const float alpha = j == 0 ? 1.0f : __builtin_amdgcn_exp2f(-delta);  // nothing is accumulated before the first tile
           m_run[rb] += delta;
           lacc[rb] *= alpha;
+          l_run[rb] *= alpha;
 #pragma unroll
           for (int db = 0; db < DB; ++db) o[db][rb] *= alpha;
 #pragma unroll
@@ -551,6 +557,7 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
         const float alpha = __builtin_amdgcn_exp2f(m_run[rb] - m_new);
         m_run[rb] = m_new;
         lacc[rb] *= alpha;
+        l_run[rb] *= alpha;
 #pragma unroll
         for (int db = 0; db < DB; ++db) o[db][rb] *= alpha;
       }
@@ -568,6 +575,7 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
           for (int i = 0; i < 4; ++i) {
             const float p = PRE ? __builtin_amdgcn_exp2f(s[2 * c + b][rb][i])
                                 : __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * c + b][rb][i], scale_log2, -mref));
+            if constexpr (SUM32) l_run[rb] += p;
             pf[c][rb][4 * b + i] = (bf16_t)p;
           }
     }
@@ -599,6 +607,7 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
 #pragma unroll
           for (int c = 0; c < NC; ++c) o[db][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[c], pf[c][rb], o[db][rb], 0, 0, 0);
       }
+      if constexpr (!SUM32)
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
@@ -614,7 +623,7 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
       __builtin_amdgcn_sched_group_barrier(0x008, RB, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
-    __builtin_amdgcn_sched_group_barrier(0x008, RB * kAhead + RB * NC, 0);
+    __builtin_amdgcn_sched_group_barrier(0x008, RB * kAhead + (SUM32 ? 0 : RB * NC), 0);
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
     lds_barrier();  // this wave's LDS stores are done
@@ -625,7 +634,11 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   const int D = H * DH;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
-    const float l = lacc[rb][0];
+    float l = lacc[rb][0];
+    if constexpr (SUM32) {  // the four lanes that share a query row
+      l = l_run[rb] + swap_rows16(l_run[rb]);
+      l += swap_halves(l);
+    }
     const float inv = 1.0f / l;
     const long q = q_wave0 + 16 * rb + lq;
     if (q < Lq) {
@@ -646,7 +659,7 @@ template <int DH, bool PRE, int RB, int KIND>
 int32_t launch_attn_pp16_tiles(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* cs,
                                long Lq, long Lk, long LqPad, long LkPad, int H, long nqt, long tile_base, long ntile,
                                hipStream_t s) {
-  size_t smem = 2 * ((size_t)128 * (DH + 16) + (size_t)DH * (128 + 16)) * sizeof(uint16_t) + (KIND == 2 ? 2 * 128 * sizeof(float) : 0);
+  size_t smem = 2 * ((size_t)128 * (DH + 16) + (size_t)DH * (128 + 16)) * sizeof(uint16_t) + (KIND == 2 || KIND == 4 ? 2 * 128 * sizeof(float) : 0);
   auto kern = attention_pp16_kernel<DH, PRE, RB, KIND>;
   static DynLdsOnce once;  // the raised dynamic-LDS limit is a per-device property of the kernel
   CHK_STATUS(once.ensure(reinterpret_cast<const void*>(kern), (int)smem));
@@ -685,6 +698,9 @@ int32_t launch_attn_pp16_kind(const uint16_t* Q, const uint16_t* K, const uint16
 template <int DH, bool PRE>
 int32_t launch_attn_pp16(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* cs, long Lq,
                          long Lk, long LqPad, long LkPad, int H, hipStream_t s) {
+  if (!CHORUS_ATTENTION_LONG_KEYS(Lk, LkPad))
+    return cs ? launch_attn_pp16_kind<DH, PRE, 4>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, s)
+              : launch_attn_pp16_kind<DH, PRE, 3>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, s);
   if (cs) return launch_attn_pp16_kind<DH, PRE, 2>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, s);
   return Lq == Lk ? launch_attn_pp16_kind<DH, PRE, 0>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, s)
                   : launch_attn_pp16_kind<DH, PRE, 1>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, s);
@@ -715,7 +731,7 @@ int32_t launch_attn_pp(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt,
 //                  the one tile is padding), and, where one round does not fill the chip, 3271 x 256 16.8 / 17.6
 bool attention_wide_tiles(long Lq, long Lk, long LkPad, int H, bool factor) {
   if (LkPad % 128) return false;
-  if (Lk >= 512) return true;
+  if (CHORUS_ATTENTION_LONG_KEYS(Lk, LkPad)) return true;
   if (Lk <= 64) return false;
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
