@@ -244,7 +244,7 @@ __global__ __launch_bounds__(256) void patch_embed_kernel(const float* __restric
 // Output head and sampler update in one pass over x: LayerNorm + modulation in fp32, one rounding to bf16, the product
 // with the head's weights, and the update of the tokens' latents, with the guided pass over x_uncond in the same
 // workgroup. What it cannot do without is reading x (and x_uncond) once (HBM-bound: 90 us for 402 MB at 32760 x 1536 with
-// guidance). Apart, the bf16 rows went to memory and back and v as well: 218 us; now 117.
+// guidance). Apart, the bf16 rows went to memory and back and v as well: 191 us; now 106.
 //
 // One workgroup of eight waves per compute unit walks over groups of 16 tokens with the head's weights in registers: a
 // wave holds all 64 columns over its eighth of D (96 registers at D = 1536). Read again for every 16 tokens they were
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_update_kernel(const floa
   }
   lds_barrier();
   // one row of a cell per thread, where that is all there is to do: its values are requested ahead
-  const bool one_each = g.pw == 2 && kHeadTok * g.C * g.ph == kHeadThreads;
+  const bool one_each = g.pw == 2 && kHeadTok * g.C * g.ph == kHeadThreads && (long)g.C * g.T * g.Hl * g.Wl <= 0x7fffffffL;
   const int cell = g.ph * g.pw, my_t = tid % kHeadTok, my_row = tid / kHeadTok, my_ch = my_row / g.ph, my_dy = my_row - my_ch * g.ph;
 
   for (long group = blockIdx.x; group < ngroups; group += gridDim.x) {
@@ -351,11 +351,11 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_update_kernel(const floa
       }
       // requests, in the order in which they are needed: the latents of this group, the rows of the next one
       typename U::template Cell<2> mine;
-      long mine_o = 0;
+      int mine_o = 0;  // 32 bits: the widest variant is at the register limit
       if (last && one_each) {
         const long tok = tok0 + my_t < Ls ? tok0 + my_t : Ls - 1;
         const long n = token_idx ? (long)token_idx[tok] : tok;
-        mine_o = g.cell(n, my_ch) + (long)my_dy * g.Wl;
+        mine_o = (int)(g.cell(n, my_ch) + (long)my_dy * g.Wl);
         upd.load(mine, n, mine_o);
       }
       if (!last)
@@ -404,7 +404,9 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_update_kernel(const floa
         const float vc[2] = {PASSES == 2 ? one(0) : vl[0], PASSES == 2 ? one(1) : vl[1]};
         if (tok0 + my_t < Ls) upd.store(mine, mine_o, vc, vl);
       } else {
-        for (int i = tid; i < kHeadTok * g.C * g.ph; i += kHeadThreads) {
+        int first = tid;
+        asm volatile("" : "+v"(first));  // made here: the loop's addresses are not kept in registers across the groups
+        for (int i = first; i < kHeadTok * g.C * g.ph; i += kHeadThreads) {
           const int t = i % kHeadTok, row = i / kHeadTok, ch = row / g.ph, dy = row - ch * g.ph;
           if (tok0 + t >= Ls) continue;
           const long n = token_idx ? (long)token_idx[tok0 + t] : tok0 + t;
