@@ -411,13 +411,24 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   // Key factors of a tile: a thread of the first two waves fetches one with the tile before and stores it in its MFMA
   // phase, one barrier ahead of the softmax phase that reads it (the other group, half an iteration behind, then still
   // reads the other buffer). Keys past the end get 1.
+  // With factors and 256 rows the kernel is at the register limit, and what a few instructions make again from the thread
+  // id must not be kept across the loop: this hides the id from the compiler, which would keep it and spill six registers
+  // (13104 x 77 on scaled queries, 40 heads, 141 -> 134 us; 32760 x 512, 12 heads, 142.3 -> 140.5). Not where the kernel
+  // scales the logits itself over short keys: there the spills cost less (13104 x 480 74.2 us, without them 76.1). The V
+  // rows' addresses stay: made again for every tile they cost 10 % of the launch.
+  constexpr bool FRESH = CS && (PRE || !SUM32);
+  auto fresh_tid = [&]() {
+    int t = tid;
+    if constexpr (FRESH) asm volatile("" : "+v"(t));
+    return t;
+  };
   float rc = 1.f;
   auto load_c = [&](int kt) {
-    const int key = kt * KTL + tid;
+    const int key = kt * KTL + fresh_tid();
     if (tid < KTL) rc = key < (int)Lk ? col_scale[key] : 1.0f;
   };
   auto store_c = [&](int buf) {
-    if (tid < KTL) smc[buf * KTL + tid] = rc;
+    if (tid < KTL) smc[buf * KTL + fresh_tid()] = rc;
   };
   // LDS row of the K tile that fragment row lane % 16 of block kb stands for
   const int krow0 = 16 * (lq >> 3) + (lq & 7);
@@ -640,9 +651,10 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
       l += swap_halves(l);
     }
     const float inv = 1.0f / l;
-    const long q = q_wave0 + 16 * rb + lq;
+    const int t = fresh_tid();
+    const long q = FRESH ? (long)qt * QROWS + (t >> 6) * 16 * RB + 16 * rb + (t & 15) : q_wave0 + 16 * rb + lq;
     if (q < Lq) {
-      uint16_t* op = O + q * (long)D + head * DH + 4 * g;
+      uint16_t* op = O + q * (long)D + head * DH + 4 * (FRESH ? (t & 63) >> 4 : g);
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
         uint2 w;

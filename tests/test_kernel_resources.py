@@ -21,6 +21,7 @@ def _scratch(source, tmp_path):
 
 @pytest.mark.parametrize("source,kernels,at_least", [
     ("glue.hip", r"head_update_kernel", 18),  # six widths, three updates
+    ("attention.hip", r"attention_pp16_kernelILi\d+ELb1E", 20),  # scaled queries: head sizes, tile sizes, kinds
 ])
 def test_no_scratch(source, kernels, at_least, tmp_path):
     got = {n: v for n, v in _scratch(source, tmp_path).items() if re.search(kernels, n)}
