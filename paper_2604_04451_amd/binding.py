@@ -149,6 +149,7 @@ def _bind_ops(lib):
         "chorus_ln_modulate": (i32, [vp, vp, i64, i32, vp, vp, vp, vp, i32, vp]),
         "chorus_qk_norm_rope": (i32, [vp, i64, vp, vp, i64, i64, i32, i32, vp, i32, i32, i32, i32, f32, vp]),
         "chorus_v_transpose": (i32, [vp, i64, vp, i64, i64, i32, vp]),
+        "chorus_attention_variant": (i32, [i64, i64, i64, i32, i32, i32, i32]),
         "chorus_attention": (i32, [vp, vp, vp, vp, vp, i64, i64, i64, i64, i32, i32, i32, vp]),
         "chorus_glue_workspace_bytes": (sz, [i32, i32, i64]),
         "chorus_patch_embed": (i32, [vp, i32, i32, i32, i32, i32, i32, vp, i64, GW, i32, vp, vp, sz, vp]),

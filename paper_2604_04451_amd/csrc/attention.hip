@@ -5,7 +5,7 @@
 // Two kernels of one design: attention_pp_kernel on v_mfma_f32_32x32x16_bf16 (64-key
 // tiles: keys padded to 64 only, and many queries on few keys), described first, and
 // attention_pp16_kernel on v_mfma_f32_16x16x32_bf16 (128-key tiles: the rest, see
-// attention_wide_tiles), whose differences are described in front of it.
+// attention_variant), whose differences are described in front of it.
 // Both take the optional per-key logit factor.
 //
 // Work split: a workgroup of 8 waves owns 256 query rows of one head (32 per wave, held in
@@ -736,26 +736,42 @@ int32_t launch_attn_pp(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt,
 
 }  // namespace
 
-// Measured with 12 heads of 128 (microseconds, 64-key kernel / 128-key kernel; f: with the key factor):
-//   half tiles     480 x 480 20.4 / 13.7, 1200 x 77 12.6 / 9.6, 128 x 128 9.7 / 8.9: the 64-key kernel has no half tile
-//   f, any launch  3271 x 77 16.8 / 15.9, 13104 x 226 61.6 / 52.0: the factors come from LDS
-//   full tiles     13104 x 480 71.4 / 66.7, 13104 x 226 50.7 / 49.5, but 13104 x 128 40.3 / 41.4, 32760 x 16 69.8 / 84.9 (half of
-//                  the one tile is padding), and, where one round does not fill the chip, 3271 x 256 16.8 / 17.6
-bool attention_wide_tiles(long Lq, long Lk, long LkPad, int H, bool factor) {
-  if (LkPad % 128) return false;
-  if (CHORUS_ATTENTION_LONG_KEYS(Lk, LkPad)) return true;
-  if (Lk <= 64) return false;
+// Under 512 keys. Launches of half tiles: the 64-key kernel has none (12 heads of 128, microseconds, 64-key kernel / 128-key
+// kernel: 480 x 480 20.4 / 13.7, 1200 x 77 12.6 / 9.6, 128 x 128 9.7 / 9.0). Launches of full tiles, time of the 128-key
+// kernel over that of the 64-key kernel on 288 to 2080 tiles:
+//   key factors, heads of 64: 0.6 to 0.9 from 70 to 511 keys: the factors come from LDS
+//   where half of the last 128-key tile or more is padding: 180 keys 0.95 to 1.14, 300 keys 0.91 to 1.12, 400 keys 0.95 to
+//   1.07 without factors, 0.85 to 1.07, mostly under 1, with them
+//   key factors, heads of 128: 70 to 90 keys 0.85 to 1.03, 100 keys 0.88 to 1.05, 110 and 128 keys (few or none masked)
+//   0.88 to 1.07, mostly over 1; 200, 226, 480 keys 0.81 to 0.99
+//   without: 70 to 128 keys 0.95 to 1.08, mostly over 1; 200 to 511 keys 0.88 to 1.03, but 1.00 to 1.05 on 156 to 240
+//   tiles, where one round does not fill the chip
+int attention_variant(long Lq, long Lk, long LkPad, int H, int dh, bool factor, int cus) {
+  if (LkPad % 128) return 3;
+  if (CHORUS_ATTENTION_LONG_KEYS(Lk, LkPad)) return 5;
+  if (Lk <= 64) return 3;
+  const long tiles = (Lq + 255) / 256 * H;
+  if (2 * tiles <= cus || (factor && dh == 64)) return 5;
+  if ((Lk + 63) / 64 % 2 && !(factor && Lk > 384)) return 3;
+  return (factor ? Lk <= 96 || Lk > 128 : Lk > 128 && tiles > cus) ? 5 : 3;
+}
+
+bool attention_wide_tiles(long Lq, long Lk, long LkPad, int H, int dh, bool factor) {
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    return false;
-  const long tiles = (Lq + 255) / 256 * H;
-  if (factor || 2 * tiles <= cus) return true;
-  return Lk > 128 && tiles > cus;
+    cus = 0;
+  return attention_variant(Lq, Lk, LkPad, H, dh, factor, cus) == 5;
 }
 
 }  // namespace chorus
 
 using namespace chorus;
+
+extern "C" int32_t chorus_attention_variant(int64_t Lq, int64_t Lk, int64_t LkPad, int32_t H, int32_t dh, int32_t factor, int32_t cus) {
+  if (Lq < 1 || Lk < 1 || LkPad < Lk || H <= 0 || cus <= 0) return CHORUS_E_ARG;
+  if ((dh != 64 && dh != 128) || LkPad % KT) return CHORUS_E_SHAPE;
+  return attention_variant((long)Lq, (long)Lk, (long)LkPad, H, dh, factor != 0, cus);
+}
 
 // variant: 0 = default choice; 3 = 64-key tiles on 32x32x16 MFMAs; 5 = 128-key tiles on 16x16x32 MFMAs
 // (LkPad % 128 == 0); 6 = the same on pre-scaled queries
@@ -771,7 +787,7 @@ extern "C" int32_t chorus_attention(const uint16_t* Q, const uint16_t* K, const 
   if (!aligned16(Q) || !aligned16(K) || !aligned16(Vt) || !aligned16(O) || !aligned16(col_scale)) return CHORUS_E_ARG;
   hipStream_t s = (hipStream_t)stream;
   const bool cs = col_scale != nullptr;
-  if (variant == 0) variant = attention_wide_tiles((long)Lq, (long)Lk, (long)LkPad, H, cs) ? 5 : 3;
+  if (variant == 0) variant = attention_wide_tiles((long)Lq, (long)Lk, (long)LkPad, H, dh, cs) ? 5 : 3;
   if (variant == 5 || variant == 6) {
     if (LkPad % 128) return CHORUS_E_SHAPE;
     if (variant == 6)

@@ -213,7 +213,7 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   // 2-3. q/k RMSNorm + RoPE into head-major layout; V into key-contiguous layout.
   // Attention in 128-key tiles takes its queries already multiplied by log2(e) / sqrt(dh): the factor enters here, in fp32
   // ahead of the one rounding to bf16.
-  const bool q_prescaled = attention_wide_tiles(Ls, Ls, Lpad, H, false);
+  const bool q_prescaled = attention_wide_tiles(Ls, Ls, Lpad, H, dh, false);
   {
     ProfScope p(CHORUS_PROF_NORM, s);
     if (!w->g_q || !w->g_k || !aligned16(w->g_q) || !aligned16(w->g_k)) return CHORUS_E_ARG;
@@ -247,7 +247,7 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
     CHK(project_text_kv(sh, w, text_ctx, b.tkv, b.kc, b.vct, stream));
   }
   // pre-scaled queries as above
-  const bool cq_prescaled = attention_wide_tiles(Ls, Lt, LtPad, H, tgaa_key_scale != nullptr);
+  const bool cq_prescaled = attention_wide_tiles(Ls, Lt, LtPad, H, dh, tgaa_key_scale != nullptr);
   {
     ProfScope p(CHORUS_PROF_NORM, s);
     CHK(chorus_qk_norm_rope(b.qkv, D, w->g_cq, b.qh, Ls, Lpad, H, dh, nullptr, sh.gT, sh.gH, sh.gW, 0,
