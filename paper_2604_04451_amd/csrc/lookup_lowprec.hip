@@ -260,12 +260,16 @@ __global__ __launch_bounds__(kWaves * 64) void lowprec_scan_kernel(const void* _
 
 // ---- candidates and exact re-rank ---------------------------------------------------------------
 // threshold = best approximate r - margin * |q| (r = cosine * |q|); every row at or above it is re-scored from its
-// fp32 row by a whole wave with the fp32 lookup's own row pass. A wave owns a run of consecutive rows and looks at the
-// scores of 64 of them at once; the rows are spread over the whole chip, so even when every row is a candidate (FP8 on
-// a query far from every entry) the re-rank costs one fp32 scan. Each workgroup reduces the scan's partial maxima
-// itself (at most 1024, four per thread). Usually a handful of waves have a row at all, so the winners meet in atomic
-// maxima in memory. (With every wave of 4096 workgroups reducing 4096 maxima, and a partial
-// result per workgroup, the re-rank of one row among 16384 took 35.9 us and its final reduction 7.5.)
+// fp32 row by a whole wave with the fp32 lookup's own row pass. A wave owns every nwaves-th row and looks at the scores of
+// 64 of them at once. Candidates tend to stand side by side (variants of a prompt are stored one after the other): dealt
+// out singly they go to different waves, in runs of consecutive rows one wave would re-score them all in series (262144 x
+// 1024 FP8, 256 neighbours among the candidates: the call 194 us, dealt out 72). So even when every row is a candidate
+// (FP8 on a query far from every entry) the re-rank costs one fp32 scan. From 16 rows a wave on, neighbouring waves run on
+// one XCD, so that a line of scores is read into one L2 (1048576 x 64: 228.4 us without, 224.4 with); below, most waves
+// find the scores in the L2 of the XCD that wrote them (4100 x 1024 FP8: 9.8 us, 10.4 elsewhere). Each workgroup reduces
+// the scan's partial maxima itself (at most 1024, four per thread). Usually a handful of waves have a row at all, so the
+// winners meet in atomic maxima in memory. (With every wave of 4096 workgroups reducing 4096 maxima, and a partial result
+// per workgroup, the re-rank of one row among 16384 took 35.9 us and its final reduction 7.5.)
 __global__ __launch_bounds__(kWaves * 64) void lowprec_rerank_kernel(const float* __restrict__ cache_emb,
                                                                      const float* __restrict__ query, long N, int d,
                                                                      const float* __restrict__ scores,
@@ -277,9 +281,11 @@ __global__ __launch_bounds__(kWaves * 64) void lowprec_rerank_kernel(const float
   __shared__ int32_t si[kWaves];
   __shared__ int32_t sc[kWaves];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const long nwaves = (long)gridDim.x * kWaves, w_id = (long)blockIdx.x * kWaves + wave;
-  const long first = w_id * N / nwaves, end = (w_id + 1) * N / nwaves;
-  float own = first + lane < end ? scores[first + lane] : -INFINITY;  // in flight beside the maxima
+  const long nwaves = (long)gridDim.x * kWaves;
+  const long w_id = (long)(N >= 16 * nwaves ? xcd_remap(blockIdx.x, gridDim.x) : blockIdx.x) * kWaves + wave;
+  const long step = 64 * nwaves;  // rows that the chip looks at in one turn
+  auto score = [&](long r0) { return r0 + lane * nwaves < N ? scores[r0 + lane * nwaves] : -INFINITY; };
+  float own = score(w_id);  // in flight beside the maxima
   const float nq = sqrtf(*qnorm2);
   float mx = -INFINITY;
   for (int j = threadIdx.x; j < nparts; j += kWaves * 64) mx = fmaxf(mx, partial_max[j]);
@@ -295,12 +301,12 @@ __global__ __launch_bounds__(kWaves * 64) void lowprec_rerank_kernel(const float
   float best = -INFINITY;
   int32_t bi = 0x7fffffff, count = 0;
   if (thr > -INFINITY) {
-    for (long r0 = first; r0 < end; r0 += 64) {
-      if (r0 != first) own = r0 + lane < end ? scores[r0 + lane] : -INFINITY;
+    for (long r0 = w_id; r0 < N; r0 += step) {
+      if (r0 != w_id) own = score(r0);
       unsigned long long todo = __ballot(own >= thr);
       count += __popcll(todo);
       while (todo) {  // ascending rows
-        const long row = r0 + __builtin_ctzll(todo);
+        const long row = r0 + __builtin_ctzll(todo) * nwaves;
         todo &= todo - 1;
         float dot, cc, qq;
         fp32_row_products(reinterpret_cast<const float4*>(cache_emb + row * (long)d), q4, n4, lane, dot, cc, qq);
