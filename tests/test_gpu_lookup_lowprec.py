@@ -101,9 +101,9 @@ def test_lowprec_lookup_near_duplicates_and_edges(fmt, code):
 
 
 @pytest.mark.parametrize("fmt,code", FMTS)
-@pytest.mark.parametrize("N,d", [(1, 16), (5, 512), (4097, 1024), (9001, 1040), (4100, 2064), (4099, 4096), (4103, 4112), (8200, 48)])
+@pytest.mark.parametrize("N,d", [(1, 16), (5, 512), (4096, 1024), (4095, 4096), (4097, 1024), (9001, 1040), (4100, 2064), (4099, 4096), (4103, 4112), (8200, 48)])
 def test_lowprec_lookup_rows_per_wave(N, d, fmt, code):
-    """Rows in registers (all chunk counts, partly filled ones) and the wide fallback, waves with one, several and no
+    """The query in registers (all chunk counts, partly filled ones; from 4097 rows on) and read per row, waves with one, several and no
     rows: the result words equal the fp32 lookup's for a query near a row that occurs twice and for one far from all."""
     print(f"[case] lowprec rows per wave N={N} d={d} {fmt}", flush=True)
     g = torch.Generator(device=DEV).manual_seed(N + d)
