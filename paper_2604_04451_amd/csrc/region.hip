@@ -101,8 +101,7 @@ constexpr int kSmallTile = kCompactThreads * 4;
 constexpr long kOneLaunchSites = 80 * 1024;
 
 __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const uint8_t* __restrict__ mask, long L,
-                                                                  int* __restrict__ idx_out, int* __restrict__ count_out,
-                                                                  bool vec) {
+                                                                  int* __restrict__ idx_out, int* __restrict__ count_out) {
   __shared__ int s_before[kCompactThreads / 64];
   const long tile0 = (long)blockIdx.x * kSmallTile, base = tile0 + 4 * threadIdx.x;
   uint32_t bits = 0;
@@ -114,24 +113,24 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const uint8_t*
     for (int b = 0; b < 4; ++b)
       if (base + b < L && mask[base + b]) bits |= 1u << b;
   }
-  int before = 0;
-  if (vec) {
-    constexpr int U = 8;  // loads in flight; past the tiles in front the last piece again, not counted
-    for (long at = (long)threadIdx.x * kBytesPerThread; at < tile0; at += (long)U * kCompactTile) {
-      u32x4 v[U];
+  // what stands in front, in aligned pieces of 16 bytes wherever the mask starts (byte by byte a mask off a 16-byte boundary
+  // took 30 us at 75600 sites instead of 6); the bytes in front of the first and behind the last piece singly
+  const long head = tile0 ? (long)(-reinterpret_cast<uintptr_t>(mask) & 15u) : 0, body = (tile0 - head) & ~15L;
+  int before = threadIdx.x < head && mask[threadIdx.x] ? 1 : 0;
+  if (threadIdx.x < 16 && head + body + threadIdx.x < tile0 && mask[head + body + threadIdx.x]) ++before;
+  constexpr int U = 8;  // loads in flight; past the pieces in front the last piece again, not counted
+  for (long at = (long)threadIdx.x * kBytesPerThread; at < body; at += (long)U * kCompactTile) {
+    u32x4 v[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        v[u] = *reinterpret_cast<const u32x4*>(mask + (at + u * kCompactTile < tile0 ? at + u * kCompactTile : at));
+    for (int u = 0; u < U; ++u)
+      v[u] = *reinterpret_cast<const u32x4*>(mask + head + (at + u * kCompactTile < body ? at + u * kCompactTile : at));
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (at + u * kCompactTile >= tile0) break;
+    for (int u = 0; u < U; ++u) {
+      if (at + u * kCompactTile >= body) break;
 #pragma unroll
-        for (int k = 0; k < 4; ++k)  // the top bit of every byte that is not zero
-          before += __popc((((v[u][k] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v[u][k]) & 0x80808080u);
-      }
+      for (int k = 0; k < 4; ++k)  // the top bit of every byte that is not zero
+        before += __popc((((v[u][k] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v[u][k]) & 0x80808080u);
     }
-  } else {
-    for (long at = (long)threadIdx.x * kBytesPerThread; at < tile0; at += kCompactTile) before += __popc(nonzero_bits16(mask, at, L));
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
@@ -267,7 +266,7 @@ int32_t chorus_region_compact(const uint8_t* mask, int64_t L, int32_t* idx_out, 
   int ntiles = (int)((L + kCompactTile - 1) / kCompactTile);
   if (L > 0 && L <= kOneLaunchSites) {
     hipLaunchKernelGGL(compact_kernel, dim3((unsigned)((L + kSmallTile - 1) / kSmallTile)), dim3(kCompactThreads), 0, s, mask, (long)L,
-                       idx_out, count_out, aligned16(mask));
+                       idx_out, count_out);
     CHORUS_LAUNCH_CHECK();
     return CHORUS_OK;
   }

@@ -1,5 +1,7 @@
 """GPU parity: region-mask pipeline (key-frame propagation + max-pool projection, Eq. 5
 dilation hierarchy) against the CPU oracle, through the C ABI. Byte work: bit-exact."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -136,7 +138,7 @@ def test_mask_pipeline_full_shape(name, Hp, Wp):
 
 
 @pytest.mark.parametrize("L", [1, 3, 4, 1023, 1024, 1025, 4097, 75600, 81919, 81920, 81921, 300001])
-@pytest.mark.parametrize("offset", [0, 1, 4])
+@pytest.mark.parametrize("offset", [0, 1, 4, 15])
 def test_compact_tiles(L, offset):
     """One launch up to 81920 sites, three beyond; masks on and off a 16- and a 4-byte boundary, any non-zero byte set."""
     print(f"[case] compact L={L} offset={offset}", flush=True)
@@ -148,3 +150,35 @@ def test_compact_tiles(L, offset):
         want = mask.nonzero()[:, 0].to(torch.int32)
         n = int(count.cpu()[0])
         assert n == want.numel() and torch.equal(idx[:n], want) and bool((idx[n:] == -7).all())
+
+
+def test_compact_off_the_boundary_takes_no_longer():
+    """A mask that starts off a 16-byte boundary (a row of a batch of masks) against an aligned one: the same work but for
+    a few bytes. Counted byte by byte it took five times as long; twice is allowed for the clock and the box."""
+    print("[case] compact off the boundary L=75600", flush=True)
+    L = 75600
+    buf = (torch.rand(L + 16, device="cuda") < 0.4).to(torch.uint8)
+    ws = torch.empty(P.load().chorus_region_compact_workspace_bytes(L), dtype=torch.uint8, device="cuda")
+    idx, count = torch.empty(L, dtype=torch.int32, device="cuda"), torch.empty(1, dtype=torch.int32, device="cuda")
+    us = []
+    for offset in (0, 1):
+        mask = buf[offset:offset + L]
+        graph = torch.cuda.CUDAGraph()
+        P.chorus_region_compact(mask, idx, count, ws)
+        torch.cuda.synchronize()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                P.chorus_region_compact(mask, idx, count, ws)
+        best = math.inf
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            graph.replay()
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3 / 20)
+        us.append(best)
+        want = mask.nonzero()[:, 0].to(torch.int32)
+        assert int(count) == want.numel() and torch.equal(idx[:want.numel()], want)
+    print(f"[info] aligned {us[0]:.1f} us, one byte off {us[1]:.1f} us", flush=True)
+    assert us[1] <= 2 * us[0], us
