@@ -20,7 +20,9 @@ __device__ __forceinline__ float sinusoid(float t, int i, int half) {
   return i < half ? cs : sn;
 }
 
-constexpr int kFeatureLds = 8192;  // more features than this (32 KB of LDS) are made in a launch of their own
+// More features than this are made in a launch of their own, once and not by every workgroup. D = 1536, with the launch /
+// without: 2048 features 20.2 / 19.9 us, 4096 21.6 / 21.9, 8192 24.2 / 27.2.
+constexpr int kFeatureLds = 2048;
 
 __global__ __launch_bounds__(256) void sinusoid_kernel(float t, int half, float* __restrict__ f) {
   const int i = blockIdx.x * 256 + threadIdx.x;
@@ -28,8 +30,10 @@ __global__ __launch_bounds__(256) void sinusoid_kernel(float t, int half, float*
 }
 
 // out[n] = sum_k W[n][k] act(x[k]) + b[n]; ACT: silu on the input vector. One wave per row n; K % 8 == 0.
-// out2 (optional) receives the same values (the two head rows). FEATURES: x is the sinusoidal features of t (K of them),
-// made by every workgroup for itself in LDS: one sine per thread instead of a launch in front of this one (4.8 us).
+// The waves of a compute unit keep enough loads in flight between them: with four of a lane's own the call was slower (D =
+// 3072 43.2 us, 40.4 with one; 1536 17.0 / 16.9). out2 (optional) receives the same values (the two head rows). FEATURES: x
+// is the sinusoidal features of t (K of them), made by every workgroup for itself in LDS: one sine per thread instead of a
+// launch in front of this one (4.8 us).
 template <bool SILU_IN, bool FEATURES>
 __global__ __launch_bounds__(256) void gemv_bf16w_kernel(const uint16_t* __restrict__ W, const float* __restrict__ x_in,
                                                          const float* __restrict__ b, float* __restrict__ out,
@@ -45,28 +49,17 @@ __global__ __launch_bounds__(256) void gemv_bf16w_kernel(const uint16_t* __restr
   if (n >= N) return;
   const uint16_t* w = W + (long)n * K;
   float acc = 0.f;
-  constexpr int U = 4;  // weight loads in flight per lane: they are what this kernel waits for
-  for (int k0 = lane * 8; k0 < K; k0 += U * 64 * 8) {
-    u32x4 u[U];
+  for (int k = lane * 8; k < K; k += 64 * 8) {
+    const u32x4 u = *reinterpret_cast<const u32x4*>(w + k);
+    const f32x4 x0 = *reinterpret_cast<const f32x4*>(x + k);
+    const f32x4 x1 = *reinterpret_cast<const f32x4*>(x + k + 4);
+    const float xv[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
 #pragma unroll
-    for (int c = 0; c < U; ++c) {
-      const int k = k0 + c * 512;
-      u[c] = *reinterpret_cast<const u32x4*>(w + (k < K ? k : k0));
-    }
-#pragma unroll
-    for (int c = 0; c < U; ++c) {
-      const int k = k0 + c * 512;
-      if (k >= K) break;
-      const f32x4 x0 = *reinterpret_cast<const f32x4*>(x + k);
-      const f32x4 x1 = *reinterpret_cast<const f32x4*>(x + k + 4);
-      const float xv[8] = {x0[0], x0[1], x0[2], x0[3], x1[0], x1[1], x1[2], x1[3]};
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        float v = xv[j];
-        if (SILU_IN) v = v / (1.0f + __expf(-v));
-        const float wv = __uint_as_float((j & 1) ? (u[c][j >> 1] & 0xffff0000u) : (u[c][j >> 1] << 16));
-        acc = __builtin_fmaf(wv, v, acc);
-      }
+    for (int j = 0; j < 8; ++j) {
+      float v = xv[j];
+      if (SILU_IN) v = v / (1.0f + __expf(-v));
+      const float wv = __uint_as_float((j & 1) ? (u[j >> 1] & 0xffff0000u) : (u[j >> 1] << 16));
+      acc = __builtin_fmaf(wv, v, acc);
     }
   }
   acc = wave_sum(acc);

@@ -233,7 +233,8 @@ def test_mfma_ceiling_runs_and_orders():
     assert 300.0 < mix < rnd * 1.02 and rnd < ones * 1.02 and ones < 2700.0
 
 
-@pytest.mark.parametrize("name,freq_dim", [("c1", 256), ("wan1p3b_small", 256), ("c1", 64)])
+@pytest.mark.parametrize("name,freq_dim", [("c1", 256), ("wan1p3b_small", 256), ("c1", 64),
+                                           ("c1", 2048), ("c1", 2056)])  # features in LDS, in a launch of their own
 def test_time_mod(name, freq_dim):
     print(f"[case] time_mod {name} freq_dim={freq_dim}", flush=True)
     bs = synth.SHAPES[name]
