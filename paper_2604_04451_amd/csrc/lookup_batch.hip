@@ -170,6 +170,40 @@ __device__ __forceinline__ void sum_slices(const float* __restrict__ part_dot, c
   }
 }
 
+// |q|, summed in one order by both kernels that divide by it, so that an entry has the same score whatever k is. The first
+// 4096 values are requested by the constructor, ahead of the partial sums, and added behind them. d % 4 == 0, 256 threads.
+struct QueryNorm {
+  static constexpr int QU = 4;
+  const f32x4* q4;
+  int n4;
+  f32x4 v[QU];
+  __device__ __forceinline__ QueryNorm(const float* q, int d, int tid) : q4(reinterpret_cast<const f32x4*>(q)), n4(d >> 2) {
+#pragma unroll
+    for (int c = 0; c < QU; ++c) v[c] = tid + 256 * c < n4 ? q4[tid + 256 * c] : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ float get(float (&sq)[4], int tid) const {
+    auto add = [](float s, const f32x4& w) {  // the roundings spelled out: not left to what each kernel's compilation contracts
+#pragma clang fp contract(off)
+      return s + (__builtin_fmaf(w[0], w[0], w[1] * w[1]) + __builtin_fmaf(w[2], w[2], w[3] * w[3]));
+    };
+    float qq = 0.f;
+#pragma unroll
+    for (int c = 0; c < QU; ++c) qq = add(qq, v[c]);
+    for (int i = tid + 256 * QU; i < n4; i += 256) qq = add(qq, q4[i]);
+    qq = wave_sum(qq);
+    if ((tid & 63) == 0) sq[tid >> 6] = qq;
+    __syncthreads();
+    return sqrtf(sq[0] + sq[1] + sq[2] + sq[3]);
+  }
+};
+
+// the score of an entry: -inf for zero norms and NaN
+__device__ __forceinline__ float batch_score(float dot, float cc, float qn) {
+  const float den = sqrtf(cc) * qn;
+  const float v = den > 0.f ? dot / den : -INFINITY;
+  return v == v ? v : -INFINITY;
+}
+
 constexpr int kWaveK = 64;  // up to this k a list is one key per lane
 
 // ---- keys: a score and its row as one integer, larger = better (higher score, then lower row); 0 = no entry ----
@@ -292,33 +326,14 @@ __global__ __launch_bounds__(256) void lookup_batch_select_kernel(const float* _
   float dot[R], cc[R];
 #pragma unroll
   for (int u = 0; u < R; ++u) dot[u] = cc[u] = 0.f;
-  // the first 4096 query values are requested ahead of the partial sums and added behind them
-  constexpr int QU = 4;
-  const int n4 = d >> 2;
-  const f32x4* q4 = reinterpret_cast<const f32x4*>(queries + (long)q * d);
-  f32x4 qv[QU];
-#pragma unroll
-  for (int c = 0; c < QU; ++c) qv[c] = tid + 256 * c < n4 ? q4[tid + 256 * c] : f32x4{0.f, 0.f, 0.f, 0.f};
+  const QueryNorm norm(queries + (long)q * d, d, tid);
   sum_slices<R, 8, R, 256>(part_dot, part_cc, KS, QP, q, Npad, j0, N, dot, cc);
-  float qq = 0.f;
-#pragma unroll
-  for (int c = 0; c < QU; ++c) qq += (qv[c][0] * qv[c][0] + qv[c][1] * qv[c][1]) + (qv[c][2] * qv[c][2] + qv[c][3] * qv[c][3]);
-  for (int i = tid + 256 * QU; i < n4; i += 256) {
-    const f32x4 v = q4[i];
-    qq += (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]);
-  }
-  qq = wave_sum(qq);
-  if (lane == 0) sq[wave] = qq;
-  __syncthreads();
-  const float qn = sqrtf(sq[0] + sq[1] + sq[2] + sq[3]);
+  const float qn = norm.get(sq, tid);
   uint64_t key[4];
 #pragma unroll
   for (int u = 0; u < R; ++u) {
     const long j = j0 + 256L * u;
-    const float den = sqrtf(cc[u]) * qn;
-    float v = den > 0.f ? dot[u] / den : -INFINITY;
-    if (!(v == v)) v = -INFINITY;
-    key[u] = j < N ? make_key(v, (uint32_t)j) : 0;
+    key[u] = j < N ? make_key(batch_score(dot[u], cc[u], qn), (uint32_t)j) : 0;
   }
   // Every wave lists the k best of its 256 entries; with several row blocks the lists of a query meet in memory, one per
   // wave while the last workgroup can take them all in one go, else one per workgroup.
@@ -394,7 +409,7 @@ __global__ __launch_bounds__(256) void lookup_batch_select_kernel(const float* _
   }
 }
 
-// Final scores alone, for k > 64
+// Final scores alone
 __global__ __launch_bounds__(256) void lookup_batch_final_kernel(const float* __restrict__ part_dot,
                                                                  const float* __restrict__ part_cc,
                                                                  const float* __restrict__ queries,
@@ -403,28 +418,18 @@ __global__ __launch_bounds__(256) void lookup_batch_final_kernel(const float* __
   constexpr int R = 4;
   __shared__ float sq[4];
   const int q = blockIdx.y;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  float qq = 0.f;
-  for (int i = tid; i < d; i += 256) {
-    const float v = queries[(long)q * d + i];
-    qq += v * v;
-  }
-  qq = wave_sum(qq);
-  if (lane == 0) sq[wave] = qq;
-  __syncthreads();
-  const float qn = sqrtf(sq[0] + sq[1] + sq[2] + sq[3]);
+  const int tid = threadIdx.x;
   const long j0 = (long)blockIdx.x * (256 * R) + tid;
   float dot[R], cc[R];
 #pragma unroll
   for (int u = 0; u < R; ++u) dot[u] = cc[u] = 0.f;
+  const QueryNorm norm(queries + (long)q * d, d, tid);
   sum_slices<R, 8, R, 256>(part_dot, part_cc, KS, QP, q, Npad, j0, N, dot, cc);
+  const float qn = norm.get(sq, tid);
 #pragma unroll
   for (int u = 0; u < R; ++u) {
     const long j = j0 + 256L * u;
-    const float den = sqrtf(cc[u]) * qn;
-    float v = den > 0.f ? dot[u] / den : -INFINITY;
-    if (!(v == v)) v = -INFINITY;
-    if (j < N) scores[(long)q * Npad + j] = v;
+    if (j < N) scores[(long)q * Npad + j] = batch_score(dot[u], cc[u], qn);
   }
 }
 

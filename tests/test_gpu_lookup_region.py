@@ -301,3 +301,15 @@ def test_lookup_batch_selection(N, k):
         assert bool((got_i[1:][equal] > got_i[:-1][equal]).all())    # equal scores by index
         assert int(hit[q]) == int(got_s[0] >= 0.75)
     assert idx[3].tolist() == list(range(k)) and bool(torch.isneginf(sc[3]).all()) and int(hit[3]) == 0
+
+
+@pytest.mark.parametrize("N,d,Q", [(700, 4096, 24), (3000, 1000, 17), (8192, 768, 32), (5000, 4100, 2)])
+def test_lookup_batch_scores_do_not_depend_on_k(N, d, Q):
+    """An entry scores the same bits whichever kernels serve the call: lists (k <= 64), scores written out (k > 64)."""
+    print(f"[case] lookup_batch scores over k N={N} d={d} Q={Q}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + d)
+    cache, queries = torch.randn(N, d, device=DEV, generator=g), torch.randn(Q, d, device=DEV, generator=g)
+    idx, sc, hit = P.chorus_cache_lookup_batch(cache, queries, 0.05, 100)
+    for k in (1, 2, 8, 9, 64, 65):
+        i, s, h = P.chorus_cache_lookup_batch(cache, queries, 0.05, k)
+        assert torch.equal(s, sc[:, :k]) and torch.equal(i, idx[:, :k]) and torch.equal(h, hit), k
