@@ -409,7 +409,7 @@ __global__ __launch_bounds__(256) void lookup_batch_select_kernel(const float* _
   }
 }
 
-// Final scores alone
+// Final scores alone, where the selection is a pass of its own
 __global__ __launch_bounds__(256) void lookup_batch_final_kernel(const float* __restrict__ part_dot,
                                                                  const float* __restrict__ part_cc,
                                                                  const float* __restrict__ queries,
@@ -433,14 +433,16 @@ __global__ __launch_bounds__(256) void lookup_batch_final_kernel(const float* __
   }
 }
 
-// k > 64, or an empty cache. One workgroup per query: k rounds over its final scores, each picking the best entry that comes after the
+// k > 64, an empty cache, or a single round over many lists. One workgroup per query: k rounds over its final scores, each picking the best entry that comes after the
 // previous winner in the order (score descending, index ascending). REG: the scores of a thread live in registers
-// (N <= 8 * 1024), else they are re-read from `scores`.
+// (N <= kTopkRegs), else they are re-read from `scores`.
+constexpr long kTopkRegs = 8 * 1024;
 template <bool REG>
 __global__ __launch_bounds__(1024) void lookup_topk_kernel(const float* __restrict__ scores, long N, long Npad, int k,
                                                            float tau, int32_t* __restrict__ out_idx,
                                                            float* __restrict__ out_score, int32_t* __restrict__ out_hit) {
   constexpr int R = 8;
+  static_assert(R * 1024 == kTopkRegs, "the scores that 1024 threads hold");
   __shared__ float sv[2][16];
   __shared__ int si[2][16];  // N < 2^31 entries per call
   const int q = blockIdx.x;
@@ -581,7 +583,11 @@ int32_t chorus_cache_lookup_batch(const float* cache_emb, int64_t N, int32_t d, 
     const float* qs = queries + (long)q0 * d;
     const long Npad = (long)p.tiles * kBR;
     const long nb = (N + 1023) / 1024;  // row blocks of the selection
-    const bool lists_fit = k <= kWaveK;
+    // Selected where the scores are made, up to 64 of them. The best entry alone a pass of its own finds as fast while it keeps
+    // the scores in registers, and the release of every (row block, query) workgroup comes to more than that launch: k = 1, 768
+    // values, apart / together: 8192 entries, 32 queries 20.1 / 21.2 us, 16 queries 16.1 / 16.6, 12 queries 15.7 / 15.5; 4096
+    // entries, 32 queries 17.2 / 17.9, 24 queries 16.5 / 16.4; beyond 8192 entries 9000 x 64, 32 queries 14.5 / 13.6.
+    const bool lists_fit = k <= kWaveK && !(k == 1 && N <= kTopkRegs && nb * Qc > 100);
     // the waves' lists take the place of the scores (128 bytes a row against at most 64 a row of a block), the arrival
     // counts stand behind them; a single row block needs neither
     uint64_t* lists = reinterpret_cast<uint64_t*>(w.scores);
@@ -606,7 +612,7 @@ int32_t chorus_cache_lookup_batch(const float* cache_emb, int64_t N, int32_t d, 
                          qs, w.scores, (long)N, Npad, d, QP, p.KS);
       CHORUS_LAUNCH_CHECK();
     }
-    if (N <= 8 * 1024)
+    if (N <= kTopkRegs)
       hipLaunchKernelGGL(lookup_topk_kernel<true>, dim3(Qc), dim3(1024), 0, s, w.scores, (long)N, Npad, k, tau,
                          out_index + (long)q0 * k, out_score + (long)q0 * k, out_hit + q0);
     else
