@@ -5,6 +5,7 @@ import ctypes as C
 import math
 import os
 import re
+import types
 
 import numpy as np
 import pytest
@@ -34,6 +35,17 @@ def test_library_exports_every_declared_symbol():
     # and the binding knows a signature for each
     assert decl <= set(lib._sigs), sorted(decl - set(lib._sigs))
     assert lib.chorus_version() >= 100
+
+
+def test_current_stream_with_and_without_the_raw_getter(monkeypatch):
+    """The binding hands over the handle of the current stream of the current device, from torch's raw getter or, where
+    torch has none, from its public interface."""
+    monkeypatch.setattr(B.torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(B.torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x7000))
+    monkeypatch.setattr(B, "_raw_stream", lambda device: 0x100 + device)
+    assert B._stream() == 0x103
+    monkeypatch.setattr(B, "_raw_stream", None)
+    assert B._stream() == 0x7000
 
 
 @pytest.mark.parametrize("N", [1, 4, 5, 8, 50])
