@@ -40,12 +40,32 @@ int32_t chorus_gemm_bf16(const uint16_t* A, const uint16_t* W, int64_t M, int32_
                          void* stream);
 
 /* chorus_gemm_bf16 with the tile kernel named by the caller, for tests and comparisons (every kernel is correct on
- * every shape the call accepts; only the speed differs): kernel 0 = the default choice by problem size,
- * 1 = 128 x 64 register-staged tiles, 2 = 256 x 128 register-staged tiles, 3 = 256 x 256 direct-to-LDS tiles,
- * 4 = 128 x 128 direct-to-LDS tiles. Anything else: CHORUS_E_ARG. */
+ * every shape the call accepts; only the speed differs): kernel 0 = the default choice by problem size, else tiles
+ * filled straight from global memory into 1 = 64 x 64 (four stages in LDS), 2 = 128 x 256 (three), 3 = 256 x 256 (two),
+ * 4 = 128 x 128 (two), 5 = 128 x 128 (three). Anything else: CHORUS_E_ARG. */
 int32_t chorus_gemm_bf16_kernel(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, int32_t epilogue,
                                 void* out, const float* bias, const float* gate0, const float* gate1, float scale,
                                 int32_t kernel, void* stream);
+
+/* The gated-residual product (CHORUS_EPI_RESID) with the kernel (1 .. 5 as above) and the number of slices of K named by the
+ * caller, for tests: a block runs its second FFN product so, in scratch that its workspace holds. Every slice but the last
+ * leaves its fp32 [M, N] result in parts (dev, slices - 1 of them, 16-byte aligned; unused with one slice), a second launch
+ * adds them in ascending order. 1 <= slices <= 4 (CHORUS_E_ARG), slices <= K / 64 (CHORUS_E_SHAPE); parts missing or too
+ * small: CHORUS_E_WORKSPACE. */
+int32_t chorus_gemm_bf16_slices(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, float* out,
+                                const float* bias, const float* gate0, const float* gate1, float scale, int32_t kernel,
+                                int32_t slices, float* parts, size_t parts_bytes, void* stream);
+
+/* What the default choice is, host only: the first head_rows rows run on kernel 3 in a launch of their own (0: the rows are
+ * not cut), the others on `kernel` in `slices` slices of K. first_bytes and rest_bytes: the scratch for the first and for
+ * the further slices (0, 0: chorus_gemm_bf16). */
+typedef struct {
+  int64_t head_rows;
+  int32_t kernel;
+  int32_t slices;
+} chorus_gemm_plan;
+int32_t chorus_gemm_bf16_plan(int64_t M, int32_t N, int32_t K, int32_t epilogue, size_t first_bytes, size_t rest_bytes,
+                              chorus_gemm_plan* out);
 
 /* out bf16 [L, D] = LN(x) * (mul_base + mul0 + mul1) + (add0 + add1), LN over D without
  * affine, eps 1e-6; mul_base = 1 if plus_one else 0; mul1/add1 may be NULL.

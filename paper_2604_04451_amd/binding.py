@@ -79,6 +79,10 @@ class TimeWeights(C.Structure):
     _fields_ = [(n, C.c_void_p) for n in ("w_t1", "b_t1", "w_t2", "b_t2", "w_tp", "b_tp")]
 
 
+class GemmPlan(C.Structure):
+    _fields_ = [("head_rows", C.c_int64), ("kernel", C.c_int32), ("slices", C.c_int32)]
+
+
 class RunResult(C.Structure):
     _fields_ = [("index", C.c_int32), ("score", C.c_float), ("hit", C.c_int32), ("K1", C.c_int32),
                 ("K2", C.c_int32), ("Ls", C.c_int32)]
@@ -146,6 +150,8 @@ def _bind_ops(lib):
     ops = {
         "chorus_gemm_bf16": (i32, [vp, vp, i64, i32, i32, i32, vp, vp, vp, vp, f32, vp]),
         "chorus_gemm_bf16_kernel": (i32, [vp, vp, i64, i32, i32, i32, vp, vp, vp, vp, f32, i32, vp]),
+        "chorus_gemm_bf16_slices": (i32, [vp, vp, i64, i32, i32, vp, vp, vp, vp, f32, i32, i32, vp, sz, vp]),
+        "chorus_gemm_bf16_plan": (i32, [i64, i32, i32, i32, sz, sz, C.POINTER(GemmPlan)]),
         "chorus_ln_modulate": (i32, [vp, vp, i64, i32, vp, vp, vp, vp, i32, vp]),
         "chorus_qk_norm_rope": (i32, [vp, i64, vp, vp, i64, i64, i32, i32, vp, i32, i32, i32, i32, f32, vp]),
         "chorus_v_transpose": (i32, [vp, i64, vp, i64, i64, i32, vp]),
@@ -541,6 +547,33 @@ def chorus_gemm_bf16(A, W, epilogue, out, bias=None, gate0=None, gate1=None, sca
     _status("chorus_gemm_bf16", lib.chorus_gemm_bf16(_p(A), _p(W), M, N, K, epilogue, _p(out), _p(bias), _p(gate0),
                                                      _p(gate1), float(scale), _stream()))
     return out
+
+
+def chorus_gemm_bf16_slices(A, W, out, kernel, slices, bias=None, gate0=None, gate1=None, scale=1.0, parts=None):
+    """out += gate * scale * (A W^T + bias) on a named kernel, K in slices (1 to 4); parts fp32, (slices - 1) M N values."""
+    lib = load()
+    _chk(A, torch.bfloat16, "A")
+    _chk(W, torch.bfloat16, "W")
+    (M, K), N = A.shape, W.shape[0]
+    if W.shape[1] != K:
+        raise TypeError("A/W inner dimensions differ")
+    _chk(out, torch.float32, "out", (M, N))
+    for n, t in (("bias", bias), ("gate0", gate0), ("gate1", gate1)):
+        _chk(t, torch.float32, n, (N,))
+    if parts is None and slices > 1:
+        parts = torch.empty((slices - 1) * M * N, dtype=torch.float32, device=A.device)
+    _chk(parts, torch.float32, "parts")
+    _status("chorus_gemm_bf16_slices",
+            lib.chorus_gemm_bf16_slices(_p(A), _p(W), M, N, K, _p(out), _p(bias), _p(gate0), _p(gate1), float(scale), int(kernel),
+                                        int(slices), _p(parts), 0 if parts is None else parts.numel() * 4, _stream()))
+    return out
+
+
+def chorus_gemm_bf16_plan(M, N, K, epilogue, first_bytes=0, rest_bytes=0):
+    """(rows of the first launch on kernel 3, kernel of the others, slices of K) of the default choice; host only."""
+    out = GemmPlan()
+    _status("chorus_gemm_bf16_plan", load().chorus_gemm_bf16_plan(M, N, K, epilogue, first_bytes, rest_bytes, C.byref(out)))
+    return out.head_rows, out.kernel, out.slices
 
 
 def chorus_ln_modulate(x, out, mul0, mul1, add0, add1, plus_one):

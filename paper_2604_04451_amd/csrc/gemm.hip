@@ -1,14 +1,7 @@
 // bf16 MFMA GEMM with fused epilogues: C = epi(A W^T + bias), A [M,K], W [N,K], both K-contiguous, fp32 accumulation.
 //
-// Two families. `gemm_w16_kernel` (below) copies its tiles straight from global memory to LDS, four tile shapes, and is
-// what a product is run on; which shape, and whether K is cut into slices, is decided by `plan_gemm` at the end of the file.
-// `gemm_bf16_kernel` is the register-staged one, kept because it can be asked for by name (kernels 1 and 2): workgroup =
-// 4 waves, tile BM x BN x 64; each k-step the A and W tiles go global -> registers -> LDS (rows padded to 72 elements so
-// the 16-byte operand reads of 16 consecutive lanes fall in distinct banks) while the MFMAs (32x32x16) of the previous
-// tile run. A wave owns a WM x WN sub-tile as (WM/32) x (WN/32) 32x32 accumulators. The W fragment is the MFMA's row
-// operand and the activation fragment its column operand, so lane l of a 32x32 accumulator holds ONE output row m = l%32
-// and the 16 output columns n = 4*(l/32) + 8*g + e (register 4g+e): four consecutive columns per register group, which
-// the epilogue moves as one 8-byte (bf16) or 16-byte (fp32) access.
+// One kernel, `gemm_w16_kernel`, that copies its tiles straight from global memory to LDS, in five tile shapes; which shape a
+// product is run on, and whether K is cut into slices, is decided by `plan_gemm` at the end of the file.
 #include <cmath>
 
 #include "chorus_ops.h"
@@ -22,7 +15,6 @@ namespace {
 constexpr int vmcnt_imm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 
 constexpr int BK = 64;
-constexpr int LS = BK + 8;  // LDS row stride in elements
 
 __device__ __forceinline__ float gelu_tanh_fast(float x) {
   // 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)),  u = sqrt(2/pi) (x + 0.044715 x^3); the exponent is taken in base 2:
@@ -49,263 +41,6 @@ struct PartPtrs {
     return slice == 0 ? first : rest + (size_t)(slice - 1) * M * N;
   }
 };
-
-
-// Epilogue for one lane: acc[i][j][4g+e] is C[m_i][n_j + 8g + e] with m_i = m_base + 32 i and
-// n_j = n_base + 32 j (n_base already includes the lane's 4*(l/32)).
-template <int EPI, int TM, int TN>
-__device__ __forceinline__ void gemm_epilogue(const f32x16 (&acc)[TM][TN], const EpiArgs& ep, long m_base, int n_base,
-                                              long M, int N) {
-  if constexpr (EPI == CHORUS_EPI_RESID) {
-    // Read-modify-write of the fp32 residual: all 4 * TM loads of a 32-column block are issued before the first store
-    // (the compiler cannot hoist them itself: it must assume a store may alias a later load), so the block costs one
-    // memory round trip instead of one per row group.
-#pragma unroll
-    for (int j = 0; j < TN; ++j) {
-      const int nj = n_base + 32 * j;
-      f32x4 cur[4][TM];
-      bool ok[4][TM];
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          const long m = m_base + 32 * i;
-          ok[g][i] = (nj + 8 * g < N) && (m < M);
-          // unconditional loads from a clamped address (predicated ones end up in scratch)
-          const long mc = m < M ? m : M - 1;
-          const int nc = nj + 8 * g < N ? nj + 8 * g : 0;
-          cur[g][i] = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(ep.out) + mc * N + nc);
-        }
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int n = nj + 8 * g;
-        if (n >= N) continue;
-        f32x4 bias = {0.f, 0.f, 0.f, 0.f};
-        if (ep.bias) bias = *reinterpret_cast<const f32x4*>(ep.bias + n);
-        f32x4 gate = {1.f, 1.f, 1.f, 1.f};
-        if (ep.gate0 || ep.gate1) {
-          gate = f32x4{0.f, 0.f, 0.f, 0.f};
-          if (ep.gate0) gate += *reinterpret_cast<const f32x4*>(ep.gate0 + n);
-          if (ep.gate1) gate += *reinterpret_cast<const f32x4*>(ep.gate1 + n);
-        }
-        gate *= ep.scale;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-          if (!ok[g][i]) continue;
-          const long m = m_base + 32 * i;
-          f32x4 v = {acc[i][j][4 * g + 0], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-          *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(ep.out) + m * N + n) = cur[g][i] + gate * (v + bias);
-        }
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int n = n_base + 32 * j + 8 * g;
-      if (n >= N) continue;  // N % 8 == 0 and n % 4 == 0: the four columns are in or out together
-      float4 bias = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (ep.bias) bias = *reinterpret_cast<const float4*>(ep.bias + n);
-      float4 gate = make_float4(1.f, 1.f, 1.f, 1.f);
-      if (EPI == CHORUS_EPI_RESID) {
-        if (ep.gate0 || ep.gate1) {
-          gate = make_float4(0.f, 0.f, 0.f, 0.f);
-          if (ep.gate0) {
-            float4 t = *reinterpret_cast<const float4*>(ep.gate0 + n);
-            gate.x += t.x; gate.y += t.y; gate.z += t.z; gate.w += t.w;
-          }
-          if (ep.gate1) {
-            float4 t = *reinterpret_cast<const float4*>(ep.gate1 + n);
-            gate.x += t.x; gate.y += t.y; gate.z += t.z; gate.w += t.w;
-          }
-        }
-        gate.x *= ep.scale; gate.y *= ep.scale; gate.z *= ep.scale; gate.w *= ep.scale;
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const long m = m_base + 32 * i;
-        if (m >= M) continue;
-        float v0 = acc[i][j][4 * g + 0] + bias.x, v1 = acc[i][j][4 * g + 1] + bias.y;
-        float v2 = acc[i][j][4 * g + 2] + bias.z, v3 = acc[i][j][4 * g + 3] + bias.w;
-        if (EPI == CHORUS_EPI_BF16 || EPI == CHORUS_EPI_GELU_BF16) {
-          if (EPI == CHORUS_EPI_GELU_BF16) {
-            v0 = gelu_tanh_fast(v0); v1 = gelu_tanh_fast(v1); v2 = gelu_tanh_fast(v2); v3 = gelu_tanh_fast(v3);
-          }
-          uint2 w;
-          w.x = pack_bf16x2(v0, v1);
-          w.y = pack_bf16x2(v2, v3);
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(ep.out) + m * N + n) = w;
-        } else if (EPI == CHORUS_EPI_F32) {
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(ep.out) + m * N + n) = make_float4(v0, v1, v2, v3);
-        } else {
-          float4* o = reinterpret_cast<float4*>(reinterpret_cast<float*>(ep.out) + m * N + n);
-          float4 c = *o;
-          c.x += gate.x * v0; c.y += gate.y * v1; c.z += gate.z * v2; c.w += gate.w * v3;
-          *o = c;
-        }
-      }
-    }
-  }
-}
-
-// fp32 residual epilogue through LDS for a 128 x 64 wave tile: 32 rows at a time are written to a private LDS
-// region as [32][64] floats (row stride 68 floats, so the 16-byte writes of 16 lanes fall in distinct banks), then
-// read back with 16 lanes per row, so every global load / store instruction moves four full 256-byte row segments
-// of the residual instead of 32-byte pieces of 32 rows. `cw` is this wave's region of 32 x 68 floats; the caller
-// guarantees that no wave still reads the main-loop LDS it overlays.
-constexpr int EPI_F32_STRIDE = 64 + 4;
-constexpr int EPI_F32_WAVE = 32 * EPI_F32_STRIDE;  // floats per wave
-
-__device__ __forceinline__ void gemm_epilogue_resid_lds(const f32x16 (&acc)[4][2], const EpiArgs& ep, float* cw, long m_wave0,
-                                                        int n_wave0, long M, int N, int lane) {
-  const int lrow = lane & 31, c4 = (lane >> 5) * 4;
-  const int rrow = lane >> 4, rcol = (lane & 15) * 4;  // read-back: 4 rows per instruction, 16 lanes per row
-  const int n = n_wave0 + rcol;
-  const bool n_ok = n < N;  // N % 8 == 0: the four columns are in or out together
-  f32x4 bias = {0.f, 0.f, 0.f, 0.f}, gate = {1.f, 1.f, 1.f, 1.f};
-  if (n_ok) {
-    if (ep.bias) bias = *reinterpret_cast<const f32x4*>(ep.bias + n);
-    if (ep.gate0 || ep.gate1) {
-      gate = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (ep.gate0) gate += *reinterpret_cast<const f32x4*>(ep.gate0 + n);
-      if (ep.gate1) gate += *reinterpret_cast<const f32x4*>(ep.gate1 + n);
-    }
-    gate *= ep.scale;
-  }
-  float* out = reinterpret_cast<float*>(ep.out);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    // the residual rows of this pass are requested before the LDS round trip
-    f32x4 cur[8];
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      long m = m_wave0 + 32 * i + 4 * it + rrow;
-      if (m > M - 1) m = M - 1;  // rows past the end read the last row (never stored)
-      cur[it] = *reinterpret_cast<const f32x4*>(out + m * N + (n_ok ? n : 0));
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 v = {acc[i][j][4 * g + 0], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-        *reinterpret_cast<f32x4*>(cw + lrow * EPI_F32_STRIDE + 32 * j + 8 * g + c4) = v;
-      }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");  // LDS ops of one wave stay in order
-#pragma unroll
-    for (int it = 0; it < 8; ++it) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(cw + (4 * it + rrow) * EPI_F32_STRIDE + rcol);
-      const long m = m_wave0 + 32 * i + 4 * it + rrow;
-      if (n_ok && m < M) *reinterpret_cast<f32x4*>(out + m * N + n) = cur[it] + gate * (v + bias);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-template <int BM, int BN, int WM, int WN, int EPI>
-__global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
-                                                        long M, int N, int K, EpiArgs ep, int tiles_m, int tiles_n) {
-  constexpr int WAVES_N = BN / WN;
-  static_assert((BM / WM) * (BN / WN) == 4, "4 waves");
-  constexpr int TM = WM / 32, TN = WN / 32;
-  constexpr int A_LD = BM * 8 / 256, B_LD = BN * 8 / 256;
-  constexpr int GM = 8;  // row-tiles per group: concurrently resident tiles form GM x (32/GM) patches
-
-  __shared__ __attribute__((aligned(16))) uint16_t sA[BM * LS];
-  __shared__ __attribute__((aligned(16))) uint16_t sB[BN * LS];
-
-  const int ntiles = tiles_m * tiles_n;
-  const int tile = xcd_remap(blockIdx.x, ntiles);
-  const int per_group = GM * tiles_n;
-  const int group = tile / per_group;
-  const int first_m = group * GM;
-  const int gsz = (tiles_m - first_m) < GM ? (tiles_m - first_m) : GM;
-  const int in_group = tile - group * per_group;
-  const int tm_idx = first_m + in_group % gsz;
-  const int tn_idx = in_group / gsz;
-  const long m0 = (long)tm_idx * BM;
-  const int n0 = tn_idx * BN;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  const int lrow = lane & 31, lk = (lane >> 5) * 8;
-
-  // per-thread load slots: slot i covers tile row (tid>>3) + 32 i, 16-byte chunk tid&7;
-  // rows past the end of the matrix are clamped (their products are never stored)
-  const int lrow0 = tid >> 3, lch = (tid & 7) * 8;
-  uint32_t aoff[A_LD], boff[B_LD];
-  const uint16_t* Abase = A + m0 * (long)K + lch;
-  const uint16_t* Bbase = W + (long)n0 * K + lch;
-#pragma unroll
-  for (int i = 0; i < A_LD; ++i) {
-    long r = lrow0 + 32 * i;
-    if (m0 + r > M - 1) r = M - 1 - m0;
-    aoff[i] = (uint32_t)(r * K);
-  }
-#pragma unroll
-  for (int i = 0; i < B_LD; ++i) {
-    int r = lrow0 + 32 * i;
-    if (n0 + r > N - 1) r = N - 1 - n0;
-    boff[i] = (uint32_t)((long)r * K);
-  }
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  u32x4 ra[A_LD], rb[B_LD];
-#pragma unroll
-  for (int i = 0; i < A_LD; ++i) ra[i] = *reinterpret_cast<const u32x4*>(Abase + aoff[i]);
-#pragma unroll
-  for (int i = 0; i < B_LD; ++i) rb[i] = *reinterpret_cast<const u32x4*>(Bbase + boff[i]);
-
-  const int KT = K / BK;
-  for (int kt = 0; kt < KT; ++kt) {
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < A_LD; ++i) {
-      *reinterpret_cast<u32x4*>(&sA[(lrow0 + 32 * i) * LS + lch]) = ra[i];
-    }
-#pragma unroll
-    for (int i = 0; i < B_LD; ++i) {
-      *reinterpret_cast<u32x4*>(&sB[(lrow0 + 32 * i) * LS + lch]) = rb[i];
-    }
-    __syncthreads();
-    if (kt + 1 < KT) {
-#pragma unroll
-      for (int i = 0; i < A_LD; ++i) ra[i] = *reinterpret_cast<const u32x4*>(Abase + (kt + 1) * BK + aoff[i]);
-#pragma unroll
-      for (int i = 0; i < B_LD; ++i) rb[i] = *reinterpret_cast<const u32x4*>(Bbase + (kt + 1) * BK + boff[i]);
-    }
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      bf16x8 af[TM], bfr[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-        af[i] = *reinterpret_cast<const bf16x8*>(&sA[(wm * WM + i * 32 + lrow) * LS + ks * 16 + lk]);
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        bfr[j] = *reinterpret_cast<const bf16x8*>(&sB[(wn * WN + j * 32 + lrow) * LS + ks * 16 + lk]);
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af[i], acc[i][j], 0, 0, 0);
-    }
-  }
-
-  if constexpr (EPI == CHORUS_EPI_RESID && TM == 4 && TN == 2 && BM * LS * 2 >= 4 * EPI_F32_WAVE * 4) {
-    __syncthreads();  // the staging regions overlay the A tile
-    gemm_epilogue_resid_lds(acc, ep, reinterpret_cast<float*>(sA) + wave * EPI_F32_WAVE, m0 + wm * WM, n0 + wn * WN, M, N, lane);
-  } else {
-    gemm_epilogue<EPI, TM, TN>(acc, ep, m0 + wm * WM + lrow, n0 + wn * WN + (lane >> 5) * 4, M, N);
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Large-problem kernel: 256 x 256 x 64 tiles, four waves (one per SIMD), each wave a 128 x 128 quadrant as 8 x 8
@@ -806,26 +541,6 @@ int32_t launch_add_parts(const PartPtrs& parts, int slices, long M, int N, const
   return CHORUS_OK;
 }
 
-template <int BM, int BN, int WM, int WN>
-int32_t launch_gemm(const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, EpiArgs ep, hipStream_t s) {
-  long tm = (M + BM - 1) / BM;
-  int tn = (N + BN - 1) / BN;
-  if (tm * tn > 0x7fffffffL) return CHORUS_E_SHAPE;
-  dim3 grid((unsigned)(tm * tn)), block(256);
-#define GEMM_LAUNCH(E) \
-  hipLaunchKernelGGL((gemm_bf16_kernel<BM, BN, WM, WN, E>), grid, block, 0, s, A, W, M, N, K, ep, (int)tm, tn)
-  switch (epi) {
-    case CHORUS_EPI_BF16: GEMM_LAUNCH(CHORUS_EPI_BF16); break;
-    case CHORUS_EPI_GELU_BF16: GEMM_LAUNCH(CHORUS_EPI_GELU_BF16); break;
-    case CHORUS_EPI_F32: GEMM_LAUNCH(CHORUS_EPI_F32); break;
-    case CHORUS_EPI_RESID: GEMM_LAUNCH(CHORUS_EPI_RESID); break;
-    default: return CHORUS_E_ARG;
-  }
-#undef GEMM_LAUNCH
-  CHORUS_LAUNCH_CHECK();
-  return CHORUS_OK;
-}
-
 // ---------------------------------------------------------------------------
 // Which tile, and in how many slices of K. The estimated time of each direct-to-LDS kernel in microseconds, from fits
 // to measurements on this chip with activations in the last-level cache and weights cold, as a request finds them
@@ -840,6 +555,7 @@ int32_t launch_gemm(const uint16_t* A, const uint16_t* W, long M, int N, int K, 
 //   64 x 64    four stages, two workgroups per unit: up to 256 tiles [9.7 / 40], growing with the tiles beyond
 // ---------------------------------------------------------------------------
 enum Tile { kTile256, kTileWide, kTile128, kTile128Deep, kTile64, kTiles };
+constexpr int kTileNumber[kTiles] = {3, 2, 4, 5, 1};  // as chorus_gemm_bf16_kernel names them
 constexpr int kTileRows[kTiles] = {256, 128, 128, 128, 64};
 constexpr int kTileCols[kTiles] = {256, 256, 128, 128, 64};
 constexpr int kMaxSlices = 4;  // more slices than this were never the fastest
@@ -938,6 +654,25 @@ int32_t check_gemm(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, i
   return CHORUS_OK;
 }
 
+// The whole choice: the first head_rows rows in whole rounds of 256 x 256 tiles (0: no cut), the others by `rest`. A last
+// round of 256 x 256 tiles that fills a small part of the chip costs most of a whole round. The rows can be cut instead:
+// the row tiles that make up whole rounds go to the 256 x 256 kernel, the rows left over to whichever kernel suits that many
+// rows, in a second launch behind the first. Taken when the estimate is better by 5 %.
+struct GemmCut {
+  long head_rows;
+  GemmPlan rest;
+};
+GemmCut plan_rows(long M, int N, int K, int epi, const GemmParts& parts) {
+  const GemmPlan whole = plan_gemm(M, N, K, epi, parts);
+  const long tiles_n256 = (N + 255) / 256, tiles256 = ((M + 255) / 256) * tiles_n256;
+  const long head_rows = tiles256 > 256 ? (tiles256 / 256 * 256 / tiles_n256) * 256 : 0;
+  if (head_rows > 0 && head_rows < M) {
+    const GemmPlan tail = plan_gemm(M - head_rows, N, K, epi, kNoParts);
+    if (tile_time(kTile256, head_rows, N, K, epi, 1) + tail.time < 0.95 * whole.time) return GemmCut{head_rows, tail};
+  }
+  return GemmCut{0, whole};
+}
+
 }  // namespace
 
 int32_t gemm_bf16_parts(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, int32_t epilogue, void* out,
@@ -948,43 +683,61 @@ int32_t gemm_bf16_parts(const uint16_t* A, const uint16_t* W, int64_t M, int32_t
   if (epilogue < CHORUS_EPI_BF16 || epilogue > CHORUS_EPI_RESID) return CHORUS_E_ARG;
   const EpiArgs ep{out, bias, gate0, gate1, scale};
   hipStream_t s = (hipStream_t)stream;
-  const GemmPlan whole = plan_gemm((long)M, N, K, epilogue, parts);
-  // A last round of 256 x 256 tiles that fills a small part of the chip costs most of a whole round. The rows can be cut
-  // instead: the row tiles that make up whole rounds go to the 256 x 256 kernel, the rows left over to whichever
-  // kernel suits that many rows, in a second launch behind the first. Taken when the estimate is better by 5 %.
-  const long tiles_n256 = (N + 255) / 256, tiles256 = ((M + 255) / 256) * tiles_n256;
-  const long head_rows = tiles256 > 256 ? (tiles256 / 256 * 256 / tiles_n256) * 256 : 0;
-  if (head_rows > 0 && head_rows < M) {
-    const long rest = (long)M - head_rows;
-    const GemmPlan tail = plan_gemm(rest, N, K, epilogue, kNoParts);
-    if (tile_time(kTile256, head_rows, N, K, epilogue, 1) + tail.time < 0.95 * whole.time) {
-      CHK_STATUS(launch_tile(kTile256, A, W, head_rows, N, K, epilogue, ep, s));
-      const size_t out_elt = (epilogue == CHORUS_EPI_F32 || epilogue == CHORUS_EPI_RESID) ? 4 : 2;
-      EpiArgs ep_rest = ep;
-      ep_rest.out = static_cast<uint8_t*>(out) + (size_t)head_rows * (size_t)N * out_elt;
-      return launch_plan(tail, A + (size_t)head_rows * (size_t)K, W, rest, N, K, epilogue, ep_rest, kNoParts, s);
-    }
-  }
-  return launch_plan(whole, A, W, (long)M, N, K, epilogue, ep, parts, s);
+  const GemmCut cut = plan_rows((long)M, N, K, epilogue, parts);
+  if (cut.head_rows == 0) return launch_plan(cut.rest, A, W, (long)M, N, K, epilogue, ep, parts, s);
+  CHK_STATUS(launch_tile(kTile256, A, W, cut.head_rows, N, K, epilogue, ep, s));
+  const size_t out_elt = (epilogue == CHORUS_EPI_F32 || epilogue == CHORUS_EPI_RESID) ? 4 : 2;
+  EpiArgs ep_rest = ep;
+  ep_rest.out = static_cast<uint8_t*>(out) + (size_t)cut.head_rows * (size_t)N * out_elt;
+  return launch_plan(cut.rest, A + (size_t)cut.head_rows * (size_t)K, W, (long)M - cut.head_rows, N, K, epilogue, ep_rest, kNoParts, s);
 }
 
 }  // namespace chorus
 
 using namespace chorus;
 
+// tile of a kernel number, -1 for none
+static int tile_of_number(int32_t kernel) {
+  for (int t = 0; t < kTiles; ++t)
+    if (kTileNumber[t] == kernel) return t;
+  return -1;
+}
+
 extern "C" int32_t chorus_gemm_bf16_kernel(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K,
                                            int32_t epilogue, void* out, const float* bias, const float* gate0,
                                            const float* gate1, float scale, int32_t kernel, void* stream) {
-  if (kernel < 0 || kernel > 4) return CHORUS_E_ARG;
   if (kernel == 0) return gemm_bf16_parts(A, W, M, N, K, epilogue, out, bias, gate0, gate1, scale, kNoParts, stream);
+  const int tile = tile_of_number(kernel);
+  if (tile < 0) return CHORUS_E_ARG;
   CHK_STATUS(check_gemm(A, W, M, N, K, out, bias, gate0, gate1));
   if (M == 0) return CHORUS_OK;
-  EpiArgs ep{out, bias, gate0, gate1, scale};
-  hipStream_t s = (hipStream_t)stream;
-  if (kernel == 1) return launch_gemm<128, 64, 64, 32>(A, W, (long)M, N, K, epilogue, ep, s);
-  if (kernel == 2) return launch_gemm<256, 128, 128, 64>(A, W, (long)M, N, K, epilogue, ep, s);
-  if (kernel == 3) return launch_tile(kTile256, A, W, (long)M, N, K, epilogue, ep, s);
-  return launch_tile(kTile128, A, W, (long)M, N, K, epilogue, ep, s);
+  return launch_tile(tile, A, W, (long)M, N, K, epilogue, EpiArgs{out, bias, gate0, gate1, scale}, (hipStream_t)stream);
+}
+
+extern "C" int32_t chorus_gemm_bf16_slices(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, float* out,
+                                           const float* bias, const float* gate0, const float* gate1, float scale,
+                                           int32_t kernel, int32_t slices, float* parts, size_t parts_bytes, void* stream) {
+  const int tile = tile_of_number(kernel);
+  if (tile < 0 || slices < 1 || slices > kMaxSlices) return CHORUS_E_ARG;
+  CHK_STATUS(check_gemm(A, W, M, N, K, out, bias, gate0, gate1));
+  if (slices > K / BK) return CHORUS_E_SHAPE;
+  if (M == 0) return CHORUS_OK;
+  const size_t one = (size_t)M * (size_t)N * sizeof(float);
+  if (slices > 1 && (!parts || !aligned16(parts) || parts_bytes < (size_t)(slices - 1) * one)) return CHORUS_E_WORKSPACE;
+  const GemmParts two{parts, one, parts + (slices > 1 ? (size_t)M * N : 0), slices > 2 ? (size_t)(slices - 2) * one : 0};
+  return launch_plan(GemmPlan{tile, slices, 0.0}, A, W, (long)M, N, K, CHORUS_EPI_RESID, EpiArgs{out, bias, gate0, gate1, scale},
+                     two, (hipStream_t)stream);
+}
+
+extern "C" int32_t chorus_gemm_bf16_plan(int64_t M, int32_t N, int32_t K, int32_t epilogue, size_t first_bytes, size_t rest_bytes,
+                                         chorus_gemm_plan* out) {
+  if (!out || M < 1 || N <= 0 || K <= 0 || epilogue < CHORUS_EPI_BF16 || epilogue > CHORUS_EPI_RESID) return CHORUS_E_ARG;
+  if (K % BK || N % 8) return CHORUS_E_SHAPE;
+  void* some = reinterpret_cast<void*>(uintptr_t{16});  // where the scratch lies does not matter
+  const GemmCut cut = plan_rows((long)M, N, K, epilogue,
+                                GemmParts{first_bytes ? some : nullptr, first_bytes, rest_bytes ? some : nullptr, rest_bytes});
+  *out = chorus_gemm_plan{cut.head_rows, kTileNumber[cut.rest.tile], cut.rest.slices};
+  return CHORUS_OK;
 }
 
 extern "C" int32_t chorus_gemm_bf16(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K,

@@ -116,6 +116,17 @@ static void sizes_and_validation() {
   EXPECT(chorus_dit_block_step(&bs, &w, (float*)p16, 0, nullptr, (const uint16_t*)p16, (const float*)p16, nullptr, 1.f, nullptr, 0, nullptr) == CHORUS_OK);
   EXPECT(chorus_gemm_bf16((const uint16_t*)p16, (const uint16_t*)p16, 8, 64, 100, 0, p16, nullptr, nullptr, nullptr, 1.f, nullptr) == CHORUS_E_SHAPE);
   EXPECT(chorus_gemm_bf16_kernel((const uint16_t*)p16, (const uint16_t*)p16, 8, 64, 64, 0, p16, nullptr, nullptr, nullptr, 1.f, 9, nullptr) == CHORUS_E_ARG);
+  EXPECT(chorus_gemm_bf16_slices((const uint16_t*)p16, (const uint16_t*)p16, 8, 64, 128, (float*)p16, nullptr, nullptr, nullptr, 1.f, 1, 5, nullptr, 0, nullptr) == CHORUS_E_ARG);
+  EXPECT(chorus_gemm_bf16_slices((const uint16_t*)p16, (const uint16_t*)p16, 8, 64, 128, (float*)p16, nullptr, nullptr, nullptr, 1.f, 1, 3, nullptr, 0, nullptr) == CHORUS_E_SHAPE);
+  EXPECT(chorus_gemm_bf16_slices((const uint16_t*)p16, (const uint16_t*)p16, 8, 64, 128, (float*)p16, nullptr, nullptr, nullptr, 1.f, 1, 2, nullptr, 0, nullptr) == CHORUS_E_WORKSPACE);
+  for (int64_t m : {1, 63, 480, 4099, 75600})
+    for (int e = 0; e < 4; ++e) {
+      chorus_gemm_plan plan;
+      EXPECT(chorus_gemm_bf16_plan(m, 1536, 8960, e, (size_t)m * 6144, (size_t)m * 12288, &plan) == CHORUS_OK);
+      EXPECT(plan.kernel >= 1 && plan.kernel <= 5 && plan.slices >= 1 && plan.slices <= 4 && plan.head_rows < m);
+    }
+  EXPECT(chorus_attention_variant(13104, 512, 512, 12, 128, 1, 256) == 5);
+  EXPECT(chorus_attention_variant(13104, 64, 64, 12, 128, 0, 256) == 3);
   EXPECT(chorus_attention((const uint16_t*)p16, (const uint16_t*)p16, (const uint16_t*)p16, (uint16_t*)p16, nullptr, 8, 8, 64, 64, 2, 96, 0, nullptr) == CHORUS_E_SHAPE);
   EXPECT(chorus_attention((const uint16_t*)p16, (const uint16_t*)p16, (const uint16_t*)p16, (uint16_t*)p16, nullptr, 8, 8, 64, 64, 2, 64, 2, nullptr) == CHORUS_E_ARG);
   // the run: a request the validation must refuse before the lookup is launched

@@ -3,6 +3,7 @@ measured, and that the sizes which other tests name reach the kernels that those
 import pytest
 
 from paper_2604_04451_amd import binding as B
+from test_gpu_gemm_slices import DEFAULT_TILES, FFN_SLICES, ffn2_scratch
 
 CUS = 256  # compute units of the GPU
 
@@ -43,3 +44,48 @@ def test_attention_variant_refuses():
         assert lib.chorus_attention_variant(*bad, 0, CUS) == B.E_ARG
     assert lib.chorus_attention_variant(8, 8, 64, 2, 64, 0, 0) == B.E_ARG
     assert lib.chorus_attention_variant(8, 8, 64, 2, 96, 0, CUS) == lib.chorus_attention_variant(8, 8, 72, 2, 64, 0, CUS) == B.E_SHAPE
+
+
+def test_gemm_cases_reach_their_tiles():
+    for (M, N, K), want in DEFAULT_TILES.items():
+        for epi, kernel in zip((B.EPI_BF16, B.EPI_RESID), want):
+            assert B.chorus_gemm_bf16_plan(M, N, K, epi) == (0, kernel, 1), (M, N, K, epi)
+    for epi in range(4):  # rows cut behind the last whole round
+        assert B.chorus_gemm_bf16_plan(4099, 4608, 1536, epi) == (3584, 5, 1)
+    assert B.chorus_gemm_bf16_plan(4452, 4096, 512, B.EPI_BF16)[0] == 4096
+    assert B.chorus_gemm_bf16_plan(13104, 1536, 8960, B.EPI_RESID) == (10752, 5, 1)
+    assert B.chorus_gemm_bf16_plan(32760, 8960, 1536, B.EPI_GELU_BF16)[1] == 3
+
+
+def _ffn2(D, H, F, Lt, Ls):
+    shape = B.make_block_shape(D, H, D // H, F, Lt, (21, 60, 90))
+    return B.chorus_gemm_bf16_plan(Ls, D, F, B.EPI_RESID, *ffn2_scratch(shape, Ls))
+
+
+def test_second_ffn_product_in_slices():
+    for (Ls, Lt, F), slices in FFN_SLICES.items():
+        assert _ffn2(256, 4, F, Lt, Ls) == (0, 1, slices), (Ls, Lt, F)
+    for Ls, kernel, slices in ((128, 1, 4), (300, 1, 2), (480, 5, 4), (700, 5, 3), (960, 4, 3), (1200, 5, 2), (1500, 4, 2),
+                               (2000, 2, 2), (3000, 4, 1), (4000, 2, 1)):
+        assert _ffn2(1536, 12, 8960, 512, Ls) == (0, kernel, slices), Ls
+    for Ls, kernel, slices in ((64, 1, 3), (128, 5, 4), (300, 2, 4), (480, 2, 3), (700, 2, 2), (960, 3, 3), (2000, 3, 3),
+                               (4000, 3, 3), (5000, 3, 1)):
+        assert _ffn2(5120, 40, 13824, 512, Ls) == (0, kernel, slices), Ls
+    # the scratch bounds the slices: none at all, one result in front, further ones behind the hidden rows
+    one = 480 * 1536 * 4
+    assert B.chorus_gemm_bf16_plan(480, 1536, 8960, B.EPI_RESID)[2] == 1
+    assert B.chorus_gemm_bf16_plan(480, 1536, 8960, B.EPI_RESID, one - 1, 8 * one)[2] == 1
+    assert B.chorus_gemm_bf16_plan(480, 1536, 8960, B.EPI_RESID, one, 0)[2] <= 2
+    assert B.chorus_gemm_bf16_plan(480, 1536, 8960, B.EPI_RESID, one, 2 * one - 1)[2] <= 3
+    assert B.chorus_gemm_bf16_plan(480, 1536, 8960, B.EPI_RESID, one, 2 * one)[2] == 4
+    assert B.chorus_gemm_bf16_plan(480, 1536, 8960, B.EPI_F32, one, 2 * one)[2] == 1  # the gated residual only
+    assert B.chorus_gemm_bf16_plan(64, 64, 128, B.EPI_RESID, one, 2 * one)[2] <= 2    # no more slices than steps
+
+
+def test_gemm_plan_refuses():
+    lib, out = B.load(), B.GemmPlan()
+    for bad in ((0, 64, 64, 0), (8, 0, 64, 0), (8, 64, 0, 0), (8, 64, 64, 4), (8, 64, 64, -1)):
+        assert lib.chorus_gemm_bf16_plan(*bad, 0, 0, B.C.byref(out)) == B.E_ARG
+    assert lib.chorus_gemm_bf16_plan(8, 64, 64, 0, 0, 0, None) == B.E_ARG
+    assert lib.chorus_gemm_bf16_plan(8, 64, 100, 0, 0, 0, B.C.byref(out)) == B.E_SHAPE
+    assert lib.chorus_gemm_bf16_plan(8, 60, 64, 0, 0, 0, B.C.byref(out)) == B.E_SHAPE

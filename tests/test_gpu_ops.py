@@ -21,10 +21,12 @@ pytestmark = pytest.mark.gpu
                                    (4099, 4608, 1536), (3000, 1536, 8960), (513, 1024, 64), (70, 8, 128),
                                    (4452, 4096, 512)])
 def test_gemm_epilogues(M, N, K):
-    """Every tile kernel (1: 128 x 64, 2: 256 x 128, 3: 256 x 256 and 4: 128 x 128 direct to LDS) and the automatic choice (0), each on
-    every shape: tiles with ragged rows and columns, a single row, fewer columns than a tile has, K of one and of
-    many steps; the four epilogues. At 4452 x 4096 x 512 the automatic choice cuts the rows: 4096 of them (one whole
-    round of 256 x 256 tiles) in one launch, the other 356 on the 128 x 64 kernel in a second."""
+    """Every tile kernel (1: 64 x 64, 2: 128 x 256, 3: 256 x 256, 4 and 5: 128 x 128 with two and three stages) and the automatic
+    choice (0), each on every shape: tiles with ragged rows and columns, a single row, fewer columns than a tile has, K of
+    one and of many steps, fewer than a kernel has stages among them; the four epilogues. At 4099 x 4608 x 1536 the automatic
+    choice cuts the rows whatever the epilogue: 3584 of them (one round of 256 x 256 tiles) in one launch, the other 515 on
+    128 x 128 tiles in a second; at 4452 x 4096 x 512 for plain bf16 output only."""
+    assert [B.chorus_gemm_bf16_plan(4099, 4608, 1536, e) for e in range(4)] == [(3584, 5, 1)] * 4
     A = synth.round_bf16(synth.normal(M, "g.A", (M, K)))
     W = synth.round_bf16(synth.normal(M, "g.W", (N, K), 0.05))
     bias = synth.normal(M, "g.b", (N,), 0.5)
@@ -35,7 +37,7 @@ def test_gemm_epilogues(M, N, K):
     ref0 = O.linear(A, W, np.zeros(N))
     gref = O.gelu_tanh(ref)
     dA, dW, db = dev_bf16(A), dev_bf16(W), dev_f32(bias)
-    for kern in (0, 1, 2, 3, 4):
+    for kern in (0, 1, 2, 3, 4, 5):
         print(f"[case] gemm M={M} N={N} K={K} kernel={kern}", flush=True)
         out = torch.empty(M, N, dtype=torch.bfloat16, device=DEV)
         B.chorus_gemm_bf16(dA, dW, B.EPI_BF16, out, db, kernel=kern)
@@ -156,9 +158,9 @@ def _attn_case(H, dh, Lq, Lk, variant, col_scale=None, q_std=1.0, seed=0, name="
                  max_abs=max(np.abs(ref).max() * 2 ** -7, 2e-3), rel_l2=5e-3)
 
 
-# variant 0 is the library's own choice (128-key tiles from 512 keys on, else 64-key tiles), 3 and 5 force the
-# 64-key and the 128-key 16x16x32-MFMA tile kernel, 6 is the latter fed with pre-scaled queries (what
-# the block launches for long self-attention): every shape runs through the kernel the block and the benchmark launch.
+# variant 0 is the library's own choice (chorus_attention_variant: 128-key tiles from 512 keys on and, where they are the
+# faster, from 65), 3 and 5 force the 64-key and the 128-key 16x16x32-MFMA tile kernel, 6 is the latter fed with pre-scaled
+# queries (what the block launches wherever the choice is 5): every shape runs through the kernels the block launches.
 ATTN_VARIANTS = [0, 3, 5, 6]
 
 
@@ -176,7 +178,7 @@ def test_attention_plain(H, dh, Lq, Lk, variant):
 def test_attention_peaked(variant):
     """Logits with std ~4: rows dominated by few keys; catches masking / rescale mistakes that
     near-uniform rows (output ~ mean V) would hide. Key counts with tails of 4, 16, 1 and 81 keys in the
-    last 128-key tile, above and below 512 and 2048 keys (the default switches tile size at 512)."""
+    last 128-key tile, above and below 2048 keys."""
     print(f"[case] attention peaked variant={variant}", flush=True)
     _attn_case(4, 128, 700, 900, variant, q_std=2.0, seed=3, name="peaked")
     _attn_case(2, 64, 333, 2000, variant, q_std=2.0, seed=4, name="peaked64")
@@ -211,8 +213,7 @@ def test_attention_variant_argument_errors():
                                         (1, 64, 260, 1027)])
 def test_attention_tgaa_column_scale(H, dh, Lq, Lt, variant):
     """Eq. 2 as a per-key logit factor, on the 64-key kernel (3), on the 16x16x32 kernel with and without pre-scaled
-    queries (5, 6) and on the default choice (0: the latter from 512 keys on); key counts that end a 128-key tile
-    on a multiple of four and off one."""
+    queries (5, 6) and on the default choice (0); key counts that end a 128-key tile on a multiple of four and off one."""
     print(f"[case] cross-attention TGAA H={H} dh={dh} Lq={Lq} Lt={Lt} variant={variant}", flush=True)
     _attn_case(H, dh, Lq, Lt, variant, col_scale=synth.tdiff_scale(Lt, 1.5), q_std=1.5, name="tgaa-all")
     _attn_case(H, dh, Lq, Lt, variant, col_scale=synth.tdiff_scale(Lt, 1.5, n_diff=max(1, Lt // 64)), q_std=1.5, name="tgaa-subset")
