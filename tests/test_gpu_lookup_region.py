@@ -275,10 +275,10 @@ def test_lookup_batch_shapes(N, d, Q, k):
     _check_topk(cache, queries, 0.75, k)
 
 
-@pytest.mark.parametrize("N,k", [(1024, 8), (1025, 9), (2049, 64), (2100, 1), (9000, 8), (9000, 9), (9000, 64), (9000, 65), (70001, 3), (8192, 1), (8193, 1)])
+@pytest.mark.parametrize("N,k", [(1024, 8), (1025, 9), (2049, 64), (2100, 1), (9000, 8), (9000, 9), (9000, 64), (9000, 65), (70001, 3), (70001, 8), (8192, 1), (8193, 1)])
 def test_lookup_batch_selection(N, k):
     """The selection's own edges: one and several row blocks, lists per wave and per workgroup, rounds (k <= 8) and the
-    sort, lists and the pass with scores (k > 64); many equal scores, rows of zero norm and scores of either sign."""
+    sort, a merge by one wave and by all four (more than 256 keys: 69 blocks of 8), lists and the pass with scores (k > 64); many equal scores, rows of zero norm and scores of either sign."""
     print(f"[case] lookup_batch selection N={N} k={k}", flush=True)
     g = torch.Generator(device=DEV).manual_seed(N + k)
     d = 64
@@ -301,6 +301,26 @@ def test_lookup_batch_selection(N, k):
         assert bool((got_i[1:][equal] > got_i[:-1][equal]).all())    # equal scores by index
         assert int(hit[q]) == int(got_s[0] >= 0.75)
     assert idx[3].tolist() == list(range(k)) and bool(torch.isneginf(sc[3]).all()) and int(hit[3]) == 0
+
+
+@pytest.mark.parametrize("N,Q,k", [(2049, 33, 8), (2049, 48, 1), (20000, 33, 9), (20000, 48, 8), (5000, 70, 4)])
+def test_lookup_batch_groups_of_queries(N, Q, k):
+    """More than 32 queries on several row blocks: every group of 32 clears and reuses the lists and the arrival counts of
+    the one before. Position by position against 64 bits, twice in a row on one workspace."""
+    print(f"[case] lookup_batch groups N={N} Q={Q} k={k}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + Q)
+    cache, queries = torch.randn(N, 96, device=DEV, generator=g), torch.randn(Q, 96, device=DEV, generator=g)
+    cache[N - 1] = cache[7]
+    ws = torch.empty(P.load().chorus_cache_lookup_batch_workspace_bytes(N, 96, Q), dtype=torch.uint8, device=DEV)
+    s64 = (queries.double() @ cache.double().T) / cache.double().norm(dim=1) / queries.double().norm(dim=1, keepdim=True)
+    want, _ = s64.sort(dim=1, descending=True)
+    for q in (queries, queries.flip(0)):
+        idx, sc, hit = P.chorus_cache_lookup_batch(cache, q, 0.2, k, ws)
+        s, w = (s64, want) if q is queries else (s64.flip(0), want.flip(0))
+        assert (sc.double() - w[:, :k]).abs().max() < 1e-6
+        assert (sc.double() - s.gather(1, idx.long())).abs().max() < 1e-6
+        assert all(len(set(r)) == k for r in idx.tolist())
+        assert torch.equal(hit, (sc[:, 0] >= 0.2).int())
 
 
 @pytest.mark.parametrize("N,d,Q", [(700, 4096, 24), (3000, 1000, 17), (8192, 768, 32), (5000, 4100, 2)])
