@@ -24,7 +24,6 @@
 // The running maximum is only refreshed when a tile exceeds it by more than 8
 // (in log2 units), which keeps exp2 arguments <= 8 and makes the accumulator
 // rescale rare; the final division by the row sum makes the result exact either way.
-#include "attention.h"
 #include "chorus_ops.h"
 #include "common.h"
 
@@ -412,23 +411,22 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   // phase, one barrier ahead of the softmax phase that reads it (the other group, half an iteration behind, then still
   // reads the other buffer). Keys past the end get 1.
   // With factors and 256 rows the kernel is at the register limit, and what a few instructions make again from the thread
-  // id must not be kept across the loop: this hides the id from the compiler, which would keep it and spill six registers
-  // (13104 x 77 on scaled queries, 40 heads, 141 -> 134 us; 32760 x 512, 12 heads, 142.3 -> 140.5). Not where the kernel
-  // scales the logits itself over short keys: there the spills cost less (13104 x 480 74.2 us, without them 76.1). The V
-  // rows' addresses stay: made again for every tile they cost 10 % of the launch.
-  constexpr bool FRESH = CS && (PRE || !SUM32);
+  // id must not be kept across the loop: this hides the id from the compiler, which would keep it and spill six registers.
+  // Over long keys that is the factors' addresses and the output's (scaled queries, 32760 x 512, 12 heads 141.3 -> 137.3 us,
+  // 13104 x 512, 40 heads 209 -> 202), over short ones the output's alone (13104 x 226, 40 heads 173 -> 165; the others as
+  // well 172). The V rows' addresses stay: made again for every tile they cost 10 % of the launch.
   auto fresh_tid = [&]() {
     int t = tid;
-    if constexpr (FRESH) asm volatile("" : "+v"(t));
+    if constexpr (CS) asm volatile("" : "+v"(t));
     return t;
   };
   float rc = 1.f;
   auto load_c = [&](int kt) {
-    const int key = kt * KTL + fresh_tid();
+    const int key = kt * KTL + (SUM32 ? tid : fresh_tid());
     if (tid < KTL) rc = key < (int)Lk ? col_scale[key] : 1.0f;
   };
   auto store_c = [&](int buf) {
-    if (tid < KTL) smc[buf * KTL + fresh_tid()] = rc;
+    if (tid < KTL) smc[buf * KTL + (SUM32 ? tid : fresh_tid())] = rc;
   };
   // LDS row of the K tile that fragment row lane % 16 of block kb stands for
   const int krow0 = 16 * (lq >> 3) + (lq & 7);
@@ -652,9 +650,9 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
     }
     const float inv = 1.0f / l;
     const int t = fresh_tid();
-    const long q = FRESH ? (long)qt * QROWS + (t >> 6) * 16 * RB + 16 * rb + (t & 15) : q_wave0 + 16 * rb + lq;
+    const long q = CS ? (long)qt * QROWS + (t >> 6) * 16 * RB + 16 * rb + (t & 15) : q_wave0 + 16 * rb + lq;
     if (q < Lq) {
-      uint16_t* op = O + q * (long)D + head * DH + 4 * (FRESH ? (t & 63) >> 4 : g);
+      uint16_t* op = O + q * (long)D + head * DH + 4 * (CS ? (t & 63) >> 4 : g);
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
         uint2 w;
@@ -734,8 +732,6 @@ int32_t launch_attn_pp(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt,
   return CHORUS_OK;
 }
 
-}  // namespace
-
 // Under 512 keys. Launches of half tiles: the 64-key kernel has none (12 heads of 128, microseconds, 64-key kernel / 128-key
 // kernel: 480 x 480 20.4 / 13.7, 1200 x 77 12.6 / 9.6, 128 x 128 9.7 / 9.0). Launches of full tiles, time of the 128-key
 // kernel over that of the 64-key kernel on 288 to 2080 tiles:
@@ -756,13 +752,7 @@ int attention_variant(long Lq, long Lk, long LkPad, int H, int dh, bool factor, 
   return (factor ? Lk <= 96 || Lk > 128 : Lk > 128 && tiles > cus) ? 5 : 3;
 }
 
-bool attention_wide_tiles(long Lq, long Lk, long LkPad, int H, int dh, bool factor) {
-  int dev = 0, cus = 0;
-  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-    cus = 0;
-  return attention_variant(Lq, Lk, LkPad, H, dh, factor, cus) == 5;
-}
-
+}  // namespace
 }  // namespace chorus
 
 using namespace chorus;
@@ -787,7 +777,12 @@ extern "C" int32_t chorus_attention(const uint16_t* Q, const uint16_t* K, const 
   if (!aligned16(Q) || !aligned16(K) || !aligned16(Vt) || !aligned16(O) || !aligned16(col_scale)) return CHORUS_E_ARG;
   hipStream_t s = (hipStream_t)stream;
   const bool cs = col_scale != nullptr;
-  if (variant == 0) variant = attention_wide_tiles((long)Lq, (long)Lk, (long)LkPad, H, dh, cs) ? 5 : 3;
+  if (variant == 0) {
+    int dev = 0, cus = 0;
+    CHORUS_HIP(hipGetDevice(&dev));
+    CHORUS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    variant = attention_variant((long)Lq, (long)Lk, (long)LkPad, H, dh, cs, cus);
+  }
   if (variant == 5 || variant == 6) {
     if (LkPad % 128) return CHORUS_E_SHAPE;
     if (variant == 6)

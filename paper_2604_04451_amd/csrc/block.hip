@@ -3,7 +3,6 @@
 // allocation). Also the optional per-kernel event timing used by benchmarks.
 #include <vector>
 
-#include "attention.h"
 #include "chorus_ops.h"
 #include "common.h"
 #include "gemm.h"
@@ -211,9 +210,9 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
     CHK(chorus_gemm_bf16(b.h, w->w_qkv, Ls, 3 * D, D, CHORUS_EPI_BF16, b.qkv, w->b_qkv, nullptr, nullptr, 1.f, stream));
   }
   // 2-3. q/k RMSNorm + RoPE into head-major layout; V into key-contiguous layout.
-  // Attention in 128-key tiles takes its queries already multiplied by log2(e) / sqrt(dh): the factor enters here, in fp32
-  // ahead of the one rounding to bf16.
-  const bool q_prescaled = attention_wide_tiles(Ls, Ls, Lpad, H, dh, false);
+  // Attention over 512 keys or more takes its queries already multiplied by log2(e) / sqrt(dh): the factor enters here, in
+  // fp32 ahead of the one rounding to bf16. Over fewer keys they are the plain queries whichever kernel runs it.
+  const bool q_prescaled = CHORUS_ATTENTION_LONG_KEYS(Ls, Lpad);
   {
     ProfScope p(CHORUS_PROF_NORM, s);
     if (!w->g_q || !w->g_k || !aligned16(w->g_q) || !aligned16(w->g_k)) return CHORUS_E_ARG;
@@ -247,7 +246,7 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
     CHK(project_text_kv(sh, w, text_ctx, b.tkv, b.kc, b.vct, stream));
   }
   // pre-scaled queries as above
-  const bool cq_prescaled = attention_wide_tiles(Ls, Lt, LtPad, H, dh, tgaa_key_scale != nullptr);
+  const bool cq_prescaled = CHORUS_ATTENTION_LONG_KEYS(Lt, LtPad);
   {
     ProfScope p(CHORUS_PROF_NORM, s);
     CHK(chorus_qk_norm_rope(b.qkv, D, w->g_cq, b.qh, Ls, Lpad, H, dh, nullptr, sh.gT, sh.gH, sh.gW, 0,

@@ -71,3 +71,42 @@ def test_short_keys_row_sums_in_fp32(H, dh, Lq, Lk, variant, factor):
     B.chorus_attention(Q, K, Vt, out, dev_f32(np.ones(Lk, np.float32)) if factor else None, Lq, Lk, variant)
     got = host_bf16(out)
     assert (got == 1 - 2.0 ** -8).all(), (got.min(), got.max(), want)
+
+
+@pytest.mark.parametrize("D,H,Ls,Lt", [(256, 4, 128, 77), (1536, 12, 480, 226), (1536, 12, 480, 77), (512, 8, 300, 16), (512, 4, 200, 512),
+                                       (1536, 12, 3300, 77)])
+@pytest.mark.parametrize("factor", [False, True])
+def test_block_cross_attention_equals_the_single_operations(D, H, Ls, Lt, factor):
+    """The cross-attention branch of a block (the other branches' output weights are zero) against the calls it stands for,
+    bit for bit. Over fewer than 512 keys its queries are the plain ones, rounded once, whichever kernel runs the
+    attention; from 512 on they carry log2(e) / sqrt(dh)."""
+    print(f"[case] block cross-attention D={D} H={H} Ls={Ls} Lt={Lt} factor={factor}", flush=True)
+    dh, g = D // H, torch.Generator(device=DEV).manual_seed(Ls + Lt)
+    rnd = lambda *s: torch.randn(*s, device=DEV, generator=g)  # noqa: E731
+    F, t = 64, {}
+    for n, o, i in (("qkv", 3 * D, D), ("o", D, D), ("cq", D, D), ("ckv", 2 * D, D), ("co", D, D), ("1", F, D), ("2", D, F)):
+        zero = n in ("o", "2")
+        t["w_" + n] = torch.zeros(o, i, dtype=torch.bfloat16, device=DEV) if zero else (rnd(o, i) * 0.05).bfloat16()
+        t["b_" + n] = torch.zeros(o, device=DEV) if zero else rnd(o) * 0.1
+    t.update(mod_table=rnd(6, D), g_q=rnd(D), g_k=rnd(D), g_cq=rnd(D), g_ck=rnd(D), ln3_w=rnd(D), ln3_b=rnd(D))
+    w = B.DeviceBlock(t, B.BlockWeights(**{n: t[n].data_ptr() for n in B._W_FIELDS}))
+    shape = B.make_block_shape(D, H, dh, F, Lt, (7, 24, 24))
+    x, ctx, t_mod = rnd(Ls, D), rnd(Lt, D).bfloat16(), rnd(6, D)
+    scale = torch.rand(Lt, device=DEV, generator=g) + 0.5 if factor else None
+    got = x.clone()
+    B.chorus_dit_block_step(shape, w, got, Ls, None, ctx, t_mod, scale, 1.25)
+
+    LtPad, Lpad, long_keys = -(-Lt // 64) * 64, -(-Ls // 256) * 256, Lt >= 512
+    h = torch.empty(Ls, D, dtype=torch.bfloat16, device=DEV)
+    B.chorus_ln_modulate(x, h, t["ln3_w"], None, t["ln3_b"], None, False)
+    q = torch.empty_like(h)
+    B.chorus_gemm_bf16(h, t["w_cq"], B.EPI_BF16, q, t["b_cq"])
+    qh = torch.empty(H, Lpad, dh, dtype=torch.bfloat16, device=DEV)
+    B.chorus_qk_norm_rope(q, 0, t["g_cq"], qh, Ls, H, dh, None, (7, 24, 24), False, float(np.float32(np.log2(np.e)) / np.sqrt(np.float32(dh))) if long_keys else 1.0)
+    kv = B.chorus_text_kv_project(shape, w, ctx).view(torch.bfloat16)
+    k, v = kv[:H * LtPad * dh].view(H, LtPad, dh), kv[kv.numel() // 2:][:D * LtPad].view(D, LtPad)
+    ao = torch.empty(Ls, D, dtype=torch.bfloat16, device=DEV)
+    B.chorus_attention(qh, k, v, ao, scale, Ls, Lt, 6 if long_keys else 0)
+    want = x.clone()
+    B.chorus_gemm_bf16(ao, t["w_co"], B.EPI_RESID, want, t["b_co"], None, None, 1.25)
+    assert torch.equal(got, want)

@@ -21,7 +21,8 @@ def _scratch(source, tmp_path):
 
 @pytest.mark.parametrize("source,kernels,at_least", [
     ("glue.hip", r"head_update_kernel", 18),  # six widths, three updates
-    ("attention.hip", r"attention_pp16_kernelILi\d+ELb1E", 20),  # scaled queries: head sizes, tile sizes, kinds
+    # all but plain queries with factors over 512 keys or more, which a block does not run
+    ("attention.hip", r"attention_pp16_kernelILi\d+E(?!Lb0ELi2ELi2E)", 38),
 ])
 def test_no_scratch(source, kernels, at_least, tmp_path):
     got = {n: v for n, v in _scratch(source, tmp_path).items() if re.search(kernels, n)}
