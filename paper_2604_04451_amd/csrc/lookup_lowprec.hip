@@ -19,7 +19,7 @@ namespace {
 
 constexpr int kWaves = 4;            // waves per workgroup of the scan and of the re-rank
 constexpr int kMaxBlocks = 1024;     // workgroups of either: four on every compute unit; beyond that a wave takes several rows
-constexpr int kMaxScanBlocks = 4096; // the workspace is laid out for this many
+constexpr int kMaxScanBlocks = 4096; // the workspace has room for this many: its size stays what callers hold
 
 inline long lp_blocks(long N) {
   long g = (N + kWaves - 1) / kWaves;

@@ -1,5 +1,6 @@
 """GPU parity of attention launches that leave compute units idle (128-row tiles throughout) and of short key sequences on
-128-key tiles, the default choice there and the pre-scaled form that the block uses, with and without key factors."""
+128-key tiles: the default choice there and the form on pre-scaled queries, with and without key factors, the row sums, and
+the cross-attention of a block against its single operations."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("H,dh,Lq,Lk", [
     (2, 128, 1, 65), (3, 64, 127, 128), (1, 128, 128, 129), (2, 64, 129, 300), (2, 128, 257, 511), (12, 128, 500, 77),  # half tiles
-    (10, 64, 3300, 130),   # full tiles, less than a round: 64-key tiles without factors, 128-key tiles with
+    (10, 64, 3300, 130),   # full tiles, less than a round: by default 64-key tiles without factors, 128-key tiles with
     (40, 64, 2000, 200),   # more than a round
     (2, 64, 70, 1), (2, 64, 70, 64),
 ])
