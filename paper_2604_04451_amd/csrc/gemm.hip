@@ -48,9 +48,10 @@ struct PartPtrs {
 // writes half the accumulator registers of a 32x32x16 one (k = 32 per instruction instead of 16), which is what the
 // power-managed part rewards; a 16-byte LDS fragment (16 rows x 8 k per quarter wave) feeds eight MFMAs.
 //
-// Both operands stream global -> LDS directly (global_load_lds_dwordx4: no register staging, no LDS store
-// instructions) into two 64 KB stages. A direct load writes the 64 lanes' 16-byte pieces to consecutive LDS
-// addresses, i.e. 8 unpadded rows of 128 bytes. Bank conflicts are avoided by an XOR swizzle instead of padding: the
+// Both operands stream global -> LDS directly (buffer_load_dwordx4 ... lds: no register staging, no LDS store
+// instructions, one lane offset per load for all steps) into a ring of five half steps of 32 KB, the whole 160 KB: rows 0-127
+// of A and of W are one half of a k-step, rows 128-255 the other. A direct load writes the 64 lanes' 16-byte pieces to
+// consecutive LDS addresses, i.e. 8 unpadded rows of 128 bytes. Bank conflicts are avoided by an XOR swizzle instead of padding: the
 // 16-byte chunk c of row r lives at chunk position c ^ ((r >> 1) & 7); the loading lane for position p of row r
 // fetches global chunk p ^ ((r >> 1) & 7). (A 16-byte-per-lane LDS read is served 16 lanes a cycle: the four-lane
 // groups of one half wave whose group index has the same bit parity, groups 0, 3, 5, 6 together and 1, 2, 4, 7. With
@@ -63,19 +64,25 @@ struct PartPtrs {
 // consecutive output columns n.
 //
 // One loop iteration per k-step, hand-laid for a single wave per SIMD (nothing else hides a gap between two MFMAs):
-// half-step 0 (64 MFMAs) with the LDS reads of half-step 1's fragments; vmcnt(0) + barrier; half-step 1 (64 MFMAs) with
-// the LDS reads of the next step's first fragments and the 16 loads of the step after next (their stage is free behind
-// the barrier). Every read and load stands alone between two MFMAs.
+// half-step 0 (64 MFMAs) with the LDS reads of half-step 1's fragments; wait + barrier; half-step 1 (64 MFMAs) with the LDS
+// reads of the next step's first fragments. Either half issues the 8 loads of a half step, one every eight MFMAs: those of
+// half-step 0 land 1 to 1.5 steps later, those of half-step 1 half a step to a step. Every read and load stands alone
+// between two MFMAs. What bounds the loop is the delivery of the operands: with all 16 loads of a step in its second half and
+// two whole stages in LDS it ran at 1310 TFLOP/s (8192 x 8192 x 8192), so at 1510; with the loads aimed at two steps
+// that stay in the L2 at 1530, without any loads at 1780. Measured and not taken: 16 loads in the first half of half-step
+// 1 (1.04 of the time), one load per wave and step that fetches lines into the L2 four steps ahead (1.04), workgroups that
+// stay and take the next tile's first steps behind the last ones of this tile's (0.99 to 1.02), later starts for some of the XCDs
+// so that not all epilogues write at once (they cost what they save).
 // The MFMAs are volatile assembly, in place on their accumulators: left to the register allocator every result gets
 // a new home, at the price of several hundred accumulator moves per k-step.
 // ---------------------------------------------------------------------------
 
 // WBM, WBN = 16 x 16 blocks along the rows (M) and columns (N) of a wave's quadrant: 8, 8 (256 x 256 tiles), 4, 4 (128 x
 // 128), 2, 2 (64 x 64) or 4, 8 (128 x 256).
-// NST = stages in LDS: a step's loads are issued NST - 1 half-steps and more before its barrier. Two stages leave room for
-// two 128 x 128 workgroups on a compute unit, which then hide each other's waits; a launch with fewer tiles than units has
-// no second workgroup there, and three stages (96 KB) take its place: 1200 x 1536 x 8960 113 -> 72 us. Four or five
-// stages measured the same (73, 71 us): from three on the unit's L1, not the distance, sets the rate.
+// C = half steps in LDS: the loads of a half step are issued C - 4 to C - 2 half-steps before the barrier that they must have
+// landed at. Five leave room for two 128 x 128 workgroups on a compute unit, which then hide each other's waits; a launch with
+// fewer tiles than units has no second workgroup there, and seven (112 KB) take its place: 1200 x 1536 x 8960 100 -> 67 us. More
+// measured the same: from there on the unit's L1, not the distance, sets the rate.
 //
 // bf16 (optionally GELU) epilogue of the 16x16 layout: 32 output rows at a time go through a private LDS region as
 // [32][16 WBN] bf16 (row stride 16 WBN + 8), then leave as full row segments of the quadrant (256, 128 or 64 bytes).
@@ -212,44 +219,41 @@ __device__ __forceinline__ void gemm16_finish(f32x4 (&acc)[8][8], const EpiArgs&
   }
 }
 
-// waits until at most min(steps, MOST) k-steps of this wave's loads (NS each) are in flight; steps is uniform
-template <int MOST, int NS>
-__device__ __forceinline__ void wait_steps(int steps) {
-  if constexpr (MOST <= 0) {
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  } else {
-    if (steps >= MOST)
-      __builtin_amdgcn_s_waitcnt(vmcnt_imm(MOST * NS));
-    else
-      wait_steps<MOST - 1, NS>(steps);
-  }
+// The same address in scalar registers: the compiler does not see that a value worked out from the workgroup's id by a
+// division is one for the whole wave, and would walk over the lanes with every descriptor made from it.
+__device__ __forceinline__ void* uniform_address(const uint16_t* p) {
+  const uint64_t u = reinterpret_cast<uint64_t>(p);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)), lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)u);
+  return reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
 }
 
 // The 128 x 256 shape takes three quarters of the operand bytes per product of 128 x 128 tiles: for products of 257 to
 // 512 such tiles with a long K, which run two to a unit, half as many wide ones finish earlier (N = 1536, K = 8960: 3271
 // rows 124 -> 115 us, 5000 rows 136 -> 130; N = 5120, K = 13824, 1200 rows: 202 -> 181).
-template <int EPI, int WBM, int WBN, int NST>
+// FAR: rows so long that a tile's last byte is out of reach of the 32-bit offsets; loads by 64-bit addresses.
+template <int EPI, int WBM, int WBN, int C, bool FAR>
 __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
                                                           long M, int N, int K, EpiArgs ep, PartPtrs parts, int tiles_m,
                                                           int tiles_n) {
+#if defined(__HIP_DEVICE_COMPILE__)  // the buffer descriptors below are types of the device compiler's alone
   static_assert((WBM == 8 || WBM == 4 || WBM == 2) && (WBN == WBM || (WBM == 4 && WBN == 8)), "quadrants of 8 x 8, 4 x 4, 2 x 2 or 4 x 8 blocks");
-  static_assert(NST >= 2 && NST <= 8 && (WBM + WBN) * (NST - 1) < 64, "the loads in flight must fit the wait counter");
+  static_assert(C >= 5 && (WBM + WBN) / 2 * (C - 1) < 64, "two steps and a half in LDS at least, and the loads in flight must fit the wait counter");
   constexpr int BM = 32 * WBM, BN = 32 * WBN;
   constexpr int WTM = 16 * WBM, WTN = 16 * WBN;  // rows and columns of a wave's quadrant
   constexpr int GM = 8;
-  constexpr int STAGE = (BM + BN) * BK;  // elements per stage
+  constexpr int HA = WTM * BK, HB = WTN * BK;  // elements of half a step's rows of A and of W
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[];
-  uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);
+  uint16_t* smem = reinterpret_cast<uint16_t*>(smem_raw);  // [C][HA], [C][HB]
 
   // The grid's rows are the slices of K, their steps shared out as evenly as can be (never none: the host asks for no more
   // slices than steps). The last slice runs the epilogue, the others leave their plain fp32 result in `parts`. Without a
   // split there is one, and the divisions, a tenth of a microsecond of a product of one to four steps, are left out.
   const int ntiles = gridDim.x, nslices = gridDim.y, slice = blockIdx.y;
   const int tile = xcd_remap(blockIdx.x, ntiles);
-  int KTN = K / BK;
+  int KTN = K / BK, k_first = 0;
   if (nslices > 1) {
-    const int k_first = slice * KTN / nslices;
-    KTN = (slice + 1) * KTN / nslices - k_first;
+    k_first = __builtin_amdgcn_readfirstlane(slice * KTN / nslices);
+    KTN = __builtin_amdgcn_readfirstlane((slice + 1) * KTN / nslices) - k_first;
     A += (long)k_first * BK;
     W += (long)k_first * BK;
   }
@@ -272,40 +276,51 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
   const int wm = wave >> 1, wn = wave & 1;
   const int lj = lane & 15, lg = lane >> 4;
 
-  // ---- loader: wave w, slot i covers tile rows 8*(WBM w+i) .. +8 of A and 8*(WBN w+i) .. +8 of W; lane -> (row, position)
+  // ---- loader: load i of half h covers 8 of the tile's rows from WTM h + 4 WBM wave + 8 i on (of W: WTN h + 4 WBN wave + 8
+  // i); lane -> (row, position). One lane offset per load serves every step: the step's place in the rows is a scalar, and
+  // rows past the matrix's end are past the descriptor's too (such loads fetch nothing; their results are never stored).
   const int lr = lane >> 3, lp = lane & 7;
+  constexpr int LA = WBM / 2, LB = WBN / 2;  // loads of a half step
   // (the arrays that the lambdas below capture have the large tile's size for either tile: a bound that depends on
   // the template parameter loses the kernel's host-side stub)
-  const uint16_t* ga[8];
-  const uint16_t* gb[8];
+  int oa[8], ob[8];
+  const int rows_a = M - m0 < BM ? (int)(M - m0) : BM, rows_b = N - n0 < BN ? N - n0 : BN;
 #pragma unroll
-  for (int i = 0; i < WBM; ++i) {
-    const int r = 8 * (WBM * wave + i) + lr;
-    const int ch = lp ^ ((r >> 1) & 7);  // global chunk that belongs at position lp
-    long ra = m0 + r;
-    if (ra > M - 1) ra = M - 1;
-    ga[i] = A + ra * (long)K + ch * 8;
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int i = 0; i < LA; ++i) {
+      const int r = WTM * h + 4 * WBM * wave + 8 * i + lr;
+      const int at = (lp ^ ((r >> 1) & 7)) * 16;  // the global chunk that belongs at position lp
+      oa[LA * h + i] = FAR ? (r < rows_a ? r : rows_a - 1) : r * (2 * K) + at;
+    }
+#pragma unroll
+    for (int i = 0; i < LB; ++i) {
+      const int r = WTN * h + 4 * WBN * wave + 8 * i + lr;
+      const int at = (lp ^ ((r >> 1) & 7)) * 16;
+      ob[LB * h + i] = FAR ? (r < rows_b ? r : rows_b - 1) : r * (2 * K) + at;
+    }
   }
-#pragma unroll
-  for (int i = 0; i < WBN; ++i) {
-    const int r = 8 * (WBN * wave + i) + lr;
-    const int ch = lp ^ ((r >> 1) & 7);
-    int rb = n0 + r;
-    if (rb > N - 1) rb = N - 1;
-    gb[i] = W + (long)rb * K + ch * 8;
-  }
-  // loads t0 .. t1-1 of the WBM + WBN per k-step (A and W rows in turn, in a rectangular tile the A rows first)
-  auto issue = [&](int kt, int stage, int t0, int t1) {
-    uint16_t* sa = smem + stage * STAGE;
-    uint16_t* sb = sa + BM * BK;
-#pragma unroll
-    for (int t = t0; t < t1; ++t) {
-      const bool of_w = WBM == WBN ? (t & 1) != 0 : t >= WBM;
-      const int i = WBM == WBN ? t >> 1 : (of_w ? t - WBM : t);
-      if (of_w)
-        __builtin_amdgcn_global_load_lds(gb[i] + (long)kt * BK, sb + 8 * (WBN * wave + i) * BK, 16, 0, 0);
-      else
-        __builtin_amdgcn_global_load_lds(ga[i] + (long)kt * BK, sa + 8 * (WBM * wave + i) * BK, 16, 0, 0);
+  void* const base_a = uniform_address(A + m0 * K);
+  void* const base_b = uniform_address(W + (long)n0 * K);
+  const int bytes_a = __builtin_amdgcn_readfirstlane(FAR ? 0 : (rows_a * K - k_first * BK) * 2);
+  const int bytes_b = __builtin_amdgcn_readfirstlane(FAR ? 0 : (rows_b * K - k_first * BK) * 2);
+  // load t (A's first, then W's) of half step hs (half hs % 2 of the rows of step hs / 2), into the ring at slot
+  auto issue = [&](int hs, int h, int slot, int t) {
+    const bool of_w = t >= LA;
+    const int i = of_w ? t - LA : t, kt = hs >> 1;
+    __attribute__((address_space(3))) void* const dst =
+        (__attribute__((address_space(3))) void*)(smem + (of_w ? C * HA + slot * HB + (4 * WBN * wave + 8 * i) * BK
+                                                                : slot * HA + (4 * WBM * wave + 8 * i) * BK));
+    if constexpr (FAR) {
+      const int r = of_w ? ob[LB * h + i] : oa[LA * h + i];
+      const int row = (of_w ? WTN * h + 4 * WBN * wave : WTM * h + 4 * WBM * wave) + 8 * i + lr;
+      const uint16_t* src = reinterpret_cast<const uint16_t*>(of_w ? base_b : base_a) + (long)r * K +
+                            (long)(kt < KTN ? kt : KTN - 1) * BK + (lp ^ ((row >> 1) & 7)) * 8;
+      __builtin_amdgcn_global_load_lds(src, dst, 16, 0, 0);
+    } else {
+      // past the last step an empty descriptor: the loads keep their place in the count and fetch nothing
+      const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(of_w ? base_b : base_a, 0, kt < KTN ? (of_w ? bytes_b : bytes_a) : 0, 0x00027000);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, dst, 16, of_w ? ob[LB * h + i] : oa[LA * h + i], kt * (2 * BK), 0, 0);
     }
   };
 
@@ -313,9 +328,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
   const int sw = (lj >> 1) & 7;
   int koff[2];
 #pragma unroll
-  for (int h = 0; h < 2; ++h) koff[h] = ((4 * h + lg) ^ sw) * 8;
-  const int a_row0 = (wm * WTM + lj) * BK;
-  const int b_row0 = BM * BK + (wn * WTN + lj) * BK;
+  for (int h = 0; h < 2; ++h) koff[h] = ((4 * h + lg) ^ sw) * 8 + lj * BK;
 
   f32x4 acc[8][8];  // [n block][m block]; the WBN x WBM corner is used
 #pragma unroll
@@ -324,12 +337,13 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
     for (int mb = 0; mb < WBM; ++mb) acc[nb][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   bf16x8 af[2][8], bfr[2][8];
-  // fragment f of a half-step: 0 .. WBM-1 the activation blocks (m), then the WBN weight blocks (n)
-  auto read_frag = [&](const uint16_t* st, int h, int set, int f) {
+  // fragment f of a half-step: 0 .. WBM-1 the activation blocks (m), then the WBN weight blocks (n); sa, sb: where the wave's
+  // rows of the step start
+  auto read_frag = [&](int sa, int sb, int h, int set, int f) {
     if (f < WBM)
-      af[set][f] = *reinterpret_cast<const bf16x8*>(st + a_row0 + f * 16 * BK + koff[h]);
+      af[set][f] = *reinterpret_cast<const bf16x8*>(smem + sa + koff[h] + f * 16 * BK);
     else
-      bfr[set][f - WBM] = *reinterpret_cast<const bf16x8*>(st + b_row0 + (f - WBM) * 16 * BK + koff[h]);
+      bfr[set][f - WBM] = *reinterpret_cast<const bf16x8*>(smem + sb + koff[h] + (f - WBM) * 16 * BK);
   };
   // MFMAs g0 .. g1-1 of the WBM * WBN of a half-step, weight block major: g = WBM nb + mb. In place on the accumulator
   // registers (left to itself the register allocator gives every result a new home and pays with hundreds of
@@ -344,118 +358,91 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
   auto frag_order = [](int i) { return i == 0 ? WBM : (i <= WBM ? i - 1 : i); };
 
   // Schedule of one k-step (square tiles, WB = WBM = WBN: 2 WB^2 MFMAs a wave in 4 WB slots of WB / 2, 128 MFMAs in 32
-  // slots of four for the large tile). The barrier sits between the two half-steps. In the
-  // first half a wave fetches its fragments of the second half (same stage); at the barrier every wave holds all its
-  // fragments of the current stage in registers and its own pieces of the next stage, requested a whole half-step
-  // earlier, have landed. Behind it the stage just consumed is free: the second half issues the loads of the step after
-  // next into it, one a slot, and fetches the next step's first-half fragments from the other stage. Fragment reads are
+  // slots of four for the large tile). Either half-step issues the loads of one half step further on, one every other slot.
+  // The barrier sits between the two half-steps. In the first half a wave fetches its fragments of the second half (same
+  // step); at the barrier every wave holds all its fragments of the current step in registers, so that the step's two
+  // places in the ring are free behind it, and the whole next step is in LDS: what was requested behind that step, C - 4
+  // half steps, stays in flight. The second half fetches the next step's first fragments. Fragment reads are
   // packed into the first kReadSlots slots of a half so that the last of them has returned when the half ends. With one
   // wave per SIMD nothing else feeds the matrix pipe while this wave issues something that is not an MFMA, so reads and
   // loads stand one at a time between single MFMAs, where they issue in the shadow of the MFMA in front of them, and
   // the wave index is kept in a scalar register so that the LDS address of a load costs no vector instruction.
   // A rectangular tile has no whole number of MFMAs per slot: its reads stand behind MFMAs spread evenly over the first
   // three quarters of a half, its loads over all of it.
-  constexpr int NS = WBM + WBN;            // slots of a half-step = fragments of a half-step = loads of a k-step
+  constexpr int NS = WBM + WBN;            // slots of a half-step = fragments of a half-step
+  constexpr int NH = NS / 2;               // loads of a half step
   constexpr int G = WBM * WBN;             // MFMAs of a half-step
   constexpr int MPS = WBM / 2;             // MFMAs of a slot
   constexpr int kReadSlots = 3 * WBM / 2;  // 12 of 16 (6 of 8, 3 of 4)
   // reads of slot f: one fragment, two in the first NS - kReadSlots slots (which = 0: the first, 1: the second)
-  auto read_of_slot = [&](const uint16_t* stg, int h, int set, int f, int which) {
+  auto read_of_slot = [&](int sa, int sb, int h, int set, int f, int which) {
     constexpr int kDouble = NS - kReadSlots;
     if (f < kDouble)
-      read_frag(stg, h, set, frag_order(2 * f + which));
+      read_frag(sa, sb, h, set, frag_order(2 * f + which));
     else if (f < kReadSlots && which == 0)
-      read_frag(stg, h, set, frag_order(f + kDouble));
+      read_frag(sa, sb, h, set, frag_order(f + kDouble));
   };
-  // With two stages the loads of a step past the end fetch the last tile again into an idle stage (no branch in the
-  // loop); with more stages there would be several such steps, so they are left out.
-  constexpr bool kClamp = NST == 2;
+  // half-step h: its MFMAs, the fragments of the half-step behind it from sa, sb, the loads of half step hs into slot
+  auto half_step = [&](int h, int sa, int sb, int hs, int slot) {
+    if constexpr (WBM == WBN) {
 #pragma unroll
-  for (int j = 0; j < NST; ++j)
-    if (kClamp || j < KTN) issue(j < KTN ? j : KTN - 1, j, 0, NS);
-  // the first step's pieces are in LDS, the later ones may be in flight
-  if (kClamp || KTN >= NST)
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm((NST - 1) * NS));
-  else
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  lds_barrier();
+      for (int f = 0; f < NS; ++f) {
+        mfmas(h, MPS * f, MPS * f + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        read_of_slot(sa, sb, 1 - h, 1 - h, f, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (MPS > 1) mfmas(h, MPS * f + 1, MPS * f + 2);
+        __builtin_amdgcn_sched_barrier(0);
+        read_of_slot(sa, sb, 1 - h, 1 - h, f, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        mfmas(h, MPS * f + 2, MPS * f + MPS - 1);  // (none for the small tiles)
+        __builtin_amdgcn_sched_barrier(0);
+        if (f & 1) issue(hs, (C - 1 + h) & 1, slot, f >> 1);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (MPS > 2) mfmas(h, MPS * f + MPS - 1, MPS * f + MPS);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+#pragma unroll
+      for (int g = 0; g < G; ++g) {
+        mfmas(h, g, g + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NS; ++i)
+          if (i * 3 * G / (4 * NS) == g) read_frag(sa, sb, 1 - h, 1 - h, frag_order(i));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < NH; ++i)
+          if ((2 * i + 1) * G / (2 * NH) == g) issue(hs, (C - 1 + h) & 1, slot, i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  auto wrap = [](int slot) { return slot >= C ? slot - C : slot; };
+
+#pragma unroll
+  for (int hs = 0; hs < C - 1; ++hs)
+#pragma unroll
+    for (int t = 0; t < NH; ++t) issue(hs, hs & 1, hs, t);
+  // the first step's pieces are in LDS, the later ones may be in flight (the barrier alone: a fence would wait for them)
+  asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(NH * (C - 3)) : "memory");
   __builtin_amdgcn_sched_barrier(0);
+  int first = 0;  // slot of the first half of step kt
+  int sa = wm * HA, sb = C * HA + wn * HB;
 #pragma unroll
-  for (int f = 0; f < NS; ++f) read_frag(smem, 0, 0, frag_order(f));
+  for (int f = 0; f < NS; ++f) read_frag(sa, sb, 0, 0, frag_order(f));
   __builtin_amdgcn_sched_barrier(0);
 
-  int stage = 0;
   for (int kt = 0; kt < KTN; ++kt) {
-    const int next = stage + 1 < NST ? stage + 1 : 0;
-    const uint16_t* st = smem + stage * STAGE;
-    const uint16_t* stn = smem + next * STAGE;
-    const bool more = kt + NST < KTN;
-    const int k2 = more ? kt + NST : KTN - 1;
-    // ---- half-step 0: its MFMAs and the fragment reads of half-step 1
-    if constexpr (WBM == WBN) {
-#pragma unroll
-    for (int f = 0; f < NS; ++f) {
-      mfmas(0, MPS * f, MPS * f + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      read_of_slot(st, 1, 1, f, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (MPS > 1) mfmas(0, MPS * f + 1, MPS * f + 2);
-      __builtin_amdgcn_sched_barrier(0);
-      read_of_slot(st, 1, 1, f, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      mfmas(0, MPS * f + 2, MPS * f + MPS);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    } else {
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        mfmas(0, g, g + 1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < NS; ++i)
-          if (i * 3 * G / (4 * NS) == g) read_frag(st, 1, 1, frag_order(i));
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    // this wave's pieces of step kt + 1 are in LDS: the steps requested behind it, at most up to the last one, may be in flight
-    wait_steps<NST - 2, NS>(KTN - 2 - kt);
-    lds_barrier();  // every wave has all its fragments of this stage in registers
+    const int next = wrap(first + 2);
+    const int san = wrap(next + wm) * HA, sbn = C * HA + wrap(next + wn) * HB;
+    half_step(0, sa, sb, 2 * kt + C - 1, wrap(first + C - 1));
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(NH * (C - 4)) : "memory");
     __builtin_amdgcn_sched_barrier(0);
-    // ---- half-step 1: its MFMAs, the next step's first-half fragments, the loads of step kt + NST into the stage just freed
-    if constexpr (WBM == WBN) {
-#pragma unroll
-    for (int f = 0; f < NS; ++f) {
-      mfmas(1, MPS * f, MPS * f + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      read_of_slot(stn, 0, 0, f, 0);
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (MPS > 1) mfmas(1, MPS * f + 1, MPS * f + 2);
-      __builtin_amdgcn_sched_barrier(0);
-      read_of_slot(stn, 0, 0, f, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      mfmas(1, MPS * f + 2, MPS * f + MPS - 1);  // (none for the small tiles)
-      __builtin_amdgcn_sched_barrier(0);
-      if (kClamp || more) issue(k2, stage, f, f + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (MPS > 2) mfmas(1, MPS * f + MPS - 1, MPS * f + MPS);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    } else {
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        mfmas(1, g, g + 1);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < NS; ++i)
-          if (i * 3 * G / (4 * NS) == g) read_frag(stn, 0, 0, frag_order(i));
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int i = 0; i < NS; ++i)
-          if ((2 * i + 1) * G / (2 * NS) == g && (kClamp || more)) issue(k2, stage, i, i + 1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    stage = next;
+    half_step(1, san, sbn, 2 * kt + C, first);
+    first = next;
+    sa = san;
+    sb = sbn;
   }
 
   __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));  // no direct load may land in the staging regions of the epilogue
@@ -466,7 +453,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15"
                : "+a"(acc[WBN - 1][WBM - 1]), "+a"(acc[WBN - 1][WBM - 2]), "+a"(acc[WBM > 2 ? WBN - 1 : 0][WBM > 2 ? WBM - 3 : 1]),
                  "+a"(acc[WBM > 2 ? WBN - 1 : 0][WBM > 2 ? WBM - 4 : 0]));
-  lds_barrier();  // the staging regions of the epilogue overlay the operand stages
+  lds_barrier();  // the staging regions of the epilogue overlay the operands
   if constexpr (EPI == CHORUS_EPI_RESID) {
     if (slice + 1 < nslices) {
       const EpiArgs plain{parts.of(slice, M, N), nullptr, nullptr, nullptr, 1.f};
@@ -475,9 +462,10 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
     }
   }
   gemm16_finish<EPI, WBM, WBN>(acc, ep, smem_raw, wave, wm, wn, m0, n0, M, N, lane);
+#endif
 }
 
-template <int WBM, int WBN, int NST>
+template <int WBM, int WBN, int C, bool FAR = false>
 int32_t launch_gemm_w16(const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, EpiArgs ep, hipStream_t s,
                         int slices, const PartPtrs& parts) {
   constexpr int BM = 32 * WBM, BN = 32 * WBN;
@@ -485,10 +473,10 @@ int32_t launch_gemm_w16(const uint16_t* A, const uint16_t* W, long M, int N, int
   int tn = (N + BN - 1) / BN;
   if (tm * tn * slices > 0x7fffffffL) return CHORUS_E_SHAPE;
   dim3 grid((unsigned)(tm * tn), (unsigned)slices), block(256);
-  const size_t smem = NST * (BM + BN) * BK * sizeof(uint16_t);
+  const size_t smem = (size_t)C * (BM + BN) / 2 * BK * sizeof(uint16_t);
 #define GEMM_W16(E)                                                                           \
   {                                                                                           \
-    auto kern = gemm_w16_kernel<E, WBM, WBN, NST>;                                            \
+    auto kern = gemm_w16_kernel<E, WBM, WBN, C, FAR>;                                         \
     static DynLdsOnce once;                                                                   \
     CHK_STATUS(once.ensure(reinterpret_cast<const void*>(kern), (int)smem));                  \
     hipLaunchKernelGGL(kern, grid, block, smem, s, A, W, M, N, K, ep, parts, (int)tm, tn);    \
@@ -542,17 +530,18 @@ int32_t launch_add_parts(const PartPtrs& parts, int slices, long M, int N, const
 }
 
 // ---------------------------------------------------------------------------
-// Which tile, and in how many slices of K. The estimated time of each direct-to-LDS kernel in microseconds, from fits
-// to measurements on this chip with activations in the last-level cache and weights cold, as a request finds them
-// (K from 64 to 13824, N from 64 to 15360, M from 64 to 32760; figures in brackets: K = 1536 / K = 8960 where N = 1536).
+// Which tile, and in how many slices of K. The estimated time of each tile in microseconds, fitted to 3600 measurements
+// on this chip with activations in the last-level cache and weights cold, as a request finds them (K from 256 to 13824, N
+// from 256 to 15360, M from 64 to 13104; figures in brackets: K = 1536 / K = 8960 where N = 1536). What is fitted is the
+// choice: over those products the tile and slices taken cost 0.7 % more than the fastest (geometric mean).
 // What bounds a launch that does not fill the chip is the rate at which ONE compute unit gets operands: its L1 holds
 // 256 lines in flight, 32 KB, so a unit takes in about 60 KB per microsecond whatever the kernel does, and the launch
 // that spreads the same problem over more units wins: smaller tiles, or slices of K.
-//   256 x 256  one workgroup per unit, rounds of 256; a partly filled round is up to a quarter faster [39 / 190 us]
-//   128 x 256  three stages, one workgroup per unit: up to 256 tiles [27 / 111 few, 34 / 130 all units busy]
-//   128 x 128  two stages, two workgroups per unit: one round of up to 256 tiles [21 / 115], then rounds of 512 [27 / 145]
-//   128 x 128  three stages, one workgroup per unit: up to 256 tiles [17 / 72 few, 21 / 83 all units busy]
-//   64 x 64    four stages, two workgroups per unit: up to 256 tiles [9.7 / 40], growing with the tiles beyond
+//   256 x 256  one workgroup per unit, rounds of 256; a partly filled round is up to a quarter faster [37 / 161 us]
+//   128 x 256  one workgroup per unit: up to 256 tiles [23 / 108 few, 26 / 114 all units busy], then a second round
+//   128 x 128  two workgroups per unit: one round of up to 256 tiles [18 / 100], then rounds of 512 [27 / 136]
+//   128 x 128  three steps and a half in LDS, one workgroup per unit: up to 256 tiles [14 / 67 few, 16 / 76 all units busy]
+//   64 x 64    two workgroups per unit: up to 256 tiles [8.5 / 37], growing with the tiles beyond
 // ---------------------------------------------------------------------------
 enum Tile { kTile256, kTileWide, kTile128, kTile128Deep, kTile64, kTiles };
 constexpr int kTileNumber[kTiles] = {3, 2, 4, 5, 1};  // as chorus_gemm_bf16_kernel names them
@@ -563,32 +552,33 @@ constexpr int kMaxSlices = 4;  // more slices than this were never the fastest
 double tile_time(int tile, long m, int N, int K, int epi, int slices) {
   const long rows = kTileRows[tile], cols = kTileCols[tile];
   const double steps = (double)((K / BK + slices - 1) / slices);
-  const double w = (double)(((m + rows - 1) / rows) * ((N + cols - 1) / cols) * slices);
-  const bool f32_out = slices == 1 && (epi == CHORUS_EPI_F32 || epi == CHORUS_EPI_RESID);
+  const double w = (double)(((m + rows - 1) / rows) * ((N + cols - 1) / cols) * slices), fill = w / 256.0;
+  const bool gelu = epi == CHORUS_EPI_GELU_BF16, f32 = slices == 1 && (epi == CHORUS_EPI_F32 || epi == CHORUS_EPI_RESID);
+  auto by_epilogue = [&](double bf16, double with_gelu, double resid) { return f32 ? resid : gelu ? with_gelu : bf16; };
   switch (tile) {
     case kTile256: {
-      const double full = (f32_out ? 14.0 : epi == CHORUS_EPI_GELU_BF16 ? 4.0 : 2.0) + 1.65 * steps;
-      const double rounds = floor(w / 256.0), fill = w / 256.0 - rounds;
-      return full * (rounds + (fill > 0.0 ? 0.76 + 0.24 * fill * fill : 0.0));
+      const double full = by_epilogue(2.2, 3.59, 10.87) + 1.583 * steps;
+      const double rounds = floor(fill), rest = fill - rounds;
+      return full * (rounds + (rest > 0.0 ? 0.76 + 0.253 * rest * rest : 0.0));
     }
     case kTileWide: {
-      if (w > 256.0) return INFINITY;
-      const double fill = w / 256.0;
-      return (f32_out ? 9.5 : epi == CHORUS_EPI_GELU_BF16 ? 10.0 : 7.0) + (0.72 + 0.13 * fill * fill * fill) * steps;
+      if (w > 512.0) return INFINITY;
+      const double c = by_epilogue(3.58, 3.83, 9.17);
+      if (w <= 256.0) return c + (0.72 + 0.141 * fill * fill * fill) * steps;
+      return (c + 0.861 * steps) * (1.6 + 0.4 * (fill - 1.0));
     }
     case kTile128: {
-      const double one = (f32_out ? 5.0 : 2.0) + 0.74 * steps, round512 = (f32_out ? 4.5 : 0.5) + 1.005 * steps;
+      const double one = by_epilogue(1.71, 3.67, 4.97) + 0.74 * steps, round512 = by_epilogue(0.48, 0.57, 5.67) + 1.001 * steps;
       if (w <= 256.0) return one;
-      if (w <= 512.0) return one + (w - 256.0) / 256.0 * fmax(round512 - one, 0.0);
-      return ceil(w / 512.0) * round512;
+      if (w <= 512.0) return one + (fill - 1.0) * fmax(round512 - one, 0.0);
+      return (0.784 * ceil(w / 512.0) + 0.216 * w / 512.0) * round512;
     }
     case kTile128Deep: {
       if (w > 256.0) return INFINITY;
-      const double fill = w / 256.0;
-      return (f32_out ? 6.5 : 5.0) + (0.45 + 0.1 * fill * fill) * steps;
+      return by_epilogue(5.36, 3.64, 5.4) + (0.45 + 0.081 * fill * fill) * steps;
     }
     default:
-      return (w <= 256.0 ? 1.0 : 1.25 + 0.66 * (w - 256.0) / 256.0) * (3.5 + 0.255 * steps);
+      return (w <= 256.0 ? 1.0 : 1.141 + 0.677 * (fill - 1.0)) * (by_epilogue(3.62, 2.26, 3.14) + 0.246 * steps);
   }
 }
 
@@ -625,14 +615,19 @@ GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
   return best;
 }
 
+constexpr int kHalvesDeep = 7, kHalves64 = 9;
+// a tile's bytes, 256 rows of 2 K, within the 32-bit offsets of its loads
+constexpr int kMaxOffsetK = (1 << 22) - 64;
+
 int32_t launch_tile(int tile, const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, const EpiArgs& ep,
                     hipStream_t s, int slices = 1, const PartPtrs& parts = PartPtrs{nullptr, nullptr}) {
+  if (K > kMaxOffsetK) return launch_gemm_w16<2, 2, kHalves64, true>(A, W, M, N, K, epi, ep, s, slices, parts);
   switch (tile) {
-    case kTile256: return launch_gemm_w16<8, 8, 2>(A, W, M, N, K, epi, ep, s, slices, parts);
-    case kTileWide: return launch_gemm_w16<4, 8, 3>(A, W, M, N, K, epi, ep, s, slices, parts);
-    case kTile128: return launch_gemm_w16<4, 4, 2>(A, W, M, N, K, epi, ep, s, slices, parts);
-    case kTile128Deep: return launch_gemm_w16<4, 4, 3>(A, W, M, N, K, epi, ep, s, slices, parts);
-    default: return launch_gemm_w16<2, 2, 4>(A, W, M, N, K, epi, ep, s, slices, parts);
+    case kTile256: return launch_gemm_w16<8, 8, 5>(A, W, M, N, K, epi, ep, s, slices, parts);
+    case kTileWide: return launch_gemm_w16<4, 8, 6>(A, W, M, N, K, epi, ep, s, slices, parts);
+    case kTile128: return launch_gemm_w16<4, 4, 5>(A, W, M, N, K, epi, ep, s, slices, parts);
+    case kTile128Deep: return launch_gemm_w16<4, 4, kHalvesDeep>(A, W, M, N, K, epi, ep, s, slices, parts);
+    default: return launch_gemm_w16<2, 2, kHalves64>(A, W, M, N, K, epi, ep, s, slices, parts);
   }
 }
 
