@@ -54,8 +54,8 @@ int32_t chorus_last_hip_error(void);
  * rows get equal scores; the lowest index wins ties. A zero-norm row or query
  * scores -inf. N == 0 gives index -1, score -inf, hit 0. d must be a multiple of 4;
  * N at most 2^31 - 2 (the index is an int32), CHORUS_E_SHAPE beyond.
- * Two launches: the scan leaves one (best value, index) pair per workgroup in ws, a single
- * workgroup picks among them.
+ * One launch: every workgroup of the scan leaves one (best value, index) pair in ws, the last one
+ * waits for them and picks. Nothing in ws has to start at any value.
  * ------------------------------------------------------------------------ */
 typedef struct {
   int32_t index;

@@ -41,8 +41,8 @@ int32_t chorus_gemm_bf16(const uint16_t* A, const uint16_t* W, int64_t M, int32_
 
 /* chorus_gemm_bf16 with the tile kernel named by the caller, for tests and comparisons (every kernel is correct on
  * every shape the call accepts; only the speed differs): kernel 0 = the default choice by problem size, else tiles
- * filled straight from global memory into 1 = 64 x 64 (four stages in LDS), 2 = 128 x 256 (three), 3 = 256 x 256 (two),
- * 4 = 128 x 128 (two), 5 = 128 x 128 (three). Anything else: CHORUS_E_ARG. */
+ * filled straight from global memory into 1 = 64 x 64 (nine half k-steps in LDS), 2 = 128 x 256 (six), 3 = 256 x 256
+ * (five), 4 = 128 x 128 (five), 5 = 128 x 128 (seven). Anything else: CHORUS_E_ARG. */
 int32_t chorus_gemm_bf16_kernel(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, int32_t epilogue,
                                 void* out, const float* bias, const float* gate0, const float* gate1, float scale,
                                 int32_t kernel, void* stream);
@@ -66,6 +66,12 @@ typedef struct {
 } chorus_gemm_plan;
 int32_t chorus_gemm_bf16_plan(int64_t M, int32_t N, int32_t K, int32_t epilogue, size_t first_bytes, size_t rest_bytes,
                               chorus_gemm_plan* out);
+
+/* chorus_cache_lookup with the length of its last workgroup's wait named by the caller, for tests of the path taken when it
+ * runs out: at most `rounds` + 1 looks for what the other workgroups leave (-1: none). Then that workgroup makes the whole
+ * result itself. rounds from -1 to 8192, what the plain call uses (CHORUS_E_ARG). */
+int32_t chorus_cache_lookup_wait(const float* cache_emb, int64_t N, int32_t d, const float* query, float tau, int32_t rounds,
+                                 chorus_lookup_result* out, void* ws, size_t ws_bytes, void* stream);
 
 /* out bf16 [L, D] = LN(x) * (mul_base + mul0 + mul1) + (add0 + add1), LN over D without
  * affine, eps 1e-6; mul_base = 1 if plus_one else 0; mul1/add1 may be NULL.

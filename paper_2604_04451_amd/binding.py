@@ -105,6 +105,7 @@ def load():
     sigs = {
         "chorus_version": (i32, []),
         "chorus_last_hip_error": (i32, []),
+        "chorus_cache_lookup_wait": (i32, [vp, i64, i32, vp, f32, i32, vp, vp, sz, vp]),
         "chorus_cache_lookup_workspace_bytes": (sz, [i64]),
         "chorus_cache_lookup": (i32, [vp, i64, i32, vp, f32, vp, vp, sz, vp]),
         "chorus_cache_lookup_static": (i32, [vp, i64, i32, vp, f32, vp, vp]),
@@ -271,6 +272,14 @@ def chorus_cache_lookup_static(cache_emb, query, tau, out):
         raise TypeError("query: wrong length")
     _status("chorus_cache_lookup_static", lib.chorus_cache_lookup_static(_p(cache_emb) if N else C.c_void_p(0), N, d,
                                                                          _p(query), float(tau), _p(out), _stream()))
+    return out
+
+
+def chorus_cache_lookup_wait(cache_emb, query, tau, rounds, out, ws):
+    """chorus_cache_lookup with the length of its last workgroup's wait named by the caller (tests)."""
+    N, d = cache_emb.shape
+    _status("chorus_cache_lookup_wait", load().chorus_cache_lookup_wait(_p(cache_emb), N, d, _p(query), float(tau), int(rounds),
+                                                                        _p(out), _p(ws), ws.numel(), _stream()))
     return out
 
 

@@ -1,7 +1,9 @@
 // Stage-1 retrieval: top-1 cosine similarity over the prompt-embedding cache
 // (Sec. 3.1 "Full Reuse"). HBM-bound: the [N, d] fp32 cache is streamed once.
+#include "chorus_ops.h"
 #include "common.h"
 #include "lookup_row.h"
+#include "tagged.h"
 
 namespace chorus {
 
@@ -9,14 +11,13 @@ thread_local int32_t g_last_hip_error = 0;
 
 namespace {
 
-constexpr int kWaves = 4;            // waves per workgroup of the scan, one cache row per wave at a time
-constexpr int kMaxScanBlocks = 4096; // beyond this many workgroups a wave walks several rows
+constexpr int kWaves = 8;            // waves per workgroup of the scan, one cache row per wave at a time
+constexpr int kMaxScanBlocks = 2048; // beyond this many workgroups a wave walks several rows
 
-// What one workgroup of the scan leaves behind: the best r_j = <q, c_j> / |c_j| among its rows and that row's
-// index (the lowest one among equal values). The header in front of the partials holds |q|^2.
-struct LookupPartial {
-  float r;
-  int32_t idx;
+// What one workgroup of the scan leaves behind (tagged words): the best r_j = <q, c_j> / |c_j| among its rows and that row's
+// index (the lowest one among equal values). In front of them the number of a launch that gave its wait up.
+struct LookupSlot {
+  uint64_t r, idx;
 };
 constexpr size_t kLookupHeaderBytes = 256;
 
@@ -24,135 +25,155 @@ inline long scan_blocks(long N) {
   long g = (N + kWaves - 1) / kWaves;
   return g < kMaxScanBlocks ? g : kMaxScanBlocks;
 }
+// The size that callers hold: 8 bytes for every four rows, up to 4096 times. Sixteen for every eight need no more.
 inline size_t lookup_scratch_bytes(long N) {
-  return kLookupHeaderBytes + align_up((size_t)(N > 0 ? scan_blocks(N) : 1) * sizeof(LookupPartial), 256);
+  long g = (N + 3) / 4;
+  g = g < 1 ? 1 : g < 4096 ? g : 4096;
+  return kLookupHeaderBytes + align_up((size_t)g * 8, 256);
+}
+static_assert(kMaxScanBlocks * sizeof(LookupSlot) <= 4096 * 8, "the slots' place in the workspace");
+
+struct Best {
+  float r = -INFINITY;
+  int32_t idx = 0x7fffffff;  // larger than any index
+  __device__ __forceinline__ void take(float other, int32_t oi) {
+    if (other > r || (other == r && oi < idx)) {
+      r = other;
+      idx = oi;
+    }
+  }
+};
+
+__device__ __forceinline__ void write_result(chorus_lookup_result* out, const Best& b, float qq, float tau) {
+  const float nq = sqrtf(qq);
+  float m = (nq > 0.f && b.r > -INFINITY) ? b.r / nq : -INFINITY;
+  if (!(m == m)) m = -INFINITY;
+  chorus_lookup_result res;
+  // every score -inf (zero-norm query or rows): index 0, like a first-maximum scan
+  res.index = (b.idx == 0x7fffffff || m == -INFINITY) ? 0 : b.idx;
+  res.score = m;
+  res.hit = m >= tau ? 1 : 0;
+  *out = res;
 }
 
 // One wave per row: lanes stride over the row in float4, then a butterfly
 // reduction. The order of additions depends only on d, never on the row index,
 // so identical rows produce identical values. The scan compares r_j = <q, c_j> / |c_j|;
-// the query norm is a positive constant for the whole scan and is applied once, in the
-// final kernel (score_j = r_j / |q|), which keeps this HBM-bound loop at 8 FMAs per
+// the query norm is a positive constant for the whole scan and is applied once, at the
+// end (score_j = r_j / |q|), which keeps this HBM-bound loop at 8 FMAs per
 // 16 bytes read. |q|^2 falls out of the query values every wave loads anyway (the same
-// additions in the same order in every wave); the first wave of the grid stores it.
+// additions in the same order in every wave).
+// The last workgroup scans nothing: it sums |q|^2 as a row of its own, collects what the others leave, divides by |q| and
+// tests the threshold. As a second launch that took 2.3 us (1000 x 768, the call 8.7 us, now 5.6) to 3.9 (4096 x 4096, cold
+// 17.0, now 16.0; scanned by the last workgroup as well 16.1); a scan of few long rows now runs on half the compute units,
+// as the workspace holds one slot for eight rows (1024 x 4096 cold 8.7 us, now 9.0; from the cache 8.6, now 8.5).
 __global__ __launch_bounds__(kWaves * 64) void lookup_scan_kernel(const float* __restrict__ cache,
-                                                                  const float* __restrict__ query, long N, int d,
-                                                                  LookupPartial* __restrict__ partial,
-                                                                  float* __restrict__ qnorm2) {
+                                                                  const float* __restrict__ query, long N, int d, float tau,
+                                                                  uint64_t number, int rounds, uint64_t* gave_up,
+                                                                  LookupSlot* slots,
+                                                                  chorus_lookup_result* __restrict__ out) {
   __shared__ float sv[kWaves];
   __shared__ int32_t si[kWaves];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float4* q4 = reinterpret_cast<const float4*>(query);
   const int n4 = d >> 2;
-  float best = -INFINITY, qq = 0.f;
-  int32_t bi = 0x7fffffff;  // larger than any index
-  const long stride = (long)gridDim.x * kWaves;
-  for (long row = (long)blockIdx.x * kWaves + wave; row < N; row += stride) {
+  Best best;
+  float qq = 0.f;
+  auto scan = [&](long row, long stride) {
+    for (; row < N; row += stride) {  // rows ascend within a wave
+      float dot, cc;
+      fp32_row_products(reinterpret_cast<const float4*>(cache + row * (long)d), q4, n4, lane, dot, cc, qq);
+      best.take(row_ratio(dot, cc), (int32_t)row);
+    }
+  };
+  auto meet = [&]() {  // the best of the workgroup's waves, in every thread
+    __syncthreads();   // (a second use may not overtake the first one's readers)
+    if (lane == 0) {
+      sv[wave] = best.r;
+      si[wave] = best.idx;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) best.take(sv[w], si[w]);
+  };
+  const int last = gridDim.x - 1;  // scans nothing
+  const uint32_t tag_r = (uint32_t)(number >> 32), tag_i = (uint32_t)number;
+  if ((int)blockIdx.x != last) {
+    scan((long)blockIdx.x * kWaves + wave, (long)last * kWaves);
+    meet();
+    if (tid == 0) {
+      leave_word(&slots[blockIdx.x].r, tag_r, __float_as_uint(best.r));
+      leave_word(&slots[blockIdx.x].idx, tag_i, (uint32_t)best.idx);
+    }
+    return;
+  }
+  constexpr int R = kMaxScanBlocks / (kWaves * 64);  // slots per thread
+  {
     float dot, cc;
-    fp32_row_products(reinterpret_cast<const float4*>(cache + row * (long)d), q4, n4, lane, dot, cc, qq);
-    const float r = row_ratio(dot, cc);
-    if (r > best) {  // rows ascend within a wave: a strict comparison keeps the lowest index
-      best = r;
-      bi = (int32_t)row;
-    }
+    fp32_row_products(q4, q4, n4, lane, dot, cc, qq);
   }
-  if (lane == 0) {
-    sv[wave] = best;
-    si[wave] = bi;
-    if (blockIdx.x == 0 && wave == 0) *qnorm2 = qq;  // wave 0 of workgroup 0 always has a row
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
+  bool here = rounds >= 0 && read_word(gave_up) != number;
+  if (here) {
+    uint64_t wr[R], wi[R];
+    for (int round = 0;; ++round) {
+      here = true;
 #pragma unroll
-    for (int w = 1; w < kWaves; ++w) {
-      if (sv[w] > best || (sv[w] == best && si[w] < bi)) {
-        best = sv[w];
-        bi = si[w];
+      for (int u = 0; u < R; ++u) {
+        const int j = tid + u * (kWaves * 64);
+        wr[u] = j < last ? read_word(&slots[j].r) : (uint64_t)tag_r << 32;
+        wi[u] = j < last ? read_word(&slots[j].idx) : (uint64_t)tag_i << 32;
       }
+#pragma unroll
+      for (int u = 0; u < R; ++u) here = here && (uint32_t)(wr[u] >> 32) == tag_r && (uint32_t)(wi[u] >> 32) == tag_i;
+      if (__all(here) || round == rounds) break;
+      __builtin_amdgcn_s_sleep(1);
     }
-    LookupPartial p;
-    p.r = best;
-    p.idx = bi;
-    partial[blockIdx.x] = p;
+    here = __syncthreads_and(here);
+    if (here) {
+#pragma unroll
+      for (int u = 0; u < R; ++u) {
+        const int j = tid + u * (kWaves * 64);
+        if (j >= last) continue;
+        best.take(__uint_as_float((uint32_t)wr[u]), (int32_t)(uint32_t)wi[u]);
+        leave_word(&slots[j].r, 0, 0);
+        leave_word(&slots[j].idx, 0, 0);
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) best.take(__shfl_xor(best.r, o, 64), __shfl_xor(best.idx, o, 64));
+    } else if (tid == 0) {
+      __hip_atomic_store(gave_up, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
+  if (!here) scan(wave, kWaves);  // alone
+  meet();
+  if (tid == 0) write_result(out, best, qq, tau);
 }
 
-// Single workgroup: maximum over the workgroup partials with the lowest index among equal maxima, then the
-// division by |q| and the threshold test.
-__global__ __launch_bounds__(256) void lookup_final_kernel(const LookupPartial* __restrict__ partial, int nparts,
-                                                           const float* __restrict__ qnorm2, long N, float tau,
-                                                           chorus_lookup_result* __restrict__ out) {
-  __shared__ float sv[4];
-  __shared__ int32_t si[4];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  float best = -INFINITY;
-  int32_t bi = 0x7fffffff;
-  for (int j = threadIdx.x; j < nparts; j += 256) {
-    const LookupPartial p = partial[j];
-    if (p.r > best || (p.r == best && p.idx < bi)) {
-      best = p.r;
-      bi = p.idx;
-    }
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const float ob = __shfl_xor(best, o, 64);
-    const int32_t oi = __shfl_xor(bi, o, 64);
-    if (ob > best || (ob == best && oi < bi)) {
-      best = ob;
-      bi = oi;
-    }
-  }
-  if (lane == 0) {
-    sv[wave] = best;
-    si[wave] = bi;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int w = 1; w < 4; ++w) {
-      if (sv[w] > best || (sv[w] == best && si[w] < bi)) {
-        best = sv[w];
-        bi = si[w];
-      }
-    }
-    chorus_lookup_result r;
-    if (N <= 0) {
-      r.index = -1;
-      r.score = -INFINITY;
-      r.hit = 0;
-    } else {
-      const float nq = sqrtf(*qnorm2);
-      float m = (nq > 0.f && best > -INFINITY) ? best / nq : -INFINITY;
-      if (!(m == m)) m = -INFINITY;
-      // every score -inf (zero-norm query or rows): index 0, like a first-maximum scan
-      r.index = (bi == 0x7fffffff || m == -INFINITY) ? 0 : bi;
-      r.score = m;
-      r.hit = m >= tau ? 1 : 0;
-    }
-    *out = r;
-  }
+// an empty cache
+__global__ void lookup_none_kernel(chorus_lookup_result* __restrict__ out) {
+  chorus_lookup_result r;
+  r.index = -1;
+  r.score = -INFINITY;
+  r.hit = 0;
+  *out = r;
 }
 
-// both launches of a lookup; `scratch` holds the header and the partials (lookup_scratch_bytes(N))
+// one launch; `scratch` holds the header and the slots (lookup_scratch_bytes(N))
 int32_t launch_lookup(const float* cache_emb, long N, int d, const float* query, float tau, chorus_lookup_result* out,
-                      void* scratch, hipStream_t s) {
-  float* qnorm2 = reinterpret_cast<float*>(scratch);
-  LookupPartial* partial = reinterpret_cast<LookupPartial*>(reinterpret_cast<uint8_t*>(scratch) + kLookupHeaderBytes);
-  int nparts = 0;
-  if (N > 0) {
-    nparts = (int)scan_blocks(N);
-    hipLaunchKernelGGL(lookup_scan_kernel, dim3((unsigned)nparts), dim3(kWaves * 64), 0, s, cache_emb, query, N, d, partial,
-                       qnorm2);
-    CHORUS_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(lookup_final_kernel, dim3(1), dim3(256), 0, s, partial, nparts, qnorm2, N, tau, out);
+                      void* scratch, int rounds, hipStream_t s) {
+  if (N > 0)
+    hipLaunchKernelGGL(lookup_scan_kernel, dim3((unsigned)scan_blocks(N) + 1), dim3(kWaves * 64), 0, s, cache_emb, query, N, d, tau,
+                       launch_number(), rounds, reinterpret_cast<uint64_t*>(scratch),
+                       reinterpret_cast<LookupSlot*>(reinterpret_cast<uint8_t*>(scratch) + kLookupHeaderBytes), out);
+  else
+    hipLaunchKernelGGL(lookup_none_kernel, dim3(1), dim3(1), 0, s, out);
   CHORUS_LAUNCH_CHECK();
   return CHORUS_OK;
 }
 
-// Scratch of the entry point that allocates nothing: the header and the largest number of partials a scan leaves
+// Scratch of the entry point that allocates nothing: the header and the largest number of slots a scan uses
 // (the scan caps its grid, so this serves every N). One copy per GPU, resident until the process ends.
-constexpr size_t kStaticScratchBytes = kLookupHeaderBytes + (size_t)kMaxScanBlocks * sizeof(LookupPartial);
+constexpr size_t kStaticScratchBytes = kLookupHeaderBytes + (size_t)kMaxScanBlocks * sizeof(LookupSlot);
 static __device__ __align__(256) uint8_t scratch[kStaticScratchBytes];
 
 // Device address of `scratch` on each GPU. In host code the array's name is only a handle for
@@ -200,7 +221,16 @@ int32_t chorus_cache_lookup(const float* cache_emb, int64_t N, int32_t d, const 
   CHK_STATUS(check_lookup_args(cache_emb, N, d, query, out));
   if (!ws || ws_bytes < chorus_cache_lookup_workspace_bytes(N)) return CHORUS_E_WORKSPACE;
   if (!aligned16(ws)) return CHORUS_E_ARG;
-  return launch_lookup(cache_emb, (long)N, d, query, tau, out, ws, (hipStream_t)stream);
+  return launch_lookup(cache_emb, (long)N, d, query, tau, out, ws, kWaitRounds, (hipStream_t)stream);
+}
+
+int32_t chorus_cache_lookup_wait(const float* cache_emb, int64_t N, int32_t d, const float* query, float tau, int32_t rounds,
+                                 chorus_lookup_result* out, void* ws, size_t ws_bytes, void* stream) {
+  CHK_STATUS(check_lookup_args(cache_emb, N, d, query, out));
+  if (rounds < -1 || rounds > kWaitRounds) return CHORUS_E_ARG;
+  if (!ws || ws_bytes < chorus_cache_lookup_workspace_bytes(N)) return CHORUS_E_WORKSPACE;
+  if (!aligned16(ws)) return CHORUS_E_ARG;
+  return launch_lookup(cache_emb, (long)N, d, query, tau, out, ws, rounds, (hipStream_t)stream);
 }
 
 int32_t chorus_cache_lookup_static(const float* cache_emb, int64_t N, int32_t d, const float* query, float tau,
@@ -209,9 +239,8 @@ int32_t chorus_cache_lookup_static(const float* cache_emb, int64_t N, int32_t d,
   if (lookup_scratch_bytes(N > 0 ? (long)N : 0) > kStaticScratchBytes) return CHORUS_E_SHAPE;
   void* ptr = nullptr;
   CHK_STATUS(static_scratch(&ptr));
-  // nothing in the scratch has to start at zero: the scan writes the query norm and every partial the final
-  // kernel reads (it reads as many as this call's scan has workgroups), so what an earlier call left is never seen
-  return launch_lookup(cache_emb, (long)N, d, query, tau, out, ptr, (hipStream_t)stream);
+  // nothing in the scratch has to start at zero: what an earlier call left does not carry this launch's number
+  return launch_lookup(cache_emb, (long)N, d, query, tau, out, ptr, kWaitRounds, (hipStream_t)stream);
 }
 
 }  // extern "C"
