@@ -317,9 +317,7 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_update_kernel(const floa
         for (int i = 0; i < KS; ++i) s[r] += (v[r][i][0] + v[r][i][1]) + (v[r][i][2] + v[r][i][3]);
       }
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-        for (int r = 0; r < 2; ++r) s[r] += __shfl_xor(s[r], o, 64);
+      for (int r = 0; r < 2; ++r) s[r] = wave_sum(s[r]);
 #pragma unroll
       for (int r = 0; r < 2; ++r) {
         s[r] *= 1.0f / (float)D;  // the mean
@@ -331,9 +329,7 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_update_kernel(const floa
         }
       }
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1)
-#pragma unroll
-        for (int r = 0; r < 2; ++r) q[r] += __shfl_xor(q[r], o, 64);
+      for (int r = 0; r < 2; ++r) q[r] = wave_sum(q[r]);
       q[0] = rsqrtf(q[0] * (1.0f / (float)D) + 1e-6f);
       q[1] = rsqrtf(q[1] * (1.0f / (float)D) + 1e-6f);
 #pragma unroll
