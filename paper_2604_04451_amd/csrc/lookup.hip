@@ -14,10 +14,10 @@ namespace {
 constexpr int kWaves = 8;            // waves per workgroup of the scan, one cache row per wave at a time
 constexpr int kMaxScanBlocks = 2048; // beyond this many workgroups a wave walks several rows
 
-// What one workgroup of the scan leaves behind (tagged words): the best r_j = <q, c_j> / |c_j| among its rows and that row's
-// index (the lowest one among equal values). In front of them the number of a launch that gave its wait up.
+// What one workgroup of the scan leaves behind (tagged words): the best r_j = <q, c_j> / |c_j| among its rows and that row
+// (the lowest one among equal values), as row_key orders them. In front of them the number of a launch that gave its wait up.
 struct LookupSlot {
-  uint64_t r, idx;
+  uint64_t r, row;
 };
 constexpr size_t kLookupHeaderBytes = 256;
 
@@ -33,24 +33,20 @@ inline size_t lookup_scratch_bytes(long N) {
 }
 static_assert(kMaxScanBlocks * sizeof(LookupSlot) <= 4096 * 8, "the slots' place in the workspace");
 
-struct Best {
-  float r = -INFINITY;
-  int32_t idx = 0x7fffffff;  // larger than any index
-  __device__ __forceinline__ void take(float other, int32_t oi) {
-    if (other > r || (other == r && oi < idx)) {
-      r = other;
-      idx = oi;
-    }
-  }
-};
+// r and its row as one integer that orders by r and, between equal r (0 and -0 are equal), by the lower row; 0: no row
+__device__ __forceinline__ uint64_t row_key(float r, uint32_t row) {
+  const uint32_t u = __float_as_uint(r + 0.0f);
+  return ((uint64_t)((u & 0x80000000u) ? ~u : (u | 0x80000000u)) << 32) | (uint32_t)~row;
+}
 
-__device__ __forceinline__ void write_result(chorus_lookup_result* out, const Best& b, float qq, float tau) {
+__device__ __forceinline__ void write_result(chorus_lookup_result* out, uint64_t key, float qq, float tau) {
+  const uint32_t ord = (uint32_t)(key >> 32);
+  const float best = __uint_as_float((ord & 0x80000000u) ? (ord & 0x7fffffffu) : ~ord);
   const float nq = sqrtf(qq);
-  float m = (nq > 0.f && b.r > -INFINITY) ? b.r / nq : -INFINITY;
+  float m = (nq > 0.f && best > -INFINITY) ? best / nq : -INFINITY;
   if (!(m == m)) m = -INFINITY;
   chorus_lookup_result res;
-  // every score -inf (zero-norm query or rows): index 0, like a first-maximum scan
-  res.index = (b.idx == 0x7fffffff || m == -INFINITY) ? 0 : b.idx;
+  res.index = m == -INFINITY ? 0 : (int32_t)~(uint32_t)key;  // every score -inf (zero-norm query or rows): like a first-maximum scan
   res.score = m;
   res.hit = m >= tau ? 1 : 0;
   *out = res;
@@ -64,37 +60,34 @@ __device__ __forceinline__ void write_result(chorus_lookup_result* out, const Be
 // 16 bytes read. |q|^2 falls out of the query values every wave loads anyway (the same
 // additions in the same order in every wave).
 // The last workgroup scans nothing: it sums |q|^2 as a row of its own, collects what the others leave, divides by |q| and
-// tests the threshold. As a second launch that took 2.3 us (1000 x 768, the call 8.7 us, now 5.6) to 3.9 (4096 x 4096, cold
-// 17.0, now 16.0; scanned by the last workgroup as well 16.1); a scan of few long rows now runs on half the compute units,
-// as the workspace holds one slot for eight rows (1024 x 4096 cold 8.7 us, now 9.0; from the cache 8.6, now 8.5).
+// tests the threshold. A second launch for that took 2.3 us (1000 x 768, the call 8.8 us, now 5.6) to 3.9 (4096 x 4096 from
+// HBM 17.3, now 14.8; 1024 x 4096 8.9 and 7.5). What is behind the scan is a chain of latencies, so the values that meet are
+// one integer each, whose maximum over a wave stays in registers (compared as pairs through the LDS crossbar the calls took
+// 16.0 and 9.0 us).
 __global__ __launch_bounds__(kWaves * 64) void lookup_scan_kernel(const float* __restrict__ cache,
                                                                   const float* __restrict__ query, long N, int d, float tau,
                                                                   uint64_t number, int rounds, uint64_t* gave_up,
                                                                   LookupSlot* slots,
                                                                   chorus_lookup_result* __restrict__ out) {
-  __shared__ float sv[kWaves];
-  __shared__ int32_t si[kWaves];
+  __shared__ uint64_t sk[kWaves];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const float4* q4 = reinterpret_cast<const float4*>(query);
   const int n4 = d >> 2;
-  Best best;
+  uint64_t best = 0;
   float qq = 0.f;
+  auto take = [&](uint64_t k) { best = k > best ? k : best; };
   auto scan = [&](long row, long stride) {
-    for (; row < N; row += stride) {  // rows ascend within a wave
+    for (; row < N; row += stride) {
       float dot, cc;
       fp32_row_products(reinterpret_cast<const float4*>(cache + row * (long)d), q4, n4, lane, dot, cc, qq);
-      best.take(row_ratio(dot, cc), (int32_t)row);
+      take(row_key(row_ratio(dot, cc), (uint32_t)row));
     }
   };
   auto meet = [&]() {  // the best of the workgroup's waves, in every thread
-    __syncthreads();   // (a second use may not overtake the first one's readers)
-    if (lane == 0) {
-      sv[wave] = best.r;
-      si[wave] = best.idx;
-    }
+    if (lane == 0) sk[wave] = best;
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) best.take(sv[w], si[w]);
+    for (int w = 0; w < kWaves; ++w) take(sk[w]);
   };
   const int last = gridDim.x - 1;  // scans nothing
   const uint32_t tag_r = (uint32_t)(number >> 32), tag_i = (uint32_t)number;
@@ -102,8 +95,8 @@ __global__ __launch_bounds__(kWaves * 64) void lookup_scan_kernel(const float* _
     scan((long)blockIdx.x * kWaves + wave, (long)last * kWaves);
     meet();
     if (tid == 0) {
-      leave_word(&slots[blockIdx.x].r, tag_r, __float_as_uint(best.r));
-      leave_word(&slots[blockIdx.x].idx, tag_i, (uint32_t)best.idx);
+      leave_word(&slots[blockIdx.x].r, tag_r, (uint32_t)(best >> 32));
+      leave_word(&slots[blockIdx.x].row, tag_i, (uint32_t)best);
     }
     return;
   }
@@ -121,7 +114,7 @@ __global__ __launch_bounds__(kWaves * 64) void lookup_scan_kernel(const float* _
       for (int u = 0; u < R; ++u) {
         const int j = tid + u * (kWaves * 64);
         wr[u] = j < last ? read_word(&slots[j].r) : (uint64_t)tag_r << 32;
-        wi[u] = j < last ? read_word(&slots[j].idx) : (uint64_t)tag_i << 32;
+        wi[u] = j < last ? read_word(&slots[j].row) : (uint64_t)tag_i << 32;
       }
 #pragma unroll
       for (int u = 0; u < R; ++u) here = here && (uint32_t)(wr[u] >> 32) == tag_r && (uint32_t)(wi[u] >> 32) == tag_i;
@@ -134,12 +127,11 @@ __global__ __launch_bounds__(kWaves * 64) void lookup_scan_kernel(const float* _
       for (int u = 0; u < R; ++u) {
         const int j = tid + u * (kWaves * 64);
         if (j >= last) continue;
-        best.take(__uint_as_float((uint32_t)wr[u]), (int32_t)(uint32_t)wi[u]);
+        take((wr[u] << 32) | (uint32_t)wi[u]);
         leave_word(&slots[j].r, 0, 0);
-        leave_word(&slots[j].idx, 0, 0);
+        leave_word(&slots[j].row, 0, 0);
       }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) best.take(__shfl_xor(best.r, o, 64), __shfl_xor(best.idx, o, 64));
+      best = wave_max_key(best);
     } else if (tid == 0) {
       __hip_atomic_store(gave_up, number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }

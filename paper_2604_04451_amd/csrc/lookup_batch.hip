@@ -5,6 +5,7 @@
 // needs about the cycles that HBM needs to deliver the cache rows; row norms are accumulated
 // from the same registers.
 #include "common.h"
+#include "lookup_row.h"
 
 namespace chorus {
 namespace {
@@ -216,30 +217,6 @@ __device__ __forceinline__ float key_score(uint64_t k) {
   return k == 0 ? -INFINITY : __uint_as_float((ord & 0x80000000u) ? (ord & 0x7fffffffu) : ~ord);
 }
 __device__ __forceinline__ int key_row(uint64_t k) { return k == 0 ? -1 : (int)~(uint32_t)k; }
-
-template <int CTRL>
-__device__ __forceinline__ uint32_t max_dpp(uint32_t k) {
-  const uint32_t o = __builtin_amdgcn_update_dpp(0, k, CTRL, 0xf, 0xf, false);
-  return o > k ? o : k;
-}
-// largest value of the wave, in every lane: four steps inside rows of 16 lanes (quad permutes, half-row and row mirror),
-// then the register-file swaps
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t k) {
-  k = max_dpp<0xB1>(k);
-  k = max_dpp<0x4E>(k);
-  k = max_dpp<0x141>(k);
-  k = max_dpp<0x140>(k);
-  uint32_t o = __float_as_uint(swap_rows16(__uint_as_float(k)));
-  k = o > k ? o : k;
-  o = __float_as_uint(swap_halves(__uint_as_float(k)));
-  return o > k ? o : k;
-}
-// largest key: the largest upper half, then the largest lower half beside it (two chains of one instruction a step; the
-// comparison of whole keys takes five)
-__device__ __forceinline__ uint64_t wave_max_key(uint64_t k) {
-  const uint32_t hi = wave_max_u32((uint32_t)(k >> 32));
-  return ((uint64_t)hi << 32) | wave_max_u32((uint32_t)(k >> 32) == hi ? (uint32_t)k : 0);
-}
 
 // The k <= 64 largest of the wave's keys (four per lane, all different but for 0), best first, one per lane (0 behind the
 // last). Few: a lane keeps its four sorted and offers its best, a round per position is one wave-wide maximum (two

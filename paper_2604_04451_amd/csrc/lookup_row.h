@@ -46,4 +46,29 @@ __device__ __forceinline__ float row_ratio(float dot, float cc) {
   return r;
 }
 
+// ---- the largest key of a wave
+template <int CTRL>
+__device__ __forceinline__ uint32_t max_dpp(uint32_t k) {
+  const uint32_t o = __builtin_amdgcn_update_dpp(0, k, CTRL, 0xf, 0xf, false);
+  return o > k ? o : k;
+}
+// largest value of the wave, in every lane: four steps inside rows of 16 lanes (quad permutes, half-row and row mirror),
+// then the register-file swaps
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t k) {
+  k = max_dpp<0xB1>(k);
+  k = max_dpp<0x4E>(k);
+  k = max_dpp<0x141>(k);
+  k = max_dpp<0x140>(k);
+  uint32_t o = __float_as_uint(swap_rows16(__uint_as_float(k)));
+  k = o > k ? o : k;
+  o = __float_as_uint(swap_halves(__uint_as_float(k)));
+  return o > k ? o : k;
+}
+// largest key: the largest upper half, then the largest lower half beside it (two chains of one instruction a step; the
+// comparison of whole keys takes five)
+__device__ __forceinline__ uint64_t wave_max_key(uint64_t k) {
+  const uint32_t hi = wave_max_u32((uint32_t)(k >> 32));
+  return ((uint64_t)hi << 32) | wave_max_u32((uint32_t)(k >> 32) == hi ? (uint32_t)k : 0);
+}
+
 }  // namespace chorus
