@@ -124,6 +124,17 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v + row_rotate<1>(v);
 }
 
+__device__ __forceinline__ int32_t wave_sum_i32(int32_t v) {
+  const auto h = __builtin_amdgcn_permlane32_swap((uint32_t)v, (uint32_t)v, false, false);
+  v = (int32_t)(h[0] + h[1]);
+  const auto r = __builtin_amdgcn_permlane16_swap((uint32_t)v, (uint32_t)v, false, false);
+  v = (int32_t)(r[0] + r[1]);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x122, 0xf, 0xf, false);
+  return v + __builtin_amdgcn_update_dpp(0, v, 0x121, 0xf, 0xf, false);
+}
+
 __device__ __forceinline__ float wave_max(float v) {
   const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   v = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));

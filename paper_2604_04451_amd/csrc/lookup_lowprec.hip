@@ -19,12 +19,19 @@ namespace {
 
 constexpr int kWaves = 4;            // waves per workgroup of the scan and of the re-rank
 constexpr int kMaxBlocks = 1024;     // workgroups of either: four on every compute unit; beyond that a wave takes several rows
+// workgroups of the scan over several rows a wave of 2 KB and more, see lp_scan_blocks
+constexpr int kScanBlocks = 512;
 constexpr int kMaxScanBlocks = 4096; // the workspace has room for this many: its size stays what callers hold
 
 inline long lp_blocks(long N) {
   long g = (N + kWaves - 1) / kWaves;
   return g < kMaxBlocks ? g : kMaxBlocks;
 }
+// Of the scan: a wave a row as far as that goes. Beyond it rows of 2 KB and more go to half as many waves, each with two rows
+// in flight: a wave's fp32 query is 16 KB through the L1 at d = 4096, as much as four of its FP8 rows (65536 x 4096 FP8 51.7
+// -> 48.9 us the call, 8192 x 4096 bf16 20.9 -> 19.4, 5000 x 4096 FP8 16.8 -> 14.6). Shorter rows want the loads in flight of
+// all waves (65536 x 768 FP8 23.3, with half as many 26.0).
+inline long lp_scan_blocks(long N, long row_bytes) { return N <= (long)kMaxBlocks * kWaves || row_bytes < 2048 ? lp_blocks(N) : kScanBlocks; }
 
 // Where the re-rank's workgroups leave what they found; the first workgroup of the scan resets it. A line each: when
 // every row is a candidate a thousand workgroups arrive, and atomics on one line are served one at a time (10 ns).
@@ -154,8 +161,8 @@ __device__ __forceinline__ void add_chunk(const u32x4& v, const float4* q, float
 }
 
 // One wave per row at a time. NC > 0: a row has at most 64 NC chunks of 16 bytes, and a lane keeps the query values of
-// its NC chunks (64 registers at d = 4096) for all its rows and has the next row's chunks in flight while it sums this
-// one. Read again for every row, the fp32 query is four times the bytes of an FP8 row, all through the L1, which is
+// its NC chunks (64 registers at d = 4096) for all its rows and has the next two rows' chunks in flight while it sums
+// this one. Read again for every row, the fp32 query is four times the bytes of an FP8 row, all through the L1, which is
 // what bound this kernel: 16384 x 4096 FP8 (67 MB) 23.8 us that way. NC = 0: any d, the query is read for every row; also the choice where a wave has only one.
 template <int FMT, int NC>
 __global__ __launch_bounds__(kWaves * 64) void lowprec_scan_kernel(const void* __restrict__ cache_lp,
@@ -179,7 +186,7 @@ __global__ __launch_bounds__(kWaves * 64) void lowprec_scan_kernel(const void* _
   };
   if constexpr (NC > 0) {
     float4 q[NC][E / 4];
-    u32x4 v[2][NC];
+    u32x4 v[3][NC];
     auto fetch = [&](u32x4 (&dst)[NC], long r) {
       const u32x4* c16 = reinterpret_cast<const u32x4*>(base + r * row_bytes);
 #pragma unroll
@@ -196,17 +203,18 @@ __global__ __launch_bounds__(kWaves * 64) void lowprec_scan_kernel(const void* _
       finish(r, dot, cc);
     };
     if (row < N) fetch(v[0], row);
+    if (row + stride < N) fetch(v[1], row + stride);
 #pragma unroll
     for (int c = 0; c < NC; ++c)
 #pragma unroll
       for (int e = 0; e < E / 4; ++e)
         q[c][e] = reinterpret_cast<const float4*>(query)[(lane + 64 * c < n16 ? lane + 64 * c : n16 - 1) * (E / 4) + e];
-    for (; row < N; row += 2 * stride) {  // two rows a turn: the buffers are named, not indexed
-      if (row + stride < N) fetch(v[1], row + stride);
-      sum(v[0], row);
-      if (row + stride < N) {
-        if (row + 2 * stride < N) fetch(v[0], row + 2 * stride);
-        sum(v[1], row + stride);
+    for (; row < N; row += 3 * stride) {  // three rows a turn: the buffers are named, not indexed
+#pragma unroll
+      for (int u = 0; u < 3; ++u) {
+        if (row + u * stride >= N) break;
+        if (row + (u + 2) * stride < N) fetch(v[(u + 2) % 3], row + (u + 2) * stride);
+        sum(v[u], row + u * stride);
       }
     }
   } else {
@@ -346,12 +354,8 @@ __global__ __launch_bounds__(64) void lowprec_final_kernel(const LpSlot* __restr
   unsigned long long key = N > 0 ? slots[threadIdx.x].best : 0;
   int32_t count = N > 0 ? slots[threadIdx.x].count : 0;
   const float nq = N > 0 ? sqrtf(*qnorm2) : 0.f;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long other = __shfl_xor(key, o, 64);
-    key = other > key ? other : key;
-    count += __shfl_xor(count, o, 64);
-  }
+  key = wave_max_key(key);
+  count = wave_sum_i32(count);
   if (threadIdx.x != 0) return;
   chorus_lookup_result r;
   if (N <= 0) {
@@ -436,14 +440,14 @@ int32_t chorus_cache_lookup_lowprec(const float* cache_emb, const void* cache_lp
   LpWs w = carve_lp((long)N, ws);
   hipStream_t s = (hipStream_t)stream;
   if (N > 0) {
-    const unsigned grid = (unsigned)lp_blocks((long)N);
+    const unsigned grid = (unsigned)lp_blocks((long)N), scan_grid = (unsigned)lp_scan_blocks((long)N, (long)d * (format == CHORUS_LP_BF16 ? 2 : 1));
     if (format == CHORUS_LP_BF16)
-      launch_lp_scan<CHORUS_LP_BF16>(cache_lp, query, (long)N, d, w, grid, s);
+      launch_lp_scan<CHORUS_LP_BF16>(cache_lp, query, (long)N, d, w, scan_grid, s);
     else
-      launch_lp_scan<CHORUS_LP_FP8>(cache_lp, query, (long)N, d, w, grid, s);
+      launch_lp_scan<CHORUS_LP_FP8>(cache_lp, query, (long)N, d, w, scan_grid, s);
     CHORUS_LAUNCH_CHECK();
     hipLaunchKernelGGL(lowprec_rerank_kernel, dim3(grid), dim3(kWaves * 64), 0, s, cache_emb, query, (long)N, d, w.scores,
-                       w.partial_max, (int)grid, w.qnorm2, (float)lowprec_margin(format, d), w.slots);
+                       w.partial_max, (int)scan_grid, w.qnorm2, (float)lowprec_margin(format, d), w.slots);
     CHORUS_LAUNCH_CHECK();
   }
   hipLaunchKernelGGL(lowprec_final_kernel, dim3(1), dim3(64), 0, s, w.slots, w.qnorm2, (long)N, tau, out, n_rescored);
