@@ -285,7 +285,9 @@ __device__ __forceinline__ uint64_t wave_topk(uint64_t (&key)[4], int k, int lan
 // lists the k best of them; the last workgroup of a query to arrive merges the lists. Lists and arrivals are
 // agent-scope atomics, as the workgroups of a query run on different XCDs, whose L2s are not coherent otherwise. With
 // the scores written out and one workgroup per query selecting from them (two launches): 23 us at 4096 x 32 queries,
-// k = 8, in this kernel 11.6; 20000 entries, 48 queries, k = 50 the whole call 538 -> 109 us.
+// k = 8, in this kernel 9.5; 20000 entries, 48 queries, k = 50 the whole call 538 -> 109 us. ONE is k = 1 (8192 x 64, 32 queries
+// 10.1 us the call, in two launches 12.0, through the lists 11.0).
+template <bool ONE>
 __global__ __launch_bounds__(256) void lookup_batch_select_kernel(const float* __restrict__ part_dot,
                                                                   const float* __restrict__ part_cc,
                                                                   const float* __restrict__ queries, uint64_t* lists,
@@ -312,6 +314,40 @@ __global__ __launch_bounds__(256) void lookup_batch_select_kernel(const float* _
     const long j = j0 + 256L * u;
     key[u] = j < N ? make_key(batch_score(dot[u], cc[u], qn), (uint32_t)j) : 0;
   }
+  // ONE: the best entry alone is a maximum, of the thread's entries, the wave's, the workgroup's, the query's.
+  if constexpr (ONE) {
+    uint64_t best = key[0] > key[1] ? key[0] : key[1];
+    best = key[2] > best ? key[2] : best;
+    best = key[3] > best ? key[3] : best;
+    best = wave_max_key(best);
+    if (lane == 0) sl[0][wave] = best;
+    __syncthreads();
+    if (wave != 0) return;
+    best = wave_max_key(sl[0][lane & 3]);
+    uint64_t* all = lists + (long)q * nb;
+    if (nb > 1) {
+      uint32_t arrived = 0;
+      if (lane == 0) {
+        __hip_atomic_store(&all[blockIdx.x], best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // as below
+        arrived = __hip_atomic_fetch_add(&done[q], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      if ((uint32_t)__builtin_amdgcn_readfirstlane((int)arrived) != (uint32_t)nb - 1) return;
+      asm volatile("" ::: "memory");
+      for (long i = lane; i < nb; i += 64) {
+        const uint64_t o = __hip_atomic_load(&all[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        best = o > best ? o : best;
+      }
+      best = wave_max_key(best);
+    }
+    if (lane == 0) {
+      const float sc = key_score(best);
+      out_idx[q] = key_row(best);
+      out_score[q] = sc;
+      out_hit[q] = (best != 0 && sc >= tau) ? 1 : 0;
+    }
+    return;
+  }
   // Every wave lists the k best of its 256 entries; with several row blocks the lists of a query meet in memory, one per
   // wave while the last workgroup can take them all in one go, else one per workgroup.
   uint64_t own = wave_topk(key, k, lane);
@@ -331,18 +367,15 @@ __global__ __launch_bounds__(256) void lookup_batch_select_kernel(const float* _
     const long at = per_wave ? (long)blockIdx.x * 4 + wave : (long)blockIdx.x;
     if (lane < k && (per_wave || wave == 0))
       __hip_atomic_store(&all[at * k + lane], own, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // Every wave waits for its own stores, the barrier joins them, and one wave releases for the workgroup: the release
-    // writes the XCD's L2 back, and with one per wave that cost 4 us of 16 at 4096 entries and 32 queries (20000
-    // entries, 48 queries, k = 50: the call 123 -> 109 us); row blocks of 512, twice as many releases, were slower for it.
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+    // Every wave waits for its own stores, the barrier joins them, one lane reports the arrival. The lists are agent-scope
+    // atomics, written and read past the L2s, so that once they have completed there is nothing to release: the fence that stood
+    // here wrote the XCD's whole L2 back (4096 entries, 32 queries, k = 8: this kernel 11.8 -> 9.5 us, the call 33.1 -> 30.7).
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (wave == 0) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      if (lane == 0) s_arrived = __hip_atomic_fetch_add(&done[q], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (tid == 0) s_arrived = __hip_atomic_fetch_add(&done[q], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (s_arrived != (uint32_t)nb - 1) return;
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    asm volatile("" ::: "memory");  // the lists are read behind the count
   } else {
     if (lane < k) sl[wave][lane] = own;
     __syncthreads();
@@ -410,7 +443,7 @@ __global__ __launch_bounds__(256) void lookup_batch_final_kernel(const float* __
   }
 }
 
-// k > 64, an empty cache, or a single round over many lists. One workgroup per query: k rounds over its final scores, each picking the best entry that comes after the
+// k > 64 or an empty cache. One workgroup per query: k rounds over its final scores, each picking the best entry that comes after the
 // previous winner in the order (score descending, index ascending). REG: the scores of a thread live in registers
 // (N <= kTopkRegs), else they are re-read from `scores`.
 constexpr long kTopkRegs = 8 * 1024;
@@ -420,86 +453,49 @@ __global__ __launch_bounds__(1024) void lookup_topk_kernel(const float* __restri
                                                            float* __restrict__ out_score, int32_t* __restrict__ out_hit) {
   constexpr int R = 8;
   static_assert(R * 1024 == kTopkRegs, "the scores that 1024 threads hold");
-  __shared__ float sv[2][16];
-  __shared__ int si[2][16];  // N < 2^31 entries per call
+  __shared__ uint64_t sk[2][16];
   const int q = blockIdx.x;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const float* sc = scores + (long)q * Npad;
-  float mine[R];
+  uint64_t mine[R];
 #pragma unroll
   for (int u = 0; u < R; ++u) {
     const long j = tid + 1024L * u;
-    mine[u] = (REG && j < N) ? sc[j] : -INFINITY;
+    mine[u] = (REG && j < N) ? make_key(sc[j], (uint32_t)j) : 0;
   }
-  unsigned taken = 0;  // REG: bit u set = this thread's entry u has been output
-  float ps = INFINITY;
-  int pj = -1;
+  uint64_t prev = ~0ull;
   for (int r = 0; r < k; ++r) {
-    float best = -INFINITY;
-    int bi = -1;
+    uint64_t best = 0;
     if (REG) {
 #pragma unroll
       for (int u = 0; u < R; ++u) {
-        const int j = tid + 1024 * u;
-        if (j < N && !(taken & (1u << u)) && (bi < 0 || mine[u] > best)) {
-          best = mine[u];
-          bi = j;
-        }
+        if (mine[u] == prev) mine[u] = 0;  // the previous winner
+        best = mine[u] > best ? mine[u] : best;
       }
     } else {
       for (long j = tid; j < N; j += 1024) {
-        const float v = sc[j];
-        const bool eligible = r == 0 || v < ps || (v == ps && j > pj);
-        if (eligible && (bi < 0 || v > best)) {  // ascending j: the first of equal values stays
-          best = v;
-          bi = (int)j;
-        }
+        const uint64_t key = make_key(sc[j], (uint32_t)j);
+        best = key < prev && key > best ? key : best;
       }
     }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      const float ob = __shfl_xor(best, o, 64);
-      const int oi = __shfl_xor(bi, o, 64);
-      if (oi >= 0 && (bi < 0 || ob > best || (ob == best && oi < bi))) {
-        best = ob;
-        bi = oi;
-      }
-    }
+    best = wave_max_key(best);
     const int buf = r & 1;  // alternating buffers: one barrier per round
-    if (lane == 0) {
-      sv[buf][wave] = best;
-      si[buf][wave] = bi;
-    }
+    if (lane == 0) sk[buf][wave] = best;
     __syncthreads();
-    // every wave reduces the 16 candidates again: lane w holds candidate w
-    float b = lane < 16 ? sv[buf][lane] : -INFINITY;
-    int i = lane < 16 ? si[buf][lane] : -1;
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) {
-      const float ob = __shfl_xor(b, o, 64);
-      const int oi = __shfl_xor(i, o, 64);
-      if (oi >= 0 && (i < 0 || ob > b || (ob == b && oi < i))) {
-        b = ob;
-        i = oi;
-      }
-    }
-    b = __shfl(b, 0, 64);
-    i = __shfl(i, 0, 64);
+    prev = wave_max_key(sk[buf][lane & 15]);  // every wave reduces the 16 candidates again
     if (tid == 0) {
-      out_idx[(long)q * k + r] = i;
-      out_score[(long)q * k + r] = i >= 0 ? b : -INFINITY;
-      if (r == 0) out_hit[q] = (i >= 0 && b >= tau) ? 1 : 0;
+      const float b = key_score(prev);
+      out_idx[(long)q * k + r] = key_row(prev);
+      out_score[(long)q * k + r] = b;
+      if (r == 0) out_hit[q] = (prev != 0 && b >= tau) ? 1 : 0;
     }
-    if (i < 0) {  // the cache is exhausted: the remaining positions are empty
+    if (prev == 0) {  // the cache is exhausted: the remaining positions are empty
       for (int rr = r + 1 + tid; rr < k; rr += 1024) {
         out_idx[(long)q * k + rr] = -1;
         out_score[(long)q * k + rr] = -INFINITY;
       }
       break;
     }
-    ps = b;
-    pj = i;
-    if (REG && (i & 1023) == tid) taken |= 1u << (unsigned)(i >> 10);
   }
 }
 
@@ -560,11 +556,7 @@ int32_t chorus_cache_lookup_batch(const float* cache_emb, int64_t N, int32_t d, 
     const float* qs = queries + (long)q0 * d;
     const long Npad = (long)p.tiles * kBR;
     const long nb = (N + 1023) / 1024;  // row blocks of the selection
-    // Selected where the scores are made, up to 64 of them. The best entry alone a pass of its own finds as fast while it keeps
-    // the scores in registers, and the release of every (row block, query) workgroup comes to more than that launch: k = 1, 768
-    // values, apart / together: 8192 entries, 32 queries 20.1 / 21.2 us, 16 queries 16.1 / 16.6, 12 queries 15.7 / 15.5; 4096
-    // entries, 32 queries 17.2 / 17.9, 24 queries 16.5 / 16.4; beyond 8192 entries 9000 x 64, 32 queries 14.5 / 13.6.
-    const bool lists_fit = k <= kWaveK && !(k == 1 && N <= kTopkRegs && nb * Qc > 100);
+    const bool lists_fit = k <= kWaveK;  // selected where the scores are made
     // the waves' lists take the place of the scores (128 bytes a row against at most 64 a row of a block), the arrival
     // counts stand behind them; a single row block needs neither
     uint64_t* lists = reinterpret_cast<uint64_t*>(w.scores);
@@ -579,9 +571,9 @@ int32_t chorus_cache_lookup_batch(const float* cache_emb, int64_t N, int32_t d, 
                            (long)N, d, Qc, p.chunks_per_slice, done);
       CHORUS_LAUNCH_CHECK();
       if (lists_fit) {
-        hipLaunchKernelGGL(lookup_batch_select_kernel, dim3((unsigned)nb, (unsigned)Qc), dim3(256), 0, s, w.part_dot, w.part_cc,
-                           qs, lists, done, (long)N, Npad, d, QP, p.KS, k, tau, out_index + (long)q0 * k,
-                           out_score + (long)q0 * k, out_hit + q0);
+        const auto select = k == 1 ? lookup_batch_select_kernel<true> : lookup_batch_select_kernel<false>;
+        hipLaunchKernelGGL(select, dim3((unsigned)nb, (unsigned)Qc), dim3(256), 0, s, w.part_dot, w.part_cc, qs, lists, done, (long)N,
+                           Npad, d, QP, p.KS, k, tau, out_index + (long)q0 * k, out_score + (long)q0 * k, out_hit + q0);
         CHORUS_LAUNCH_CHECK();
         continue;
       }
