@@ -31,12 +31,14 @@ __device__ __forceinline__ uint32_t nonzero_bits16(const uint8_t* __restrict__ m
 __device__ __forceinline__ int block_exclusive_scan(int v, int* total) {
   __shared__ int wsum[kCompactThreads / 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // in registers: within rows of 16 lanes, then the last lane of a row into the next one, and lane 31 into the upper half
   int inc = v;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    int t = __shfl_up(inc, o, 64);
-    if (lane >= o) inc += t;
-  }
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x111, 0xf, 0xf, false);
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x112, 0xf, 0xf, false);
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x114, 0xf, 0xf, false);
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x118, 0xf, 0xf, false);
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x142, 0xa, 0xf, false);
+  inc += __builtin_amdgcn_update_dpp(0, inc, 0x143, 0xc, 0xf, false);
   if (lane == 63) wsum[wave] = inc;
   __syncthreads();
   int off = 0, tot = 0;
@@ -132,8 +134,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_kernel(const uint8_t*
         before += __popc((((v[u][k] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | v[u][k]) & 0x80808080u);
     }
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) before += __shfl_xor(before, o, 64);
+  before = wave_sum_i32(before);
   if ((threadIdx.x & 63) == 0) s_before[threadIdx.x >> 6] = before;
   int total;
   int off = block_exclusive_scan(__popc(bits), &total);  // (its barrier covers s_before)
