@@ -226,7 +226,7 @@ def _chk(t, dtype, name, shape=None):
         raise TypeError(f"{name}: expected {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise TypeError(f"{name}: must be contiguous")
-    if shape is not None and tuple(t.shape) != tuple(shape):
+    if shape is not None and t.shape != shape and tuple(t.shape) != tuple(shape):  # a torch.Size is a tuple
         raise TypeError(f"{name}: expected shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
@@ -895,14 +895,25 @@ def chorus_mask_pooled_extent(n: int, k: int, lead: int = 0) -> int:
     return r
 
 
+def _pooled(n, k, lead):
+    """chorus_mask_pooled_extent, worked out here (a call into the library costs as much as all three) unless it is to refuse."""
+    return lead - (lead - n) // k if k > 0 and 0 <= lead <= n else chorus_mask_pooled_extent(n, k, lead)
+
+
+# Between them the mask calls' own Python took as long as their launches: with a generator, three library calls and a new
+# array type per call, masks -> hierarchy -> compaction of a 480p clip 21.0 us, now 20.0.
+_Radii = C.c_int32 * 3
+
+
 def chorus_mask_project(key_masks, frame_key, Tp, window, t_lead=0, out=None):
     """key_masks uint8 [Kf, Hp, Wp], frame_key int32 [Tp] or None -> uint8 [To, Ho, Wo]."""
     lib = load()
     _chk(key_masks, torch.uint8, "key_masks")
     _chk(frame_key, torch.int32, "frame_key", (Tp,))
     Kf, Hp, Wp = key_masks.shape
-    kt, kh, kw = (int(v) for v in window)
-    shape = (chorus_mask_pooled_extent(Tp, kt, t_lead), chorus_mask_pooled_extent(Hp, kh), chorus_mask_pooled_extent(Wp, kw))
+    kt, kh, kw = window
+    kt, kh, kw = int(kt), int(kh), int(kw)
+    shape = (_pooled(Tp, kt, t_lead), _pooled(Hp, kh, 0), _pooled(Wp, kw, 0))
     if out is None:
         out = torch.empty(shape, dtype=torch.uint8, device=key_masks.device)
     _chk(out, torch.uint8, "out", shape)
@@ -918,8 +929,8 @@ def chorus_mask_hierarchy(mask_base, r_edit, r_see, want_edit=True, want_see=Tru
     T, H, W = mask_base.shape
     edit = torch.empty_like(mask_base) if want_edit else None
     see = torch.empty_like(mask_base) if want_see else None
-    re = (C.c_int32 * 3)(*[int(v) for v in r_edit]) if r_edit is not None else None
-    rs = (C.c_int32 * 3)(*[int(v) for v in r_see])
+    re = _Radii(*map(int, r_edit)) if r_edit is not None else None
+    rs = _Radii(*map(int, r_see))
     _status("chorus_mask_hierarchy", lib.chorus_mask_hierarchy(_p(mask_base), T, H, W, re, rs, _p(edit), _p(see), _stream()))
     return edit, see
 
