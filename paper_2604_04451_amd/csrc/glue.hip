@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256) void unpatch_update_kernel(const float* __rest
 // ---------------------------------------------------------------------------
 // Patch embedding in one pass: x[token][n] = sum_k W[n][k] patch[token][k] + b[n], the fp32 patch split into a bf16
 // value and a bf16 remainder whose products share one fp32 accumulator. What it cannot do without is writing x once
-// (201 MB at 32760 x 1536); as a gather and two GEMMs it wrote x, read it and wrote it again: 153 us there, now 52 (streaming stores: 70).
+// (201 MB at 32760 x 1536); as a gather and two GEMMs it wrote x, read it and wrote it again: 153 us there, now 47 (streaming stores: 70).
 //
 // A workgroup takes 64 tokens and a range of columns. Its four waves gather the patches (lanes along tokens, so that a
 // wave reads 512 contiguous bytes per latent row) into LDS as [64][hi 64 | lo 64] bf16; each wave then holds all of it
@@ -212,31 +212,50 @@ __global__ __launch_bounds__(256) void patch_embed_kernel(const float* __restric
   for (int m = 0; m < 4; ++m)
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) a[m][ks] = *reinterpret_cast<const bf16x8*>(sp + (16 * m + lj) * kEmbedStride + 32 * ks + 8 * lg);
-  constexpr int NB = 2;  // 16-column blocks in flight
-  for (int n0 = n_begin + 16 * NB * wave; n0 < n_end; n0 += 64 * NB) {
-    bf16x8 w[NB][2];
-    f32x4 bv[NB];
+  constexpr int NB = 2;  // 16-column blocks at a time
+  // The weights of the next blocks are requested ahead of this block's stores: memory operations complete in order, so
+  // weights requested behind stores arrive when those have drained.
+  bf16x8 w[2][NB][2];
+  f32x4 bv[2][NB];
+  auto fetch = [&](int set, int n0) {
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
       const int n = n0 + 16 * b + lj < D ? n0 + 16 * b + lj : D - 1;
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) w[b][ks] = *reinterpret_cast<const bf16x8*>(W + (long)n * kEmbedP + 32 * ks + 8 * lg);
+      for (int ks = 0; ks < 2; ++ks) w[set][b][ks] = *reinterpret_cast<const bf16x8*>(W + (long)n * kEmbedP + 32 * ks + 8 * lg);
       const int nc = n0 + 16 * b + 4 * lg;  // the lane's four output columns: D % 8 == 0, in or out together
-      bv[b] = f32x4{0.f, 0.f, 0.f, 0.f};
-      if (bias && nc < D) bv[b] = *reinterpret_cast<const f32x4*>(bias + nc);
+      bv[set][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (bias && nc < D) bv[set][b] = *reinterpret_cast<const f32x4*>(bias + nc);
     }
+  };
+  auto block = [&](int set, int n0) {
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
-      const long tok = tok0 + 16 * m + lj;
+      f32x4 r[NB];
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b][ks & 1], a[m][ks], acc, 0, 0, 0);
+        for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[set][b][ks & 1], a[m][ks], acc, 0, 0, 0);
+        r[b] = acc + bv[set][b];
+      }
+      const long tok = tok0 + 16 * m + lj;
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
         const int nc = n0 + 16 * b + 4 * lg;
-        if (tok < Ls && nc < n_end) *reinterpret_cast<f32x4*>(x + tok * (long)D + nc) = acc + bv[b];
+        if (tok < Ls && nc < n_end) *reinterpret_cast<f32x4*>(x + tok * (long)D + nc) = r[b];
       }
     }
+  };
+  int n0 = n_begin + 16 * NB * wave;
+  if (n0 < n_end) fetch(0, n0);
+  for (; n0 < n_end; n0 += 2 * 64 * NB) {  // two turns: the sets are named, not indexed
+    const int n1 = n0 + 64 * NB;
+    if (n1 < n_end) fetch(1, n1);
+    block(0, n0);
+    if (n1 >= n_end) break;
+    if (n1 + 64 * NB < n_end) fetch(0, n1 + 64 * NB);
+    block(1, n1);
   }
 }
 
