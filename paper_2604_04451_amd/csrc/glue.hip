@@ -263,7 +263,7 @@ __global__ __launch_bounds__(256) void patch_embed_kernel(const float* __restric
 // Output head and sampler update in one pass over x: LayerNorm + modulation in fp32, one rounding to bf16, the product
 // with the head's weights, and the update of the tokens' latents, with the guided pass over x_uncond in the same
 // workgroup. What it cannot do without is reading x (and x_uncond) once (HBM-bound: 90 us for 402 MB at 32760 x 1536 with
-// guidance). Apart, the bf16 rows went to memory and back and v as well: 191 us; now 106.
+// guidance). Apart, the bf16 rows went to memory and back and v as well: 191 us; now 99.
 //
 // One workgroup of eight waves per compute unit walks over groups of 16 tokens with the head's weights in registers: a
 // wave holds all 64 columns over its eighth of D (96 registers at D = 1536). Read again for every 16 tokens they were
@@ -296,16 +296,14 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_update_kernel(const floa
   const int lj = lane & 15, lg = lane >> 4;
   const long ngroups = (Ls + kHeadTok - 1) / kHeadTok;
   f32x4 v[2][KS];
-  auto fetch = [&](const float* src, long group) {
+  auto fetch = [&](const float* src, long group, int r) {
+    const long tok = group * kHeadTok + 2 * wave + r < Ls ? group * kHeadTok + 2 * wave + r : Ls - 1;
+    const f32x4* row = reinterpret_cast<const f32x4*>(src + tok * (long)D);
 #pragma unroll
-    for (int r = 0; r < 2; ++r) {
-      const long tok = group * kHeadTok + 2 * wave + r < Ls ? group * kHeadTok + 2 * wave + r : Ls - 1;
-      const f32x4* row = reinterpret_cast<const f32x4*>(src + tok * (long)D);
-#pragma unroll
-      for (int i = 0; i < KS; ++i) v[r][i] = row[lane + 64 * i];
-    }
+    for (int i = 0; i < KS; ++i) v[r][i] = row[lane + 64 * i];
   };
-  fetch(x, blockIdx.x);
+  fetch(x, blockIdx.x, 0);
+  fetch(x, blockIdx.x, 1);
   bf16x8 w[4][KS];
 #pragma unroll
   for (int nb = 0; nb < 4; ++nb) {
@@ -328,43 +326,8 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_update_kernel(const floa
 #pragma unroll
     for (int pass = 0; pass < PASSES; ++pass) {
       const bool last = pass + 1 == PASSES;
-      float s[2], q[2];
-#pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        s[r] = 0.f;
-#pragma unroll
-        for (int i = 0; i < KS; ++i) s[r] += (v[r][i][0] + v[r][i][1]) + (v[r][i][2] + v[r][i][3]);
-      }
-#pragma unroll
-      for (int r = 0; r < 2; ++r) s[r] = wave_sum(s[r]);
-#pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        s[r] *= 1.0f / (float)D;  // the mean
-        q[r] = 0.f;
-#pragma unroll
-        for (int i = 0; i < KS; ++i) {
-          const float a = v[r][i][0] - s[r], b = v[r][i][1] - s[r], c = v[r][i][2] - s[r], d = v[r][i][3] - s[r];
-          q[r] += (a * a + b * b) + (c * c + d * d);
-        }
-      }
-#pragma unroll
-      for (int r = 0; r < 2; ++r) q[r] = wave_sum(q[r]);
-      q[0] = rsqrtf(q[0] * (1.0f / (float)D) + 1e-6f);
-      q[1] = rsqrtf(q[1] * (1.0f / (float)D) + 1e-6f);
-#pragma unroll
-      for (int i = 0; i < KS; ++i) {
-        const f32x4 mu = reinterpret_cast<const f32x4*>(s_mul)[lane + 64 * i];
-        const f32x4 ad = reinterpret_cast<const f32x4*>(s_add)[lane + 64 * i];
-#pragma unroll
-        for (int r = 0; r < 2; ++r) {
-          float y[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = (v[r][i][e] - s[r]) * q[r] * mu[e] + ad[e];
-          *reinterpret_cast<uint2*>(s_h + (2 * wave + r) * HS + 4 * (lane + 64 * i)) =
-              make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
-        }
-      }
-      // requests, in the order in which they are needed: the latents of this group, the rows of the next one
+      // requests, in the order in which they are needed: the latents of this group, then each of the next rows as soon as this
+      // one's registers are free (with both rows requested behind the second one nothing was in flight while they were normalised)
       typename U::template Cell<2> mine;
       int mine_o = 0;  // 32 bits: the widest variant is at the register limit
       if (last && one_each) {
@@ -373,10 +336,34 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_update_kernel(const floa
         mine_o = (int)(g.cell(n, my_ch) + (long)my_dy * g.Wl);
         upd.load(mine, n, mine_o);
       }
-      if (!last)
-        fetch(xu, group);
-      else if (group + gridDim.x < ngroups)
-        fetch(x, group + gridDim.x);
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        float s = 0.f, q = 0.f;
+#pragma unroll
+        for (int i = 0; i < KS; ++i) s += (v[r][i][0] + v[r][i][1]) + (v[r][i][2] + v[r][i][3]);
+        s = wave_sum(s) * (1.0f / (float)D);  // the mean
+#pragma unroll
+        for (int i = 0; i < KS; ++i) {
+          const float a = v[r][i][0] - s, b = v[r][i][1] - s, c = v[r][i][2] - s, d = v[r][i][3] - s;
+          q += (a * a + b * b) + (c * c + d * d);
+        }
+        q = rsqrtf(wave_sum(q) * (1.0f / (float)D) + 1e-6f);
+#pragma unroll
+        for (int i = 0; i < KS; ++i) {
+          const f32x4 mu = reinterpret_cast<const f32x4*>(s_mul)[lane + 64 * i];
+          const f32x4 ad = reinterpret_cast<const f32x4*>(s_add)[lane + 64 * i];
+          float y[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = (v[r][i][e] - s) * q * mu[e] + ad[e];
+          *reinterpret_cast<uint2*>(s_h + (2 * wave + r) * HS + 4 * (lane + 64 * i)) =
+              make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+        }
+        if (!last)
+          fetch(xu, group, r);
+        else if (group + gridDim.x < ngroups)
+          fetch(x, group + gridDim.x, r);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       lds_barrier();  // the 16 rows are in LDS, and the previous partial v have been read
       f32x4 acc[4];
 #pragma unroll
