@@ -205,9 +205,13 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
     ProfScope p(CHORUS_PROF_NORM, s);
     CHK(chorus_ln_modulate(x, b.h, Ls, D, row(tab, 1), row(t_mod, 1), row(tab, 0), row(t_mod, 0), 1, stream));
   }
+  // without a cached projection the text's keys and values are projected and prepared beside the tokens'
   {
     ProfScope p(CHORUS_PROF_GEMM, s);
-    CHK(chorus_gemm_bf16(b.h, w->w_qkv, Ls, 3 * D, D, CHORUS_EPI_BF16, b.qkv, w->b_qkv, nullptr, nullptr, 1.f, stream));
+    if (text_kv)
+      CHK(chorus_gemm_bf16(b.h, w->w_qkv, Ls, 3 * D, D, CHORUS_EPI_BF16, b.qkv, w->b_qkv, nullptr, nullptr, 1.f, stream));
+    else
+      CHK(gemm_bf16_two(b.h, w->w_qkv, Ls, 3 * D, D, b.qkv, w->b_qkv, text_ctx, w->w_ckv, Lt, 2 * D, b.tkv, w->b_ckv, stream));
   }
   // 2-3. q/k RMSNorm + RoPE into head-major layout; V into key-contiguous layout.
   // Attention over 512 keys or more takes its queries already multiplied by log2(e) / sqrt(dh): the factor enters here, in
@@ -216,8 +220,10 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   {
     ProfScope p(CHORUS_PROF_NORM, s);
     if (!w->g_q || !w->g_k || !aligned16(w->g_q) || !aligned16(w->g_k)) return CHORUS_E_ARG;
+    if (!text_kv && (!w->g_ck || !aligned16(w->g_ck))) return CHORUS_E_ARG;
+    const PrepareText text{b.tkv, b.tkv + D, 2L * D, w->g_ck, b.kc, b.vct, Lt, LtPad};
     CHK(attn_prepare(b.qkv, b.qkv + D, b.qkv + 2 * D, 3L * D, w->g_q, w->g_k, b.qh, b.kh, b.vt, Ls, Lpad, H, dh, token_idx, sh.gH,
-                     sh.gW, 1, q_prescaled ? CHORUS_ATTENTION_Q_PRESCALE(dh) : 1.0f, stream));
+                     sh.gW, 1, q_prescaled ? CHORUS_ATTENTION_Q_PRESCALE(dh) : 1.0f, stream, text_kv ? nullptr : &text));
   }
   // 4. self-attention over exactly the Ls rows, output projection, gated residual
   {
@@ -242,8 +248,6 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   if (text_kv) {
     kc = text_kv;
     vct = text_kv + text_kv_half_bytes(sh) / 2;
-  } else {
-    CHK(project_text_kv(sh, w, text_ctx, b.tkv, b.kc, b.vct, stream));
   }
   // pre-scaled queries as above
   const bool cq_prescaled = CHORUS_ATTENTION_LONG_KEYS(Lt, LtPad);

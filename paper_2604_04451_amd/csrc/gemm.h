@@ -20,4 +20,9 @@ int32_t gemm_bf16_parts(const uint16_t* A, const uint16_t* W, int64_t M, int32_t
                         const float* bias, const float* gate0, const float* gate1, float scale, const GemmParts& parts,
                         void* stream);
 
+// out = A W^T + bias and out2 = A2 W2^T + bias2, bf16, the same K: in one launch where that does not fill the chip
+int32_t gemm_bf16_two(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, uint16_t* out, const float* bias,
+                      const uint16_t* A2, const uint16_t* W2, int64_t M2, int32_t N2, uint16_t* out2, const float* bias2,
+                      void* stream);
+
 }  // namespace chorus

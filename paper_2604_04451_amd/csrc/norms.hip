@@ -2,6 +2,8 @@
 //  - LayerNorm + AdaLN modulation / affine, fp32 residual stream -> bf16 GEMM operand
 //  - RMSNorm over the full width + 3-D RoPE, token-major bf16 -> head-major bf16
 //  - V transpose into the key-contiguous layout the attention kernel reads
+#include <type_traits>
+
 #include "chorus_ops.h"
 #include "common.h"
 #include "norms.h"
@@ -10,6 +12,8 @@ namespace chorus {
 namespace {
 
 constexpr float kEps = 1e-6f;
+
+struct NoText {};  // the preparation of the tokens alone
 
 // One wave per row. NV > 0: D == NV*256 and the row lives in registers (one HBM
 // read). NV == 0: any D % 4 == 0, the row is re-read from cache for each pass.
@@ -272,28 +276,47 @@ __global__ __launch_bounds__(256) void v_transpose_kernel(const uint16_t* __rest
 // took longer to start than to run (128 tokens of width 256: 3.6 + 3.6 + 2.8 us and two gaps). A wave that did both rows
 // of a token, for one set of angles, held twice the registers (width 5120, 75600 tokens: 957 us against 897 of the three
 // launches) and was the longer chain where the chip is not filled (block of 128 tokens 69.7 us, now 68.9).
-template <int NCH>
+template <int NCH, class TEXT>
 __global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                            const uint16_t* __restrict__ v, long ld,
                                                            const float* __restrict__ gain_q, const float* __restrict__ gain_k,
                                                            uint16_t* __restrict__ qh, uint16_t* __restrict__ kh,
                                                            uint16_t* __restrict__ vt, long L, long Lpad, int H, int dh,
                                                            const int* __restrict__ token_idx, int gH, int gW, int rope,
-                                                           float q_scale, int row_blocks, int v_tiles) {
+                                                           float q_scale, int row_blocks, int v_tiles, int first2,
+                                                           TEXT text) {
   __shared__ union {
     struct {
       float cos[4][64], sin[4][64];
     } rot;
     uint16_t tile[64][64 + 2];
   } sm;
-  if ((int)blockIdx.x >= row_blocks) {
-    const int b = blockIdx.x - row_blocks;
+  int block = blockIdx.x;
+  if constexpr (std::is_same_v<TEXT, PrepareText>) {
+    if (block >= first2) {  // the workgroups behind the tokens': the text
+      block -= first2;
+      q = nullptr;
+      k = text.k;
+      v = text.v;
+      ld = text.ld;
+      gain_k = text.gain_k;
+      kh = text.kh;
+      vt = text.vt;
+      L = text.L;
+      Lpad = text.Lpad;
+      rope = 0;
+      row_blocks = (int)((text.Lpad + 3) / 4);
+      v_tiles = (int)(text.Lpad / 64);
+    }
+  }
+  if (block >= row_blocks) {
+    const int b = block - row_blocks;
     transpose_tile(sm.tile, v, ld, vt, L, Lpad, (long)(b % v_tiles) * 64, b / v_tiles * 64);
     return;
   }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, D = H * dh;
-  const bool of_q = q && !(blockIdx.x & 1);
-  const long row = (long)(q ? blockIdx.x >> 1 : blockIdx.x) * 4 + wave;
+  const bool of_q = q && !(block & 1);
+  const long row = (long)(q ? block >> 1 : block) * 4 + wave;
   if (row >= Lpad) return;
   uint16_t* out = of_q ? qh : kh;
   if (row >= L) {
@@ -312,17 +335,27 @@ __global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __res
 
 int32_t attn_prepare(const uint16_t* q, const uint16_t* k, const uint16_t* v, long ld, const float* gain_q, const float* gain_k,
                      uint16_t* qh, uint16_t* kh, uint16_t* vt, long L, long Lpad, int H, int dh, const int32_t* token_idx, int gH,
-                     int gW, int rope, float q_scale, void* stream) {
+                     int gW, int rope, float q_scale, void* stream, const PrepareText* text) {
   const int D = H * dh;
-  const long row_blocks = (Lpad + 3) / 4 * (q ? 2 : 1), v_tiles = Lpad / 64, blocks = row_blocks + v_tiles * (D / 64);
+  const long row_blocks = (Lpad + 3) / 4 * (q ? 2 : 1), v_tiles = Lpad / 64, first2 = row_blocks + v_tiles * (D / 64);
+  const long blocks = first2 + (text ? (text->Lpad + 3) / 4 + text->Lpad / 64 * (D / 64) : 0);
   if (blocks > 0x7fffffffL) return CHORUS_E_SHAPE;
-#define PREPARE(NCH)                                                                                                       \
-  hipLaunchKernelGGL(attn_prepare_kernel<NCH>, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, q, k, v, ld, gain_q, \
-                     gain_k, qh, kh, vt, L, Lpad, H, dh, token_idx, gH, gW, rope, q_scale, (int)row_blocks, (int)v_tiles)
+#define PREPARE_AS(NCH, TEXT, text)                                                                                           \
+  hipLaunchKernelGGL((attn_prepare_kernel<NCH, TEXT>), dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, q, k, v, ld,  \
+                     gain_q, gain_k, qh, kh, vt, L, Lpad, H, dh, token_idx, gH, gW, rope, q_scale, (int)row_blocks, (int)v_tiles, \
+                     (int)first2, text)
+#define PREPARE(NCH)                           \
+  do {                                         \
+    if (text)                                  \
+      PREPARE_AS(NCH, PrepareText, *text);     \
+    else                                       \
+      PREPARE_AS(NCH, NoText, NoText{});       \
+  } while (0)
   if (D == 1536) PREPARE(3);
   else if (D == 5120) PREPARE(10);
   else if (D == 512) PREPARE(1);
   else PREPARE(0);
+#undef PREPARE_AS
 #undef PREPARE
   CHORUS_LAUNCH_CHECK();
   return CHORUS_OK;
