@@ -600,7 +600,9 @@ double tile_time(int tile, long m, int N, int K, int epi, int slices) {
     case kTile128: {
       const double one = by_epilogue(1.71, 3.67, 4.97) + 0.74 * steps, round512 = by_epilogue(0.48, 0.57, 5.67) + 1.001 * steps;
       if (w <= 256.0) return one;
-      if (w <= 512.0) return one + (fill - 1.0) * fmax(round512 - one, 0.0);
+      // with bf16 outputs half as many second workgroups cost the whole of it (1200 x 4608 x 1536, 360 tiles: 27.0 us, 128 x 256 24.3)
+      const double second = f32 || epi == CHORUS_EPI_RESID ? fill - 1.0 : fmin(2.0 * (fill - 1.0), 1.0);
+      if (w <= 512.0) return one + second * fmax(round512 - one, 0.0);
       return (0.784 * ceil(w / 512.0) + 0.216 * w / 512.0) * round512;
     }
     case kTile128Deep: {
