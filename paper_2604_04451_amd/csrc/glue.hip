@@ -5,6 +5,7 @@
 // step written as the Euler update, chorus_head_update_solver the multistep form with
 // classifier-free guidance and the latent fusion of Eq. 6 folded into the same pass.
 #include <cmath>
+#include <type_traits>
 
 #include "chorus_ops.h"
 #include "common.h"
@@ -336,33 +337,54 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_update_kernel(const floa
         mine_o = (int)(g.cell(n, my_ch) + (long)my_dy * g.Wl);
         upd.load(mine, n, mine_o);
       }
+      auto normalise = [&](auto first, auto end) {
+        float s[2], q[2];
 #pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        float s = 0.f, q = 0.f;
+        for (int r = first; r < end; ++r) {
+          s[r] = 0.f;
 #pragma unroll
-        for (int i = 0; i < KS; ++i) s += (v[r][i][0] + v[r][i][1]) + (v[r][i][2] + v[r][i][3]);
-        s = wave_sum(s) * (1.0f / (float)D);  // the mean
-#pragma unroll
-        for (int i = 0; i < KS; ++i) {
-          const float a = v[r][i][0] - s, b = v[r][i][1] - s, c = v[r][i][2] - s, d = v[r][i][3] - s;
-          q += (a * a + b * b) + (c * c + d * d);
+          for (int i = 0; i < KS; ++i) s[r] += (v[r][i][0] + v[r][i][1]) + (v[r][i][2] + v[r][i][3]);
         }
-        q = rsqrtf(wave_sum(q) * (1.0f / (float)D) + 1e-6f);
+#pragma unroll
+        for (int r = first; r < end; ++r) s[r] = wave_sum(s[r]) * (1.0f / (float)D);  // the mean
+#pragma unroll
+        for (int r = first; r < end; ++r) {
+          q[r] = 0.f;
+#pragma unroll
+          for (int i = 0; i < KS; ++i) {
+            const float a = v[r][i][0] - s[r], b = v[r][i][1] - s[r], c = v[r][i][2] - s[r], d = v[r][i][3] - s[r];
+            q[r] += (a * a + b * b) + (c * c + d * d);
+          }
+        }
+#pragma unroll
+        for (int r = first; r < end; ++r) q[r] = rsqrtf(wave_sum(q[r]) * (1.0f / (float)D) + 1e-6f);
 #pragma unroll
         for (int i = 0; i < KS; ++i) {
           const f32x4 mu = reinterpret_cast<const f32x4*>(s_mul)[lane + 64 * i];
           const f32x4 ad = reinterpret_cast<const f32x4*>(s_add)[lane + 64 * i];
-          float y[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = (v[r][i][e] - s) * q * mu[e] + ad[e];
-          *reinterpret_cast<uint2*>(s_h + (2 * wave + r) * HS + 4 * (lane + 64 * i)) =
-              make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+          for (int r = first; r < end; ++r) {
+            float y[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) y[e] = (v[r][i][e] - s[r]) * q[r] * mu[e] + ad[e];
+            *reinterpret_cast<uint2*>(s_h + (2 * wave + r) * HS + 4 * (lane + 64 * i)) =
+                make_uint2(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]));
+          }
         }
-        if (!last)
-          fetch(xu, group, r);
-        else if (group + gridDim.x < ngroups)
-          fetch(x, group + gridDim.x, r);
+      };
+      using R0 = std::integral_constant<int, 0>;
+      using R1 = std::integral_constant<int, 1>;
+      using R2 = std::integral_constant<int, 2>;
+      const float* next = !last ? xu : group + gridDim.x < ngroups ? x : nullptr;
+      if (next) {
+        const long next_group = last ? group + gridDim.x : group;
+        normalise(R0{}, R1{});
+        fetch(next, next_group, 0);
         __builtin_amdgcn_sched_barrier(0);
+        normalise(R1{}, R2{});
+        fetch(next, next_group, 1);
+      } else {
+        normalise(R0{}, R2{});  // nothing to request: both rows' chains together (98 tokens 19.3 -> 19.1 us with the embedding)
       }
       lds_barrier();  // the 16 rows are in LDS, and the previous partial v have been read
       f32x4 acc[4];
