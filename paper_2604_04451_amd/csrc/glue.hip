@@ -264,7 +264,7 @@ __global__ __launch_bounds__(256) void patch_embed_kernel(const float* __restric
 // Output head and sampler update in one pass over x: LayerNorm + modulation in fp32, one rounding to bf16, the product
 // with the head's weights, and the update of the tokens' latents, with the guided pass over x_uncond in the same
 // workgroup. What it cannot do without is reading x (and x_uncond) once (HBM-bound: 90 us for 402 MB at 32760 x 1536 with
-// guidance). Apart, the bf16 rows went to memory and back and v as well: 191 us; now 99.
+// guidance). Apart, the bf16 rows went to memory and back and v as well: 191 us; now 100.
 //
 // One workgroup of eight waves per compute unit walks over groups of 16 tokens with the head's weights in registers: a
 // wave holds all 64 columns over its eighth of D (96 registers at D = 1536). Read again for every 16 tokens they were
@@ -384,7 +384,9 @@ __global__ __launch_bounds__(kHeadThreads, 2) void head_update_kernel(const floa
         normalise(R1{}, R2{});
         fetch(next, next_group, 1);
       } else {
-        normalise(R0{}, R2{});  // nothing to request: both rows' chains together (98 tokens 19.3 -> 19.1 us with the embedding)
+        // nothing to request: both rows' chains together (embedding and head: 98 tokens 19.3 -> 18.8 us, 32760 without
+        // guidance 105.6 -> 102.4, with guidance 151.0 -> 153.0)
+        normalise(R0{}, R2{});
       }
       lds_barrier();  // the 16 rows are in LDS, and the previous partial v have been read
       f32x4 acc[4];

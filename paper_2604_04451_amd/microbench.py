@@ -61,7 +61,7 @@ def main():
     out = torch.empty(3, dtype=torch.int32, device=DEV)
     ws = torch.empty(1 << 16, dtype=torch.uint8, device=DEV)
     med, best = timeit(lambda i: B.chorus_cache_lookup(caches[i % 10], q, 0.75, out, ws), n)
-    report("cache_lookup 4096x4096 fp32 (2 launches)", N * d * 4 + d * 4, med, best)
+    report("cache_lookup 4096x4096 fp32 (1 launch)", N * d * 4 + d * 4, med, best)
     # the same scan for a batch of queries with top-8 candidates each (the cache is streamed once per 32 queries)
     for Q in (1, 16, 32):
         qs = torch.randn(Q, d, device=DEV, generator=g)
