@@ -421,6 +421,16 @@ int32_t chorus_mask_project(const uint8_t* key_masks, int32_t Kf, const int32_t*
 int32_t chorus_mask_hierarchy(const uint8_t* mask_base, int32_t T, int32_t H, int32_t W, const int32_t r_edit[3],
                               const int32_t r_see[3], uint8_t* mask_edit, uint8_t* mask_see, void* stream);
 
+/* How chorus_mask_hierarchy runs a grid, host only, for tests: the radii its kernels are given (cut at the grid, which does not
+ * change the result), the rows of a strip, the number of strips a frame and the LDS of a workgroup; strip 0 where rows are too
+ * wide for that and every site looks through its box. Refuses what the call refuses, an empty grid and r_edit == NULL. */
+typedef struct {
+  int32_t r_edit[3], r_see[3];
+  int32_t strip, nstrips, lds_bytes;
+} chorus_hierarchy_plan;
+int32_t chorus_mask_hierarchy_plan(int32_t T, int32_t H, int32_t W, const int32_t r_edit[3], const int32_t r_see[3],
+                                   chorus_hierarchy_plan* out);
+
 /* ------------------------------------------------------------------------
  * Per-kernel timing for benchmarks. chorus_prof_enable takes a bit mask of kernel
  * classes (bit c = class c; 0 = off, the default). For the enabled classes

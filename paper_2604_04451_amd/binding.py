@@ -83,6 +83,11 @@ class GemmPlan(C.Structure):
     _fields_ = [("head_rows", C.c_int64), ("kernel", C.c_int32), ("slices", C.c_int32)]
 
 
+class HierarchyPlan(C.Structure):
+    _fields_ = [("r_edit", C.c_int32 * 3), ("r_see", C.c_int32 * 3), ("strip", C.c_int32), ("nstrips", C.c_int32),
+                ("lds_bytes", C.c_int32)]
+
+
 class RunResult(C.Structure):
     _fields_ = [("index", C.c_int32), ("score", C.c_float), ("hit", C.c_int32), ("K1", C.c_int32),
                 ("K2", C.c_int32), ("Ls", C.c_int32)]
@@ -186,6 +191,7 @@ def _bind_ops(lib):
         "chorus_mask_pooled_extent": (i32, [i32, i32, i32]),
         "chorus_mask_project": (i32, [vp, i32, vp, i32, i32, i32, i32, i32, i32, i32, vp, vp]),
         "chorus_mask_hierarchy": (i32, [vp, i32, i32, i32, C.POINTER(i32), C.POINTER(i32), vp, vp, vp]),
+        "chorus_mask_hierarchy_plan": (i32, [i32, i32, i32, C.POINTER(i32), C.POINTER(i32), C.POINTER(HierarchyPlan)]),
         "chorus_time_mod_workspace_bytes": (sz, [i32, i32]),
         "chorus_time_mod": (i32, [f32, i32, i32, C.POINTER(TimeWeights), vp, vp, vp, sz, vp]),
         "chorus_mfma_ceiling_workspace_bytes": (sz, []),
@@ -933,6 +939,13 @@ def chorus_mask_hierarchy(mask_base, r_edit, r_see, want_edit=True, want_see=Tru
     rs = _Radii(*map(int, r_see))
     _status("chorus_mask_hierarchy", lib.chorus_mask_hierarchy(_p(mask_base), T, H, W, re, rs, _p(edit), _p(see), _stream()))
     return edit, see
+
+
+def chorus_mask_hierarchy_plan(T, H, W, r_edit, r_see):
+    """(r_edit and r_see as the kernels get them, rows of a strip, strips a frame, LDS bytes); host only."""
+    p = HierarchyPlan()
+    _status("chorus_mask_hierarchy_plan", load().chorus_mask_hierarchy_plan(T, H, W, _Radii(*r_edit), _Radii(*r_see), C.byref(p)))
+    return tuple(p.r_edit), tuple(p.r_see), p.strip, p.nstrips, p.lds_bytes
 
 
 def chorus_denoise_run_workspace_bytes(model: ModelShape, N: int) -> int:

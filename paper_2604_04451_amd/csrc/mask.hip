@@ -2,6 +2,7 @@
 // fused with the max-pool projection onto the latent / token grid, and the two box
 // dilations that give M_edit and M_see. Byte masks, any non-zero byte is "set",
 // outputs are 0/1. Integer work: results are exact.
+#include "chorus_ops.h"
 #include "common.h"
 
 namespace chorus {
@@ -93,8 +94,8 @@ __global__ __launch_bounds__(kProjThreads) void mask_project_kernel(const uint8_
 
 // Eq. 5 with box kernels is separable, and a row of sites is a row of bits. One workgroup per (frame t, strip of rows): a wave
 // takes a row of the strip or of its r_see rows of halo, 64 sites at a time, ORs them over the time window and leaves the
-// ballot in LDS; a thread per 64 sites of an output row then ORs the rows of the window along y and their bits shifted by up
-// to the radius along x, for both radii; the bits leave as bytes. Sites beyond the grid count as 0. (On bytes throughout, each
+// ballot in LDS; a thread per 64 sites then ORs a row's bits shifted by up to the radius along x, then another the rows of
+// the window along y, for both radii; the bits leave as bytes. Sites beyond the grid count as 0. (On bytes throughout, each
 // step a loop over a neighbourhood in LDS, 6.4 us at 21 x 30 x 52, now 5.4.)
 constexpr int kHierThreads = 256;
 constexpr int kHierLdsBytes = 48 * 1024;
@@ -219,6 +220,35 @@ __global__ __launch_bounds__(256) void mask_hierarchy_kernel(const uint8_t* __re
   if (see) see[i] = any_see ? 1 : 0;
 }
 
+// The radii that the kernels are given are cut at the grid: a radius of n - 1 reaches every one of n sites, so a larger one (a
+// caller's "everything") has the same result; the kernels' loops then take at most 2 n - 1 steps and their sums stay in 32 bits.
+// Strips of rows: enough workgroups to spread over the chip, each strip with its r_see halo within the LDS budget (two
+// sets of bits per row held, before and after the pass along x, and one per row of the strip); strip 0: the rows do not fit,
+// the kernel that takes a site at a time.
+chorus_hierarchy_plan plan_hierarchy(int T, int H, int W, const int32_t* r_edit, const int32_t* r_see) {
+  chorus_hierarchy_plan p{};
+  const int n[3] = {T, H, W};
+  for (int a = 0; a < 3; ++a) {
+    p.r_edit[a] = r_edit[a] < n[a] ? r_edit[a] : n[a] - 1;
+    p.r_see[a] = r_see[a] < n[a] ? r_see[a] : n[a] - 1;
+  }
+  const long halo = 2L * p.r_see[1], word = ((long)W + 63) / 64 * 8;
+  auto lds = [&](long strip) { return (4 * (strip + halo < H ? strip + halo : (long)H) + 2 * strip) * word; };
+  int nstrips = (128 + T - 1) / T;
+  if (nstrips > H) nstrips = H;
+  long strip = (H + nstrips - 1) / nstrips;
+  if (lds(strip) > kHierLdsBytes) {
+    const long cut = (kHierLdsBytes / word - 4 * halo) / 6, whole = (kHierLdsBytes / word - 4L * H) / 2;
+    const long fit = cut > whole ? cut : whole;  // the halo's rows beyond the strip's own, or every row of the grid
+    strip = fit < strip ? fit : strip;
+  }
+  if (strip < 1) return p;
+  p.strip = (int)strip;
+  p.nstrips = (int)((H + strip - 1) / strip);
+  p.lds_bytes = (int)lds(strip);
+  return p;
+}
+
 }  // namespace chorus
 
 using namespace chorus;
@@ -263,25 +293,25 @@ int32_t chorus_mask_hierarchy(const uint8_t* mask_base, int32_t T, int32_t H, in
   if (mask_base == mask_edit || mask_base == mask_see) return CHORUS_E_ARG;  // every site reads its neighbours
   if (n > 0x7fffffffLL - 256) return CHORUS_E_SHAPE;
   hipStream_t s = (hipStream_t)stream;
-  // strips of rows: enough workgroups to spread over the chip, each strip with its r_see halo within the LDS budget (two
-  // sets of bits per row held, before and after the pass along x, and one per row of the strip)
-  const long halo = 2L * (r_see[1] < H ? r_see[1] : H), word = ((long)W + 63) / 64 * 8;
-  const long rows_fit = (kHierLdsBytes / word - 4 * halo) / 6;
-  if (rows_fit >= 1) {
-    int nstrips = (128 + T - 1) / T;
-    if (nstrips > H) nstrips = H;
-    if (nstrips < 1) nstrips = 1;
-    int strip = (H + nstrips - 1) / nstrips;
-    if (strip > rows_fit) strip = (int)rows_fit;
-    nstrips = (H + strip - 1) / strip;
-    const size_t lds = (size_t)((4 * (strip + halo) + 2 * strip) * word);
-    hipLaunchKernelGGL(mask_hierarchy_lds_kernel, dim3((unsigned)((long)T * nstrips)), dim3(kHierThreads), lds, s, mask_base,
-                       T, H, W, re[0], re[1], re[2], r_see[0], r_see[1], r_see[2], strip, nstrips, mask_edit, mask_see);
-  } else {
-    hipLaunchKernelGGL(mask_hierarchy_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, mask_base, T, H, W, re[0],
-                       re[1], re[2], r_see[0], r_see[1], r_see[2], mask_edit, mask_see);
-  }
+  const chorus_hierarchy_plan p = plan_hierarchy(T, H, W, re, r_see);
+  if (p.strip > 0)
+    hipLaunchKernelGGL(mask_hierarchy_lds_kernel, dim3((unsigned)((long)T * p.nstrips)), dim3(kHierThreads), (size_t)p.lds_bytes, s,
+                       mask_base, T, H, W, p.r_edit[0], p.r_edit[1], p.r_edit[2], p.r_see[0], p.r_see[1], p.r_see[2], p.strip,
+                       p.nstrips, mask_edit, mask_see);
+  else
+    hipLaunchKernelGGL(mask_hierarchy_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, mask_base, T, H, W, p.r_edit[0],
+                       p.r_edit[1], p.r_edit[2], p.r_see[0], p.r_see[1], p.r_see[2], mask_edit, mask_see);
   CHORUS_LAUNCH_CHECK();
+  return CHORUS_OK;
+}
+
+int32_t chorus_mask_hierarchy_plan(int32_t T, int32_t H, int32_t W, const int32_t r_edit[3], const int32_t r_see[3],
+                                   chorus_hierarchy_plan* out) {
+  if (T < 1 || H < 1 || W < 1 || !r_edit || !r_see || !out) return CHORUS_E_ARG;
+  for (int a = 0; a < 3; ++a)
+    if (r_edit[a] < 0 || r_see[a] < r_edit[a]) return CHORUS_E_ARG;
+  if ((int64_t)T * H > 0x7fffffffLL || (int64_t)T * H * W > 0x7fffffffLL - 256) return CHORUS_E_SHAPE;
+  *out = plan_hierarchy(T, H, W, r_edit, r_see);
   return CHORUS_OK;
 }
 

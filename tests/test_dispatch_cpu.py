@@ -89,3 +89,30 @@ def test_gemm_plan_refuses():
     assert lib.chorus_gemm_bf16_plan(8, 64, 64, 0, 0, 0, None) == B.E_ARG
     assert lib.chorus_gemm_bf16_plan(8, 64, 100, 0, 0, 0, B.C.byref(out)) == B.E_SHAPE
     assert lib.chorus_gemm_bf16_plan(8, 60, 64, 0, 0, 0, B.C.byref(out)) == B.E_SHAPE
+
+
+@pytest.mark.parametrize("T,H,W", [(1, 1, 1), (21, 30, 52), (21, 45, 80), (1, 1024, 64), (1, 1500, 40), (3, 900, 100), (1, 40, 3000),
+                                   (2, 4, 90000), (1, 4, 400000)])
+def test_mask_hierarchy_radii_end_at_the_grid(T, H, W):
+    """A radius beyond the grid reaches what the grid's extent reaches; the kernels loop over what they are given."""
+    last, held_before = (T - 1, H - 1, W - 1), None
+    for big in (max(T, H, W), 10 ** 6, 2 ** 30, 2 ** 31 - 1):
+        for re in ((0, 0, 0), (big, big, big)):
+            got = B.chorus_mask_hierarchy_plan(T, H, W, re, (big, big, big))
+            assert got[0] == (last if re[0] else (0, 0, 0)) and got[1] == last
+            assert held_before is None or got[2:] == held_before
+            held_before = got[2:]
+    for r in range(5):
+        re, rs, strip, nstrips, lds = B.chorus_mask_hierarchy_plan(T, H, W, (r, 0, r), (r + 1, r, r + 2))
+        assert re == (min(r, T - 1), 0, min(r, W - 1)) and rs == (min(r + 1, T - 1), min(r, H - 1), min(r + 2, W - 1))
+        if strip:  # two sets of bits per row held, before and after the pass along x, and one per row of the strip
+            assert (nstrips - 1) * strip < H <= nstrips * strip
+            assert lds == (4 * min(H, strip + 2 * rs[1]) + 2 * strip) * -(-W // 64) * 8 <= 48 * 1024
+        else:
+            assert W > 64 * 100
+
+
+def test_mask_hierarchy_plan_refuses():
+    for T, H, W, re, rs, want in ((0, 1, 1, (0,) * 3, (0,) * 3, B.E_ARG), (1, 1, 1, (1, 0, 0), (0,) * 3, B.E_ARG),
+                                  (1, 1, 1, (0, -1, 0), (0,) * 3, B.E_ARG), (2, 2 ** 15, 2 ** 15, (0,) * 3, (0,) * 3, B.E_SHAPE)):
+        assert B.load().chorus_mask_hierarchy_plan(T, H, W, B._Radii(*re), B._Radii(*rs), B.C.byref(B.HierarchyPlan())) == want

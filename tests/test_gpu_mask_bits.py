@@ -17,6 +17,7 @@ def _mask(shape, p, seed):
 
 
 def _dilate(m, r):
+    r = [min(a, n) for a, n in zip(r, m.shape)]  # further there is nothing to reach
     k = [2 * a + 1 for a in r]
     return F.max_pool3d((m != 0).double()[None, None], k, 1, r)[0, 0].to(torch.uint8)
 
@@ -24,6 +25,8 @@ def _dilate(m, r):
 @pytest.mark.parametrize("T,H,W,re,rs", [
     (1, 1, 1, (0, 0, 0), (2, 2, 2)), (3, 5, 63, (1, 1, 1), (1, 2, 2)), (3, 5, 64, (0, 1, 2), (1, 2, 3)), (2, 7, 65, (1, 0, 1), (6, 1, 4)),
     (9, 4, 130, (2, 1, 65), (5, 2, 70)), (2, 3, 200, (0, 0, 64), (0, 1, 128)), (21, 30, 52, (1, 1, 1), (1, 2, 2)),
+    (3, 30, 52, (0, 1, 10 ** 6), (0, 1, 10 ** 6)), (3, 9, 70, (1, 2, 3), (2 ** 31 - 1,) * 3), (1, 1100, 3, (2 ** 31 - 1,) * 3, (2 ** 31 - 1,) * 3),
+    (1, 4, 90000, (0, 2 ** 31 - 1, 1), (2 ** 31 - 1, 2 ** 31 - 1, 2)),
     (1, 40, 3000, (0, 2, 1), (0, 3, 2)), (1, 9, 30000, (0, 1, 1), (0, 1, 2)), (1, 4, 90000, (0, 0, 1), (0, 1, 2))])
 def test_hierarchy(T, H, W, re, rs):
     print(f"[case] hierarchy {T}x{H}x{W} {re} {rs}", flush=True)
