@@ -257,7 +257,7 @@ extern "C" {
 
 int32_t chorus_mask_pooled_extent(int32_t n, int32_t k, int32_t lead) {
   if (k < 1 || lead < 0 || n < lead) return CHORUS_E_ARG;
-  return lead + (n - lead + k - 1) / k;
+  return lead + (int32_t)(((int64_t)n - lead + k - 1) / k);
 }
 
 int32_t chorus_mask_project(const uint8_t* key_masks, int32_t Kf, const int32_t* frame_key, int32_t Tp, int32_t Hp,
@@ -271,6 +271,10 @@ int32_t chorus_mask_project(const uint8_t* key_masks, int32_t Kf, const int32_t*
   if (To * Ho > 0x7fffffffLL || (int64_t)Kf * Hp * Wp > 0x7fffffffffLL) return CHORUS_E_SHAPE;
   const size_t lds = (size_t)((Wp + 15) / 16) * 16;
   if (lds > 64 * 1024) return CHORUS_E_SHAPE;
+  // a window longer than the axis holds all of it, and the kernel's t0 + kt and y0 + kh stay in 32 bits
+  kt = kt < Tp ? kt : Tp;
+  kh = kh < Hp ? kh : Hp;
+  kw = kw < Wp ? kw : Wp;
   hipStream_t s = (hipStream_t)stream;
   hipLaunchKernelGGL(mask_project_kernel, dim3((unsigned)(To * Ho)), dim3(kProjThreads), lds, s, key_masks, Kf, frame_key, Tp, Hp,
                      Wp, kt, kh, kw, t_lead, (int)Ho, (int)Wo, out);

@@ -98,6 +98,7 @@ static void sizes_and_validation() {
   EXPECT(chorus_time_mod_workspace_bytes(1536, 256) > 0 && chorus_text_project_workspace_bytes(512, 1536) > 0);
   EXPECT(chorus_mfma_ceiling_workspace_bytes() > 0);
   EXPECT(chorus_mask_pooled_extent(81, 4, 1) == 21 && chorus_mask_pooled_extent(5, 0, 0) < 0 && chorus_mask_pooled_extent(5, 2, 6) < 0);
+  EXPECT(chorus_mask_pooled_extent(81, 2147483647, 1) == 2 && chorus_mask_pooled_extent(2147483647, 2, 0) == 1 << 30);
   EXPECT(chorus_cache_lowprec_bytes(10, 64, CHORUS_LP_BF16) == 1280);
   // argument validation: every call returns before any device work
   EXPECT(chorus_cache_lookup((const float*)p16, 4, 6, (const float*)p16, 0.5f, &lr, p16, 1024, nullptr) == CHORUS_E_SHAPE);

@@ -132,6 +132,8 @@ def test_mask_entry_points_validate_and_pooled_extent_matches_oracle():
     null, p16 = C.c_void_p(0), C.c_void_p(16)
     for n, k, lead in [(81, 4, 1), (480, 16, 0), (17, 4, 0), (5, 7, 0), (1, 1, 1), (0, 3, 0), (9, 2, 9)]:
         assert lib.chorus_mask_pooled_extent(n, k, lead) == O.pooled_extent(n, k, lead)
+    for n, k, lead in ((81, 2 ** 31 - 1, 1), (2 ** 31 - 1, 2 ** 31 - 1, 0), (2 ** 31 - 1, 2, 7), (1, 2 ** 31 - 1, 1)):  # sums beyond 32 bits
+        assert lib.chorus_mask_pooled_extent(n, k, lead) == O.pooled_extent(n, k, lead) == B._pooled(n, k, lead)
     assert lib.chorus_mask_pooled_extent(8, 0, 0) == B.E_ARG
     assert lib.chorus_mask_pooled_extent(8, 2, 9) == B.E_ARG
     # project: window < 1, t_lead > Tp, identity frame map with Kf != Tp, null pointers; empty input is OK

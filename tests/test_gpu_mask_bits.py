@@ -37,11 +37,12 @@ def test_hierarchy(T, H, W, re, rs):
 
 
 @pytest.mark.parametrize("Hp,Wp,kt,kh,kw", [(33, 854, 4, 16, 16), (20, 207, 11, 16, 16), (64, 1000, 17, 16, 12), (7, 5, 3, 3, 2),
-                                            (40, 17, 9, 18, 16), (17, 16, 1, 1, 1), (65, 33, 8, 64, 32)])
+                                            (40, 17, 9, 18, 16), (17, 16, 1, 1, 1), (65, 33, 8, 64, 32), (9, 37, 2 ** 31 - 1, 4, 8),
+                                            (9, 37, 4, 2 ** 31 - 1, 2 ** 31 - 1), (9, 36, 20, 10, 40)])
 def test_project(Hp, Wp, kt, kh, kw):
-    Tp, Kf = 1 + 2 * kt + 1, 6
+    Tp, Kf = 1 + 2 * (kt if kt < 100 else 4) + 1, 6
     print(f"[case] project {Hp}x{Wp} window {kt} {kh} {kw}", flush=True)
-    store = _mask((Kf * Hp * Wp + 5,), 3.0 / (kh * kw), Wp)
+    store = _mask((Kf * Hp * Wp + 5,), 3.0 / (min(kh, Hp) * min(kw, Wp)), Wp)
     for off in (0, 5):  # from an aligned address and from another
         keys = store[off:off + Kf * Hp * Wp].view(Kf, Hp, Wp)
         fk = torch.tensor([(i * 5) % (Kf + 2) - 1 for i in range(Tp)], dtype=torch.int32, device="cuda")  # -1 and Kf: none
@@ -50,5 +51,6 @@ def test_project(Hp, Wp, kt, kh, kw):
         for o, frames in enumerate(wins):
             ks = [int(fk[t]) for t in frames if 0 <= int(fk[t]) < Kf]
             any_ = (keys[ks] != 0).any(0) if ks else torch.zeros(Hp, Wp, dtype=torch.bool, device="cuda")
-            want = F.max_pool2d(any_.double()[None, None], (kh, kw), (kh, kw), ceil_mode=True)[0, 0].to(torch.uint8)
+            win = (min(kh, Hp), min(kw, Wp))
+            want = F.max_pool2d(any_.double()[None, None], win, win, ceil_mode=True)[0, 0].to(torch.uint8)
             assert torch.equal(got[o], want[:got.shape[1], :got.shape[2]]), (off, o)
