@@ -55,7 +55,9 @@ int32_t chorus_last_hip_error(void);
  * scores -inf. N == 0 gives index -1, score -inf, hit 0. d must be a multiple of 4;
  * N at most 2^31 - 2 (the index is an int32), CHORUS_E_SHAPE beyond.
  * One launch: every workgroup of the scan leaves one (best value, index) pair in ws, the last one
- * waits for them and picks. Nothing in ws has to start at any value.
+ * waits for them and picks (for 57 ms at least; then it scans the cache alone). Under stream capture, and for
+ * caches of more than 2^32 values, two launches, in which nothing waits. Nothing in ws has to start at any
+ * value, and nothing that a call or a replay leaves there counts for another.
  * ------------------------------------------------------------------------ */
 typedef struct {
   int32_t index;
@@ -75,11 +77,14 @@ int32_t chorus_cache_lookup(const float* cache_emb, int64_t N, int32_t d, const 
  * image (one copy per GPU, held until the process ends) instead of a caller buffer. The call
  * makes no hipMalloc / hipFree and no allocating library call; the first call on a device
  * resolves the array's address there (make that call outside graph capture).
- * All calls on one GPU share that array: calls that overlap in time on one GPU (two streams,
- * two threads) race and may return each other's result; calls on one stream, or otherwise
- * ordered, are safe, and nothing a call leaves in the array is read by the next.
- * Limits: N at most 2^31 - 2 as for chorus_cache_lookup (the array serves every such N, the
- * scan never uses more than 4096 workgroups); device ordinals 0..63. CHORUS_E_SHAPE beyond.
+ * All calls on one GPU share that array, so calls on it must not overlap in time on one GPU (two
+ * streams, two threads): they overwrite each other's partial results, and may wait for ones that
+ * never arrive (57 ms and more, then the cache is scanned by one workgroup) or, as two launches,
+ * return each other's result. Calls on one stream, or otherwise ordered, are safe, and nothing a
+ * call leaves in the array is taken for its own by another.
+ * Limits: N at most 2^31 - 2 as for chorus_cache_lookup (the array serves every such N: the scan
+ * never uses more than 2048 workgroups, 4096 as two launches); device ordinals 0..63.
+ * CHORUS_E_SHAPE beyond.
  * ------------------------------------------------------------------------ */
 int32_t chorus_cache_lookup_static(const float* cache_emb, int64_t N, int32_t d, const float* query, float tau,
                                    chorus_lookup_result* out, void* stream);

@@ -69,7 +69,7 @@ int32_t chorus_gemm_bf16_plan(int64_t M, int32_t N, int32_t K, int32_t epilogue,
 
 /* chorus_cache_lookup with the length of its last workgroup's wait named by the caller, for tests of the path taken when it
  * runs out: at most `rounds` + 1 looks for what the other workgroups leave (-1: none). Then that workgroup makes the whole
- * result itself. rounds from -1 to 8192, what the plain call uses (CHORUS_E_ARG). */
+ * result itself. rounds from -1 to 2^18, what the plain call uses (CHORUS_E_ARG). Calls that run as two launches do not wait. */
 int32_t chorus_cache_lookup_wait(const float* cache_emb, int64_t N, int32_t d, const float* query, float tau, int32_t rounds,
                                  chorus_lookup_result* out, void* ws, size_t ws_bytes, void* stream);
 
