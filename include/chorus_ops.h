@@ -67,6 +67,10 @@ typedef struct {
 int32_t chorus_gemm_bf16_plan(int64_t M, int32_t N, int32_t K, int32_t epilogue, size_t first_bytes, size_t rest_bytes,
                               chorus_gemm_plan* out);
 
+/* Two products with bf16 outputs over the same K, as a block runs QKV and the text's keys and values: *kernel is the kernel (1 or
+ * 5) of the one launch that takes both, 0 where each takes a launch of its own. Host only. */
+int32_t chorus_gemm_bf16_two_plan(int64_t M, int32_t N, int64_t M2, int32_t N2, int32_t K, int32_t* kernel);
+
 /* chorus_cache_lookup with the length of its last workgroup's wait named by the caller, for tests of the path taken when it
  * runs out: at most `rounds` + 1 looks for what the other workgroups leave (-1: none). Then that workgroup makes the whole
  * result itself. rounds from -1 to 2^18, what the plain call uses (CHORUS_E_ARG). Calls that run as two launches do not wait. */

@@ -157,6 +157,7 @@ def _bind_ops(lib):
         "chorus_gemm_bf16": (i32, [vp, vp, i64, i32, i32, i32, vp, vp, vp, vp, f32, vp]),
         "chorus_gemm_bf16_kernel": (i32, [vp, vp, i64, i32, i32, i32, vp, vp, vp, vp, f32, i32, vp]),
         "chorus_gemm_bf16_slices": (i32, [vp, vp, i64, i32, i32, vp, vp, vp, vp, f32, i32, i32, vp, sz, vp]),
+        "chorus_gemm_bf16_two_plan": (i32, [i64, i32, i64, i32, i32, C.POINTER(i32)]),
         "chorus_gemm_bf16_plan": (i32, [i64, i32, i32, i32, sz, sz, C.POINTER(GemmPlan)]),
         "chorus_ln_modulate": (i32, [vp, vp, i64, i32, vp, vp, vp, vp, i32, vp]),
         "chorus_qk_norm_rope": (i32, [vp, i64, vp, vp, i64, i64, i32, i32, vp, i32, i32, i32, i32, f32, vp]),
@@ -589,6 +590,13 @@ def chorus_gemm_bf16_plan(M, N, K, epilogue, first_bytes=0, rest_bytes=0):
     out = GemmPlan()
     _status("chorus_gemm_bf16_plan", load().chorus_gemm_bf16_plan(M, N, K, epilogue, first_bytes, rest_bytes, C.byref(out)))
     return out.head_rows, out.kernel, out.slices
+
+
+def chorus_gemm_bf16_two_plan(M, N, M2, N2, K):
+    """Kernel of the launch that takes both products of a block's QKV and text projections, 0: a launch each; host only."""
+    kernel = C.c_int32(-1)
+    _status("chorus_gemm_bf16_two_plan", load().chorus_gemm_bf16_two_plan(M, N, M2, N2, K, C.byref(kernel)))
+    return kernel.value
 
 
 def chorus_ln_modulate(x, out, mul0, mul1, add0, add1, plus_one):

@@ -579,10 +579,14 @@ constexpr int kTileRows[kTiles] = {256, 128, 128, 128, 64};
 constexpr int kTileCols[kTiles] = {256, 256, 128, 128, 64};
 constexpr int kMaxSlices = 4;  // more slices than this were never the fastest
 
-double tile_time(int tile, long m, int N, int K, int epi, int slices) {
+long tile_count(int tile, long m, int N) {
   const long rows = kTileRows[tile], cols = kTileCols[tile];
+  return ((m + rows - 1) / rows) * ((N + cols - 1) / cols);
+}
+
+double tiles_time(int tile, long tiles, int K, int epi, int slices) {
   const double steps = (double)((K / BK + slices - 1) / slices);
-  const double w = (double)(((m + rows - 1) / rows) * ((N + cols - 1) / cols) * slices), fill = w / 256.0;
+  const double w = (double)(tiles * slices), fill = w / 256.0;
   const bool gelu = epi == CHORUS_EPI_GELU_BF16, f32 = slices == 1 && (epi == CHORUS_EPI_F32 || epi == CHORUS_EPI_RESID);
   auto by_epilogue = [&](double bf16, double with_gelu, double resid) { return f32 ? resid : gelu ? with_gelu : bf16; };
   switch (tile) {
@@ -612,6 +616,10 @@ double tile_time(int tile, long m, int N, int K, int epi, int slices) {
     default:
       return (w <= 256.0 ? 1.0 : 1.141 + 0.677 * (fill - 1.0)) * (by_epilogue(3.62, 2.26, 3.14) + 0.246 * steps);
   }
+}
+
+double tile_time(int tile, long m, int N, int K, int epi, int slices) {
+  return tiles_time(tile, tile_count(tile, m, N), K, epi, slices);
 }
 
 constexpr GemmParts kNoParts{nullptr, 0, nullptr, 0};
@@ -708,6 +716,7 @@ int32_t check_gemm(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, i
 struct GemmCut {
   long head_rows;
   GemmPlan rest;
+  double time;  // of both launches
 };
 GemmCut plan_rows(long M, int N, int K, int epi, const GemmParts& parts) {
   const GemmPlan whole = plan_gemm(M, N, K, epi, parts);
@@ -715,29 +724,55 @@ GemmCut plan_rows(long M, int N, int K, int epi, const GemmParts& parts) {
   const long head_rows = tiles256 > 256 ? (tiles256 / 256 * 256 / tiles_n256) * 256 : 0;
   if (head_rows > 0 && head_rows < M) {
     const GemmPlan tail = plan_gemm(M - head_rows, N, K, epi, kNoParts);
-    if (tile_time(kTile256, head_rows, N, K, epi, 1) + tail.time < 0.95 * whole.time) return GemmCut{head_rows, tail};
+    const double time = tile_time(kTile256, head_rows, N, K, epi, 1) + tail.time;
+    if (time < 0.95 * whole.time) return GemmCut{head_rows, tail, time};
   }
-  return GemmCut{0, whole};
+  return GemmCut{0, whole, whole.time};
+}
+
+// The tile on which two products with bf16 outputs and the same K run in one launch, kTiles: each in a launch of its own,
+// whichever is the fastest by the estimates for the tiles of both together. 64 x 64 tiles up to one round of two workgroups a
+// unit, the deep 128 x 128 ones up to two rounds of one; beyond that the estimates of cold weights are too low, and the best
+// tiles of the larger product are other ones. Measured (tokens and text tokens, QKV and the text's keys and values; 64 x 64 / deep /
+// apart, us): width 256, 128 and 16 4.8 / 5.7 / 7.8; width 1536, 100 and 16 9.9 / 18.2 / 17.9, 480 and 512 29.2 / 19.9 / 33.7, 800
+// and 16 30.2 / 28.1 / 24.5, 900 and 512 40.9 / 33.3 / 39.4; width 5120, 100 and 512 160 / 113 / 129, 200 and 16 99 / 89 / 77, 200 and 512
+// 179 / 152 / 129. Over 91 such pairs the choice is 1.2 % slower than the best (geometric mean), and never slower than apart.
+int plan_two(long M, int N, long M2, int N2, int K) {
+  if (K > kMaxOffsetK) return kTiles;
+  const long small = tile_count(kTile64, M, N) + tile_count(kTile64, M2, N2);
+  const long deep = tile_count(kTile128Deep, M, N) + tile_count(kTile128Deep, M2, N2);
+  double best = plan_rows(M, N, K, CHORUS_EPI_BF16, kNoParts).time + plan_rows(M2, N2, K, CHORUS_EPI_BF16, kNoParts).time;
+  int tile = kTiles;
+  auto consider = [&](int t, double time) {
+    if (time < best) {
+      best = time;
+      tile = t;
+    }
+  };
+  if (small <= 512) consider(kTile64, tiles_time(kTile64, small, K, CHORUS_EPI_BF16, 1));
+  if (deep <= 512)
+    consider(kTile128Deep, tiles_time(kTile128Deep, deep < 256 ? deep : 256, K, CHORUS_EPI_BF16, 1) +
+                               (deep > 256 ? tiles_time(kTile128Deep, deep - 256, K, CHORUS_EPI_BF16, 1) : 0.0));
+  return tile;
 }
 
 }  // namespace
 
-// Where the first product's launch leaves most of the chip idle the second one's tiles run beside it (a block of 128 tokens of
-// width 256 with 16 text tokens, its text keys and values prepared beside the tokens' in the same way: 62.9 -> 56.8 us); larger ones take a
-// launch each.
+// One launch where plan_two says so (a block of 128 tokens of width 256 with 16 text tokens, its text keys and values prepared
+// beside the tokens' in the same way: 62.9 -> 56.8 us).
 int32_t gemm_bf16_two(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, uint16_t* out, const float* bias,
                       const uint16_t* A2, const uint16_t* W2, int64_t M2, int32_t N2, uint16_t* out2, const float* bias2,
                       void* stream) {
   CHK_STATUS(check_gemm(A, W, M, N, K, out, bias, nullptr, nullptr));
   CHK_STATUS(check_gemm(A2, W2, M2, N2, K, out2, bias2, nullptr, nullptr));
-  if (M > 0 && M2 > 0 && K <= kMaxOffsetK) {
-    const GemmCut cut = plan_rows((long)M, N, K, CHORUS_EPI_BF16, kNoParts);
+  if (M > 0 && M2 > 0) {
     const EpiArgs ep{out, bias, nullptr, nullptr, 1.f};
     const Twin twin{A2, W2, out2, bias2, (long)M2, N2, 0, 0, 0};
-    if (cut.head_rows == 0 && cut.rest.tile == kTile64)
-      return launch_two<2, 2, kHalves64>(A, W, (long)M, N, K, ep, twin, (hipStream_t)stream);
-    if (cut.head_rows == 0 && cut.rest.tile == kTile128Deep)
-      return launch_two<4, 4, kHalvesDeep>(A, W, (long)M, N, K, ep, twin, (hipStream_t)stream);
+    switch (plan_two((long)M, N, (long)M2, N2, K)) {
+      case kTile64: return launch_two<2, 2, kHalves64>(A, W, (long)M, N, K, ep, twin, (hipStream_t)stream);
+      case kTile128Deep: return launch_two<4, 4, kHalvesDeep>(A, W, (long)M, N, K, ep, twin, (hipStream_t)stream);
+      default: break;
+    }
   }
   CHK_STATUS(gemm_bf16_parts(A, W, M, N, K, CHORUS_EPI_BF16, out, bias, nullptr, nullptr, 1.f, kNoParts, stream));
   return gemm_bf16_parts(A2, W2, M2, N2, K, CHORUS_EPI_BF16, out2, bias2, nullptr, nullptr, 1.f, kNoParts, stream);
@@ -805,6 +840,14 @@ extern "C" int32_t chorus_gemm_bf16_plan(int64_t M, int32_t N, int32_t K, int32_
   const GemmCut cut = plan_rows((long)M, N, K, epilogue,
                                 GemmParts{first_bytes ? some : nullptr, first_bytes, rest_bytes ? some : nullptr, rest_bytes});
   *out = chorus_gemm_plan{cut.head_rows, kTileNumber[cut.rest.tile], cut.rest.slices};
+  return CHORUS_OK;
+}
+
+extern "C" int32_t chorus_gemm_bf16_two_plan(int64_t M, int32_t N, int64_t M2, int32_t N2, int32_t K, int32_t* kernel) {
+  if (!kernel || M < 1 || M2 < 1 || N <= 0 || N2 <= 0 || K <= 0) return CHORUS_E_ARG;
+  if (K % BK || N % 8 || N2 % 8) return CHORUS_E_SHAPE;
+  const int tile = plan_two((long)M, N, (long)M2, N2, K);
+  *kernel = tile == kTiles ? 0 : kTileNumber[tile];
   return CHORUS_OK;
 }
 

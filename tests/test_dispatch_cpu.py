@@ -3,6 +3,7 @@ measured, and that the sizes which other tests name reach the kernels that those
 import pytest
 
 from paper_2604_04451_amd import binding as B
+from test_gpu_block_text import CASES as TEXT_CASES
 from test_gpu_gemm_slices import DEFAULT_TILES, FFN_SLICES, ffn2_scratch
 
 CUS = 256  # compute units of the GPU
@@ -80,6 +81,26 @@ def test_second_ffn_product_in_slices():
     assert B.chorus_gemm_bf16_plan(480, 1536, 8960, B.EPI_RESID, one, 2 * one)[2] == 4
     assert B.chorus_gemm_bf16_plan(480, 1536, 8960, B.EPI_F32, one, 2 * one)[2] == 1  # the gated residual only
     assert B.chorus_gemm_bf16_plan(64, 64, 128, B.EPI_RESID, one, 2 * one)[2] <= 2    # no more slices than steps
+
+
+def test_two_products_in_one_launch():
+    """Where one launch for both is the faster one as measured: by the tiles of both together, not of the first alone."""
+    two = lambda D, Ls, Lt: B.chorus_gemm_bf16_two_plan(Ls, 3 * D, Lt, 2 * D, D)  # noqa: E731
+    for D, _, _, Ls, Lt, kernel in TEXT_CASES:
+        assert two(D, Ls, Lt) == kernel, (D, Ls, Lt)
+    for D, Ls, Lt in ((256, 128, 16), (256, 1200, 512), (1536, 100, 16), (1536, 200, 77)):
+        assert two(D, Ls, Lt) == 1, (D, Ls, Lt)
+    for D, Ls, Lt in ((256, 4000, 512), (1536, 640, 226), (1536, 900, 512), (5120, 100, 77), (5120, 100, 512)):
+        assert two(D, Ls, Lt) == 5, (D, Ls, Lt)
+    for D, Ls, Lt in ((1536, 800, 16), (1536, 800, 512), (1536, 300, 2048), (5120, 64, 512), (5120, 160, 16), (5120, 160, 77),
+                      (5120, 200, 16), (5120, 200, 512), (5120, 256, 512), (5120, 100, 2048)):
+        assert two(D, Ls, Lt) == 0, (D, Ls, Lt)
+    assert B.chorus_gemm_bf16_two_plan(64, 64, 64, 64, 1 << 22) == 0  # rows beyond 32-bit offsets
+    out = B.C.c_int32()
+    for bad in ((0, 64, 8, 64, 64), (8, 64, 0, 64, 64), (8, 0, 8, 64, 64), (8, 64, 8, 64, 0)):
+        assert B.load().chorus_gemm_bf16_two_plan(*bad, B.C.byref(out)) == B.E_ARG
+    for bad in ((8, 60, 8, 64, 64), (8, 64, 8, 60, 64), (8, 64, 8, 64, 100)):
+        assert B.load().chorus_gemm_bf16_two_plan(*bad, B.C.byref(out)) == B.E_SHAPE
 
 
 def test_gemm_plan_refuses():

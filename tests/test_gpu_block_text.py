@@ -9,8 +9,13 @@ from paper_2604_04451_amd import binding as B
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("D,H,F,Ls,Lt", [(256, 4, 1024, 1, 1), (256, 4, 1024, 64, 16), (256, 4, 1024, 129, 130), (512, 8, 1024, 300, 77),
-                                         (1536, 12, 2048, 300, 512), (1536, 12, 2048, 480, 65), (1536, 12, 2048, 1500, 512)])
+# D, H, F, tokens, text tokens, and the kernel of the launch that takes both products (0: a launch each)
+CASES = [(256, 4, 1024, 1, 1, 1), (256, 4, 1024, 64, 16, 1), (256, 4, 1024, 129, 130, 1), (512, 8, 1024, 300, 77, 1),
+         (1536, 12, 2048, 300, 512, 5), (1536, 12, 2048, 480, 65, 5), (1536, 12, 2048, 800, 16, 0), (1536, 12, 2048, 900, 512, 5),
+         (1536, 12, 2048, 300, 2048, 0), (1536, 12, 2048, 1500, 512, 0)]
+
+
+@pytest.mark.parametrize("D,H,F,Ls,Lt", [c[:5] for c in CASES])
 def test_text_beside_the_tokens(D, H, F, Ls, Lt):
     print(f"[case] block with its text D={D} Ls={Ls} Lt={Lt}", flush=True)
     g = torch.Generator(device="cuda")
