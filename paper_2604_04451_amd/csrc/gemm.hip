@@ -108,7 +108,9 @@ __device__ __forceinline__ void gemm16_epilogue_bf16(const f32x4 (&acc)[8][8], c
     for (int mh = 0; mh < 2; ++mh)
 #pragma unroll
       for (int nb = 0; nb < WBN; ++nb) {
-        const f32x4& a = acc[nb][2 * mp + mh];
+        f32x4 a = acc[nb][2 * mp + mh];
+        // one block at a time out of the accumulators: of the large tile's, fetched together, 8 to 12 bytes a lane spilled
+        if (WBM == 8 && mh) asm volatile("" : "+v"(a));
         float v0 = a[0] + bias[nb].x, v1 = a[1] + bias[nb].y, v2 = a[2] + bias[nb].z, v3 = a[3] + bias[nb].w;
         if (EPI == CHORUS_EPI_GELU_BF16) {
           v0 = gelu_tanh_fast(v0); v1 = gelu_tanh_fast(v1); v2 = gelu_tanh_fast(v2); v3 = gelu_tanh_fast(v3);

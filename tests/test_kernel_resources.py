@@ -21,6 +21,7 @@ def _scratch(source, tmp_path):
 
 @pytest.mark.parametrize("source,kernels,at_least", [
     ("glue.hip", r"head_update_kernel", 18),  # six widths, three updates
+    ("gemm.hip", r"gemm_w16_kernel", 26),  # five tiles and the far one, four epilogues; two tiles with a second product
     # all but plain queries with factors over 512 keys or more, which a block does not run
     ("attention.hip", r"attention_pp16_kernelILi\d+E(?!Lb0ELi2ELi2E)", 38),
 ])
