@@ -42,7 +42,9 @@ int32_t chorus_gemm_bf16(const uint16_t* A, const uint16_t* W, int64_t M, int32_
 /* chorus_gemm_bf16 with the tile kernel named by the caller, for tests and comparisons (every kernel is correct on
  * every shape the call accepts; only the speed differs): kernel 0 = the default choice by problem size, else tiles
  * filled straight from global memory into 1 = 64 x 64 (nine half k-steps in LDS), 2 = 128 x 256 (six), 3 = 256 x 256
- * (five), 4 = 128 x 128 (five), 5 = 128 x 128 (seven). Anything else: CHORUS_E_ARG. */
+ * (five), 4 = 128 x 128 (five), 5 = 128 x 128 (seven). Anything else: CHORUS_E_ARG. Rows of K > 2^22 - 64 values are out of
+ * reach of the 32-bit offsets of these kernels: every number, and the default choice, is then 64 x 64 tiles loaded by 64-bit
+ * addresses. */
 int32_t chorus_gemm_bf16_kernel(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, int32_t epilogue,
                                 void* out, const float* bias, const float* gate0, const float* gate1, float scale,
                                 int32_t kernel, void* stream);

@@ -575,6 +575,9 @@ int32_t launch_add_parts(const PartPtrs& parts, int slices, long M, int N, const
 //   128 x 128  three steps and a half in LDS, one workgroup per unit: up to 256 tiles [14 / 67 few, 16 / 76 all units busy]
 //   64 x 64    two workgroups per unit: up to 256 tiles [8.5 / 37], growing with the tiles beyond
 // ---------------------------------------------------------------------------
+// a tile's bytes, 256 rows of 2 K, within the 32-bit offsets of its loads; longer rows are 64 x 64 tiles' alone
+constexpr int kMaxOffsetK = (1 << 22) - 64;
+
 enum Tile { kTile256, kTileWide, kTile128, kTile128Deep, kTile64, kTiles };
 constexpr int kTileNumber[kTiles] = {3, 2, 4, 5, 1};  // as chorus_gemm_bf16_kernel names them
 constexpr int kTileRows[kTiles] = {256, 128, 128, 128, 64};
@@ -621,6 +624,7 @@ double tiles_time(int tile, long tiles, int K, int epi, int slices) {
 }
 
 double tile_time(int tile, long m, int N, int K, int epi, int slices) {
+  if (K > kMaxOffsetK && tile != kTile64) return INFINITY;
   return tiles_time(tile, tile_count(tile, m, N), K, epi, slices);
 }
 
@@ -637,7 +641,7 @@ struct GemmPlan {
 // Measured where N = 1536, K = 8960, slices against the best whole tile: 128 rows 17 / 40 us, 480 rows 31 / 39, 1200
 // rows 51 / 67, 2000 rows (two slices of 128 x 256 tiles) 74 / 77; from about 2300 rows a whole tile fills the chip.
 GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
-  GemmPlan best{kTile256, 1, INFINITY};
+  GemmPlan best{kTile64, 1, INFINITY};
   for (int t = 0; t < kTiles; ++t) {
     const double v = tile_time(t, m, N, K, epi, 1);
     if (v < best.time) best = GemmPlan{t, 1, v};
@@ -658,8 +662,6 @@ GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
 }
 
 constexpr int kHalvesDeep = 7, kHalves64 = 9;
-// a tile's bytes, 256 rows of 2 K, within the 32-bit offsets of its loads
-constexpr int kMaxOffsetK = (1 << 22) - 64;
 
 int32_t launch_tile(int tile, const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, const EpiArgs& ep,
                     hipStream_t s, int slices = 1, const PartPtrs& parts = PartPtrs{nullptr, nullptr}) {

@@ -103,6 +103,15 @@ def test_two_products_in_one_launch():
         assert B.load().chorus_gemm_bf16_two_plan(*bad, B.C.byref(out)) == B.E_SHAPE
 
 
+def test_rows_beyond_32_bit_offsets_are_planned_as_they_run():
+    for M, N in ((70, 72), (4500, 4608), (20000, 8960)):
+        for epi in range(4):
+            assert B.chorus_gemm_bf16_plan(M, N, (1 << 22) + 64, epi) == (0, 1, 1), (M, N, epi)
+    head, kernel, slices = B.chorus_gemm_bf16_plan(70, 72, (1 << 22) + 64, B.EPI_RESID, 1 << 20, 1 << 20)
+    assert (head, kernel) == (0, 1) and slices > 1
+    assert B.chorus_gemm_bf16_plan(20000, 8960, (1 << 22) - 64, B.EPI_BF16)[1] == 3
+
+
 def test_gemm_plan_refuses():
     lib, out = B.load(), B.GemmPlan()
     for bad in ((0, 64, 64, 0), (8, 0, 64, 0), (8, 64, 0, 0), (8, 64, 64, 4), (8, 64, 64, -1)):

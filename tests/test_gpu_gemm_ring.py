@@ -36,15 +36,35 @@ def test_steps_and_edges(kernel, steps):
         _check(M, N, 64 * steps, kernel, B.EPI_F32 if steps % 2 else B.EPI_RESID)
 
 
-@pytest.mark.parametrize("kernel", [0, 1, 3])
-def test_rows_beyond_32_bit_offsets(kernel):
+FAR_K = (1 << 22) + 64
+
+
+def _far_operands(M, N):
     """256 rows of 2 K bytes pass 2^31 from K = 2^22 on; sums of 2^22 products of -1, 0 and 1 stay whole in fp32."""
-    M, N, K = 70, 72, (1 << 22) + 64
-    A, W = _ints((M, K), 5, -1, 2), _ints((N, K), 6, -1, 2)
+    A, W = _ints((M, FAR_K), 5, -1, 2), _ints((N, FAR_K), 6, -1, 2)
     want = torch.zeros(M, N, dtype=torch.float64, device="cuda")
-    for k in range(0, K, 1 << 16):
+    for k in range(0, FAR_K, 1 << 16):
         want += (A[:, k:k + (1 << 16)] @ W[:, k:k + (1 << 16)].T).double()
+    return A.bfloat16(), W.bfloat16(), want
+
+
+@pytest.mark.parametrize("kernel", [0, 3])  # the default choice and a named kernel, which stands for the one by 64-bit addresses
+def test_rows_beyond_32_bit_offsets(kernel):
+    M, N = 130, 72
+    A, W, want = _far_operands(M, N)
     out = torch.empty(M, N, device="cuda")
     print(f"[case] gemm far rows kernel={kernel}", flush=True)
-    B.chorus_gemm_bf16(A.bfloat16(), W.bfloat16(), B.EPI_F32, out, None, kernel=kernel)
+    B.chorus_gemm_bf16(A, W, B.EPI_F32, out, None, kernel=kernel)
     assert torch.equal(out.double(), want)
+
+
+def test_rows_beyond_32_bit_offsets_in_slices():
+    M, N = 70, 136
+    A, W, want = _far_operands(M, N)
+    for slices in (2, 3, 4):
+        print(f"[case] gemm far rows slices={slices}", flush=True)
+        out = _ints((M, N), 7)
+        ref = out.double() + want
+        parts = torch.full((slices - 1, M, N), float("nan"), device="cuda")
+        B.chorus_gemm_bf16_slices(A, W, out, 1, slices, parts=parts.view(-1))
+        assert torch.equal(out.double(), ref)
