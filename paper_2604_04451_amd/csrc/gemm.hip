@@ -243,9 +243,9 @@ __device__ __forceinline__ void* uniform_address(const uint16_t* p) {
   return reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
 }
 
-// The 128 x 256 shape takes three quarters of the operand bytes per product of 128 x 128 tiles: for products of 257 to
-// 512 such tiles with a long K, which run two to a unit, half as many wide ones finish earlier (N = 1536, K = 8960: 3271
-// rows 124 -> 115 us, 5000 rows 136 -> 130; N = 5120, K = 13824, 1200 rows: 202 -> 181).
+// The 128 x 256 shape takes three quarters of the operand bytes per product of 128 x 128 tiles: for products of about 400 to
+// 512 such tiles with a long K, which run two to a unit, half as many wide ones finish earlier (N = 1536, K = 8960: 5000 rows
+// 132 -> 117 us; N = 5120, K = 13824, 1200 rows: 202 -> 172; with 312 tiles, 3271 rows of the former, 109 and 112).
 // FAR: rows so long that a tile's last byte is out of reach of the 32-bit offsets; loads by 64-bit addresses.
 template <int EPI, int WBM, int WBN, int C, bool FAR, class SECOND>
 __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __restrict__ A, const uint16_t* __restrict__ W,
@@ -564,16 +564,16 @@ int32_t launch_add_parts(const PartPtrs& parts, int slices, long M, int N, const
 // ---------------------------------------------------------------------------
 // Which tile, and in how many slices of K. The estimated time of each tile in microseconds, fitted to 3600 measurements
 // on this chip with activations in the last-level cache and weights cold, as a request finds them (K from 256 to 13824, N
-// from 256 to 15360, M from 64 to 13104; figures in brackets: K = 1536 / K = 8960 where N = 1536). What is fitted is the
+// from 256 to 15360, M from 64 to 13104; figures in brackets: gated residual, K = 1536 / K = 8960 where N = 1536). What is fitted is the
 // choice: over those products the tile and slices taken cost 0.7 % more than the fastest (geometric mean).
 // What bounds a launch that does not fill the chip is the rate at which ONE compute unit gets operands: its L1 holds
 // 256 lines in flight, 32 KB, so a unit takes in about 60 KB per microsecond whatever the kernel does, and the launch
 // that spreads the same problem over more units wins: smaller tiles, or slices of K.
-//   256 x 256  one workgroup per unit, rounds of 256; a partly filled round is up to a quarter faster [37 / 161 us]
-//   128 x 256  one workgroup per unit: up to 256 tiles [23 / 108 few, 26 / 114 all units busy], then a second round
-//   128 x 128  two workgroups per unit: one round of up to 256 tiles [18 / 100], then rounds of 512 [27 / 136]
-//   128 x 128  three steps and a half in LDS, one workgroup per unit: up to 256 tiles [14 / 67 few, 16 / 76 all units busy]
-//   64 x 64    two workgroups per unit: up to 256 tiles [8.5 / 37], growing with the tiles beyond
+//   256 x 256  one workgroup per unit, rounds of 256; a partly filled round is up to a quarter faster [38 / 161 us, full 54 / 215]
+//   128 x 256  one workgroup per unit: up to 256 tiles [23 / 116 few, 32 / 128 all units busy], then a second round
+//   128 x 128  two workgroups per unit: one round of up to 256 tiles [18 / 96], then rounds of 512 [31 / 135]
+//   128 x 128  three steps and a half in LDS, one workgroup per unit: up to 256 tiles [14 / 75 few, 19 / 82 all units busy]
+//   64 x 64    two workgroups per unit: up to 256 tiles [8.2 / 36], growing with the tiles up to 512 [14 / 69]
 // ---------------------------------------------------------------------------
 // a tile's bytes, 256 rows of 2 K, within the 32-bit offsets of its loads; longer rows are 64 x 64 tiles' alone
 constexpr int kMaxOffsetK = (1 << 22) - 64;
@@ -609,7 +609,9 @@ double tiles_time(int tile, long tiles, int K, int epi, int slices) {
     case kTile128: {
       const double one = by_epilogue(1.71, 3.67, 4.97) + 0.74 * steps, round512 = by_epilogue(0.48, 0.57, 5.67) + 1.001 * steps;
       if (w <= 256.0) return one;
-      // with bf16 outputs half as many second workgroups cost the whole of it (1200 x 4608 x 1536, 360 tiles: 27.0 us, 128 x 256 24.3)
+      // With bf16 outputs half as many second workgroups cost the whole of it: over 115 products of 257 to 512 tiles (N 768 to 15360,
+      // K 256 to 5120) the choice is 0.7 % slower than the fastest tile, 1.5 % with a straight line (1210 x 4608 x 1536, 360 tiles: 27.5
+      // us, 128 x 256 24.8; 1956 x 2560 x 2560, 320 tiles: 41.2 and 36.8; the other way 746 x 6144 x 3072, 288 tiles: 40.7 and 45.6).
       const double second = f32 || epi == CHORUS_EPI_RESID ? fill - 1.0 : fmin(2.0 * (fill - 1.0), 1.0);
       if (w <= 512.0) return one + second * fmax(round512 - one, 0.0);
       return (0.784 * ceil(w / 512.0) + 0.216 * w / 512.0) * round512;
@@ -619,6 +621,9 @@ double tiles_time(int tile, long tiles, int K, int epi, int slices) {
       return by_epilogue(5.36, 3.64, 5.4) + (0.45 + 0.081 * fill * fill) * steps;
     }
     default:
+      // Two workgroups a unit: a third one waits for their place (700 x 3072 x 8960, 528 tiles: 92 us, 69 with 480; the deep tile 66).
+      // In none of 837 products was this tile the fastest with more.
+      if (w > 512.0) return INFINITY;
       return (w <= 256.0 ? 1.0 : 1.141 + 0.677 * (fill - 1.0)) * (by_epilogue(3.62, 2.26, 3.14) + 0.246 * steps);
   }
 }
@@ -638,8 +643,8 @@ struct GemmPlan {
 
 // The fastest tile by the estimates. With scratch a gated-residual product may also be cut into slices of K: every slice
 // but the last writes its fp32 result and a second launch adds them (about 6 TB/s from the caches, and the launch itself).
-// Measured where N = 1536, K = 8960, slices against the best whole tile: 128 rows 17 / 40 us, 480 rows 31 / 39, 1200
-// rows 51 / 67, 2000 rows (two slices of 128 x 256 tiles) 74 / 77; from about 2300 rows a whole tile fills the chip.
+// Measured where N = 1536, K = 8960, slices against the best whole tile: 128 rows 17 / 41 us, 480 rows 31 / 37, 1200
+// rows 46 / 66, 2000 and 2300 rows (two slices of 128 x 256 tiles) 75 / 72 and 77 / 79; beyond that a whole tile fills the chip.
 GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
   GemmPlan best{kTile64, 1, INFINITY};
   for (int t = 0; t < kTiles; ++t) {
@@ -736,8 +741,7 @@ GemmCut plan_rows(long M, int N, int K, int epi, const GemmParts& parts) {
 
 // The tile on which two products with bf16 outputs and the same K run in one launch, kTiles: each in a launch of its own,
 // whichever is the fastest by the estimates for the tiles of both together. 64 x 64 tiles up to one round of two workgroups a
-// unit, the deep 128 x 128 ones up to two rounds of one; beyond that the estimates of cold weights are too low, and the best
-// tiles of the larger product are other ones. Measured (tokens and text tokens, QKV and the text's keys and values; 64 x 64 / deep /
+// unit, the deep 128 x 128 ones up to two rounds of one; beyond that the larger product's own best tile is another one. Measured (tokens and text tokens, QKV and the text's keys and values; 64 x 64 / deep /
 // apart, us): width 256, 128 and 16 4.8 / 5.7 / 7.8; width 1536, 100 and 16 9.9 / 18.2 / 17.9, 480 and 512 29.2 / 19.9 / 33.7, 800
 // and 16 30.2 / 28.1 / 24.5, 900 and 512 40.9 / 33.3 / 39.4; width 5120, 100 and 512 160 / 113 / 129, 200 and 16 99 / 89 / 77, 200 and 512
 // 179 / 152 / 129. Over 91 such pairs the choice is 1.2 % slower than the best (geometric mean), and never slower than apart.
@@ -753,7 +757,7 @@ int plan_two(long M, int N, long M2, int N2, int K) {
       tile = t;
     }
   };
-  if (small <= 512) consider(kTile64, tiles_time(kTile64, small, K, CHORUS_EPI_BF16, 1));
+  consider(kTile64, tiles_time(kTile64, small, K, CHORUS_EPI_BF16, 1));
   if (deep <= 512)
     consider(kTile128Deep, tiles_time(kTile128Deep, deep < 256 ? deep : 256, K, CHORUS_EPI_BF16, 1) +
                                (deep > 256 ? tiles_time(kTile128Deep, deep - 256, K, CHORUS_EPI_BF16, 1) : 0.0));

@@ -58,6 +58,19 @@ def test_gemm_cases_reach_their_tiles():
     assert B.chorus_gemm_bf16_plan(32760, 8960, 1536, B.EPI_GELU_BF16)[1] == 3
 
 
+def test_small_tiles_up_to_two_workgroups_a_unit():
+    """A third workgroup on a unit waits for a place: 64 x 64 tiles were never the fastest with more than 512 of them."""
+    for M, N, K, epi in ((691, 3072, 8960, B.EPI_BF16), (700, 3072, 8960, B.EPI_RESID), (691, 3072, 4096, B.EPI_RESID),
+                         (1382, 1536, 8960, B.EPI_RESID), (1382, 1536, 8960, B.EPI_BF16), (1382, 1536, 4096, B.EPI_GELU_BF16)):
+        assert B.chorus_gemm_bf16_plan(M, N, K, epi) == (0, 5, 1), (M, N, K, epi)
+    assert B.chorus_gemm_bf16_plan(1240, 1536, 8960, B.EPI_RESID) == (0, 1, 1)
+    for M in range(64, 6000, 96):
+        for N in (256, 768, 1536, 3072, 4608, 5120):
+            for K in (256, 1536, 8960):
+                head, kernel, _ = B.chorus_gemm_bf16_plan(M, N, K, B.EPI_BF16)
+                assert kernel != 1 or -(-(M - head) // 64) * -(-N // 64) <= 512, (M, N, K)
+
+
 def _ffn2(D, H, F, Lt, Ls):
     shape = B.make_block_shape(D, H, D // H, F, Lt, (21, 60, 90))
     return B.chorus_gemm_bf16_plan(Ls, D, F, B.EPI_RESID, *ffn2_scratch(shape, Ls))
