@@ -721,7 +721,8 @@ int32_t check_gemm(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, i
 // The whole choice: the first head_rows rows in whole rounds of 256 x 256 tiles (0: no cut), the others by `rest`. A last
 // round of 256 x 256 tiles that fills a small part of the chip costs most of a whole round. The rows can be cut instead:
 // the row tiles that make up whole rounds go to the 256 x 256 kernel, the rows left over to whichever kernel suits that many
-// rows, in a second launch behind the first. Taken when the estimate is better by 5 %.
+// rows, in a second launch behind the first. Taken when the estimate is better by 5 %; with up to three k-steps it was slower
+// wherever it was taken (gated residual, 22 products with K = 64 and 128: 1.06 to 1.16 times; 4500 x 4608 x 128 36 us, whole 31).
 struct GemmCut {
   long head_rows;
   GemmPlan rest;
@@ -730,7 +731,7 @@ struct GemmCut {
 GemmCut plan_rows(long M, int N, int K, int epi, const GemmParts& parts) {
   const GemmPlan whole = plan_gemm(M, N, K, epi, parts);
   const long tiles_n256 = (N + 255) / 256, tiles256 = ((M + 255) / 256) * tiles_n256;
-  const long head_rows = tiles256 > 256 ? (tiles256 / 256 * 256 / tiles_n256) * 256 : 0;
+  const long head_rows = tiles256 > 256 && K >= 4 * BK ? (tiles256 / 256 * 256 / tiles_n256) * 256 : 0;
   if (head_rows > 0 && head_rows < M) {
     const GemmPlan tail = plan_gemm(M - head_rows, N, K, epi, kNoParts);
     const double time = tile_time(kTile256, head_rows, N, K, epi, 1) + tail.time;

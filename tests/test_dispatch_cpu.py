@@ -58,6 +58,15 @@ def test_gemm_cases_reach_their_tiles():
     assert B.chorus_gemm_bf16_plan(32760, 8960, 1536, B.EPI_GELU_BF16)[1] == 3
 
 
+def test_rows_are_not_cut_with_few_steps():
+    for M, N in ((3700, 4608), (4500, 4608), (8000, 4608), (13104, 1536), (2300, 8960), (30000, 768)):
+        for K in (64, 128, 192):
+            for epi in range(4):
+                head, kernel, _ = B.chorus_gemm_bf16_plan(M, N, K, epi)
+                assert head == 0 and (epi < B.EPI_F32 or kernel == 4), (M, N, K, epi)
+    assert B.chorus_gemm_bf16_plan(3700, 4608, 256, B.EPI_RESID)[0] == 3584
+
+
 def test_small_tiles_up_to_two_workgroups_a_unit():
     """A third workgroup on a unit waits for a place: 64 x 64 tiles were never the fastest with more than 512 of them."""
     for M, N, K, epi in ((691, 3072, 8960, B.EPI_BF16), (700, 3072, 8960, B.EPI_RESID), (691, 3072, 4096, B.EPI_RESID),
