@@ -95,7 +95,7 @@ __device__ __forceinline__ uint64_t meet(uint64_t best) {
 // second launch for that took 2.3 us (1000 x 768, the call 8.8 us, now 5.6) to 3.9 (4096 x 4096 from HBM 17.3, now 14.8; 1024 x
 // 4096 8.9 and 7.5). What is behind the scan is a chain of latencies, so the values that meet are one integer each, whose
 // maximum over a wave stays in registers (compared as pairs through the LDS crossbar the calls took 16.0 and 9.0 us).
-__global__ __launch_bounds__(kWaves * 64) void lookup_kernel(const float* __restrict__ cache, const float* __restrict__ query,
+__global__ __launch_bounds__(kWaves * 64) void lookup_scan_kernel(const float* __restrict__ cache, const float* __restrict__ query,
                                                              long N, int d, float tau, uint64_t number, int rounds,
                                                              LookupSlot* slots, chorus_lookup_result* __restrict__ out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -146,7 +146,7 @@ __global__ __launch_bounds__(kWaves * 64) void lookup_kernel(const float* __rest
 }
 
 // In two launches, where nothing waits.
-__global__ __launch_bounds__(kWavesTwo * 64) void lookup_scan_kernel(const float* __restrict__ cache,
+__global__ __launch_bounds__(kWavesTwo * 64) void lookup_rows_kernel(const float* __restrict__ cache,
                                                                      const float* __restrict__ query, long N, int d,
                                                                      uint64_t* __restrict__ keys) {
   uint64_t best = 0;
@@ -197,12 +197,12 @@ int32_t launch_lookup(const float* cache_emb, long N, int d, const float* query,
   if (N <= 0) {
     hipLaunchKernelGGL(lookup_none_kernel, dim3(1), dim3(1), 0, s, out);
   } else if ((size_t)N * (size_t)d <= kMaxWaitValues && !is_captured(s)) {
-    hipLaunchKernelGGL(lookup_kernel, dim3((unsigned)scan_blocks(N, kWaves, kMaxScanBlocks) + 1), dim3(kWaves * 64), 0, s, cache_emb,
+    hipLaunchKernelGGL(lookup_scan_kernel, dim3((unsigned)scan_blocks(N, kWaves, kMaxScanBlocks) + 1), dim3(kWaves * 64), 0, s, cache_emb,
                        query, N, d, tau, launch_number(), rounds, reinterpret_cast<LookupSlot*>(slots), out);
   } else {
     const int n = scan_blocks(N, kWavesTwo, kMaxScanBlocksTwo);
     uint64_t* keys = reinterpret_cast<uint64_t*>(slots);
-    hipLaunchKernelGGL(lookup_scan_kernel, dim3((unsigned)n), dim3(kWavesTwo * 64), 0, s, cache_emb, query, N, d, keys);
+    hipLaunchKernelGGL(lookup_rows_kernel, dim3((unsigned)n), dim3(kWavesTwo * 64), 0, s, cache_emb, query, N, d, keys);
     CHORUS_LAUNCH_CHECK();
     hipLaunchKernelGGL(lookup_collect_kernel, dim3(1), dim3(kWaves * 64), 0, s, keys, n, query, d, tau, out);
   }

@@ -119,7 +119,8 @@ def test_workspace_sizes_scale_with_rows():
     a = lib.chorus_dit_block_workspace_bytes(C.byref(sh), 13104)
     b = lib.chorus_dit_block_workspace_bytes(C.byref(sh), 32760)
     assert 0 < a < b < 3 * (1 << 30)
-    # the scan leaves 8 bytes per workgroup of four rows (at most 4096 workgroups) behind a 256-byte header
+    # behind a 256-byte header the scan leaves 8 bytes per workgroup of four rows as two launches (at most 4096 of them), 16 per eight
+    # rows as one (at most 2048)
     assert lib.chorus_cache_lookup_workspace_bytes(4096) >= 256 + 1024 * 8
     assert lib.chorus_cache_lookup_workspace_bytes(1 << 24) == lib.chorus_cache_lookup_workspace_bytes(1 << 20) >= 256 + 4096 * 8
     assert lib.chorus_cache_lookup_workspace_bytes(0) >= 256
