@@ -133,6 +133,19 @@ int32_t chorus_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* V
                          const float* col_scale, int64_t Lq, int64_t Lk, int64_t LqPad, int64_t LkPad, int32_t H,
                          int32_t dh, int32_t variant, void* stream);
 
+/* Self-attention on pre-scaled queries (as variant 6, the same layouts, L = Lq = Lk, LPad % 128 == 0) with its last tiles in slices
+ * of the keys, as a block runs it where chorus_attention_slices_plan says so; for tests and comparisons. The first `whole` of the
+ * ceil(L / 256) H tiles of 256 queries (row tiles fastest) run as they do there, the others in `slices` (2 to the number of 128-key
+ * tiles) workgroups each. scratch: 16-byte aligned device memory, 139264 bytes (73728 for heads of 64) for every slice of a
+ * tile but one, and 4 bytes for each of them and 8 for each tile, rounded up to 256; CHORUS_E_WORKSPACE if it is smaller. */
+int32_t chorus_attention_slices(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, int64_t L, int64_t LPad,
+                                int32_t H, int32_t dh, int64_t whole, int32_t slices, void* scratch, size_t scratch_bytes,
+                                void* stream);
+/* What a block's self-attention over L tokens (512 or more) does on a GPU of `cus` compute units with two pieces of scratch: *slices
+ * 0: chorus_attention's variant 6; else the tiles from *whole on in that many slices. Host only. */
+int32_t chorus_attention_slices_plan(int64_t L, int32_t H, int32_t dh, int32_t cus, size_t first_bytes, size_t rest_bytes,
+                                     int64_t* whole, int32_t* slices);
+
 /* ------------------------------------------------------------------------
  * Step glue (stand-ins that close the denoising loop around the blocks; the
  * paper's sampler is DPM++ with default settings, whose coefficients it does not

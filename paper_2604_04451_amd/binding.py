@@ -164,6 +164,8 @@ def _bind_ops(lib):
         "chorus_v_transpose": (i32, [vp, i64, vp, i64, i64, i32, vp]),
         "chorus_attention_variant": (i32, [i64, i64, i64, i32, i32, i32, i32]),
         "chorus_attention": (i32, [vp, vp, vp, vp, vp, i64, i64, i64, i64, i32, i32, i32, vp]),
+        "chorus_attention_slices": (i32, [vp, vp, vp, vp, i64, i64, i32, i32, i64, i32, vp, sz, vp]),
+        "chorus_attention_slices_plan": (i32, [i64, i32, i32, i32, sz, sz, C.POINTER(i64), C.POINTER(i32)]),
         "chorus_glue_workspace_bytes": (sz, [i32, i32, i64]),
         "chorus_patch_embed": (i32, [vp, i32, i32, i32, i32, i32, i32, vp, i64, GW, i32, vp, vp, sz, vp]),
         "chorus_head_update": (i32, [vp, vp, i64, vp, GW, vp, f32, i32, i32, i32, i32, i32, i32, i32, vp, sz, vp]),
@@ -655,6 +657,28 @@ def chorus_attention(Q, K, Vt, O, col_scale, Lq, Lk, variant=0):
     _status("chorus_attention", lib.chorus_attention(_p(Q), _p(K), _p(Vt), _p(O), _p(col_scale), Lq, Lk, LqPad, LkPad,
                                                      H, dh, int(variant), _stream()))
     return O
+
+
+def chorus_attention_slices(Q, K, Vt, O, L, whole, slices, scratch):
+    """Self-attention of pre-scaled queries whose tiles from `whole` on run in slices of the keys; scratch uint8."""
+    lib = load()
+    for n, t in (("Q", Q), ("K", K), ("Vt", Vt), ("O", O)):
+        _chk(t, torch.bfloat16, n)
+    H, LPad, dh = Q.shape
+    if K.shape != Q.shape or tuple(Vt.shape) != (H * dh, LPad) or O.shape[1] != H * dh or O.shape[0] < L:
+        raise TypeError("shape mismatch")
+    _chk(scratch, torch.uint8, "scratch")
+    _status("chorus_attention_slices", lib.chorus_attention_slices(_p(Q), _p(K), _p(Vt), _p(O), L, LPad, H, dh, int(whole),
+                                                                   int(slices), _p(scratch), scratch.numel(), _stream()))
+    return O
+
+
+def chorus_attention_slices_plan(L, H, dh, cus, first_bytes, rest_bytes):
+    """(tiles of 256 queries that run whole, slices of the others; 0: none) of a block's self-attention; host only."""
+    whole, slices = C.c_int64(-1), C.c_int32(-1)
+    _status("chorus_attention_slices_plan", load().chorus_attention_slices_plan(L, H, dh, cus, first_bytes, rest_bytes,
+                                                                                C.byref(whole), C.byref(slices)))
+    return whole.value, slices.value
 
 
 # ------------------------------------------------------------- step glue

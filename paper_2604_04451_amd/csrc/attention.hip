@@ -24,6 +24,7 @@
 // The running maximum is only refreshed when a tile exceeds it by more than 8
 // (in log2 units), which keeps exp2 arguments <= 8 and makes the accumulator
 // rescale rare; the final division by the row sum makes the result exact either way.
+#include "attention.h"
 #include "chorus_ops.h"
 #include "common.h"
 
@@ -286,6 +287,36 @@ __global__ __launch_bounds__(512, 2) void attention_pp_kernel(
   }
 }
 
+// Slices of the keys. A last round of tiles that leaves half of the compute units idle or more runs `slices` workgroups a tile, each over
+// its share of the 128-key tiles (`units`) and from a reference of its own; the last of a tile's workgroups to end puts it together:
+//   every workgroup takes a number (`ticket`); all but the last leave their unnormalised fp32 result, row sums and references in
+//   a slab and report it (`done`); the last keeps its own in registers, waits until the others have reported, and adds all of them
+//   in the order of their keys, so that the result does not depend on who was last.
+// The wait ends: it is for workgroups that have taken their number, which run and have nothing to wait for but their own stores.
+// Slabs and counts are agent-scope accesses past the L2s (the workgroups of a tile run on different XCDs); a slab is reported when its
+// stores have completed. ticket and done start at zero (attn_prepare clears them).
+struct KeySlices {
+  uint32_t* words;  // ticket [tiles], done [tiles], which slice a slab holds [tiles][slices - 1]; then slabs
+  float* slab1;     // the slabs that do not fit there
+  int tiles, slices, units;
+  int slab0, n0;    // where the first slab stands behind `words`, in 32-bit words, and how many stand there
+  static constexpr bool kSliced = true;
+};
+struct WholeKeys {
+  static constexpr bool kSliced = false;
+};
+// 8-byte words of one lane in a slab: the results in halves of four, then (reference, row sum) per block of rows
+constexpr int slab_words(int dh, int rb) { return (dh / 16 * 2 + 1) * rb; }
+
+__device__ __forceinline__ void store_pair(float* p, float a, float b) {
+  const uint64_t v = ((uint64_t)__float_as_uint(b) << 32) | __float_as_uint(a);
+  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 load_pair(const float* p) {
+  const uint64_t v = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float2(__uint_as_float((uint32_t)v), __uint_as_float((uint32_t)(v >> 32)));
+}
+
 // ---------------------------------------------------------------------------
 // The same ping-pong kernel on v_mfma_f32_16x16x32_bf16, 128-key tiles, no column scale. Per flop this shape writes
 // half the accumulator registers of the 32x32x16 one and a result block is accumulated by four MFMAs in a row (the
@@ -314,9 +345,9 @@ __global__ __launch_bounds__(512, 2) void attention_pp_kernel(
 // KIND 3 and 4 are 1 and 2 for fewer than 512 keys: the row sums are taken by the vector pipe, in fp32 over the
 // probabilities before they are rounded, as attention_pp_kernel takes them. Over a few tiles that costs next to nothing, and a
 // call has the same denominator whichever of the two kernels runs it.
-template <int DH, bool PRE, int RB, int KIND>
+template <int DH, bool PRE, int RB, int KIND, class KEYS>
 __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
-    const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ Vt,
+    KEYS keys_arg, const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K, const uint16_t* __restrict__ Vt,
     uint16_t* __restrict__ O, const float* __restrict__ col_scale, long Lq, long Lk, long LqPad, long LkPad, int H,
     int n_qtiles, int tile_base, float scale_log2) {
   constexpr bool CS = KIND == 2 || KIND == 4, SUM32 = KIND >= 3;
@@ -336,8 +367,17 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   uint16_t* smv = smk + 2 * KTL * KS;                      // [2][DH][VS]
   float* smc = reinterpret_cast<float*>(smv + 2 * DH * VS);  // [2][KTL]: the key factors of two tiles (CS)
 
-  // this launch covers the tiles tile_base .. tile_base + gridDim.x - 1 of the H * n_qtiles of its tile size
-  const int tile_id = tile_base + xcd_remap(blockIdx.x, gridDim.x);
+  // this launch covers the tiles tile_base .. tile_base + gridDim.x - 1 of the H * n_qtiles of its tile size, or in slices a
+  // keys.slices-th as many
+  int tile_id = tile_base + xcd_remap(blockIdx.x, gridDim.x), first_kt = 0;
+  if constexpr (KEYS::kSliced) {
+    const KeySlices& keys = keys_arg;
+    const int at = tile_id - tile_base, t = at / keys.slices, slice = at - t * keys.slices;
+    tile_id = tile_base + t;
+    first_kt = slice * keys.units / keys.slices;
+    const long end = (long)((slice + 1) * keys.units / keys.slices) * KTL;
+    Lk = (Lk < end ? Lk : end) - (long)first_kt * KTL;
+  }
   const int head = tile_id / n_qtiles;
   const int qt = tile_id - head * n_qtiles;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -345,8 +385,8 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   const int lq = lane & 15, g = lane >> 4;
   const long q_wave0 = (long)qt * QROWS + wave * 16 * RB;
 
-  const uint16_t* Kh = K + (long)head * LkPad * DH;
-  const uint16_t* Vh = Vt + (long)head * DH * LkPad;
+  const uint16_t* Kh = K + ((long)head * LkPad + (long)first_kt * KTL) * DH;
+  const uint16_t* Vh = Vt + (long)head * DH * LkPad + (long)first_kt * KTL;
 
   bf16x8 qf[RB][KC];
 #pragma unroll
@@ -640,6 +680,123 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   }
   if (group == 0) lds_barrier();  // every wave executes the same number of barriers
 
+  if constexpr (KEYS::kSliced) {
+    static_assert(PRE && !SUM32, "the references are those of scaled queries, the row sums the matrix pipe's");
+    constexpr int W = slab_words(DH, RB);
+    // What the thread's and the workgroup's ids give is made again here, and the arguments are read again, instead of kept across the
+    // loop: with a register more alive there its LDS reads lose their lead over the MFMAs (112 tiles of 13104 keys in halves 294 us, so
+    // about 150).
+    int tid = threadIdx.x, block = blockIdx.x;
+    typedef const __attribute__((address_space(4))) KeySlices* ArgPtr;
+    ArgPtr arg = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+v"(tid), "+s"(block), "+s"(arg));
+    const KeySlices keys{arg->words, arg->slab1, arg->tiles, arg->slices, arg->units, arg->slab0, arg->n0};
+    tid &= NT - 1;
+    const int lane = tid & 63, wave = tid >> 6;
+    const int place = xcd_remap(block, gridDim.x), slot = place / keys.slices, slice = place - slot * keys.slices;
+    uint32_t *const ticket = keys.words + slot, *const done = ticket + keys.tiles, *const slice_of = keys.words + 2 * keys.tiles;
+    const int others = keys.slices - 1, slab_first = slot * others;
+    uint32_t* flag = reinterpret_cast<uint32_t*>(smem_raw);
+    if (tid == 0) flag[0] = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int number = __builtin_amdgcn_readfirstlane((int)flag[0]);
+    auto slab = [&](int i) {
+      const int at = slab_first + i;
+      return (at < keys.n0 ? reinterpret_cast<float*>(keys.words + keys.slab0) + (size_t)at * W * 1024 : keys.slab1 + (size_t)(at - keys.n0) * W * 1024) +
+             ((size_t)wave * W * 64 + lane) * 2;
+    };
+    if (number < others) {
+      float* p = slab(number);
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          store_pair(p + 128 * (2 * (DB * rb + db)), o[db][rb][0], o[db][rb][1]);
+          store_pair(p + 128 * (2 * (DB * rb + db) + 1), o[db][rb][2], o[db][rb][3]);
+        }
+        store_pair(p + 128 * (2 * DB * RB + rb), m_run[rb], lacc[rb][0]);
+      }
+      if (tid == 0) __hip_atomic_store(&slice_of[slab_first + number], (uint32_t)slice, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's stores have completed, past the L2
+      __syncthreads();
+      if (tid == 0) __hip_atomic_fetch_add(done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    if (tid == 0)
+      while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint32_t)others) __builtin_amdgcn_s_sleep(2);
+    __syncthreads();
+    asm volatile("" ::: "memory");  // the slabs are read behind the count
+    // the largest reference, then the slices in the order of their keys, half of the results at a time
+    float m_all[RB], own_l[RB];
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      m_all[rb] = m_run[rb];
+      own_l[rb] = lacc[rb][0];
+    }
+#pragma unroll 1
+    for (int i = 0; i < others; ++i)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) m_all[rb] = fmaxf(m_all[rb], load_pair(slab(i) + 128 * (2 * DB * RB + rb)).x);
+    constexpr int HB = DB / 2;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      f32x4 sum[HB][RB];
+      float l[RB];
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        l[rb] = 0.f;
+#pragma unroll
+        for (int db = 0; db < HB; ++db) sum[db][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll 1
+      for (int sl = 0; sl <= others; ++sl) {
+        // fused multiply-adds by name: both branches round alike
+        if (sl == slice) {
+#pragma unroll
+          for (int rb = 0; rb < RB; ++rb) {
+            const float f = __builtin_amdgcn_exp2f(m_run[rb] - m_all[rb]);
+            l[rb] = __builtin_fmaf(f, own_l[rb], l[rb]);
+#pragma unroll
+            for (int db = 0; db < HB; ++db)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) sum[db][rb][e] = __builtin_fmaf(f, o[HB * half + db][rb][e], sum[db][rb][e]);
+          }
+          continue;
+        }
+        int i = 0;
+        while (i + 1 < others &&
+               __hip_atomic_load(&slice_of[slab_first + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint32_t)sl)
+          ++i;
+        const float* p = slab(__builtin_amdgcn_readfirstlane(i));
+        float2 ml[RB], v[2 * HB * RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          ml[rb] = load_pair(p + 128 * (2 * DB * RB + rb));
+#pragma unroll
+          for (int k = 0; k < 2 * HB; ++k) v[2 * HB * rb + k] = load_pair(p + 128 * (2 * (DB * rb + HB * half) + k));
+        }
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          const float f = __builtin_amdgcn_exp2f(ml[rb].x - m_all[rb]);
+          l[rb] = __builtin_fmaf(f, ml[rb].y, l[rb]);
+#pragma unroll
+          for (int db = 0; db < HB; ++db) {
+            const float2 a = v[2 * (HB * rb + db)], b = v[2 * (HB * rb + db) + 1];
+            const f32x4 w = {a.x, a.y, b.x, b.y};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sum[db][rb][e] = __builtin_fmaf(f, w[e], sum[db][rb][e]);
+          }
+        }
+      }
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        lacc[rb][0] = l[rb];
+#pragma unroll
+        for (int db = 0; db < HB; ++db) o[HB * half + db][rb] = sum[db][rb];
+      }
+    }
+  }
+
   const int D = H * DH;
 #pragma unroll
   for (int rb = 0; rb < RB; ++rb) {
@@ -664,17 +821,17 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   }
 }
 
-// One launch of the 16x16x32 kernel with RB blocks of 16 query rows per wave over the tiles tile_base .. + ntile - 1.
-template <int DH, bool PRE, int RB, int KIND>
+// One launch of the 16x16x32 kernel with RB blocks of 16 query rows per wave over the tiles from tile_base on, a workgroup a tile or a slice of one.
+template <int DH, bool PRE, int RB, int KIND, class KEYS = WholeKeys>
 int32_t launch_attn_pp16_tiles(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* cs,
-                               long Lq, long Lk, long LqPad, long LkPad, int H, long nqt, long tile_base, long ntile,
-                               hipStream_t s) {
+                               long Lq, long Lk, long LqPad, long LkPad, int H, long nqt, long tile_base, long groups,
+                               hipStream_t s, KEYS keys = KEYS{}) {
   size_t smem = 2 * ((size_t)128 * (DH + 16) + (size_t)DH * (128 + 16)) * sizeof(uint16_t) + (KIND == 2 || KIND == 4 ? 2 * 128 * sizeof(float) : 0);
-  auto kern = attention_pp16_kernel<DH, PRE, RB, KIND>;
+  auto kern = attention_pp16_kernel<DH, PRE, RB, KIND, KEYS>;
   static DynLdsOnce once;  // the raised dynamic-LDS limit is a per-device property of the kernel
   CHK_STATUS(once.ensure(reinterpret_cast<const void*>(kern), (int)smem));
   const float scale_log2 = 1.4426950408889634f / sqrtf((float)DH);
-  hipLaunchKernelGGL(kern, dim3((unsigned)ntile), dim3(512), smem, s, Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H,
+  hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(512), smem, s, keys, Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H,
                      (int)nqt, (int)tile_base, scale_log2);
   CHORUS_LAUNCH_CHECK();
   return CHORUS_OK;
@@ -684,16 +841,16 @@ int32_t launch_attn_pp16_tiles(const uint16_t* Q, const uint16_t* K, const uint1
 // 36.2 -> 24.8 us). Else 256 query rows per workgroup. One workgroup fits a CU, so a launch runs in rounds of as many workgroups as the device
 // has CUs. When the last round would be at most half full, its tiles run as workgroups of 128 rows instead (one block
 // of 16 rows per wave: the same K / V stream for half the arithmetic, 0.63-0.67 of a full workgroup's time), twice as
-// many of them, in a second launch behind the first: the partly filled round then takes two thirds of a full one.
+// many of them, in a second launch behind the first: the partly filled round then takes two thirds of a full one. (With scratch, as a
+// block has it, and long keys the last round runs in slices instead: attention_slices.)
 template <int DH, bool PRE, int KIND>
 int32_t launch_attn_pp16_kind(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* cs, long Lq,
                               long Lk, long LqPad, long LkPad, int H, hipStream_t s) {
   const long nqt = (Lq + 255) / 256;
   const long tiles = nqt * H;
   if (2 * tiles > 0x7fffffffL) return CHORUS_E_SHAPE;
-  int dev = 0, cus = 0;
-  CHORUS_HIP(hipGetDevice(&dev));
-  CHORUS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  const int cus = device_cus();
+  if (cus < 0) return cus;
   if (2 * tiles <= cus)
     return launch_attn_pp16_tiles<DH, PRE, 1, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, 2 * nqt, 0, 2 * tiles, s);
   const long tail = cus > 0 ? tiles % cus : 0;
@@ -752,10 +909,110 @@ int attention_variant(long Lq, long Lk, long LkPad, int H, int dh, bool factor, 
   return (factor ? Lk <= 96 || Lk > 128 : Lk > 128 && tiles > cus) ? 5 : 3;
 }
 
+// Counts, slice numbers, then a slab for every slice of a tile but one.
+struct SliceScratch {
+  size_t counts, slab;
+  long slabs;
+};
+SliceScratch slice_scratch(int dh, int sliced, int slices) {
+  const long slabs = (long)sliced * (slices - 1);
+  return SliceScratch{align_up((size_t)(2L * sliced + slabs) * 4, 256), (size_t)slab_words(dh, 2) * 512 * 8, slabs};
+}
+bool slices_fit(const SliceScratch& r, const AttnScratch& sc) {
+  if (!sc.first || !aligned16(sc.first) || !aligned16(sc.rest) || sc.first_bytes < r.counts) return false;
+  return (long)((sc.first_bytes - r.counts) / r.slab + (sc.rest ? sc.rest_bytes / r.slab : 0)) >= r.slabs;
+}
+
+template <int DH>
+int32_t launch_attn_sliced(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, long L, long LPad, int H,
+                           const AttnSlices& p, const AttnScratch& sc, hipStream_t s) {
+  const long nqt = (L + 255) / 256;
+  const SliceScratch r = slice_scratch(DH, p.sliced, p.slices);
+  if (!slices_fit(r, sc)) return CHORUS_E_WORKSPACE;
+  if (p.whole > 0) CHK_STATUS((launch_attn_pp16_tiles<DH, true, 2, 0>(Q, K, Vt, O, nullptr, L, L, LPad, LPad, H, nqt, 0, p.whole, s)));
+  const KeySlices keys{static_cast<uint32_t*>(sc.first), static_cast<float*>(sc.rest), p.sliced, p.slices, (int)((L + 127) / 128),
+                       (int)(r.counts / 4), (int)((sc.first_bytes - r.counts) / r.slab)};
+  return launch_attn_pp16_tiles<DH, true, 2, 0, KeySlices>(Q, K, Vt, O, nullptr, L, L, LPad, LPad, H, nqt, p.whole,
+                                                           (long)p.sliced * p.slices, s, keys);
+}
+
+__global__ __launch_bounds__(256) void clear_words_kernel(uint32_t* p, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) p[i] = 0;
+}
+
+// Five slices and more were never faster by more than 1 us.
+constexpr int kMaxKeySlices = 4;
+
 }  // namespace
+
+int device_cus() {
+  int dev = 0, cus = 0;
+  CHORUS_HIP(hipGetDevice(&dev));
+  CHORUS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+  return cus;
+}
+
+// The tiles of a last round that fills half of the chip or less: in as many slices as there are units for, four at most, where the sweep
+// over the keys is long enough for what a slice costs beside it, about 20 us of chip time (its first loads, the ping-pong's start
+// and end, and 139 KB a slab out and in). Whole call, halves of 128 rows as before / slices, us: 13104 tokens, 12 heads (112 tiles, two
+// slices) 853 / 786; 8100 (128, two) 329 / 311; 5632 (8, four; 44 key tiles) 216 / 190, in two slices 208; 6000 (32, four) 230 / 202; 40
+// heads: 7168 tokens (96, two) 802 / 793, 3300 (8, four; 26 key tiles) 221 / 212, 2000 (64, three; 16) 91 / 90; 4 heads of 64, 3584 tokens
+// (56, four; 28) 30.6 / 28. Slower: 2560 tokens, 12 heads (120, two; 20 key tiles) 44 / 43 to 45, 1792, 40 heads (24, four; 14) 82 / 84.
+AttnSlices attention_slices(long L, int H, int dh, int cus, const AttnScratch& scratch) {
+  const AttnSlices none{0, 0, 0};
+  const long tiles = (L + 255) / 256 * H, units = (L + 127) / 128;
+  if (cus <= 0 || tiles > 0x7fffffffL / 2) return none;
+  const long sliced = tiles % cus;
+  if (sliced == 0 || 2 * sliced > cus) return none;
+  for (int slices = (int)(cus / sliced < kMaxKeySlices ? cus / sliced : kMaxKeySlices); slices >= 2; --slices)
+    if (slices_fit(slice_scratch(dh, (int)sliced, slices), scratch))
+      return units < (slices == 2 ? 40 : 24) ? none : AttnSlices{tiles - sliced, (int)sliced, slices};
+  return none;
+}
+
+int32_t attention_sliced(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, long L, long LPad, int H, int dh,
+                         const AttnSlices& plan, const AttnScratch& scratch, void* stream) {
+  return dh == 128 ? launch_attn_sliced<128>(Q, K, Vt, O, L, LPad, H, plan, scratch, (hipStream_t)stream)
+                   : launch_attn_sliced<64>(Q, K, Vt, O, L, LPad, H, plan, scratch, (hipStream_t)stream);
+}
+
 }  // namespace chorus
 
 using namespace chorus;
+
+extern "C" int32_t chorus_attention_slices(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, int64_t L,
+                                           int64_t LPad, int32_t H, int32_t dh, int64_t whole, int32_t slices, void* scratch,
+                                           size_t scratch_bytes, void* stream) {
+  if (L < 0 || H <= 0 || whole < 0 || slices < 2) return CHORUS_E_ARG;
+  if (L == 0) return CHORUS_OK;
+  if (!Q || !K || !Vt || !O) return CHORUS_E_ARG;
+  if ((dh != 64 && dh != 128) || LPad < L || LPad % 128 || LPad > 0x7fffffffL) return CHORUS_E_SHAPE;
+  if (!aligned16(Q) || !aligned16(K) || !aligned16(Vt) || !aligned16(O)) return CHORUS_E_ARG;
+  const long tiles = ((long)L + 255) / 256 * H, units = ((long)L + 127) / 128;
+  if (whole >= tiles || slices > units || (tiles - whole) * slices > 65536) return CHORUS_E_SHAPE;
+  if (!scratch || !aligned16(scratch)) return CHORUS_E_WORKSPACE;
+  const AttnScratch sc{scratch, scratch_bytes, nullptr, 0};
+  const AttnSlices plan{(long)whole, (int)(tiles - whole), slices};
+  if (!slices_fit(slice_scratch(dh, plan.sliced, slices), sc)) return CHORUS_E_WORKSPACE;
+  const int words = attention_slices_words(plan);
+  hipLaunchKernelGGL(clear_words_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
+                     static_cast<uint32_t*>(scratch), words);
+  CHORUS_LAUNCH_CHECK();
+  return attention_sliced(Q, K, Vt, O, (long)L, (long)LPad, H, dh, plan, sc, stream);
+}
+
+extern "C" int32_t chorus_attention_slices_plan(int64_t L, int32_t H, int32_t dh, int32_t cus, size_t first_bytes, size_t rest_bytes,
+                                                int64_t* whole, int32_t* slices) {
+  if (L < 1 || H <= 0 || cus <= 0 || !whole || !slices) return CHORUS_E_ARG;
+  if (dh != 64 && dh != 128) return CHORUS_E_SHAPE;
+  void* some = reinterpret_cast<void*>(uintptr_t{16});  // where the scratch lies does not matter
+  const AttnSlices p = attention_slices((long)L, H, dh, cus, AttnScratch{first_bytes ? some : nullptr, first_bytes,
+                                                                         rest_bytes ? some : nullptr, rest_bytes});
+  *whole = p.whole;
+  *slices = p.slices;
+  return CHORUS_OK;
+}
 
 extern "C" int32_t chorus_attention_variant(int64_t Lq, int64_t Lk, int64_t LkPad, int32_t H, int32_t dh, int32_t factor, int32_t cus) {
   if (Lq < 1 || Lk < 1 || LkPad < Lk || H <= 0 || cus <= 0) return CHORUS_E_ARG;
@@ -778,9 +1035,8 @@ extern "C" int32_t chorus_attention(const uint16_t* Q, const uint16_t* K, const 
   hipStream_t s = (hipStream_t)stream;
   const bool cs = col_scale != nullptr;
   if (variant == 0) {
-    int dev = 0, cus = 0;
-    CHORUS_HIP(hipGetDevice(&dev));
-    CHORUS_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
+    const int cus = device_cus();
+    if (cus < 0) return cus;
     variant = attention_variant((long)Lq, (long)Lk, (long)LkPad, H, dh, cs, cus);
   }
   if (variant == 5 || variant == 6) {

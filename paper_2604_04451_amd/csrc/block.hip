@@ -3,6 +3,7 @@
 // allocation). Also the optional per-kernel event timing used by benchmarks.
 #include <vector>
 
+#include "attention.h"
 #include "chorus_ops.h"
 #include "common.h"
 #include "gemm.h"
@@ -59,6 +60,7 @@ struct BlockWs {
   uint16_t* kc;     // [H, LtPad, dh]
   uint16_t* vct;    // [D, LtPad]
   size_t bytes;
+  AttnScratch attn;     // for self-attention: h, and the projection once its queries, keys and values are prepared
   GemmParts ffn_parts;  // what the second FFN product may use for slices of K: h and ao, and everything behind the FFN hidden
 };
 
@@ -91,6 +93,7 @@ BlockWs carve(const chorus_block_shape& sh, long Ls, void* base) {
   w.kc = take(LtPad * D);
   w.vct = take(LtPad * D);
   w.bytes = off;
+  w.attn = AttnScratch{w.h, (size_t)Ls * D * 2, w.qkv, (size_t)Ls * 3 * D * 2};
   w.ffn_parts = GemmParts{w.h, a0, p + a0 + ffn_bytes, w.bytes - a0 - ffn_bytes};
   return w;
 }
@@ -217,18 +220,28 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   // Attention over 512 keys or more takes its queries already multiplied by log2(e) / sqrt(dh): the factor enters here, in
   // fp32 ahead of the one rounding to bf16. Over fewer keys they are the plain queries whichever kernel runs it.
   const bool q_prescaled = CHORUS_ATTENTION_LONG_KEYS(Ls, Lpad);
+  AttnSlices slices{0, 0, 0};
+  if (q_prescaled) {
+    const int cus = device_cus();
+    if (cus < 0) return cus;
+    slices = attention_slices(Ls, H, dh, cus, b.attn);
+  }
   {
     ProfScope p(CHORUS_PROF_NORM, s);
     if (!w->g_q || !w->g_k || !aligned16(w->g_q) || !aligned16(w->g_k)) return CHORUS_E_ARG;
     if (!text_kv && (!w->g_ck || !aligned16(w->g_ck))) return CHORUS_E_ARG;
     const PrepareText text{b.tkv, b.tkv + D, 2L * D, w->g_ck, b.kc, b.vct, Lt, LtPad};
     CHK(attn_prepare(b.qkv, b.qkv + D, b.qkv + 2 * D, 3L * D, w->g_q, w->g_k, b.qh, b.kh, b.vt, Ls, Lpad, H, dh, token_idx, sh.gH,
-                     sh.gW, 1, q_prescaled ? CHORUS_ATTENTION_Q_PRESCALE(dh) : 1.0f, stream, text_kv ? nullptr : &text));
+                     sh.gW, 1, q_prescaled ? CHORUS_ATTENTION_Q_PRESCALE(dh) : 1.0f, stream, text_kv ? nullptr : &text,
+                     static_cast<uint32_t*>(b.attn.first), attention_slices_words(slices)));
   }
   // 4. self-attention over exactly the Ls rows, output projection, gated residual
   {
     ProfScope p(CHORUS_PROF_SELF_ATTN, s);
-    CHK(chorus_attention(b.qh, b.kh, b.vt, b.ao, nullptr, Ls, Ls, Lpad, Lpad, H, dh, q_prescaled ? 6 : 0, stream));
+    if (slices.slices)
+      CHK(attention_sliced(b.qh, b.kh, b.vt, b.ao, Ls, Lpad, H, dh, slices, b.attn, stream));
+    else
+      CHK(chorus_attention(b.qh, b.kh, b.vt, b.ao, nullptr, Ls, Ls, Lpad, Lpad, H, dh, q_prescaled ? 6 : 0, stream));
   }
   {
     ProfScope p(CHORUS_PROF_GEMM, s);

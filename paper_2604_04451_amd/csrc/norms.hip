@@ -284,7 +284,7 @@ __global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __res
                                                            uint16_t* __restrict__ vt, long L, long Lpad, int H, int dh,
                                                            const int* __restrict__ token_idx, int gH, int gW, int rope,
                                                            float q_scale, int row_blocks, int v_tiles, int first2,
-                                                           TEXT text) {
+                                                           uint32_t* __restrict__ clear, int n_clear, TEXT text) {
   __shared__ union {
     struct {
       float cos[4][64], sin[4][64];
@@ -292,6 +292,7 @@ __global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __res
     uint16_t tile[64][64 + 2];
   } sm;
   int block = blockIdx.x;
+  if (block == 0 && (int)threadIdx.x < n_clear) clear[threadIdx.x] = 0;
   if constexpr (std::is_same_v<TEXT, PrepareText>) {
     if (block >= first2) {  // the workgroups behind the tokens': the text
       block -= first2;
@@ -335,15 +336,15 @@ __global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __res
 
 int32_t attn_prepare(const uint16_t* q, const uint16_t* k, const uint16_t* v, long ld, const float* gain_q, const float* gain_k,
                      uint16_t* qh, uint16_t* kh, uint16_t* vt, long L, long Lpad, int H, int dh, const int32_t* token_idx, int gH,
-                     int gW, int rope, float q_scale, void* stream, const PrepareText* text) {
+                     int gW, int rope, float q_scale, void* stream, const PrepareText* text, uint32_t* clear, int n_clear) {
   const int D = H * dh;
   const long row_blocks = (Lpad + 3) / 4 * (q ? 2 : 1), v_tiles = Lpad / 64, first2 = row_blocks + v_tiles * (D / 64);
   const long blocks = first2 + (text ? (text->Lpad + 3) / 4 + text->Lpad / 64 * (D / 64) : 0);
-  if (blocks > 0x7fffffffL) return CHORUS_E_SHAPE;
+  if (blocks > 0x7fffffffL || n_clear > 256) return CHORUS_E_SHAPE;
 #define PREPARE_AS(NCH, TEXT, text)                                                                                           \
   hipLaunchKernelGGL((attn_prepare_kernel<NCH, TEXT>), dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, q, k, v, ld,  \
                      gain_q, gain_k, qh, kh, vt, L, Lpad, H, dh, token_idx, gH, gW, rope, q_scale, (int)row_blocks, (int)v_tiles, \
-                     (int)first2, text)
+                     (int)first2, clear, n_clear, text)
 #define PREPARE(NCH)                           \
   do {                                         \
     if (text)                                  \

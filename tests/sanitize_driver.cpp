@@ -127,6 +127,12 @@ static void sizes_and_validation() {
       EXPECT(plan.kernel >= 1 && plan.kernel <= 5 && plan.slices >= 1 && plan.slices <= 4 && plan.head_rows < m);
     }
   EXPECT(chorus_attention_variant(13104, 512, 512, 12, 128, 1, 256) == 5);
+  int64_t whole = -1;
+  int32_t slices = -1;
+  EXPECT(chorus_attention_slices_plan(13104, 12, 128, 256, 40u << 20, 120u << 20, &whole, &slices) == CHORUS_OK && whole == 512 && slices == 2);
+  EXPECT(chorus_attention_slices_plan(13104, 12, 128, 256, 0, 0, &whole, &slices) == CHORUS_OK && slices == 0);
+  EXPECT(chorus_attention_slices_plan(13104, 12, 96, 256, 0, 0, &whole, &slices) == CHORUS_E_SHAPE);
+  EXPECT(chorus_attention_slices(nullptr, nullptr, nullptr, nullptr, 1, 128, 1, 64, 0, 2, nullptr, 0, nullptr) == CHORUS_E_ARG);
   EXPECT(chorus_attention_variant(13104, 64, 64, 12, 128, 0, 256) == 3);
   EXPECT(chorus_attention((const uint16_t*)p16, (const uint16_t*)p16, (const uint16_t*)p16, (uint16_t*)p16, nullptr, 8, 8, 64, 64, 2, 96, 0, nullptr) == CHORUS_E_SHAPE);
   EXPECT(chorus_attention((const uint16_t*)p16, (const uint16_t*)p16, (const uint16_t*)p16, (uint16_t*)p16, nullptr, 8, 8, 64, 64, 2, 64, 2, nullptr) == CHORUS_E_ARG);

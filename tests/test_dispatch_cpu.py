@@ -25,6 +25,24 @@ def test_attention_long_and_short_keys(factor):
     assert _attention(13104, 400, 40, 128, factor) == (5 if factor else 3)
 
 
+def _slices(L, H, dh=128, first=None, rest=None):
+    D = H * dh  # a block's scratch: its normalised rows and its projection
+    return B.chorus_attention_slices_plan(L, H, dh, CUS, 2 * L * D if first is None else first, 6 * L * D if rest is None else rest)
+
+
+def test_attention_slices():
+    assert _slices(13104, 12) == (512, 2) and _slices(75600, 40) == (11776, 4) and _slices(8100, 12) == (256, 2)
+    assert _slices(32760, 12) == _slices(16380, 12) == (0, 0)          # whole rounds
+    assert _slices(3271, 12) == _slices(3000, 40) == (0, 0)            # a last round that is more than half full
+    assert _slices(1200, 12) == _slices(2560, 12) == _slices(1792, 40) == (0, 0)  # too few keys
+    assert _slices(5120, 3, 128, 1 << 30) == (0, 4) and _slices(5121, 4, 128, 1 << 30) == (0, 3)
+    assert _slices(5120, 3) == (0, 2) and _slices(3584, 4, 64) == (0, 0)  # as many slices as there is scratch for
+    need = 2 * 112 * 4 + 112 * 4
+    need = -(-need // 256) * 256 + 112 * 139264
+    assert _slices(13104, 12, 128, need, 0) == (512, 2) and _slices(13104, 12, 128, need - 1, 0) == (0, 0)
+    assert _slices(13104, 12, 128, need - 1, 139264) == (512, 2) and _slices(13104, 12, 128, 0, 1 << 30) == (0, 0)
+
+
 def test_attention_full_tiles():
     for Lq, H in ((3271, 12), (13104, 12), (13104, 40)):             # 156, 624, 2080 tiles of 256 rows
         for Lk in (65, 77, 96, 200, 226, 480, 511):
