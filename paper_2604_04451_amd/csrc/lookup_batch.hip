@@ -1,8 +1,8 @@
 // Batched top-k retrieval (Sec. 3.1 "Full Reuse" for a queue of requests): the k best cache
 // entries by cosine similarity for each of Q prompt embeddings, with ONE pass over the
 // [N, d] fp32 cache per 32 queries instead of one per query. The scan is a [N, d] x [d, Q]
-// contraction in fp32, so it runs on the fp32 matrix pipe (16x16x4), which at 16-32 queries
-// needs about the cycles that HBM needs to deliver the cache rows; row norms are accumulated
+// contraction in fp32, so it runs on the fp32 matrix pipe (16x16x4), which with 32 queries
+// needs about half the time that HBM needs to deliver the cache rows; row norms are accumulated
 // from the same registers.
 #include "common.h"
 #include "lookup_row.h"
@@ -10,136 +10,189 @@
 namespace chorus {
 namespace {
 
-constexpr int kRB = 1;        // 16-row blocks per wave
-constexpr int kBR = 64 * kRB;  // cache rows per workgroup, 16 kRB per wave
-constexpr int kBK = 64;       // floats of every row per step (256 bytes: two full cache lines)
-constexpr int kLS = kBK + 4;  // LDS row stride in floats (16-byte aligned, staggers the banks)
+constexpr int kBlock = 64;   // rows that partial sums are padded to
+constexpr int kBK = 64;      // floats of every row per step (256 bytes: two full cache lines)
+constexpr int kRing = 3;     // steps of cache rows a wave has in LDS or on their way there
 
 struct BatchPlan {
+  int waves;             // of a workgroup: 16 rows each
   int tiles;             // row tiles
   int KS;                // slices along d
   int chunks_per_slice;  // kBK-float steps per slice
+  long Npad;             // rows of the partial sums
 };
 
-inline BatchPlan plan_batch(long N, int d) {
-  BatchPlan p;
-  p.tiles = (int)((N + kBR - 1) / kBR);
+// Slices along d that the workspace has room for; their partial sums are added in a fixed order afterwards.
+inline int max_slices(long N, int d) {
+  const long blocks = (N + kBlock - 1) / kBlock;
   const int nchunks = (d + kBK - 1) / kBK;
-  // As many workgroups as fit the chip at once, four on each of 256 CUs, and no more: a few beyond that are a second round
-  // (20000 x 4096, 32 queries: 1252 workgroups 130 us the call, 939 108). Partial sums of the slices are added in a fixed order
-  // afterwards.
-  int want = p.tiles > 0 ? 1024 / p.tiles : 1;
-  if (want < 1) want = 1;
-  if (want > nchunks) want = nchunks;
-  if (want > 16) want = 16;  // every slice writes and re-reads its own partial sums
-  p.chunks_per_slice = (nchunks + want - 1) / want;
-  p.KS = (nchunks + p.chunks_per_slice - 1) / p.chunks_per_slice;
-  return p;
+  long most = blocks > 0 ? 1024 / blocks : 1;
+  if (most > nchunks) most = nchunks;
+  if (most > 16) most = 16;
+  return most < 1 ? 1 : (int)most;
 }
 
-// part_dot [KS][Qp][Npad] (row fastest, Npad = N rounded up to 128), part_cc [KS][Npad]; Qp = 16 * QB
-template <int QB>
-__global__ __launch_bounds__(256) void lookup_batch_scores_kernel(const float* __restrict__ cache,
-                                                                  const float* __restrict__ queries,
-                                                                  float* __restrict__ part_dot,
-                                                                  float* __restrict__ part_cc, long N, int d, int Q,
-                                                                  int chunks_per_slice, uint32_t* __restrict__ done) {
+// The number of slices and the workgroup's size by an estimate of the two kernels' time in microseconds. What bounds the scan is what a
+// compute unit takes in: 24 KB a microsecond while it is by itself (its loads in flight over the latency of HBM), 21.5 with all
+// 256 (5.5 TB/s); the queries come from the L2 at about three times that. A workgroup of eight waves has a unit to itself (128 KB of LDS), its
+// successor starts cold; of four waves two share one. Each slice's partial sums cost the selection 0.15 us. Measured (rows x d,
+// queries: eight waves / four waves, slices), whole call, us: 4096 x 4096, 32: 25.9 (8) / 27.2 (8), 28.8 (16); 20000 x 4096, 32: 87 (3) / 94
+// (3), 113 (1); 20000 x 1024, 32: 41.3 (1) / 38.5 (3), 39.2 (2); 2000 x 4096, 24: 19.3 (16) / 17.5 (8), 19.0 (16); 500 x 4096, 32: 17.7 (16)
+// / 14.5 (16), 17.0 (8); 12000 x 512, 32: 22.6 (2) / 22.5 (1), 22.9 (4).
+inline BatchPlan plan_batch(long N, int d, int QP) {
+  const int nchunks = (d + kBK - 1) / kBK, most = max_slices(N, d);
+  BatchPlan best{};
+  double best_time = 0.0;
+  for (int waves = 4; waves <= 8; waves += 4) {
+    const long tiles = (N + 16 * waves - 1) / (16 * waves), slots = waves == 8 ? 256 : 512;
+    for (int want = 1; want <= most; ++want) {
+      const int per = (nchunks + want - 1) / want, KS = (nchunks + per - 1) / per;
+      const long groups = tiles * KS;
+      const double kb = (double)((groups + 255) / 256) * per * (4.0 * waves + 0.0875 * QP), later = (double)((groups + slots - 1) / slots - 1);
+      const double time = kb / (groups < 230 ? 24.0 : 21.5) + 2.5 + later * (waves == 8 ? 5.0 : 1.5) + 0.15 * KS;
+      if (best_time == 0.0 || time < best_time) {
+        best_time = time;
+        best = BatchPlan{waves, (int)tiles, KS, per, 0};
+      }
+    }
+  }
+  best.Npad = (N + kBlock - 1) / kBlock * kBlock;
+  return best;
+}
+
+// part_dot [KS][Qp][Npad] (row fastest), part_cc [KS][Npad]; Qp = 16 QB.
+// A wave owns 16 rows. Their next steps stream global -> LDS directly into a ring of its own, so that no wave waits for another's rows:
+// only the queries' values, two steps of them at a time in two buffers, are shared, and only at their change stands a barrier. (With
+// rows and queries staged through registers and two barriers a step the scan of 4096 x 4096 with 32 queries took 23.9 us, so 17.5 to 19;
+// the fp32 matrix pipe needs 7 of them, HBM 12.)
+// A direct load writes the 64 lanes' 16-byte pieces side by side (four rows of 256 bytes, or two of a query's 512); the 16-byte piece c
+// of row r lives at position c ^ (r % 16), which spreads the 16 rows of a fragment read over all banks.
+template <int QB, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void lookup_batch_scores_kernel(const float* __restrict__ cache,
+                                                                         const float* __restrict__ queries,
+                                                                         float* __restrict__ part_dot,
+                                                                         float* __restrict__ part_cc, long N, long Npad, int d,
+                                                                         int Q, int chunks_per_slice,
+                                                                         uint32_t* __restrict__ done) {
   constexpr int QP = 16 * QB;
-  __shared__ __attribute__((aligned(16))) float sA[kBR * kLS];
-  __shared__ __attribute__((aligned(16))) float sB[QP * kLS];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int LB = 8 * QB / NW;       // a wave's loads of two steps of the queries
+  constexpr int AW = kRing * 16 * kBK;  // floats of a wave's ring
+  extern __shared__ __attribute__((aligned(1024))) float smem[];
+  float* const sB = smem;  // [2][QP][2 kBK]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  float* const sA = smem + 2 * QP * 2 * kBK + wave * AW;  // [kRing][16][kBK]
   if (done && blockIdx.x == 0 && blockIdx.y == 0 && tid < QP) done[tid] = 0;  // arrivals of the selection's workgroups
-  const long row0 = (long)blockIdx.x * kBR;
-  const long Npad = (long)gridDim.x * kBR;
+  const long row0 = ((long)blockIdx.x * NW + wave) * 16;
   const int ks = blockIdx.y;
   const int c0 = ks * chunks_per_slice;
   const int nchunks = (d + kBK - 1) / kBK;
-  const int c1 = c0 + chunks_per_slice < nchunks ? c0 + chunks_per_slice : nchunks;
+  const int n = __builtin_amdgcn_readfirstlane((c0 + chunks_per_slice < nchunks ? c0 + chunks_per_slice : nchunks) - c0);
 
-  // loader role: 16 threads per row segment of 256 bytes
-  const int lcol = tid & 15, lrow = tid >> 4;
-  f32x4 ra[2][4 * kRB], rb[2][QB];  // two chunks in flight
-  auto load_chunk = [&](int st, int c) {
-    const int k = c * kBK + 4 * lcol;
+  const float* rowp[4];
 #pragma unroll
-    for (int i = 0; i < 4 * kRB; ++i) {
-      const long r = row0 + lrow + 16 * i;
-      const bool ok = r < N && k < d;
-      const float* p = cache + (ok ? r : 0) * (long)d + (ok ? k : 0);
-      f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
-      ra[st][i] = ok ? v : f32x4{0.f, 0.f, 0.f, 0.f};
-    }
+  for (int i = 0; i < 4; ++i) {
+    const long r = row0 + 4 * i + (lane >> 4);
+    rowp[i] = cache + (r < N ? r : N - 1) * (long)d;  // rows past the end read the last one
+  }
+  typedef __attribute__((address_space(3))) void* Lds;
+  auto issue_rows = [&](int c, int slot) {
 #pragma unroll
-    for (int i = 0; i < QB; ++i) {
-      const int q = lrow + 16 * i;
-      const bool ok = q < Q && k < d;
-      const float* p = queries + (long)(ok ? q : 0) * d + (ok ? k : 0);
-      f32x4 v = *reinterpret_cast<const f32x4*>(p);
-      rb[st][i] = ok ? v : f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < 4; ++i) {
+      int k = (c0 + c) * kBK + 4 * ((lane & 15) ^ (4 * i + (lane >> 4)));
+      k = k < d ? k : d - 4;  // masked where it is used
+      __builtin_amdgcn_global_load_lds(rowp[i] + k, (Lds)(sA + (slot * 16 + 4 * i) * kBK), 16, 0, 2);  // non-temporal
     }
   };
-  auto store_chunk = [&](int st) {
+  auto issue_queries = [&](int s) {  // steps 2 s and 2 s + 1
 #pragma unroll
-    for (int i = 0; i < 4 * kRB; ++i) *reinterpret_cast<f32x4*>(&sA[(lrow + 16 * i) * kLS + 4 * lcol]) = ra[st][i];
-#pragma unroll
-    for (int i = 0; i < QB; ++i) *reinterpret_cast<f32x4*>(&sB[(lrow + 16 * i) * kLS + 4 * lcol]) = rb[st][i];
+    for (int i = 0; i < LB; ++i) {
+      const int q0 = 2 * (wave * LB + i), q = q0 + (lane >> 5);
+      int k = (c0 + 2 * s) * kBK + 4 * ((lane & 31) ^ (q & 15));
+      k = k < d ? k : d - 4;
+      __builtin_amdgcn_global_load_lds(queries + (long)(q < Q ? q : Q - 1) * d + k, (Lds)(sB + ((s & 1) * QP + q0) * 2 * kBK), 16, 0, 0);
+    }
   };
 
-  // compute role: a wave owns 32 rows = two 16-row blocks; lane = (row or query l % 16, k quarter l / 16)
   const int l16 = lane & 15, kq = lane >> 4;
-  f32x4 acc[kRB][QB];
+  f32x4 acc[QB];
 #pragma unroll
-  for (int r = 0; r < kRB; ++r)
+  for (int q = 0; q < QB; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float cc = 0.f;
+  auto compute = [&](const f32x4 (&a)[4], int c, bool mask) {
+    const float* b0 = sB + ((c >> 1) & 1) * QP * 2 * kBK;
 #pragma unroll
-    for (int q = 0; q < QB; ++q) acc[r][q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float cc[kRB] = {};
-
-  // chunk c + 1 is already in flight when chunk c is stored, and chunk c + 2 is requested right after: two chunks
-  // (64 KB per workgroup) are on their way during the MFMAs. Past the slice the loads are masked to zeros.
-  auto step = [&](int st, int c) {
-    __syncthreads();  // the previous step's reads are done
-    store_chunk(st);
-    __syncthreads();
-    if (c + 2 < c1) load_chunk(st, c + 2);
+    for (int j = 0; j < 4; ++j) {
+      f32x4 av = a[j], b[QB];
 #pragma unroll
-    for (int j = 0; j < kBK / 16; ++j) {
-      f32x4 a[kRB], b[QB];
+      for (int q = 0; q < QB; ++q)
+        b[q] = *reinterpret_cast<const f32x4*>(b0 + (16 * q + l16) * 2 * kBK + 4 * (((c & 1) * 16 + 4 * j + kq) ^ l16));
+      if (mask && (c0 + c) * kBK + 16 * j + 4 * kq >= d) {
+        av = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int r = 0; r < kRB; ++r) a[r] = *reinterpret_cast<const f32x4*>(&sA[(16 * kRB * wave + 16 * r + l16) * kLS + 16 * j + 4 * kq]);
-#pragma unroll
-      for (int q = 0; q < QB; ++q) b[q] = *reinterpret_cast<const f32x4*>(&sB[(16 * q + l16) * kLS + 16 * j + 4 * kq]);
-#pragma unroll
-      for (int r = 0; r < kRB; ++r) {
-        cc[r] += a[r][0] * a[r][0] + a[r][1] * a[r][1] + a[r][2] * a[r][2] + a[r][3] * a[r][3];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int q = 0; q < QB; ++q) acc[r][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[r][e], b[q][e], acc[r][q], 0, 0, 0);
+        for (int q = 0; q < QB; ++q) b[q] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
+      cc += av[0] * av[0] + av[1] * av[1] + av[2] * av[2] + av[3] * av[3];
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int q = 0; q < QB; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], b[q][e], acc[q], 0, 0, 0);
     }
   };
-  if (c0 < c1) load_chunk(0, c0);
-  if (c0 + 1 < c1) load_chunk(1, c0 + 1);
-  for (int c = c0; c < c1; c += 2) {
-    step(0, c);
-    if (c + 1 < c1) step(1, c + 1);
-  }
-  // row norms: the four k quarters of a row sit in lanes l16, l16 + 16, l16 + 32, l16 + 48
-#pragma unroll
-  for (int r = 0; r < kRB; ++r) {
-    cc[r] += __shfl_xor(cc[r], 16, 64);
-    cc[r] += __shfl_xor(cc[r], 32, 64);
-    const long row = row0 + 16 * kRB * wave + 16 * r + l16;
-    if (kq == 0) part_cc[(long)ks * Npad + row] = cc[r];
-  }
-  // accumulator elements 0..3 of lane (l16, kq): rows 4 kq .. 4 kq + 3 of the block, query l16 (rows past N hold zeros)
-#pragma unroll
-  for (int r = 0; r < kRB; ++r)
-#pragma unroll
-    for (int q = 0; q < QB; ++q) {
-      const long row = row0 + 16 * kRB * wave + 16 * r + 4 * kq;
-      *reinterpret_cast<f32x4*>(&part_dot[((long)ks * QP + 16 * q + l16) * Npad + row]) = acc[r][q];
+
+  issue_queries(0);
+  issue_rows(0, 0);
+  if (1 < n) issue_rows(1, 1);
+  if (2 < n) issue_rows(2, 2);
+  int slot = 0;
+  // Loads in flight at step c: rows c .. c + 2, and from an even step on the queries of the next two, requested ahead of the rows of
+  // step c + 3. Loads retire in order: at most as many as were requested behind what the step needs may be left.
+  for (int c = 0; c < n; ++c) {
+    const bool more = c + kRing <= n;  // rows c + 1 and c + 2 have been requested
+    if ((c & 1) == 0) {
+      if (more)
+        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      else
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      if (c + 2 < n) issue_queries((c >> 1) + 1);  // into the buffer that everyone has left behind the barrier
+    } else if (more) {
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 + LB) : "memory");
+    } else {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
+    f32x4 a[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      a[j] = *reinterpret_cast<const f32x4*>(sA + (slot * 16 + l16) * kBK + 4 * ((4 * j + kq) ^ l16));
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(a[3])::"memory");
+    if (c + kRing < n) issue_rows(c + kRing, slot);
+    slot = slot == kRing - 1 ? 0 : slot + 1;
+    if ((c0 + c + 1) * kBK <= d)
+      compute(a, c, false);
+    else
+      compute(a, c, true);
+  }
+  if (row0 >= Npad) return;  // the second half of the last tile
+  // row norms: the four k quarters of a row sit in lanes l16, l16 + 16, l16 + 32, l16 + 48
+  cc += __shfl_xor(cc, 16, 64);
+  cc += __shfl_xor(cc, 32, 64);
+  if (kq == 0) part_cc[(long)ks * Npad + row0 + l16] = cc;
+  // accumulator elements 0..3 of lane (l16, kq): rows 4 kq .. 4 kq + 3 of the block, query l16
+#pragma unroll
+  for (int q = 0; q < QB; ++q)
+    *reinterpret_cast<f32x4*>(&part_dot[((long)ks * QP + 16 * q + l16) * Npad + row0 + 4 * kq]) = acc[q];
+}
+
+template <int QB, int NW>
+int32_t launch_scores(const float* cache, const float* queries, float* part_dot, float* part_cc, long N, int d, int Q,
+                      const BatchPlan& p, uint32_t* done, hipStream_t s) {
+  constexpr size_t smem = (size_t)(2 * 16 * QB * 2 * kBK + NW * kRing * 16 * kBK) * sizeof(float);
+  auto kern = lookup_batch_scores_kernel<QB, NW>;
+  static DynLdsOnce once;
+  CHK_STATUS(once.ensure(reinterpret_cast<const void*>(kern), (int)smem));
+  hipLaunchKernelGGL(kern, dim3((unsigned)p.tiles, (unsigned)p.KS), dim3(64 * NW), smem, s, cache, queries, part_dot, part_cc, N,
+                     p.Npad, d, Q, p.chunks_per_slice, done);
+  CHORUS_LAUNCH_CHECK();
+  return CHORUS_OK;
 }
 
 // dot[u], cc[u] (u < RU) += the partial sums of entry j + STRIDE u over the KS slices, in ascending slice order
@@ -508,9 +561,8 @@ struct BatchWs {
 
 BatchWs carve_batch(long N, int d, int Qc, void* base) {
   BatchWs w;
-  const BatchPlan p = plan_batch(N, d);
-  const int QP = Qc > 16 ? 32 : 16;
-  const long rows = p.tiles > 0 ? (long)p.tiles * kBR : kBR;  // padded to whole row tiles
+  const int QP = Qc > 16 ? 32 : 16, slices = max_slices(N, d);
+  const long rows = N > 0 ? (N + kBlock - 1) / kBlock * kBlock : kBlock;
   const BytePtr b(base);
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -518,8 +570,8 @@ BatchWs carve_batch(long N, int d, int Qc, void* base) {
     off += align_up(bytes, 256);
     return r;
   };
-  w.part_dot = (float*)take((size_t)p.KS * rows * QP * 4);
-  w.part_cc = (float*)take((size_t)p.KS * rows * 4);
+  w.part_dot = (float*)take((size_t)slices * rows * QP * 4);
+  w.part_cc = (float*)take((size_t)slices * rows * 4);
   w.scores = (float*)take((size_t)32 * rows * 4);
   w.bytes = off;
   return w;
@@ -548,13 +600,13 @@ int32_t chorus_cache_lookup_batch(const float* cache_emb, int64_t N, int32_t d, 
   if (N > 0x7fffff00LL) return CHORUS_E_SHAPE;
   if (!ws || !aligned16(ws) || ws_bytes < chorus_cache_lookup_batch_workspace_bytes(N, d, Q)) return CHORUS_E_WORKSPACE;
   hipStream_t s = (hipStream_t)stream;
-  const BatchPlan p = plan_batch((long)N, d);
   for (int q0 = 0; q0 < Q; q0 += 32) {
     const int Qc = Q - q0 < 32 ? Q - q0 : 32;
     const int QP = Qc > 16 ? 32 : 16;
     BatchWs w = carve_batch((long)N, d, Q > 32 ? 32 : Q, ws);
     const float* qs = queries + (long)q0 * d;
-    const long Npad = (long)p.tiles * kBR;
+    const BatchPlan p = plan_batch((long)N, d, QP);
+    const long Npad = p.Npad;
     const long nb = (N + 1023) / 1024;  // row blocks of the selection
     const bool lists_fit = k <= kWaveK;  // selected where the scores are made
     // the waves' lists take the place of the scores (128 bytes a row against at most 64 a row of a block), the arrival
@@ -562,14 +614,9 @@ int32_t chorus_cache_lookup_batch(const float* cache_emb, int64_t N, int32_t d, 
     uint64_t* lists = reinterpret_cast<uint64_t*>(w.scores);
     uint32_t* done = lists_fit && nb > 1 ? reinterpret_cast<uint32_t*>(lists + nb * 4 * 32 * kWaveK) : nullptr;
     if (N > 0) {
-      const dim3 grid((unsigned)p.tiles, (unsigned)p.KS);
-      if (QP == 32)
-        hipLaunchKernelGGL(lookup_batch_scores_kernel<2>, grid, dim3(256), 0, s, cache_emb, qs, w.part_dot, w.part_cc,
-                           (long)N, d, Qc, p.chunks_per_slice, done);
-      else
-        hipLaunchKernelGGL(lookup_batch_scores_kernel<1>, grid, dim3(256), 0, s, cache_emb, qs, w.part_dot, w.part_cc,
-                           (long)N, d, Qc, p.chunks_per_slice, done);
-      CHORUS_LAUNCH_CHECK();
+      auto scores = p.waves == 8 ? (QP == 32 ? launch_scores<2, 8> : launch_scores<1, 8>)
+                                 : (QP == 32 ? launch_scores<2, 4> : launch_scores<1, 4>);
+      CHK_STATUS(scores(cache_emb, qs, w.part_dot, w.part_cc, (long)N, d, Qc, p, done, s));
       if (lists_fit) {
         const auto select = k == 1 ? lookup_batch_select_kernel<true> : lookup_batch_select_kernel<false>;
         hipLaunchKernelGGL(select, dim3((unsigned)nb, (unsigned)Qc), dim3(256), 0, s, w.part_dot, w.part_cc, qs, lists, done, (long)N,
