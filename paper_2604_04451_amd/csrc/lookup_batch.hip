@@ -114,10 +114,14 @@ __global__ __launch_bounds__(64 * NW, 2) void lookup_batch_scores_kernel(const f
   };
 
   const int l16 = lane & 15, kq = lane >> 4;
-  f32x4 acc[QB];
+  // a sum per quarter of a step, added at the end: four short chains of additions in place of a long one (error of the scores against
+  // 64 bits at 4096 x 4096 1.5e-7 with one, 0.8e-7 with four, 1.1e-7 with sixteen slices of one chain each as before)
+  f32x4 acc[4][QB];
 #pragma unroll
-  for (int q = 0; q < QB; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float cc = 0.f;
+  for (int j = 0; j < 4; ++j)
+#pragma unroll
+    for (int q = 0; q < QB; ++q) acc[j][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float cc4[4] = {0.f, 0.f, 0.f, 0.f};
   auto compute = [&](const f32x4 (&a)[4], int c, bool mask) {
     const float* b0 = sB + ((c >> 1) & 1) * QP * 2 * kBK;
 #pragma unroll
@@ -131,11 +135,11 @@ __global__ __launch_bounds__(64 * NW, 2) void lookup_batch_scores_kernel(const f
 #pragma unroll
         for (int q = 0; q < QB; ++q) b[q] = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-      cc += av[0] * av[0] + av[1] * av[1] + av[2] * av[2] + av[3] * av[3];
+      cc4[j] += av[0] * av[0] + av[1] * av[1] + av[2] * av[2] + av[3] * av[3];
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int q = 0; q < QB; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], b[q][e], acc[q], 0, 0, 0);
+        for (int q = 0; q < QB; ++q) acc[j][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], b[q][e], acc[j][q], 0, 0, 0);
     }
   };
 
@@ -173,13 +177,14 @@ __global__ __launch_bounds__(64 * NW, 2) void lookup_batch_scores_kernel(const f
   }
   if (row0 >= Npad) return;  // the second half of the last tile
   // row norms: the four k quarters of a row sit in lanes l16, l16 + 16, l16 + 32, l16 + 48
+  float cc = (cc4[0] + cc4[1]) + (cc4[2] + cc4[3]);
   cc += __shfl_xor(cc, 16, 64);
   cc += __shfl_xor(cc, 32, 64);
   if (kq == 0) part_cc[(long)ks * Npad + row0 + l16] = cc;
   // accumulator elements 0..3 of lane (l16, kq): rows 4 kq .. 4 kq + 3 of the block, query l16
 #pragma unroll
   for (int q = 0; q < QB; ++q)
-    *reinterpret_cast<f32x4*>(&part_dot[((long)ks * QP + 16 * q + l16) * Npad + row0 + 4 * kq]) = acc[q];
+    *reinterpret_cast<f32x4*>(&part_dot[((long)ks * QP + 16 * q + l16) * Npad + row0 + 4 * kq]) = (acc[0][q] + acc[1][q]) + (acc[2][q] + acc[3][q]);
 }
 
 template <int QB, int NW>
