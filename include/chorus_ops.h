@@ -69,6 +69,18 @@ typedef struct {
 int32_t chorus_gemm_bf16_plan(int64_t M, int32_t N, int32_t K, int32_t epilogue, size_t first_bytes, size_t rest_bytes,
                               chorus_gemm_plan* out);
 
+/* The gated residual (CHORUS_EPI_RESID) on a named kernel (1, 2, 3 or 5) with K in `slices` (1 to 4) chained slices: each adds its part to
+ * `out` itself, one behind the other, no scratch but a count a tile: counts dev, n_counts of at least as many as the kernel's
+ * tiles (CHORUS_E_WORKSPACE), cleared by the call. N up to 2^20. For tests and comparisons. */
+int32_t chorus_gemm_bf16_chain(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, float* out, const float* bias,
+                               const float* gate0, const float* gate1, float scale, int32_t kernel, int32_t slices, uint32_t* counts,
+                               int32_t n_counts, void* stream);
+/* What a block does with its gated-residual products (its second FFN product with that scratch, the others with 0, 0):
+ * chorus_gemm_bf16_plan, or a chain where one is estimated to be
+ * faster (*chained 1; `kernel` and `slices` are the chain's, of the rows behind head_rows). Host only. */
+int32_t chorus_gemm_bf16_chain_plan(int64_t M, int32_t N, int32_t K, size_t first_bytes, size_t rest_bytes, chorus_gemm_plan* out,
+                                    int32_t* chained);
+
 /* Two products with bf16 outputs over the same K, as a block runs QKV and the text's keys and values: *kernel is the kernel (1 or
  * 5) of the one launch that takes both, 0 where each takes a launch of its own. Host only. */
 int32_t chorus_gemm_bf16_two_plan(int64_t M, int32_t N, int64_t M2, int32_t N2, int32_t K, int32_t* kernel);

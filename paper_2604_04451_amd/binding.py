@@ -166,6 +166,8 @@ def _bind_ops(lib):
         "chorus_attention": (i32, [vp, vp, vp, vp, vp, i64, i64, i64, i64, i32, i32, i32, vp]),
         "chorus_attention_slices": (i32, [vp, vp, vp, vp, i64, i64, i32, i32, i64, i32, vp, sz, vp]),
         "chorus_attention_slices_plan": (i32, [i64, i32, i32, i32, sz, sz, C.POINTER(i64), C.POINTER(i32)]),
+        "chorus_gemm_bf16_chain": (i32, [vp, vp, i64, i32, i32, vp, vp, vp, vp, f32, i32, i32, vp, i32, vp]),
+        "chorus_gemm_bf16_chain_plan": (i32, [i64, i32, i32, sz, sz, C.POINTER(GemmPlan), C.POINTER(i32)]),
         "chorus_glue_workspace_bytes": (sz, [i32, i32, i64]),
         "chorus_patch_embed": (i32, [vp, i32, i32, i32, i32, i32, i32, vp, i64, GW, i32, vp, vp, sz, vp]),
         "chorus_head_update": (i32, [vp, vp, i64, vp, GW, vp, f32, i32, i32, i32, i32, i32, i32, i32, vp, sz, vp]),
@@ -585,6 +587,34 @@ def chorus_gemm_bf16_slices(A, W, out, kernel, slices, bias=None, gate0=None, ga
             lib.chorus_gemm_bf16_slices(_p(A), _p(W), M, N, K, _p(out), _p(bias), _p(gate0), _p(gate1), float(scale), int(kernel),
                                         int(slices), _p(parts), 0 if parts is None else parts.numel() * 4, _stream()))
     return out
+
+
+def chorus_gemm_bf16_chain(A, W, out, kernel, slices, bias=None, gate0=None, gate1=None, scale=1.0, counts=None):
+    """out += gate * scale * (A W^T + bias), K in slices that add to out one behind the other; counts int32, one a tile."""
+    lib = load()
+    _chk(A, torch.bfloat16, "A")
+    _chk(W, torch.bfloat16, "W")
+    (M, K), N = A.shape, W.shape[0]
+    if W.shape[1] != K:
+        raise TypeError("A/W inner dimensions differ")
+    _chk(out, torch.float32, "out", (M, N))
+    for n, t in (("bias", bias), ("gate0", gate0), ("gate1", gate1)):
+        _chk(t, torch.float32, n, (N,))
+    if counts is None:
+        counts = torch.empty(-(-M // 64) * -(-N // 64), dtype=torch.int32, device=A.device)
+    _chk(counts, torch.int32, "counts")
+    _status("chorus_gemm_bf16_chain",
+            lib.chorus_gemm_bf16_chain(_p(A), _p(W), M, N, K, _p(out), _p(bias), _p(gate0), _p(gate1), float(scale), int(kernel),
+                                       int(slices), _p(counts), counts.numel(), _stream()))
+    return out
+
+
+def chorus_gemm_bf16_chain_plan(M, N, K, first_bytes=0, rest_bytes=0):
+    """(rows of the first launch on kernel 3, kernel of the others, slices of K, chained) of a block's second FFN product; host only."""
+    out, chained = GemmPlan(), C.c_int32(-1)
+    _status("chorus_gemm_bf16_chain_plan",
+            load().chorus_gemm_bf16_chain_plan(M, N, K, first_bytes, rest_bytes, C.byref(out), C.byref(chained)))
+    return out.head_rows, out.kernel, out.slices, bool(chained.value)
 
 
 def chorus_gemm_bf16_plan(M, N, K, epilogue, first_bytes=0, rest_bytes=0):

@@ -60,8 +60,12 @@ struct BlockWs {
   uint16_t* kc;     // [H, LtPad, dh]
   uint16_t* vct;    // [D, LtPad]
   size_t bytes;
-  AttnScratch attn;     // for self-attention: h, and the projection once its queries, keys and values are prepared
-  GemmParts ffn_parts;  // what the second FFN product may use for slices of K: h and ao, and everything behind the FFN hidden
+  // counts of the gated-residual products, kGemmCounts each, where nothing is kept between the launch that clears them and the product:
+  // in front of h during self-attention, in the keys' place during cross-attention, in the attention output's place during the FFN. A
+  // product of few rows has fewer counts than the place of its rows holds.
+  uint32_t *o_counts, *co_counts;
+  AttnScratch attn;     // for self-attention: h behind the counts, and the projection once its queries, keys and values are prepared
+  GemmParts ffn_parts;  // what the second FFN product may use for slices of K: h and ao, and everything behind the FFN hidden; or counts, in ao's place
 };
 
 inline long pad_rows(long L) { return (long)align_up((size_t)L, 256); }
@@ -93,8 +97,11 @@ BlockWs carve(const chorus_block_shape& sh, long Ls, void* base) {
   w.kc = take(LtPad * D);
   w.vct = take(LtPad * D);
   w.bytes = off;
-  w.attn = AttnScratch{w.h, (size_t)Ls * D * 2, w.qkv, (size_t)Ls * 3 * D * 2};
-  w.ffn_parts = GemmParts{w.h, a0, p + a0 + ffn_bytes, w.bytes - a0 - ffn_bytes};
+  w.o_counts = reinterpret_cast<uint32_t*>(w.h);
+  w.co_counts = reinterpret_cast<uint32_t*>(w.kh);
+  const size_t count_bytes = kGemmCounts * sizeof(uint32_t), h_bytes = (size_t)Ls * D * 2;
+  w.attn = AttnScratch{p + count_bytes, h_bytes > count_bytes ? h_bytes - count_bytes : 0, w.qkv, (size_t)Ls * 3 * D * 2};  // h is in front
+  w.ffn_parts = GemmParts{w.h, a0, p + a0 + ffn_bytes, w.bytes - a0 - ffn_bytes, reinterpret_cast<uint32_t*>(w.ao)};
   return w;
 }
 
@@ -233,7 +240,7 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
     const PrepareText text{b.tkv, b.tkv + D, 2L * D, w->g_ck, b.kc, b.vct, Lt, LtPad};
     CHK(attn_prepare(b.qkv, b.qkv + D, b.qkv + 2 * D, 3L * D, w->g_q, w->g_k, b.qh, b.kh, b.vt, Ls, Lpad, H, dh, token_idx, sh.gH,
                      sh.gW, 1, q_prescaled ? CHORUS_ATTENTION_Q_PRESCALE(dh) : 1.0f, stream, text_kv ? nullptr : &text,
-                     static_cast<uint32_t*>(b.attn.first), attention_slices_words(slices)));
+                     b.o_counts, kGemmCounts + attention_slices_words(slices)));
   }
   // 4. self-attention over exactly the Ls rows, output projection, gated residual
   {
@@ -245,12 +252,13 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   }
   {
     ProfScope p(CHORUS_PROF_GEMM, s);
-    CHK(chorus_gemm_bf16(b.ao, w->w_o, Ls, D, D, CHORUS_EPI_RESID, x, w->b_o, row(tab, 2), row(t_mod, 2), 1.f, stream));
+    CHK(gemm_bf16_parts(b.ao, w->w_o, Ls, D, D, CHORUS_EPI_RESID, x, w->b_o, row(tab, 2), row(t_mod, 2), 1.f,
+                        GemmParts{nullptr, 0, nullptr, 0, b.o_counts}, stream));
   }
   // 5. cross-attention with TGAA
   {
     ProfScope p(CHORUS_PROF_NORM, s);
-    CHK(chorus_ln_modulate(x, b.h, Ls, D, w->ln3_w, nullptr, w->ln3_b, nullptr, 0, stream));
+    CHK(ln_modulate(x, b.h, Ls, D, w->ln3_w, nullptr, w->ln3_b, nullptr, 0, b.co_counts, kGemmCounts, stream));
   }
   {
     ProfScope p(CHORUS_PROF_GEMM, s);
@@ -275,12 +283,13 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   }
   {
     ProfScope p(CHORUS_PROF_GEMM, s);
-    CHK(chorus_gemm_bf16(b.ao, w->w_co, Ls, D, D, CHORUS_EPI_RESID, x, w->b_co, nullptr, nullptr, gamma_o, stream));
+    CHK(gemm_bf16_parts(b.ao, w->w_co, Ls, D, D, CHORUS_EPI_RESID, x, w->b_co, nullptr, nullptr, gamma_o,
+                        GemmParts{nullptr, 0, nullptr, 0, b.co_counts}, stream));
   }
   // 6. FFN
   {
     ProfScope p(CHORUS_PROF_NORM, s);
-    CHK(chorus_ln_modulate(x, b.h, Ls, D, row(tab, 4), row(t_mod, 4), row(tab, 3), row(t_mod, 3), 1, stream));
+    CHK(ln_modulate(x, b.h, Ls, D, row(tab, 4), row(t_mod, 4), row(tab, 3), row(t_mod, 3), 1, b.ffn_parts.counts, kGemmCounts, stream));
   }
   {
     ProfScope p(CHORUS_PROF_GEMM, s);

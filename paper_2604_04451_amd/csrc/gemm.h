@@ -13,7 +13,10 @@ struct GemmParts {
   size_t first_bytes;
   void* rest;
   size_t rest_bytes;
+  // kGemmCounts words that are zero when the product starts, or null: the slices may then add to the residual one behind the other instead
+  uint32_t* counts;
 };
+constexpr int kGemmCounts = 256;
 
 // chorus_gemm_bf16 with scratch; the number of slices depends on the sizes given here and on nothing else
 int32_t gemm_bf16_parts(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, int32_t epilogue, void* out,

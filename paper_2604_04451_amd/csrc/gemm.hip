@@ -136,14 +136,24 @@ __device__ __forceinline__ void gemm16_epilogue_bf16(const f32x4 (&acc)[8][8], c
   }
 }
 
+// The same address in scalar registers: the compiler does not see that a value worked out from the workgroup's id by a
+// division is one for the whole wave, and would walk over the lanes with every descriptor made from it.
+__device__ __forceinline__ void* uniform_address(const uint16_t* p) {
+  const uint64_t u = reinterpret_cast<uint64_t>(p);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)), lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)u);
+  return reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
+}
+
 // fp32 gated-residual epilogue of the 16x16 layout: 16 output rows at a time through a private LDS region as
 // [16][16 WBN] fp32 (row stride 16 WBN + 4), read back with 4 WBN lanes per row; the residual rows are requested before the
 // LDS round trip. out[m][n] += gate[n] * scale * (acc + bias[n]).
 template <int WBN> constexpr int e16_f32_stride() { return 16 * WBN + 4; }
 template <int WBN> constexpr int e16_f32_wave() { return 16 * e16_f32_stride<WBN>(); }  // floats per wave
-template <int WBM, int WBN>
+// CHAIN: what another workgroup of the tile wrote is read and what the next one reads is written past the L2s (agent scope).
+template <int WBM, int WBN, bool CHAIN = false>
 __device__ __forceinline__ void gemm16_epilogue_resid(const f32x4 (&acc)[8][8], const EpiArgs& ep, float* cw, long m_wave0,
                                                       int n_wave0, long M, int N, int lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
   constexpr int E16_F32_STRIDE = e16_f32_stride<WBN>();
   constexpr int LPR = 4 * WBN, RPI = 64 / LPR;  // read-back: LPR lanes x 16 bytes per row, RPI rows per instruction
   const int lj = lane & 15, lg = lane >> 4;
@@ -161,6 +171,10 @@ __device__ __forceinline__ void gemm16_epilogue_resid(const f32x4 (&acc)[8][8], 
     gate *= ep.scale;
   }
   float* out = reinterpret_cast<float*>(ep.out);
+  constexpr int kAgent = 16;  // cache policy bit sc1
+  const long m_base = m_wave0 < M ? m_wave0 : M - 1;  // never in front of the descriptor's first row
+  const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(uniform_address(reinterpret_cast<const uint16_t*>(out + m_base * N)), 0, -1, 0x00027000);
+  auto offset = [&](long m) { return ((int)(m - m_base) * N + n) * 4; };
   // The residual rows of block mb + 1 are requested before the results of block mb are stored: memory operations
   // retire in order, so a load issued behind a block's stores could only be consumed once those stores had drained.
   f32x4 cur[2][WBN];
@@ -169,7 +183,10 @@ __device__ __forceinline__ void gemm16_epilogue_resid(const f32x4 (&acc)[8][8], 
     for (int it = 0; it < WBN; ++it) {
       long m = m_wave0 + 16 * mb + RPI * it + rrow;
       if (m > M - 1) m = M - 1;  // rows past the end read the last row (never stored)
-      dst[it] = *reinterpret_cast<const f32x4*>(out + m * N + (n_ok ? n : 0));
+      if constexpr (CHAIN)
+        dst[it] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, offset(m) - (n_ok ? 0 : 4 * n), 0, kAgent));
+      else
+        dst[it] = *reinterpret_cast<const f32x4*>(out + m * N + (n_ok ? n : 0));
     }
   };
   fetch(0, cur[0]);
@@ -184,11 +201,17 @@ __device__ __forceinline__ void gemm16_epilogue_resid(const f32x4 (&acc)[8][8], 
     for (int it = 0; it < WBN; ++it) {
       const f32x4 v = *reinterpret_cast<const f32x4*>(cw + (RPI * it + rrow) * E16_F32_STRIDE + rcol);
       const long m = m_wave0 + 16 * mb + RPI * it + rrow;
-      if (n_ok && m < M) *reinterpret_cast<f32x4*>(out + m * N + n) = cur[mb & 1][it] + gate * (v + bias);
+      const f32x4 r = cur[mb & 1][it] + gate * (v + bias);
+      if constexpr (CHAIN) {
+        if (n_ok && m < M) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, r), rsrc, offset(m), 0, kAgent);
+      } else {
+        if (n_ok && m < M) *reinterpret_cast<f32x4*>(out + m * N + n) = r;
+      }
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
     __builtin_amdgcn_sched_barrier(0);
   }
+#endif
 }
 
 // Epilogue of the 4-wave 16x16 kernels: wave (wm, wn) holds rows m0 + 16 WBM wm .. + 16 WBM, columns
@@ -229,19 +252,21 @@ struct Twin {
   const float* bias;
   long M;
   int N, tiles_m, tiles_n, first;
-  static constexpr bool kTwo = true;
+  static constexpr bool kTwo = true, kChain = false;
 };
 struct Alone {  // no second product
-  static constexpr bool kTwo = false;
+  static constexpr bool kTwo = false, kChain = false;
 };
-
-// The same address in scalar registers: the compiler does not see that a value worked out from the workgroup's id by a
-// division is one for the whole wave, and would walk over the lanes with every descriptor made from it.
-__device__ __forceinline__ void* uniform_address(const uint16_t* p) {
-  const uint64_t u = reinterpret_cast<uint64_t>(p);
-  const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)), lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)u);
-  return reinterpret_cast<void*>(((uint64_t)hi << 32) | lo);
-}
+// The gated residual in slices of K without scratch: every slice adds its part to the residual itself, in the order of the slices. A
+// slice waits for its tile's count to reach its number; the slices in front of it have lower workgroup numbers, so that they started
+// before it, and the first one waits for nothing: the wait ends. The counts start at zero. Slices of equal length would all end
+// together and then wait for each other's updates: each is a few steps longer than the one in front of it instead (3271 x 1536 x 8960, three
+// slices of 256 x 256 tiles: 100 us with equal ones, 87 with five steps more each).
+struct Chain {
+  uint32_t* count;  // [tiles]
+  int stagger;      // steps that a slice is longer than the one in front of it
+  static constexpr bool kTwo = false, kChain = true;
+};
 
 // The 128 x 256 shape takes three quarters of the operand bytes per product of 128 x 128 tiles: for products of about 400 to
 // 512 such tiles with a long K, which run two to a unit, half as many wide ones finish earlier (N = 1536, K = 8960: 5000 rows
@@ -284,8 +309,14 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
   const int tile = xcd_remap(block, ntiles);
   int KTN = K / BK, k_first = 0;
   if (nslices > 1) {
-    k_first = __builtin_amdgcn_readfirstlane(slice * KTN / nslices);
-    KTN = __builtin_amdgcn_readfirstlane((slice + 1) * KTN / nslices) - k_first;
+    auto start = [&](int i) {
+      if constexpr (SECOND::kChain)
+        return i * KTN / nslices - twin.stagger * i * (nslices - i) / 2;
+      else
+        return i * KTN / nslices;
+    };
+    k_first = __builtin_amdgcn_readfirstlane(start(slice));
+    KTN = __builtin_amdgcn_readfirstlane(start(slice + 1)) - k_first;
     A += (long)k_first * BK;
     W += (long)k_first * BK;
   }
@@ -486,6 +517,25 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
                : "+a"(acc[WBN - 1][WBM - 1]), "+a"(acc[WBN - 1][WBM - 2]), "+a"(acc[WBM > 2 ? WBN - 1 : 0][WBM > 2 ? WBM - 3 : 1]),
                  "+a"(acc[WBM > 2 ? WBN - 1 : 0][WBM > 2 ? WBM - 4 : 0]));
   lds_barrier();  // the staging regions of the epilogue overlay the operands
+  if constexpr (SECOND::kChain) {
+    static_assert(EPI == CHORUS_EPI_RESID, "slices of the gated residual");
+    uint32_t* const count = twin.count + tile;
+    if (slice > 0) {
+      if (tid == 0)
+        while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint32_t)slice) __builtin_amdgcn_s_sleep(1);
+      __syncthreads();
+      asm volatile("" ::: "memory");  // the residual is read behind the count
+      ep.bias = nullptr;              // went in with the first slice
+    }
+    gemm16_epilogue_resid<WBM, WBN, true>(acc, ep, reinterpret_cast<float*>(smem_raw) + wave * e16_f32_wave<WBN>(), m0 + wm * WTM,
+                                          n0 + wn * WTN, M, N, lane);
+    if (slice + 1 < nslices) {
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's stores have completed, past the L2
+      __syncthreads();
+      if (tid == 0) __hip_atomic_store(count, (uint32_t)slice + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    return;
+  }
   if constexpr (EPI == CHORUS_EPI_RESID) {
     if (slice + 1 < nslices) {
       const EpiArgs plain{parts.of(slice, M, N), nullptr, nullptr, nullptr, 1.f};
@@ -633,19 +683,45 @@ double tile_time(int tile, long m, int N, int K, int epi, int slices) {
   return tiles_time(tile, tile_count(tile, m, N), K, epi, slices);
 }
 
-constexpr GemmParts kNoParts{nullptr, 0, nullptr, 0};
+constexpr GemmParts kNoParts{nullptr, 0, nullptr, 0, nullptr};
 
 struct GemmPlan {
   int tile;
   int slices;
   double time;
+  bool chain = false;  // the slices add to the residual one behind the other
 };
+
+// Chained slices: steps that a slice is longer than the one in front of it (about what an update of the residual takes), and the time.
+// Every slice needs a compute unit from the start. Fitted to 16 products: microseconds a step and what does not depend on K (the last
+// update of the residual among it). Measured, best plan without / with a chain, us: 3271 x 1536 x 8960 114 to 118 / 84 to 92 (256 x 256,
+// three slices), 4500 115 / 107 (two), 2352 72 / 71 (128 x 256, two), 2000 78 / 70, 1350 68 / 56 (three), 1100 50 / 46 (128 x 128, two), 480 31
+// / 34; 1200 x 5120 x 13824 179 / 152 (256 x 256, two), 960 173 / 125 (three), 544 101 / 96 (128 x 256, two).
+// 300 x 5120 x 5120 45 / 30 (128 x 128, two), 200 38 / 28 (three), 960 72 / 64 (256 x 256, three). With fewer steps a slice the updates are the
+// larger part: 1200 x 1536 x 1536 14 to 16.5 / 17, 4500 28 / 39.
+constexpr int kMaxChain = 4, kChainTiles = 256, kChainSteps = 16;
+int chain_stagger(int tile, int K, int slices) {
+  const int want = tile == kTile256 || tile == kTileWide ? 5 : 8, most = K / BK / slices;
+  return want * (slices - 1) < most ? want : most / slices;  // the first slice keeps half of its steps
+}
+double chain_time(int tile, long m, int N, int K, int slices) {
+  const long tiles = tile_count(tile, m, N);
+  if (tile == kTile128 || K > kMaxOffsetK || N > 1 << 20 || tiles * slices > kChainTiles || K / BK / slices < kChainSteps) return INFINITY;
+  const double fill = (double)(tiles * slices) / 256.0;
+  const double steps = (double)(K / BK) / slices + 0.5 * (slices - 1) * chain_stagger(tile, K, slices);
+  switch (tile) {
+    case kTile256: return 16.3 + 5.0 * (slices - 2) + (1.17 + fmax(fill - 0.8, 0.0)) * steps;
+    case kTileWide: return 15.0 + 2.0 * (slices - 2) + 0.72 * steps;
+    case kTile128Deep: return 5.4 + 1.7 * (slices - 2) + (0.45 + 0.081 * fill * fill) * steps;
+    default: return 6.0 + 2.5 * (slices - 2) + 0.246 * steps;
+  }
+}
 
 // The fastest tile by the estimates. With scratch a gated-residual product may also be cut into slices of K: every slice
 // but the last writes its fp32 result and a second launch adds them (about 6 TB/s from the caches, and the launch itself).
 // Measured where N = 1536, K = 8960, slices against the best whole tile: 128 rows 17 / 41 us, 480 rows 31 / 37, 1200
 // rows 46 / 66, 2000 and 2300 rows (two slices of 128 x 256 tiles) 75 / 72 and 77 / 79; beyond that a whole tile fills the chip.
-GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
+GemmPlan plan_slices(long m, int N, int K, int epi, const GemmParts& parts) {
   GemmPlan best{kTile64, 1, INFINITY};
   for (int t = 0; t < kTiles; ++t) {
     const double v = tile_time(t, m, N, K, epi, 1);
@@ -666,7 +742,48 @@ GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
   return best;
 }
 
+// The same, or a chain where one may be taken and is estimated to be faster.
+GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
+  GemmPlan best = plan_slices(m, N, K, epi, parts);
+  if (!parts.counts || epi != CHORUS_EPI_RESID) return best;
+  const double without = best.time;
+  for (int sl = 2; sl <= kMaxChain && sl <= K / BK; ++sl)
+    for (int t = 0; t < kTiles; ++t) {
+      const double v = chain_time(t, m, N, K, sl);
+      if (v < 0.97 * without && v < best.time) best = GemmPlan{t, sl, v, true};
+    }
+  return best;
+}
+
 constexpr int kHalvesDeep = 7, kHalves64 = 9;
+
+template <int WBM, int WBN, int C>
+int32_t launch_chain(const uint16_t* A, const uint16_t* W, long M, int N, int K, const EpiArgs& ep, int slices, uint32_t* count,
+                     int stagger, hipStream_t s) {
+  constexpr int BM = 32 * WBM, BN = 32 * WBN;
+  const long tm = (M + BM - 1) / BM;
+  const int tn = (N + BN - 1) / BN;
+  const size_t smem = (size_t)C * (BM + BN) / 2 * BK * sizeof(uint16_t);
+  auto kern = gemm_w16_kernel<CHORUS_EPI_RESID, WBM, WBN, C, false, Chain>;
+  static DynLdsOnce once;
+  CHK_STATUS(once.ensure(reinterpret_cast<const void*>(kern), (int)smem));
+  hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn), (unsigned)slices), dim3(256), smem, s, A, W, M, N, K, ep, PartPtrs{nullptr, nullptr},
+                     (int)tm, tn, Chain{count, stagger});
+  CHORUS_LAUNCH_CHECK();
+  return CHORUS_OK;
+}
+
+int32_t launch_chain_tile(int tile, const uint16_t* A, const uint16_t* W, long M, int N, int K, const EpiArgs& ep, int slices,
+                          uint32_t* counts, hipStream_t s) {
+  const int stagger = chain_stagger(tile, K, slices);
+  switch (tile) {
+    case kTile256: return launch_chain<8, 8, 5>(A, W, M, N, K, ep, slices, counts, stagger, s);
+    case kTileWide: return launch_chain<4, 8, 6>(A, W, M, N, K, ep, slices, counts, stagger, s);
+    case kTile128Deep: return launch_chain<4, 4, kHalvesDeep>(A, W, M, N, K, ep, slices, counts, stagger, s);
+    case kTile64: return launch_chain<2, 2, kHalves64>(A, W, M, N, K, ep, slices, counts, stagger, s);
+    default: return CHORUS_E_ARG;
+  }
+}
 
 int32_t launch_tile(int tile, const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, const EpiArgs& ep,
                     hipStream_t s, int slices = 1, const PartPtrs& parts = PartPtrs{nullptr, nullptr}) {
@@ -682,6 +799,7 @@ int32_t launch_tile(int tile, const uint16_t* A, const uint16_t* W, long M, int 
 
 int32_t launch_plan(const GemmPlan& p, const uint16_t* A, const uint16_t* W, long M, int N, int K, int epi, const EpiArgs& ep,
                     const GemmParts& parts, hipStream_t s) {
+  if (p.chain) return launch_chain_tile(p.tile, A, W, M, N, K, ep, p.slices, parts.counts, s);
   const PartPtrs pp{static_cast<float*>(parts.first), static_cast<float*>(parts.rest)};
   CHK_STATUS(launch_tile(p.tile, A, W, M, N, K, epi, ep, s, p.slices, pp));
   return p.slices > 1 ? launch_add_parts(pp, p.slices, M, N, ep, s) : CHORUS_OK;
@@ -733,7 +851,7 @@ GemmCut plan_rows(long M, int N, int K, int epi, const GemmParts& parts) {
   const long tiles_n256 = (N + 255) / 256, tiles256 = ((M + 255) / 256) * tiles_n256;
   const long head_rows = tiles256 > 256 && K >= 4 * BK ? (tiles256 / 256 * 256 / tiles_n256) * 256 : 0;
   if (head_rows > 0 && head_rows < M) {
-    const GemmPlan tail = plan_gemm(M - head_rows, N, K, epi, kNoParts);
+    const GemmPlan tail = plan_gemm(M - head_rows, N, K, epi, GemmParts{nullptr, 0, nullptr, 0, parts.counts});
     const double time = tile_time(kTile256, head_rows, N, K, epi, 1) + tail.time;
     if (time < 0.95 * whole.time) return GemmCut{head_rows, tail, time};
   }
@@ -801,7 +919,8 @@ int32_t gemm_bf16_parts(const uint16_t* A, const uint16_t* W, int64_t M, int32_t
   const size_t out_elt = (epilogue == CHORUS_EPI_F32 || epilogue == CHORUS_EPI_RESID) ? 4 : 2;
   EpiArgs ep_rest = ep;
   ep_rest.out = static_cast<uint8_t*>(out) + (size_t)cut.head_rows * (size_t)N * out_elt;
-  return launch_plan(cut.rest, A + (size_t)cut.head_rows * (size_t)K, W, (long)M - cut.head_rows, N, K, epilogue, ep_rest, kNoParts, s);
+  return launch_plan(cut.rest, A + (size_t)cut.head_rows * (size_t)K, W, (long)M - cut.head_rows, N, K, epilogue, ep_rest,
+                     GemmParts{nullptr, 0, nullptr, 0, parts.counts}, s);
 }
 
 }  // namespace chorus
@@ -836,7 +955,7 @@ extern "C" int32_t chorus_gemm_bf16_slices(const uint16_t* A, const uint16_t* W,
   if (M == 0) return CHORUS_OK;
   const size_t one = (size_t)M * (size_t)N * sizeof(float);
   if (slices > 1 && (!parts || !aligned16(parts) || parts_bytes < (size_t)(slices - 1) * one)) return CHORUS_E_WORKSPACE;
-  const GemmParts two{parts, one, parts + (slices > 1 ? (size_t)M * N : 0), slices > 2 ? (size_t)(slices - 2) * one : 0};
+  const GemmParts two{parts, one, parts + (slices > 1 ? (size_t)M * N : 0), slices > 2 ? (size_t)(slices - 2) * one : 0, nullptr};
   return launch_plan(GemmPlan{tile, slices, 0.0}, A, W, (long)M, N, K, CHORUS_EPI_RESID, EpiArgs{out, bias, gate0, gate1, scale},
                      two, (hipStream_t)stream);
 }
@@ -847,7 +966,7 @@ extern "C" int32_t chorus_gemm_bf16_plan(int64_t M, int32_t N, int32_t K, int32_
   if (K % BK || N % 8) return CHORUS_E_SHAPE;
   void* some = reinterpret_cast<void*>(uintptr_t{16});  // where the scratch lies does not matter
   const GemmCut cut = plan_rows((long)M, N, K, epilogue,
-                                GemmParts{first_bytes ? some : nullptr, first_bytes, rest_bytes ? some : nullptr, rest_bytes});
+                                GemmParts{first_bytes ? some : nullptr, first_bytes, rest_bytes ? some : nullptr, rest_bytes, nullptr});
   *out = chorus_gemm_plan{cut.head_rows, kTileNumber[cut.rest.tile], cut.rest.slices};
   return CHORUS_OK;
 }
@@ -864,4 +983,38 @@ extern "C" int32_t chorus_gemm_bf16(const uint16_t* A, const uint16_t* W, int64_
                                     int32_t epilogue, void* out, const float* bias, const float* gate0,
                                     const float* gate1, float scale, void* stream) {
   return gemm_bf16_parts(A, W, M, N, K, epilogue, out, bias, gate0, gate1, scale, kNoParts, stream);
+}
+
+__global__ __launch_bounds__(256) void clear_counts_kernel(uint32_t* p, int n) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < n) p[i] = 0;
+}
+
+extern "C" int32_t chorus_gemm_bf16_chain(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, float* out,
+                                          const float* bias, const float* gate0, const float* gate1, float scale, int32_t kernel,
+                                          int32_t slices, uint32_t* counts, int32_t n_counts, void* stream) {
+  const int tile = tile_of_number(kernel);
+  if (tile < 0 || tile == kTile128 || slices < 1 || slices > kMaxChain) return CHORUS_E_ARG;
+  CHK_STATUS(check_gemm(A, W, M, N, K, out, bias, gate0, gate1));
+  if (slices > K / BK || K > kMaxOffsetK || N > 1 << 20) return CHORUS_E_SHAPE;
+  if (M == 0) return CHORUS_OK;
+  const long tiles = tile_count(tile, (long)M, N);
+  if (tiles * slices > 0x7fffffffL / 256) return CHORUS_E_SHAPE;
+  if (!counts || n_counts < tiles) return CHORUS_E_WORKSPACE;
+  hipStream_t s = (hipStream_t)stream;
+  hipLaunchKernelGGL(clear_counts_kernel, dim3((unsigned)((tiles + 255) / 256)), dim3(256), 0, s, counts, (int)tiles);
+  CHORUS_LAUNCH_CHECK();
+  return launch_chain_tile(tile, A, W, (long)M, N, K, EpiArgs{out, bias, gate0, gate1, scale}, slices, counts, s);
+}
+
+extern "C" int32_t chorus_gemm_bf16_chain_plan(int64_t M, int32_t N, int32_t K, size_t first_bytes, size_t rest_bytes, chorus_gemm_plan* out,
+                                               int32_t* chained) {
+  if (!out || !chained || M < 1 || N <= 0 || K <= 0) return CHORUS_E_ARG;
+  if (K % BK || N % 8) return CHORUS_E_SHAPE;
+  void* some = reinterpret_cast<void*>(uintptr_t{16});  // where the scratch lies does not matter
+  const GemmCut cut = plan_rows((long)M, N, K, CHORUS_EPI_RESID, GemmParts{first_bytes ? some : nullptr, first_bytes,
+                                rest_bytes ? some : nullptr, rest_bytes, static_cast<uint32_t*>(some)});
+  *out = chorus_gemm_plan{cut.head_rows, kTileNumber[cut.rest.tile], cut.rest.slices};
+  *chained = cut.rest.chain;
+  return CHORUS_OK;
 }

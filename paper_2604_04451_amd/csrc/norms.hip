@@ -22,7 +22,9 @@ __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restric
                                                           long L, int D, const float* __restrict__ mul0,
                                                           const float* __restrict__ mul1,
                                                           const float* __restrict__ add0,
-                                                          const float* __restrict__ add1, float mul_base) {
+                                                          const float* __restrict__ add1, float mul_base,
+                                                          uint32_t* __restrict__ clear, int n_clear) {
+  if (blockIdx.x == 0 && (int)threadIdx.x < n_clear) clear[threadIdx.x] = 0;
   // the two modulation vectors are the same for every row: the workgroup combines them once into LDS
   // ((base + mul0 + mul1) and (add0 + add1)) while the rows' loads are in flight
   extern __shared__ __attribute__((aligned(16))) float s_tab[];  // [2][D]
@@ -292,7 +294,8 @@ __global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __res
     uint16_t tile[64][64 + 2];
   } sm;
   int block = blockIdx.x;
-  if (block == 0 && (int)threadIdx.x < n_clear) clear[threadIdx.x] = 0;
+  if (block == 0)
+    for (int i = threadIdx.x; i < n_clear; i += 256) clear[i] = 0;
   if constexpr (std::is_same_v<TEXT, PrepareText>) {
     if (block >= first2) {  // the workgroups behind the tokens': the text
       block -= first2;
@@ -340,7 +343,7 @@ int32_t attn_prepare(const uint16_t* q, const uint16_t* k, const uint16_t* v, lo
   const int D = H * dh;
   const long row_blocks = (Lpad + 3) / 4 * (q ? 2 : 1), v_tiles = Lpad / 64, first2 = row_blocks + v_tiles * (D / 64);
   const long blocks = first2 + (text ? (text->Lpad + 3) / 4 + text->Lpad / 64 * (D / 64) : 0);
-  if (blocks > 0x7fffffffL || n_clear > 256) return CHORUS_E_SHAPE;
+  if (blocks > 0x7fffffffL) return CHORUS_E_SHAPE;
 #define PREPARE_AS(NCH, TEXT, text)                                                                                           \
   hipLaunchKernelGGL((attn_prepare_kernel<NCH, TEXT>), dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, q, k, v, ld,  \
                      gain_q, gain_k, qh, kh, vt, L, Lpad, H, dh, token_idx, gH, gW, rope, q_scale, (int)row_blocks, (int)v_tiles, \
@@ -362,6 +365,29 @@ int32_t attn_prepare(const uint16_t* q, const uint16_t* k, const uint16_t* v, lo
   return CHORUS_OK;
 }
 
+int32_t ln_modulate(const float* x, uint16_t* out, long L, int D, const float* mul0, const float* mul1, const float* add0,
+                    const float* add1, int plus_one, uint32_t* clear, int n_clear, void* stream) {
+  if (!x || !out || !mul0 || !add0) return CHORUS_E_ARG;
+  if (D % 4) return CHORUS_E_SHAPE;
+  if (!aligned16(x) || !aligned16(out) || !aligned16(mul0) || !aligned16(add0) || !aligned16(mul1) || !aligned16(add1))
+    return CHORUS_E_ARG;
+  hipStream_t s = (hipStream_t)stream;
+  dim3 grid((unsigned)((L + 3) / 4)), block(256);
+  float base = plus_one ? 1.0f : 0.0f;
+  const size_t tab_bytes = (size_t)2 * D * sizeof(float);
+  if (tab_bytes > 64 * 1024 || n_clear > 256) return CHORUS_E_SHAPE;
+#define LAUNCH_LN(NV) \
+  hipLaunchKernelGGL((ln_modulate_kernel<NV>), grid, block, tab_bytes, s, x, out, (long)L, D, mul0, mul1, add0, add1, base, clear, \
+                     n_clear)
+  if (D == 256) LAUNCH_LN(1);
+  else if (D == 1536) LAUNCH_LN(6);
+  else if (D == 5120) LAUNCH_LN(20);
+  else LAUNCH_LN(0);
+#undef LAUNCH_LN
+  CHORUS_LAUNCH_CHECK();
+  return CHORUS_OK;
+}
+
 }  // namespace chorus
 
 using namespace chorus;
@@ -372,24 +398,7 @@ int32_t chorus_ln_modulate(const float* x, uint16_t* out, int64_t L, int32_t D, 
                            const float* add0, const float* add1, int32_t plus_one, void* stream) {
   if (L < 0 || D <= 0) return CHORUS_E_ARG;
   if (L == 0) return CHORUS_OK;
-  if (!x || !out || !mul0 || !add0) return CHORUS_E_ARG;
-  if (D % 4) return CHORUS_E_SHAPE;
-  if (!aligned16(x) || !aligned16(out) || !aligned16(mul0) || !aligned16(add0) || !aligned16(mul1) || !aligned16(add1))
-    return CHORUS_E_ARG;
-  hipStream_t s = (hipStream_t)stream;
-  dim3 grid((unsigned)((L + 3) / 4)), block(256);
-  float base = plus_one ? 1.0f : 0.0f;
-  const size_t tab_bytes = (size_t)2 * D * sizeof(float);
-  if (tab_bytes > 64 * 1024) return CHORUS_E_SHAPE;
-#define LAUNCH_LN(NV) \
-  hipLaunchKernelGGL((ln_modulate_kernel<NV>), grid, block, tab_bytes, s, x, out, (long)L, D, mul0, mul1, add0, add1, base)
-  if (D == 256) LAUNCH_LN(1);
-  else if (D == 1536) LAUNCH_LN(6);
-  else if (D == 5120) LAUNCH_LN(20);
-  else LAUNCH_LN(0);
-#undef LAUNCH_LN
-  CHORUS_LAUNCH_CHECK();
-  return CHORUS_OK;
+  return ln_modulate(x, out, (long)L, D, mul0, mul1, add0, add1, plus_one, nullptr, 0, stream);
 }
 
 int32_t chorus_qk_norm_rope(const uint16_t* in, int64_t ld, const float* gain, uint16_t* out, int64_t L, int64_t Lpad,

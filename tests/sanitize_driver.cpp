@@ -127,6 +127,10 @@ static void sizes_and_validation() {
       EXPECT(plan.kernel >= 1 && plan.kernel <= 5 && plan.slices >= 1 && plan.slices <= 4 && plan.head_rows < m);
     }
   EXPECT(chorus_attention_variant(13104, 512, 512, 12, 128, 1, 256) == 5);
+  chorus_gemm_plan chain_plan;
+  int32_t chained = -1;
+  EXPECT(chorus_gemm_bf16_chain_plan(3271, 1536, 8960, 0, 0, &chain_plan, &chained) == CHORUS_OK && chained == 1 && chain_plan.slices == 3);
+  EXPECT(chorus_gemm_bf16_chain(nullptr, nullptr, 8, 64, 128, nullptr, nullptr, nullptr, nullptr, 1.f, 1, 2, nullptr, 0, nullptr) == CHORUS_E_ARG);
   int64_t whole = -1;
   int32_t slices = -1;
   EXPECT(chorus_attention_slices_plan(13104, 12, 128, 256, 40u << 20, 120u << 20, &whole, &slices) == CHORUS_OK && whole == 512 && slices == 2);

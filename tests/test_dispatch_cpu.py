@@ -123,6 +123,29 @@ def test_second_ffn_product_in_slices():
     assert B.chorus_gemm_bf16_plan(64, 64, 128, B.EPI_RESID, one, 2 * one)[2] <= 2    # no more slices than steps
 
 
+def test_residual_products_in_chained_slices():
+    """The choice that a block makes: a chain where every slice has a unit and 16 steps or more, and it is estimated to be faster."""
+    plan = lambda M, N, K, first=0, rest=0: B.chorus_gemm_bf16_chain_plan(M, N, K, first, rest)  # noqa: E731
+    for M, want in ((3271, (0, 3, 3, True)), (4500, (0, 3, 2, True)), (2000, (0, 2, 2, True)), (1350, (0, 2, 3, True)), (1100, (0, 5, 2, True))):
+        assert plan(M, 1536, 8960, 4 * M * 1536) == want, M
+    assert plan(480, 1536, 8960, 4 * 480 * 1536, 8 * 480 * 1536) == (0, 5, 4, False)  # slices with scratch
+    assert plan(13104, 1536, 8960) == (10752, 2, 2, True)                            # the rows behind the last whole round
+    for M in (300, 1200, 3271, 13104):
+        assert not plan(M, 1536, 1536)[3] and not plan(M, 256, 1024)[3]              # too few steps
+    assert plan(6000, 1536, 8960)[2:] == plan(32760, 1536, 8960)[2:] == plan(75600, 5120, 13824)[2:] == (1, False)
+    assert plan(960, 5120, 13824) == plan(960, 5120, 5120) == (0, 3, 3, True)
+    assert not plan(300, 1 << 21, 4096)[3] and not plan(64, 64, 1 << 22)[3]          # out of the 32-bit offsets' reach
+    for M in range(64, 6000, 160):
+        for N, K in ((768, 3072), (1536, 8960), (3072, 4096), (5120, 5120)):
+            head, kernel, slices, chained = plan(M, N, K)
+            rows, cols = {1: (64, 64), 2: (128, 256), 3: (256, 256), 4: (128, 128), 5: (128, 128)}[kernel]
+            assert not chained or (-(-(M - head) // rows) * -(-N // cols) * slices <= 256 and K // 64 // slices >= 16), (M, N, K)
+    out, chained = B.GemmPlan(), B.C.c_int32()
+    for bad, status in (((0, 64, 64), B.E_ARG), ((8, 64, 100), B.E_SHAPE), ((8, 60, 64), B.E_SHAPE)):
+        assert B.load().chorus_gemm_bf16_chain_plan(*bad, 0, 0, B.C.byref(out), B.C.byref(chained)) == status
+    assert B.load().chorus_gemm_bf16_chain_plan(8, 64, 64, 0, 0, None, B.C.byref(chained)) == B.E_ARG
+
+
 def test_two_products_in_one_launch():
     """Where one launch for both is the faster one as measured: by the tiles of both together, not of the first alone."""
     two = lambda D, Ls, Lt: B.chorus_gemm_bf16_two_plan(Ls, 3 * D, Lt, 2 * D, D)  # noqa: E731

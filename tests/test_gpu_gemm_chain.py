@@ -1,0 +1,87 @@
+"""GPU parity of the gated residual in chained slices of K (each slice adds to the residual behind the one in front of it) and of the
+block's products that take it."""
+import pytest
+import torch
+
+from paper_2604_04451_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+TILES = {1: (64, 64), 2: (128, 256), 3: (256, 256), 5: (128, 128)}
+
+
+def _ints(shape, seed, lo=-2, hi=3):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return torch.randint(lo, hi, shape, generator=g, device="cuda").to(torch.float32)
+
+
+@pytest.mark.parametrize("kernel", list(TILES))
+@pytest.mark.parametrize("steps,slices", [(1, 1), (2, 2), (7, 3), (9, 4), (30, 2), (61, 3), (80, 4)])
+def test_chain(kernel, steps, slices):
+    """Small integers: every order of summation gives the same bits. Rows and columns that end inside a tile, on its edge and behind it;
+    slices of one step, of unequal length and (from 30 steps on) each longer than the one in front of it; a count that starts anywhere."""
+    rows, cols = TILES[kernel]
+    for M, N in ((1, 8), (rows - 1, cols), (rows, cols - 8), (2 * rows + 3, 2 * cols + 24)):
+        K = 64 * steps
+        print(f"[case] gemm chain kernel={kernel} M={M} N={N} K={K} slices={slices}", flush=True)
+        A, W, b, g0, g1 = _ints((M, K), 1), _ints((N, K), 2), _ints((N,), 3), _ints((N,), 5), _ints((N,), 6)
+        out = _ints((M, N), 4)
+        counts = torch.full((-(-M // rows) * -(-N // cols),), 77, dtype=torch.int32, device="cuda")
+        for gates, scale, want in (((g0, g1), 2.0, out + 2 * (g0 + g1) * (A @ W.T + b)), ((None, None), 0.5, out + 0.5 * (A @ W.T + b))):
+            buf = torch.cat((out, torch.full((2, N), 7.0, device="cuda")))
+            B.chorus_gemm_bf16_chain(A.bfloat16(), W.bfloat16(), buf[:M], kernel, slices, b, *gates, scale, counts)
+            assert torch.equal(buf[:M], want) and bool((buf[M:] == 7.0).all())
+
+
+def test_chain_refuses():
+    A, W = torch.zeros(8, 128, dtype=torch.bfloat16, device="cuda"), torch.zeros(64, 128, dtype=torch.bfloat16, device="cuda")
+    out, counts = torch.zeros(8, 64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    for kernel, slices, n in ((4, 2, 1), (0, 2, 1), (6, 2, 1), (1, 0, 1), (1, 5, 1), (1, 3, 1), (1, 2, 0)):
+        with pytest.raises(B.ChorusError):
+            B.chorus_gemm_bf16_chain(A, W, out, kernel, slices, counts=counts[:n])
+
+
+# (D, H, F, Ls): blocks whose O, cross-O and second FFN products are chained (True), by chorus_gemm_bf16_chain_plan
+BLOCKS = {(1536, 12, 4096, 300): (False, True), (2048, 16, 4096, 1000): (True, True), (2560, 20, 4096, 150): (True, True),
+          (1024, 8, 8192, 1000): (False, True)}
+
+
+@pytest.mark.parametrize("D,H,F,Ls", list(BLOCKS))
+def test_block_with_chained_products(D, H, F, Ls):
+    """Three replays of a captured block with other work in between, on a workspace that starts anywhere, against the call outside, and
+    that against float64 of the FFN branch (its hidden rows rounded to bf16, as are its inputs: 5 roundings of 2^-9 / sqrt(3) at most)."""
+    chained = lambda K: B.chorus_gemm_bf16_chain_plan(Ls, D, K, 4 * Ls * D)[3]  # noqa: E731
+    assert (chained(D), chained(F)) == BLOCKS[D, H, F, Ls]
+    print(f"[case] block chained D={D} F={F} Ls={Ls}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(D + F)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)  # noqa: E731
+    t = {}
+    for n, o, i in (("qkv", 3 * D, D), ("o", D, D), ("cq", D, D), ("ckv", 2 * D, D), ("co", D, D), ("1", F, D), ("2", D, F)):
+        t["w_" + n], t["b_" + n] = (rnd(o, i) * 0.02).bfloat16(), rnd(o) * 0.05
+    t.update(mod_table=rnd(6, D) * 0.3, g_q=rnd(D), g_k=rnd(D), g_cq=rnd(D), g_ck=rnd(D), ln3_w=rnd(D), ln3_b=rnd(D))
+    w = B.DeviceBlock(t, B.BlockWeights(**{n: t[n].data_ptr() for n in B._W_FIELDS}))
+    shape = B.make_block_shape(D, H, D // H, F, 40, (1, 32, 32))
+    x, ctx, t_mod = rnd(Ls, D), rnd(40, D).bfloat16(), rnd(6, D) * 0.3
+    ws = torch.full((B.chorus_dit_block_workspace_bytes(shape, Ls),), 255, dtype=torch.uint8, device="cuda")
+    want = x.clone()
+    B.chorus_dit_block_step(shape, w, want, Ls, None, ctx, t_mod, None, 1.0, ws)
+    got = x.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.chorus_dit_block_step(shape, w, got, Ls, None, ctx, t_mod, None, 1.0, ws)
+    for _ in range(3):
+        got.copy_(x)
+        ws.fill_(85)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
+    for n in ("o", "co"):  # the FFN alone
+        t["w_" + n].zero_()
+        t["b_" + n].zero_()
+    y = x.clone()
+    B.chorus_dit_block_step(shape, w, y, Ls, None, ctx, t_mod, None, 1.0, ws)
+    xd, m = x.double(), (t["mod_table"] + t_mod).double()
+    h = (xd - xd.mean(1, keepdim=True)) * (xd.var(1, unbiased=False, keepdim=True) + 1e-6).rsqrt() * (1 + m[4]) + m[3]
+    f = torch.nn.functional.gelu(h @ t["w_1"].double().T + t["b_1"].double(), approximate="tanh") @ t["w_2"].double().T + t["b_2"].double()
+    delta = m[5] * f
+    assert float(((y.double() - xd) - delta).norm() / delta.norm()) < 5 * 2.0 ** -9 / 3 ** 0.5
