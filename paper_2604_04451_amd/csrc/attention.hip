@@ -953,18 +953,23 @@ int device_cus() {
   return cus;
 }
 
-// The tiles of a last round that fills half of the chip or less: in as many slices as there are units for, four at most, where the sweep
+// The tiles of a last round that fills two thirds of the chip or less: in as many slices as there are units for, four at most, where the sweep
 // over the keys is long enough for what a slice costs beside it, about 20 us of chip time (its first loads, the ping-pong's start
 // and end, and 139 KB a slab out and in). Whole call, halves of 128 rows as before / slices, us: 13104 tokens, 12 heads (112 tiles, two
 // slices) 853 / 786; 8100 (128, two) 329 / 311; 5632 (8, four; 44 key tiles) 216 / 190, in two slices 208; 6000 (32, four) 230 / 202; 40
 // heads: 7168 tokens (96, two) 802 / 793, 3300 (8, four; 26 key tiles) 221 / 212, 2000 (64, three; 16) 91 / 90; 4 heads of 64, 3584 tokens
-// (56, four; 28) 30.6 / 28. Slower: 2560 tokens, 12 heads (120, two; 20 key tiles) 44 / 43 to 45, 1792, 40 heads (24, four; 14) 82 / 84.
+// (56, four; 28) 30.6 / 28. Up to two thirds of the chip, three slices a tile in two rounds: 8840 tokens, 12 heads (164; 70 key tiles)
+// whole tiles 410 / slices 392, 3271 (156; 26) 75 / 84. Slower: 2560 tokens, 12 heads (120, two; 20 key tiles) 44 / 43 to 45, 1792, 40 heads (24, four; 14) 82 / 84.
 AttnSlices attention_slices(long L, int H, int dh, int cus, const AttnScratch& scratch) {
   const AttnSlices none{0, 0, 0};
   const long tiles = (L + 255) / 256 * H, units = (L + 127) / 128;
   if (cus <= 0 || tiles > 0x7fffffffL / 2) return none;
   const long sliced = tiles % cus;
-  if (sliced == 0 || 2 * sliced > cus) return none;
+  if (sliced == 0) return none;
+  if (2 * sliced > cus) {
+    if (3 * sliced > 2L * cus || units < 60 || !slices_fit(slice_scratch(dh, (int)sliced, 3), scratch)) return none;
+    return AttnSlices{tiles - sliced, (int)sliced, 3};
+  }
   for (int slices = (int)(cus / sliced < kMaxKeySlices ? cus / sliced : kMaxKeySlices); slices >= 2; --slices)
     if (slices_fit(slice_scratch(dh, (int)sliced, slices), scratch))
       return units < (slices == 2 ? 40 : 24) ? none : AttnSlices{tiles - sliced, (int)sliced, slices};

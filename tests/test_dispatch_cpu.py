@@ -37,6 +37,7 @@ def test_attention_slices():
     assert _slices(1200, 12) == _slices(2560, 12) == _slices(1792, 40) == (0, 0)  # too few keys
     assert _slices(5120, 3, 128, 1 << 30) == (0, 4) and _slices(5121, 4, 128, 1 << 30) == (0, 3)
     assert _slices(5120, 3) == (0, 2) and _slices(3584, 4, 64) == (0, 0)  # as many slices as there is scratch for
+    assert _slices(8840, 12) == (256, 3) and _slices(9400, 12) == (0, 0)  # 164 and 188 tiles
     need = 2 * 112 * 4 + 112 * 4
     need = -(-need // 256) * 256 + 112 * 139264
     assert _slices(13104, 12, 128, need, 0) == (512, 2) and _slices(13104, 12, 128, need - 1, 0) == (0, 0)
