@@ -300,10 +300,21 @@ struct KeySlices {
   float* slab1;     // the slabs that do not fit there
   int tiles, slices, units;
   int slab0, n0;    // where the first slab stands behind `words`, in 32-bit words, and how many stand there
-  static constexpr bool kSliced = true;
+  static constexpr bool kSliced = true, kRun = false;
 };
 struct WholeKeys {
-  static constexpr bool kSliced = false;
+  static constexpr bool kSliced = false, kRun = false;
+};
+// A workgroup a unit that walks over its share of `tiles` tiles. The loop over a tile's keys runs on into the next tile's: the next queries
+// are requested in the last softmax phase, when this tile's are no longer needed, the next first keys in their usual place, and the finished
+// tile leaves in the next first softmax phase, under the other group's MFMAs. A workgroup that ends instead leaves its unit to one
+// that starts cold: about 9 us a tile.
+struct TileRun {
+  const uint16_t *Q, *K, *Vt;
+  uint16_t* O;
+  long Lq, LqPad, LkPad;
+  int H, n_qtiles, tiles, stride;
+  static constexpr bool kSliced = false, kRun = true;
 };
 // 8-byte words of one lane in a slab: the results in halves of four, then (reference, row sum) per block of rows
 constexpr int slab_words(int dh, int rb) { return (dh / 16 * 2 + 1) * rb; }
@@ -370,6 +381,14 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   // this launch covers the tiles tile_base .. tile_base + gridDim.x - 1 of the H * n_qtiles of its tile size, or in slices a
   // keys.slices-th as many
   int tile_id = tile_base + xcd_remap(blockIdx.x, gridDim.x), first_kt = 0;
+  int stride = 1, runs = 1;  // TileRun: the workgroups of an XCD take its range of tiles in turn, neighbours at a time
+  if constexpr (KEYS::kRun) {
+    const int xcd = blockIdx.x % 8, q = keys_arg.tiles / 8, r = keys_arg.tiles % 8, mine = q + (xcd < r), local = blockIdx.x / 8;
+    stride = keys_arg.stride;
+    runs = (mine - local + stride - 1) / stride;
+    if (runs <= 0) return;
+    tile_id = tile_base + xcd * q + (xcd < r ? xcd : r) + local;
+  }
   if constexpr (KEYS::kSliced) {
     const KeySlices& keys = keys_arg;
     const int at = tile_id - tile_base, t = at / keys.slices, slice = at - t * keys.slices;
@@ -383,20 +402,24 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int group = wave >> 2;
   const int lq = lane & 15, g = lane >> 4;
-  const long q_wave0 = (long)qt * QROWS + wave * 16 * RB;
 
   const uint16_t* Kh = K + ((long)head * LkPad + (long)first_kt * KTL) * DH;
   const uint16_t* Vh = Vt + (long)head * DH * LkPad + (long)first_kt * KTL;
 
   bf16x8 qf[RB][KC];
+  auto load_q = [&](const uint16_t* Q, long Lq, long LqPad, int of_head, int of_qt) {
 #pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    long q = q_wave0 + 16 * rb + lq;
-    if (q > Lq - 1) q = Lq - 1;
-    const uint16_t* qp = Q + ((long)head * LqPad + q) * DH + 8 * g;
+    for (int rb = 0; rb < RB; ++rb) {
+      int t = tid;
+      if constexpr (CS && KEYS::kRun) asm volatile("" : "+v"(t));  // as fresh_tid below
+      long q = (long)of_qt * QROWS + (t >> 6) * 16 * RB + 16 * rb + (t & 15);
+      if (q > Lq - 1) q = Lq - 1;
+      const uint16_t* qp = Q + ((long)of_head * LqPad + q) * DH + 8 * ((t & 63) >> 4);
 #pragma unroll
-    for (int kc = 0; kc < KC; ++kc) qf[rb][kc] = *reinterpret_cast<const bf16x8*>(qp + 32 * kc);
-  }
+      for (int kc = 0; kc < KC; ++kc) qf[rb][kc] = *reinterpret_cast<const bf16x8*>(qp + 32 * kc);
+    }
+  };
+  load_q(Q, Lq, LqPad, head, qt);
 
   f32x4 o[DB][RB];
 #pragma unroll
@@ -421,18 +444,23 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   const int ntiles = (int)((Lk + KTL - 1) / KTL);
   u32x4 rk[K_LD], rv[V_LD];
 
-  auto load_k = [&](int kt) {
+  auto load_k_of = [&](const uint16_t* base, int kt) {
 #pragma unroll
     for (int i = 0; i < K_LD; ++i)
-      rk[i] = *reinterpret_cast<const u32x4*>(Kh + (long)kt * KTL * DH + (tid + NT * i) * 8);
+      rk[i] = *reinterpret_cast<const u32x4*>(base + (long)kt * KTL * DH + (uint32_t)((tid + NT * i) * 8));
   };
-  auto load_v = [&](int kt) {
+  auto load_v_of = [&](const uint16_t* base, int kt) {
 #pragma unroll
     for (int i = 0; i < V_LD; ++i) {
       int id = tid + NT * i, row = id / (KTL / 8), ch = id % (KTL / 8);
-      rv[i] = *reinterpret_cast<const u32x4*>(Vh + (long)row * LkPad + (long)kt * KTL + ch * 8);
+      if constexpr (KEYS::kRun)  // a scalar base and a 32-bit offset: 128 rows of at most 2^23 keys
+        rv[i] = *reinterpret_cast<const u32x4*>(base + (long)kt * KTL + (uint32_t)(row * (int)LkPad + ch * 8));
+      else
+        rv[i] = *reinterpret_cast<const u32x4*>(base + (long)row * LkPad + (long)kt * KTL + ch * 8);
     }
   };
+  auto load_k = [&](int kt) { load_k_of(Kh, kt); };
+  auto load_v = [&](int kt) { load_v_of(Vh, kt); };
   auto store_k = [&](int buf) {
 #pragma unroll
     for (int i = 0; i < K_LD; ++i) {
@@ -452,9 +480,8 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   // reads the other buffer). Keys past the end get 1.
   // With factors and 256 rows the kernel is at the register limit, and what a few instructions make again from the thread
   // id must not be kept across the loop: this hides the id from the compiler, which would keep it and spill six registers.
-  // Over long keys that is the factors' addresses and the output's (scaled queries, 32760 x 512, 12 heads 141.3 -> 137.3 us,
-  // 13104 x 512, 40 heads 209 -> 202), over short ones the output's alone (13104 x 226, 40 heads 173 -> 165; the others as
-  // well 172). The V rows' addresses stay: made again for every tile they cost 10 % of the launch.
+  // That is the factors' addresses and the output's (scaled queries, 32760 x 512, 12 heads 141.3 -> 137.3 us, 13104 x 512, 40 heads
+  // 209 -> 202, 13104 x 226, 40 heads 173 -> 165). The V rows' addresses stay: made again for every tile they cost 10 % of the launch.
   auto fresh_tid = [&]() {
     int t = tid;
     if constexpr (CS) asm volatile("" : "+v"(t));
@@ -462,11 +489,11 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   };
   float rc = 1.f;
   auto load_c = [&](int kt) {
-    const int key = kt * KTL + (SUM32 ? tid : fresh_tid());
+    const int key = kt * KTL + fresh_tid();
     if (tid < KTL) rc = key < (int)Lk ? col_scale[key] : 1.0f;
   };
   auto store_c = [&](int buf) {
-    if (tid < KTL) smc[buf * KTL + (SUM32 ? tid : fresh_tid())] = rc;
+    if (tid < KTL) smc[buf * KTL + fresh_tid()] = rc;
   };
   // LDS row of the K tile that fragment row lane % 16 of block kb stands for
   const int krow0 = 16 * (lq >> 3) + (lq & 7);
@@ -528,11 +555,71 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
   __syncthreads();
   if (group == 1) lds_barrier();  // run one phase behind group 0
 
-  for (int j = 0; j < ntiles; ++j) {
+  // TileRun: the arguments again, read where they are needed instead of kept in scalar registers across the loop
+  typedef const __attribute__((address_space(4))) KEYS* ArgPtr;
+  auto args = [&]() {
+    ArgPtr a = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return a;
+  };
+  // the rows of a tile leave
+  auto finish = [&](uint16_t* O, long Lq, int D, int head, int qt) {
+    const long q_wave0 = (long)qt * QROWS + wave * 16 * RB;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+      float l = lacc[rb][0];
+      if constexpr (SUM32) {  // the four lanes that share a query row
+        l = l_run[rb] + swap_rows16(l_run[rb]);
+        l += swap_halves(l);
+      }
+      const float inv = 1.0f / l;
+      const int t = fresh_tid();
+      const long q = CS ? (long)qt * QROWS + (t >> 6) * 16 * RB + 16 * rb + (t & 15) : q_wave0 + 16 * rb + lq;
+      if (q < Lq) {
+        uint16_t* op = O + q * (long)D + head * DH + 4 * (CS ? (t & 63) >> 4 : g);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          uint2 w;
+          w.x = pack_bf16x2(o[db][rb][0] * inv, o[db][rb][1] * inv);
+          w.y = pack_bf16x2(o[db][rb][2] * inv, o[db][rb][3] * inv);
+          *reinterpret_cast<uint2*>(op + 16 * db) = w;
+        }
+      }
+    }
+  };
+  bool started = false;  // a tile is waiting to leave
+  int parity = 0;        // of all key tiles so far
+  for (int j = 0; KEYS::kRun || j < ntiles;) {  // j: which tile of keys
+    const int buf = KEYS::kRun ? parity : j & 1;  // where in LDS it is
     // ================= VALU phase: softmax of tile j =================
     __builtin_amdgcn_sched_barrier(0);
+    const bool last_kt = j == ntiles - 1;
+    const bool on = KEYS::kRun && runs > 1;  // another tile of queries behind this one
+    const uint16_t *Kn = Kh, *Vn = Vh;       // its keys and values
+    if constexpr (KEYS::kRun) {
+      if (j == 0 && started) {
+        const ArgPtr a = args();
+        const int t = tile_id - a->stride, nq = a->n_qtiles, of_head = t / nq;
+        finish(a->O, a->Lq, a->H * DH, of_head, t - of_head * nq);
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          lacc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+          l_run[rb] = 0.f;
+#pragma unroll
+          for (int db = 0; db < DB; ++db) o[db][rb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (on && j + 2 >= ntiles) {
+        const ArgPtr a = args();
+        const int t = tile_id + a->stride, nq = a->n_qtiles, of_head = t / nq;
+        Kn = a->K + (long)of_head * a->LkPad * DH;
+        Vn = a->Vt + (long)of_head * DH * a->LkPad;
+        if (last_kt) load_q(a->Q, a->Lq, a->LqPad, of_head, t - of_head * nq);
+      }
+    }
     if constexpr (CS) {
-      const float* cfs = smc + (j & 1) * KTL + 16 * (g >> 1) + 4 * (g & 1);
+      const float* cfs = smc + buf * KTL + 16 * (g >> 1) + 4 * (g & 1);
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb) {
         const f32x4 cf = *reinterpret_cast<const f32x4*>(cfs + 32 * (kb >> 1) + 8 * (kb & 1));
@@ -543,20 +630,26 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
             s[kb][rb][i] = PRE ? __builtin_fmaf(s[kb][rb][i], cf[i], -m_run[rb]) : s[kb][rb][i] * cf[i];
         if (kb % 2 == 1) __builtin_amdgcn_sched_barrier(0);  // two factors in flight at a time: there are no registers for eight
       }
-      load_c(j + 1 < ntiles ? j + 1 : ntiles - 1);
+      load_c(!last_kt ? j + 1 : on ? 0 : ntiles - 1);
       __builtin_amdgcn_sched_barrier(0);
     }
-    // the global prefetch of the tiles that the next MFMA phase stores: K(j+2), V(j+1) (past the end the last tile again)
-    load_k(j + 2 < ntiles ? j + 2 : ntiles - 1);
-    load_v(j + 1 < ntiles ? j + 1 : ntiles - 1);
-    if (j == ntiles - 1 && (Lk % KTL) != 0) {
-      const long key0 = (long)j * KTL + 16 * (g >> 1) + 4 * (g & 1);
+    // the global prefetch of the tiles that the next MFMA phase stores: K(j+2), V(j+1) (past the end the next tile's first, or the last again)
+    load_k_of(j + 2 < ntiles ? Kh : Kn, j + 2 < ntiles ? j + 2 : on ? j + 2 - ntiles : ntiles - 1);
+    load_v_of(last_kt ? Vn : Vh, !last_kt ? j + 1 : on ? 0 : ntiles - 1);
+    if (last_kt && (Lk % KTL) != 0) {
+      // Long keys: compared here. Hoisted out of the loop the 32 results take 64 scalar registers, and what that displaces costs the LDS
+      // reads of the MFMA phase their lead where registers are short (with factors, and where workgroups walk over tiles). Over a few
+      // tiles of keys the comparisons themselves cost more (13104 x 226 with factors, 40 heads 165 -> 173 us).
+      const int gg = CS && !SUM32 ? (fresh_tid() & 63) >> 4 : g;
+      int rest = (int)(Lk - (long)j * KTL) - (16 * (gg >> 1) + 4 * (gg & 1));
+      if constexpr (!SUM32) asm volatile("" : "+v"(rest));
 #pragma unroll
       for (int kb = 0; kb < KB; ++kb)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const long key = key0 + 32 * (kb >> 1) + 8 * (kb & 1) + i;
-          if (key >= Lk) {
+          const bool past = SUM32 ? (long)j * KTL + 16 * (g >> 1) + 4 * (g & 1) + 32 * (kb >> 1) + 8 * (kb & 1) + i >= Lk
+                                  : 32 * (kb >> 1) + 8 * (kb & 1) + i >= rest;
+          if (past) {
 #pragma unroll
             for (int rb = 0; rb < RB; ++rb) s[kb][rb][i] = -INFINITY;
           }
@@ -640,11 +733,11 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
 
     // ================= MFMA phase: O += V(j) P(j); S(j+1) = K(j+1) Q^T =================
     __builtin_amdgcn_s_setprio(1);
-    store_k(j & 1);
-    store_v((j + 1) & 1);
-    if constexpr (CS) store_c((j + 1) & 1);
+    store_k(buf);
+    store_v(buf ^ 1);
+    if constexpr (CS) store_c(buf ^ 1);
     {
-      const int vb = j & 1;
+      const int vb = buf;
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
         bf16x8 vf[NC];
@@ -662,7 +755,12 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
 #pragma unroll
         for (int c = 0; c < NC; ++c) lacc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[c][rb], lacc[rb], 0, 0, 0);
     }
-    compute_s((j + 1) & 1);
+    if constexpr (KEYS::kRun) {
+      // the next tile's references start at zero
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb) m_run[rb] = last_kt ? 0.f : m_run[rb];
+    }
+    compute_s(buf ^ 1);
     // issue order: LDS stores, then LDS operand reads kept ahead of the MFMAs (one read feeds two)
     constexpr int kAhead = 6;  // more reads in flight cost the registers the schedule needs; fewer expose LDS latency
     __builtin_amdgcn_sched_group_barrier(0x200, K_LD + V_LD, 0);
@@ -677,6 +775,19 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
     __builtin_amdgcn_sched_barrier(0);
     lds_barrier();  // this wave's LDS stores are done
     __builtin_amdgcn_sched_barrier(0);
+    ++j;
+    if constexpr (KEYS::kRun) {
+      parity ^= 1;
+      if (last_kt) {
+        if (!on) break;
+        j = 0;
+        --runs;
+        tile_id += args()->stride;
+        Kh = Kn;
+        Vh = Vn;
+        started = true;
+      }
+    }
   }
   if (group == 0) lds_barrier();  // every wave executes the same number of barriers
 
@@ -797,27 +908,12 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
     }
   }
 
-  const int D = H * DH;
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb) {
-    float l = lacc[rb][0];
-    if constexpr (SUM32) {  // the four lanes that share a query row
-      l = l_run[rb] + swap_rows16(l_run[rb]);
-      l += swap_halves(l);
-    }
-    const float inv = 1.0f / l;
-    const int t = fresh_tid();
-    const long q = CS ? (long)qt * QROWS + (t >> 6) * 16 * RB + 16 * rb + (t & 15) : q_wave0 + 16 * rb + lq;
-    if (q < Lq) {
-      uint16_t* op = O + q * (long)D + head * DH + 4 * (CS ? (t & 63) >> 4 : g);
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        uint2 w;
-        w.x = pack_bf16x2(o[db][rb][0] * inv, o[db][rb][1] * inv);
-        w.y = pack_bf16x2(o[db][rb][2] * inv, o[db][rb][3] * inv);
-        *reinterpret_cast<uint2*>(op + 16 * db) = w;
-      }
-    }
+  if constexpr (KEYS::kRun) {
+    const ArgPtr a = args();
+    const int nq = a->n_qtiles, of_head = tile_id / nq;
+    finish(a->O, a->Lq, a->H * DH, of_head, tile_id - of_head * nq);
+  } else {
+    finish(O, Lq, H * DH, head, qt);
   }
 }
 
@@ -837,6 +933,30 @@ int32_t launch_attn_pp16_tiles(const uint16_t* Q, const uint16_t* K, const uint1
   return CHORUS_OK;
 }
 
+// More tiles than CUs: workgroups that stay and walk over the tiles (TileRun), over 512 keys and more, where the walk fits the registers
+// (not plain queries with factors). A tile of the text cross-attention, four tiles of keys, takes 15 us so, 22 in a workgroup of its own
+// (32760 x 512, 12 heads 130 -> 106 us, 75600 x 512, 40 heads 1006 -> 820); self-attention gains its start and end (32760 tokens 4655 ->
+// 4640). Its offsets into the values have 32 bits.
+template <bool PRE, int KIND> constexpr bool kWalks = KIND <= 2 && (PRE || KIND != 2);
+template <bool PRE, int KIND>
+bool walks(long tiles, long LkPad, int cus) { return kWalks<PRE, KIND> && tiles > cus && cus % 8 == 0 && LkPad <= 1 << 23; }
+
+// the first `tiles` tiles of 256 rows
+template <int DH, bool PRE, int KIND>
+int32_t launch_attn_full(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* cs, long Lq, long Lk,
+                         long LqPad, long LkPad, int H, long tiles, int cus, hipStream_t s) {
+  const long nqt = (Lq + 255) / 256;
+  if constexpr (kWalks<PRE, KIND>)
+    if (walks<PRE, KIND>(tiles, LkPad, cus))
+      return launch_attn_pp16_tiles<DH, PRE, 2, KIND, TileRun>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, nqt, 0, cus, s,
+                                                               TileRun{Q, K, Vt, O, Lq, LqPad, LkPad, H, (int)nqt, (int)tiles, cus / 8});
+  return launch_attn_pp16_tiles<DH, PRE, 2, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, nqt, 0, tiles, s);
+}
+
+// Keys from which on a last round of few tiles is worth a launch of its own: with fewer the walk's third tile costs less than
+// another start (13104 x 512 with factors 64.4 us in a launch and one of half tiles, 57 in one; 2000 x 600, 40 heads 42.4 and 43.9).
+constexpr int kRunKeys = 5;
+
 // Launches of at most half as many 256-row tiles as CUs run as workgroups of 128 rows throughout (1200 tokens, 12 heads:
 // 36.2 -> 24.8 us). Else 256 query rows per workgroup. One workgroup fits a CU, so a launch runs in rounds of as many workgroups as the device
 // has CUs. When the last round would be at most half full, its tiles run as workgroups of 128 rows instead (one block
@@ -854,12 +974,10 @@ int32_t launch_attn_pp16_kind(const uint16_t* Q, const uint16_t* K, const uint16
   if (2 * tiles <= cus)
     return launch_attn_pp16_tiles<DH, PRE, 1, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, 2 * nqt, 0, 2 * tiles, s);
   const long tail = cus > 0 ? tiles % cus : 0;
-  if (tiles > cus && tail > 0 && 2 * tail <= cus) {
-    CHK_STATUS((launch_attn_pp16_tiles<DH, PRE, 2, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, nqt, 0, tiles - tail, s)));
-    return launch_attn_pp16_tiles<DH, PRE, 1, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, 2 * nqt, 2 * (tiles - tail),
-                                                    2 * tail, s);
-  }
-  return launch_attn_pp16_tiles<DH, PRE, 2, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, nqt, 0, tiles, s);
+  const bool halves = tiles > cus && tail > 0 && 2 * tail <= cus && (!walks<PRE, KIND>(tiles, LkPad, cus) || (Lk + 127) / 128 >= kRunKeys);
+  CHK_STATUS((launch_attn_full<DH, PRE, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, halves ? tiles - tail : tiles, cus, s)));
+  if (!halves) return CHORUS_OK;
+  return launch_attn_pp16_tiles<DH, PRE, 1, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, 2 * nqt, 2 * (tiles - tail), 2 * tail, s);
 }
 
 template <int DH, bool PRE>
@@ -929,7 +1047,11 @@ int32_t launch_attn_sliced(const uint16_t* Q, const uint16_t* K, const uint16_t*
   const long nqt = (L + 255) / 256;
   const SliceScratch r = slice_scratch(DH, p.sliced, p.slices);
   if (!slices_fit(r, sc)) return CHORUS_E_WORKSPACE;
-  if (p.whole > 0) CHK_STATUS((launch_attn_pp16_tiles<DH, true, 2, 0>(Q, K, Vt, O, nullptr, L, L, LPad, LPad, H, nqt, 0, p.whole, s)));
+  if (p.whole > 0) {
+    const int cus = device_cus();
+    if (cus < 0) return cus;
+    CHK_STATUS((launch_attn_full<DH, true, 0>(Q, K, Vt, O, nullptr, L, L, LPad, LPad, H, p.whole, cus, s)));
+  }
   const KeySlices keys{static_cast<uint32_t*>(sc.first), static_cast<float*>(sc.rest), p.sliced, p.slices, (int)((L + 127) / 128),
                        (int)(r.counts / 4), (int)((sc.first_bytes - r.counts) / r.slab)};
   return launch_attn_pp16_tiles<DH, true, 2, 0, KeySlices>(Q, K, Vt, O, nullptr, L, L, LPad, LPad, H, nqt, p.whole,
