@@ -208,6 +208,15 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   const int D = sh.D, F = sh.F, H = sh.H, dh = sh.dh, Lt = sh.Lt;
   const long Lpad = pad_rows(Ls), LtPad = pad_text(Lt);
   const float* tab = w->mod_table;
+  // the gated-residual products' scratch, with counts where they are used; the launches in front clear what is used and nothing else
+  auto chained = [&](GemmParts parts, int K) {
+    if (!gemm_bf16_chained(Ls, D, K, parts)) parts.counts = nullptr;
+    return parts;
+  };
+  const GemmParts o_parts = chained(GemmParts{nullptr, 0, nullptr, 0, b.o_counts}, D);
+  const GemmParts co_parts = chained(GemmParts{nullptr, 0, nullptr, 0, b.co_counts}, D);
+  const GemmParts ffn_parts = chained(b.ffn_parts, F);
+  auto words = [](const GemmParts& parts) { return parts.counts ? kGemmCounts : 0; };
   auto row = [&](const float* base, int r) { return base + (size_t)r * D; };
 
   // 1. AdaLN modulation -> QKV projection
@@ -240,7 +249,7 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
     const PrepareText text{b.tkv, b.tkv + D, 2L * D, w->g_ck, b.kc, b.vct, Lt, LtPad};
     CHK(attn_prepare(b.qkv, b.qkv + D, b.qkv + 2 * D, 3L * D, w->g_q, w->g_k, b.qh, b.kh, b.vt, Ls, Lpad, H, dh, token_idx, sh.gH,
                      sh.gW, 1, q_prescaled ? CHORUS_ATTENTION_Q_PRESCALE(dh) : 1.0f, stream, text_kv ? nullptr : &text,
-                     b.o_counts, kGemmCounts + attention_slices_words(slices)));
+                     o_parts.counts ? b.o_counts : static_cast<uint32_t*>(b.attn.first), words(o_parts) + attention_slices_words(slices)));
   }
   // 4. self-attention over exactly the Ls rows, output projection, gated residual
   {
@@ -253,12 +262,12 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   {
     ProfScope p(CHORUS_PROF_GEMM, s);
     CHK(gemm_bf16_parts(b.ao, w->w_o, Ls, D, D, CHORUS_EPI_RESID, x, w->b_o, row(tab, 2), row(t_mod, 2), 1.f,
-                        GemmParts{nullptr, 0, nullptr, 0, b.o_counts}, stream));
+                        o_parts, stream));
   }
   // 5. cross-attention with TGAA
   {
     ProfScope p(CHORUS_PROF_NORM, s);
-    CHK(ln_modulate(x, b.h, Ls, D, w->ln3_w, nullptr, w->ln3_b, nullptr, 0, b.co_counts, kGemmCounts, stream));
+    CHK(ln_modulate(x, b.h, Ls, D, w->ln3_w, nullptr, w->ln3_b, nullptr, 0, b.co_counts, words(co_parts), stream));
   }
   {
     ProfScope p(CHORUS_PROF_GEMM, s);
@@ -284,17 +293,17 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   {
     ProfScope p(CHORUS_PROF_GEMM, s);
     CHK(gemm_bf16_parts(b.ao, w->w_co, Ls, D, D, CHORUS_EPI_RESID, x, w->b_co, nullptr, nullptr, gamma_o,
-                        GemmParts{nullptr, 0, nullptr, 0, b.co_counts}, stream));
+                        co_parts, stream));
   }
   // 6. FFN
   {
     ProfScope p(CHORUS_PROF_NORM, s);
-    CHK(ln_modulate(x, b.h, Ls, D, row(tab, 4), row(t_mod, 4), row(tab, 3), row(t_mod, 3), 1, b.ffn_parts.counts, kGemmCounts, stream));
+    CHK(ln_modulate(x, b.h, Ls, D, row(tab, 4), row(t_mod, 4), row(tab, 3), row(t_mod, 3), 1, b.ffn_parts.counts, words(ffn_parts), stream));
   }
   {
     ProfScope p(CHORUS_PROF_GEMM, s);
     CHK(chorus_gemm_bf16(b.h, w->w_1, Ls, F, D, CHORUS_EPI_GELU_BF16, b.ffn, w->b_1, nullptr, nullptr, 1.f, stream));
-    CHK(gemm_bf16_parts(b.ffn, w->w_2, Ls, D, F, CHORUS_EPI_RESID, x, w->b_2, row(tab, 5), row(t_mod, 5), 1.f, b.ffn_parts,
+    CHK(gemm_bf16_parts(b.ffn, w->w_2, Ls, D, F, CHORUS_EPI_RESID, x, w->b_2, row(tab, 5), row(t_mod, 5), 1.f, ffn_parts,
                         stream));
   }
   return CHORUS_OK;

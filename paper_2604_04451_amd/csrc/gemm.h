@@ -17,6 +17,8 @@ struct GemmParts {
   uint32_t* counts;
 };
 constexpr int kGemmCounts = 256;
+// Whether a gated-residual product of that size uses the counts: if not, nothing has to clear them.
+bool gemm_bf16_chained(int64_t M, int32_t N, int32_t K, const GemmParts& parts);
 
 // chorus_gemm_bf16 with scratch; the number of slices depends on the sizes given here and on nothing else
 int32_t gemm_bf16_parts(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, int32_t epilogue, void* out,

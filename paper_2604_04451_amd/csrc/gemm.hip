@@ -905,6 +905,10 @@ int32_t gemm_bf16_two(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N
   return gemm_bf16_parts(A2, W2, M2, N2, K, CHORUS_EPI_BF16, out2, bias2, nullptr, nullptr, 1.f, kNoParts, stream);
 }
 
+bool gemm_bf16_chained(int64_t M, int32_t N, int32_t K, const GemmParts& parts) {
+  return parts.counts && K / BK >= 2 * kChainSteps && plan_rows((long)M, N, K, CHORUS_EPI_RESID, parts).rest.chain;
+}
+
 int32_t gemm_bf16_parts(const uint16_t* A, const uint16_t* W, int64_t M, int32_t N, int32_t K, int32_t epilogue, void* out,
                         const float* bias, const float* gate0, const float* gate1, float scale, const GemmParts& parts,
                         void* stream) {
