@@ -128,17 +128,18 @@ int32_t chorus_v_transpose(const uint16_t* in, int64_t ld, uint16_t* out, int64_
  *   col_scale dev [Lk] fp32, 16-byte aligned, or NULL
  * dh in {64,128}; LkPad % 64 == 0, LkPad >= Lk >= 1; rows/cols beyond Lq/Lk are padding
  * (finite values).
- * variant: 0 = the default choice, 3 or 5 as chorus_attention_variant says; 3 = 64-key tiles on 32x32x16 MFMAs; 5 =
+ * variant: 0 = the default choice, 3, 5 or 7 as chorus_attention_variant says; 3 = 64-key tiles on 32x32x16 MFMAs; 5 =
  * 128-key tiles on 16x16x32 MFMAs; 6 = as 5 for a Q that holds the queries already multiplied by log2(e) / sqrt(dh)
  * (CHORUS_ATTENTION_Q_PRESCALE(dh), applied in fp32 by the producer before its rounding to bf16): the same
  * function of the unscaled queries, with one vector instruction less per logit when col_scale is NULL. 5 and 6
- * give CHORUS_E_SHAPE when LkPad % 128 != 0. Any other value: CHORUS_E_ARG.
+ * give CHORUS_E_SHAPE when LkPad % 128 != 0. 7 = no tiles, for few queries on at most 128 keys with heads of 64
+ * (CHORUS_E_SHAPE otherwise). Any other value: CHORUS_E_ARG.
  * Over fewer than 512 keys every variant sums the probabilities of a row in fp32 before they are rounded to bf16; from
  * 512 keys on 5 and 6 sum the rounded ones, which are what weights the values. */
 #define CHORUS_ATTENTION_Q_PRESCALE(dh) (1.4426950408889634f / sqrtf((float)(dh)))
 #define CHORUS_ATTENTION_LONG_KEYS(Lk, LkPad) ((LkPad) % 128 == 0 && (Lk) >= 512)
-/* What variant 0 takes on a GPU of `cus` compute units (3 or 5; factor != 0: with col_scale): 5 for
- * CHORUS_ATTENTION_LONG_KEYS, and on 65 to 511 keys padded to 128 where it is the faster. Host only. CHORUS_E_ARG,
+/* What variant 0 takes on a GPU of `cus` compute units (3, 5 or 7; factor != 0: with col_scale): 7 for at most 128 keys, heads of 64
+ * and at most half as many tiles of 256 queries as units, 5 for CHORUS_ATTENTION_LONG_KEYS, and on 65 to 511 keys padded to 128 where it is the faster. Host only. CHORUS_E_ARG,
  * CHORUS_E_SHAPE as chorus_attention. */
 int32_t chorus_attention_variant(int64_t Lq, int64_t Lk, int64_t LkPad, int32_t H, int32_t dh, int32_t factor, int32_t cus);
 int32_t chorus_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O,

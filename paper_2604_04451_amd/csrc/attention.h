@@ -26,6 +26,11 @@ AttnSlices attention_slices(long L, int H, int dh, int cus, const AttnScratch& s
 inline int attention_slices_words(const AttnSlices& p) { return 2 * p.sliced; }
 int32_t attention_sliced(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, long L, long LPad, int H, int dh,
                          const AttnSlices& plan, const AttnScratch& scratch, void* stream);
+// Whether attention over Lk keys takes its queries as the rows of their projection, and that attention: chorus_qk_norm_rope without
+// rotation and with scale 1 on q [Lq, H * dh], then chorus_attention's default choice, in one launch, the same bits.
+bool attention_raw_queries(long Lq, long Lk, long LkPad, int H, int dh, bool factor, int cus);
+int32_t attention_raw(const uint16_t* q, const float* gain, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* col_scale, long Lq,
+                      long Lk, long LkPad, int H, void* stream);
 // compute units of the current device; a negative status on failure
 int device_cus();
 

@@ -991,6 +991,157 @@ int32_t launch_attn_pp16(const uint16_t* Q, const uint16_t* K, const uint16_t* V
                   : launch_attn_pp16_kind<DH, PRE, 1>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, s);
 }
 
+// ---------------------------------------------------------------------------
+// Few keys (at most 128) for few queries, heads of 64: nothing to stream, so nothing to stage. A wave takes 16 queries of one head and all
+// keys: it requests its queries, the keys, the values and the factors at once, as MFMA operands straight from memory, and is through after
+// one latency, where the kernels above go through LDS, barriers and two phases (128 queries, 4 heads: 16 keys with factors 7.9 us
+// behind 3.0 of normalisation, here 6.9 with it; 128 keys 6.4 in either). What is left is the wave's own instructions. Operand layout, logits, sums and their order are those of attention_pp16_kernel over one tile of
+// keys on plain queries, so its bits too. Every wave reads all keys: with many queries the L1s would be the bound.
+// NORM: the queries come as their projection's rows [Lq, H * 64]: the wave normalises its 16 rows itself, as qk_norm_rope_kernel does it (the
+// same order of additions), H * 64 <= 512.
+// ---------------------------------------------------------------------------
+struct NormalisedQ {
+  static constexpr bool kNorm = false;
+};
+struct RawQ {
+  const float* gain;
+  static constexpr bool kNorm = true;
+};
+template <int NC, class QUERIES>
+__global__ __launch_bounds__(256) void attention_few_kernel(const uint16_t* __restrict__ Q, const uint16_t* __restrict__ K,
+                                                            const uint16_t* __restrict__ Vt, uint16_t* __restrict__ O,
+                                                            const float* __restrict__ col_scale, long Lq, int Lk, long LqPad,
+                                                            long LkPad, int H, float scale_log2, QUERIES queries) {
+  constexpr int DH = 64, KB = 2 * NC, KC = DH / 32, DB = DH / 16;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, lq = lane & 15, g = lane >> 4;
+  const int head = blockIdx.y, D = H * DH;
+  const long q0 = (long)blockIdx.x * 64 + wave * 16;
+  if (q0 >= Lq) return;
+  const long q = q0 + lq < Lq ? q0 + lq : Lq - 1;
+  const uint16_t* Kh = K + (long)head * LkPad * DH;
+  const uint16_t* Vh = Vt + (long)head * DH * LkPad;
+  bf16x8 qf[KC], kf[KB][KC], vf[DB][NC];
+  u32x4 rows[QUERIES::kNorm ? 16 : 1];
+  if constexpr (QUERIES::kNorm) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const long row = q0 + r < Lq ? q0 + r : Lq - 1;
+      rows[r] = u32x4{0u, 0u, 0u, 0u};
+      if (8 * lane < D) rows[r] = *reinterpret_cast<const u32x4*>(Q + row * D + 8 * lane);
+    }
+  }
+#pragma unroll
+  for (int kc = 0; kc < KC; ++kc)
+    qf[kc] = *reinterpret_cast<const bf16x8*>(QUERIES::kNorm ? Q + q * D + head * DH + 32 * kc + 8 * g
+                                                              : Q + ((long)head * LqPad + q) * DH + 32 * kc + 8 * g);
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc)
+      kf[kb][kc] = *reinterpret_cast<const bf16x8*>(Kh + (32 * (kb >> 1) + 16 * (lq >> 3) + 8 * (kb & 1) + (lq & 7)) * DH + 32 * kc + 8 * g);
+  // the four keys of a lane in block kb
+  auto key = [&](int kb) { return 32 * (kb >> 1) + 16 * (g >> 1) + 8 * (kb & 1) + 4 * (g & 1); };
+  f32x4 cf[KB];
+  if (col_scale) {
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) cf[kb][i] = key(kb) + i < Lk ? col_scale[key(kb) + i] : 1.0f;
+  }
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) vf[db][c] = *reinterpret_cast<const bf16x8*>(Vh + (long)(16 * db + lq) * LkPad + 32 * c + 8 * g);
+  if constexpr (QUERIES::kNorm) {
+    float mine = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      float ss = 0.f;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float a = __uint_as_float(rows[r][k] << 16), b = __uint_as_float(rows[r][k] & 0xffff0000u);
+        ss += a * a + b * b;
+      }
+      const float rstd = rsqrtf(wave_sum(ss) / (float)D + 1e-6f);
+      if (lq == r) mine = rstd;
+    }
+    const u32x4* raw = reinterpret_cast<const u32x4*>(qf);
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) {
+      const f32x4* gain = reinterpret_cast<const f32x4*>(queries.gain + head * DH + 32 * kc + 8 * g);
+      const f32x4 ga = gain[0], gb = gain[1];
+      const float gv[8] = {ga[0], ga[1], ga[2], ga[3], gb[0], gb[1], gb[2], gb[3]};
+      const u32x4 w = raw[kc];
+      u32x4 o;
+#pragma unroll
+      for (int k = 0; k < 4; ++k)
+        o[k] = pack_bf16x2(__uint_as_float(w[k] << 16) * mine * gv[2 * k], __uint_as_float(w[k] & 0xffff0000u) * mine * gv[2 * k + 1]);
+      qf[kc] = __builtin_bit_cast(bf16x8, o);
+    }
+  }
+  f32x4 s[KB];
+  float mx = -INFINITY;
+#pragma unroll
+  for (int kb = 0; kb < KB; ++kb) {
+    s[kb] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int kc = 0; kc < KC; ++kc) s[kb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][kc], qf[kc], s[kb], 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (col_scale) s[kb][i] *= cf[kb][i];
+      if (key(kb) + i >= Lk) s[kb][i] = -INFINITY;
+      mx = fmaxf(mx, s[kb][i]);
+    }
+  }
+  mx = fmaxf(mx, swap_rows16(mx));
+  mx = fmaxf(mx, swap_halves(mx));
+  const float mref = mx * scale_log2;
+  bf16x8 pf[NC];
+  float l = 0.f;
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * c + b][i], scale_log2, -mref));
+        l += p;
+        pf[c][4 * b + i] = (bf16_t)p;
+      }
+  l += swap_rows16(l);
+  l += swap_halves(l);
+  const float inv = 1.0f / l;
+  uint16_t* op = O + q * (long)D + head * DH + 4 * g;
+#pragma unroll
+  for (int db = 0; db < DB; ++db) {
+    f32x4 o = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < NC; ++c) o = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[db][c], pf[c], o, 0, 0, 0);
+    if (q0 + lq < Lq) *reinterpret_cast<uint2*>(op + 16 * db) = make_uint2(pack_bf16x2(o[0] * inv, o[1] * inv), pack_bf16x2(o[2] * inv, o[3] * inv));
+  }
+}
+
+constexpr int kFewKeys = 128;
+template <class QUERIES>
+int32_t launch_attn_few(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* cs, long Lq, long Lk,
+                        long LqPad, long LkPad, int H, const QUERIES& queries, hipStream_t s) {
+  if (H > 65535 || Lq > 0x7fffffffL) return CHORUS_E_SHAPE;
+  const dim3 grid((unsigned)((Lq + 63) / 64), (unsigned)H);
+  const float scale_log2 = 1.4426950408889634f / sqrtf(64.f);
+#define ATTN_FEW(NC) \
+  hipLaunchKernelGGL((attention_few_kernel<NC, QUERIES>), grid, dim3(256), 0, s, Q, K, Vt, O, cs, Lq, (int)Lk, LqPad, LkPad, H, scale_log2, queries)
+  switch ((Lk + 31) / 32) {
+    case 1: ATTN_FEW(1); break;
+    case 2: ATTN_FEW(2); break;
+    case 3: ATTN_FEW(3); break;
+    case 4: ATTN_FEW(4); break;
+    default: return CHORUS_E_SHAPE;
+  }
+#undef ATTN_FEW
+  CHORUS_LAUNCH_CHECK();
+  return CHORUS_OK;
+}
+
 template <int DH, int KTL, bool CS>
 int32_t launch_attn_pp(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* cs, long Lq,
                        long Lk, long LqPad, long LkPad, int H, hipStream_t s) {
@@ -1018,10 +1169,11 @@ int32_t launch_attn_pp(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt,
 //   without: 70 to 128 keys 0.95 to 1.08, mostly over 1; 200 to 511 keys 0.88 to 1.03, but 1.00 to 1.05 on 156 to 240
 //   tiles, where one round does not fill the chip
 int attention_variant(long Lq, long Lk, long LkPad, int H, int dh, bool factor, int cus) {
+  const long tiles = (Lq + 255) / 256 * H;
+  if (dh == 64 && Lk <= kFewKeys && 2 * tiles <= cus) return 7;
   if (LkPad % 128) return 3;
   if (CHORUS_ATTENTION_LONG_KEYS(Lk, LkPad)) return 5;
   if (Lk <= 64) return 3;
-  const long tiles = (Lq + 255) / 256 * H;
   if (2 * tiles <= cus || (factor && dh == 64)) return 5;
   if ((Lk + 63) / 64 % 2 && !(factor && Lk > 384)) return 3;
   return (factor ? Lk <= 96 || Lk > 128 : Lk > 128 && tiles > cus) ? 5 : 3;
@@ -1098,6 +1250,16 @@ AttnSlices attention_slices(long L, int H, int dh, int cus, const AttnScratch& s
   return none;
 }
 
+bool attention_raw_queries(long Lq, long Lk, long LkPad, int H, int dh, bool factor, int cus) {
+  return H * dh <= 512 && attention_variant(Lq, Lk, LkPad, H, dh, factor, cus) == 7;
+}
+
+int32_t attention_raw(const uint16_t* q, const float* gain, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* col_scale, long Lq,
+                      long Lk, long LkPad, int H, void* stream) {
+  if (!gain || !aligned16(gain) || !aligned16(q)) return CHORUS_E_ARG;
+  return launch_attn_few(q, K, Vt, O, col_scale, Lq, Lk, 0, LkPad, H, RawQ{gain}, (hipStream_t)stream);
+}
+
 int32_t attention_sliced(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, long L, long LPad, int H, int dh,
                          const AttnSlices& plan, const AttnScratch& scratch, void* stream) {
   return dh == 128 ? launch_attn_sliced<128>(Q, K, Vt, O, L, LPad, H, plan, scratch, (hipStream_t)stream)
@@ -1153,7 +1315,7 @@ extern "C" int32_t chorus_attention(const uint16_t* Q, const uint16_t* K, const 
                                     const float* col_scale, int64_t Lq, int64_t Lk, int64_t LqPad, int64_t LkPad,
                                     int32_t H, int32_t dh, int32_t variant, void* stream) {
   if (Lq < 0 || Lk < 0 || H <= 0) return CHORUS_E_ARG;
-  if (variant != 0 && variant != 3 && variant != 5 && variant != 6) return CHORUS_E_ARG;
+  if (variant != 0 && variant != 3 && variant != 5 && variant != 6 && variant != 7) return CHORUS_E_ARG;
   if (Lq == 0) return CHORUS_OK;
   if (Lk < 1) return CHORUS_E_SHAPE;
   if (!Q || !K || !Vt || !O) return CHORUS_E_ARG;
@@ -1165,6 +1327,10 @@ extern "C" int32_t chorus_attention(const uint16_t* Q, const uint16_t* K, const 
     const int cus = device_cus();
     if (cus < 0) return cus;
     variant = attention_variant((long)Lq, (long)Lk, (long)LkPad, H, dh, cs, cus);
+  }
+  if (variant == 7) {
+    if (dh != 64 || Lk > kFewKeys) return CHORUS_E_SHAPE;
+    return launch_attn_few(Q, K, Vt, O, col_scale, Lq, Lk, LqPad, LkPad, H, NormalisedQ{}, s);
   }
   if (variant == 5 || variant == 6) {
     if (LkPad % 128) return CHORUS_E_SHAPE;

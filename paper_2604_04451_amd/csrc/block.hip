@@ -236,12 +236,9 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   // Attention over 512 keys or more takes its queries already multiplied by log2(e) / sqrt(dh): the factor enters here, in
   // fp32 ahead of the one rounding to bf16. Over fewer keys they are the plain queries whichever kernel runs it.
   const bool q_prescaled = CHORUS_ATTENTION_LONG_KEYS(Ls, Lpad);
-  AttnSlices slices{0, 0, 0};
-  if (q_prescaled) {
-    const int cus = device_cus();
-    if (cus < 0) return cus;
-    slices = attention_slices(Ls, H, dh, cus, b.attn);
-  }
+  const int cus = device_cus();
+  if (cus < 0) return cus;
+  const AttnSlices slices = q_prescaled ? attention_slices(Ls, H, dh, cus, b.attn) : AttnSlices{0, 0, 0};
   {
     ProfScope p(CHORUS_PROF_NORM, s);
     if (!w->g_q || !w->g_k || !aligned16(w->g_q) || !aligned16(w->g_k)) return CHORUS_E_ARG;
@@ -281,14 +278,18 @@ int32_t block_step_impl(const chorus_block_shape* shape, const chorus_block_weig
   }
   // pre-scaled queries as above
   const bool cq_prescaled = CHORUS_ATTENTION_LONG_KEYS(Lt, LtPad);
-  {
+  const bool raw_queries = attention_raw_queries(Ls, Lt, LtPad, H, dh, tgaa_key_scale != nullptr, cus);
+  if (!raw_queries) {
     ProfScope p(CHORUS_PROF_NORM, s);
     CHK(chorus_qk_norm_rope(b.qkv, D, w->g_cq, b.qh, Ls, Lpad, H, dh, nullptr, sh.gT, sh.gH, sh.gW, 0,
                             cq_prescaled ? CHORUS_ATTENTION_Q_PRESCALE(dh) : 1.0f, stream));
   }
   {
     ProfScope p(CHORUS_PROF_CROSS_ATTN, s);
-    CHK(chorus_attention(b.qh, kc, vct, b.ao, tgaa_key_scale, Ls, Lt, Lpad, LtPad, H, dh, cq_prescaled ? 6 : 0, stream));
+    if (raw_queries)
+      CHK(attention_raw(b.qkv, w->g_cq, kc, vct, b.ao, tgaa_key_scale, Ls, Lt, LtPad, H, stream));
+    else
+      CHK(chorus_attention(b.qh, kc, vct, b.ao, tgaa_key_scale, Ls, Lt, Lpad, LtPad, H, dh, cq_prescaled ? 6 : 0, stream));
   }
   {
     ProfScope p(CHORUS_PROF_GEMM, s);

@@ -25,6 +25,14 @@ def test_attention_long_and_short_keys(factor):
     assert _attention(13104, 400, 40, 128, factor) == (5 if factor else 3)
 
 
+def test_attention_few_keys():
+    for Lq, Lk, H in ((128, 128, 4), (1, 1, 1), (300, 77, 8), (2048, 16, 16), (8192, 65, 4)):  # up to 128 tiles of 256 queries
+        for factor in (False, True):
+            assert _attention(Lq, Lk, H, 64, factor) == _attention(Lq, Lk, H, 64, factor, pad=64) == 7
+            assert _attention(Lq, Lk, H, 128, factor) != 7
+    assert _attention(128, 129, 4, 64, False) == _attention(2049, 128, 16, 64, True) == 5 and _attention(2049, 16, 16, 64, False) == 3
+
+
 def _slices(L, H, dh=128, first=None, rest=None):
     D = H * dh  # a block's scratch: its normalised rows and its projection
     return B.chorus_attention_slices_plan(L, H, dh, CUS, 2 * L * D if first is None else first, 6 * L * D if rest is None else rest)

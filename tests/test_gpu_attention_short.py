@@ -36,6 +36,25 @@ def test_key_factors_follow_their_tile(Lk):
         _attn_case(12, 64, Lq, Lk, 6, col_scale=cs, q_std=2.0, seed=Lk, name="factors")
 
 
+@pytest.mark.parametrize("H,Lq,Lk", [(1, 1, 1), (2, 15, 31), (3, 16, 32), (2, 17, 33), (4, 63, 64), (1, 65, 65), (2, 64, 96), (4, 130, 97),
+                                     (9, 200, 128)])
+@pytest.mark.parametrize("factor", [False, True])
+def test_attention_few_keys(H, Lq, Lk, factor):
+    """The kernel without tiles at the edges of its 16 queries and 32 keys, against the oracle and, bit for bit, against the one that
+    stages a tile of 128 keys."""
+    print(f"[case] attention few keys H={H} Lq={Lq} Lk={Lk} factor={factor}", flush=True)
+    cs = (0.25 + 1.75 * synth.stream(Lk, "cs").random(Lk)).astype(np.float32) if factor else None
+    _attn_case(H, 64, Lq, Lk, 7, col_scale=cs, q_std=2.0, seed=Lq + Lk, name="few")
+    g, pad = torch.Generator(device=DEV).manual_seed(Lk), -(-Lk // 128) * 128
+    q, k, vt = (torch.randn(s, device=DEV, generator=g).bfloat16() for s in ((H, 256, 64), (H, pad, 64), (H * 64, pad)))
+    k[:, Lk:], vt[:, Lk:] = 0, 0
+    a, b = (torch.zeros(Lq, H * 64, dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    dcs = dev_f32(cs) if factor else None
+    B.chorus_attention(q, k, vt, a, dcs, Lq, Lk, 7)
+    B.chorus_attention(q, k, vt, b, dcs, Lq, Lk, 5)
+    assert torch.equal(a, b)
+
+
 def _bf16(x):
     return synth.round_bf16(np.float32(x)).astype(np.float64)
 
