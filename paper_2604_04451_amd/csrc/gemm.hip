@@ -700,15 +700,18 @@ struct GemmPlan {
 // 300 x 5120 x 5120 45 / 30 (128 x 128, two), 200 38 / 28 (three), 960 72 / 64 (256 x 256, three). With fewer steps a slice the updates are the
 // larger part: 1200 x 1536 x 1536 14 to 16.5 / 17, 4500 28 / 39.
 constexpr int kMaxChain = 4, kChainTiles = 256, kChainSteps = 16;
+constexpr int chain_update(int tile) { return tile == kTile256 || tile == kTileWide ? 5 : 8; }
 int chain_stagger(int tile, int K, int slices) {
-  const int want = tile == kTile256 || tile == kTileWide ? 5 : 8, most = K / BK / slices;
+  const int want = chain_update(tile), most = K / BK / slices;
   return want * (slices - 1) < most ? want : most / slices;  // the first slice keeps half of its steps
 }
 double chain_time(int tile, long m, int N, int K, int slices) {
   const long tiles = tile_count(tile, m, N);
   if (tile == kTile128 || K > kMaxOffsetK || N > 1 << 20 || tiles * slices > kChainTiles || K / BK / slices < kChainSteps) return INFINITY;
   const double fill = (double)(tiles * slices) / 256.0;
-  const double steps = (double)(K / BK) / slices + 0.5 * (slices - 1) * chain_stagger(tile, K, slices);
+  // The whole update also where the slices are too short to be that far apart: it is waited for there (65 to 128 rows x 5120 x 5120,
+  // four slices of 20 steps: a block with two of them 285 us at 78 rows, 273 with whole tiles).
+  const double steps = (double)(K / BK) / slices + 0.5 * (slices - 1) * chain_update(tile);
   switch (tile) {
     case kTile256: return 16.3 + 5.0 * (slices - 2) + (1.17 + fmax(fill - 0.8, 0.0)) * steps;
     case kTileWide: return 15.0 + 2.0 * (slices - 2) + 0.72 * steps;
