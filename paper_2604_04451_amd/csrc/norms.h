@@ -21,7 +21,7 @@ int32_t attn_prepare(const uint16_t* q, const uint16_t* k, const uint16_t* v, lo
                      int gW, int rope, float q_scale, void* stream, const PrepareText* text = nullptr, uint32_t* clear = nullptr,
                      int n_clear = 0);
 
-// chorus_ln_modulate in a launch that also clears n_clear words (at most 256) at `clear`
+// chorus_ln_modulate in a launch that also clears n_clear words at `clear`
 int32_t ln_modulate(const float* x, uint16_t* out, long L, int D, const float* mul0, const float* mul1, const float* add0,
                     const float* add1, int plus_one, uint32_t* clear, int n_clear, void* stream);
 

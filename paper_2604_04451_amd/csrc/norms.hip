@@ -15,16 +15,29 @@ constexpr float kEps = 1e-6f;
 
 struct NoText {};  // the preparation of the tokens alone
 
+// Words that a launch clears beside its work. Launches that clear none are kernels of their own: the two further arguments and a
+// branch in front of the first load cost each of them 0.2 us (blocks of 20 to 60 tokens of width 1536, four launches: 1 %).
+struct NoClear {
+  __device__ void operator()() const {}
+};
+struct Clear {
+  uint32_t* words;
+  int n;
+  __device__ void operator()() const {
+    if (blockIdx.x == 0)
+      for (int i = threadIdx.x; i < n; i += 256) words[i] = 0;
+  }
+};
+
 // One wave per row. NV > 0: D == NV*256 and the row lives in registers (one HBM
 // read). NV == 0: any D % 4 == 0, the row is re-read from cache for each pass.
-template <int NV>
+template <int NV, class CLEAR>
 __global__ __launch_bounds__(256) void ln_modulate_kernel(const float* __restrict__ x, uint16_t* __restrict__ out,
                                                           long L, int D, const float* __restrict__ mul0,
                                                           const float* __restrict__ mul1,
                                                           const float* __restrict__ add0,
-                                                          const float* __restrict__ add1, float mul_base,
-                                                          uint32_t* __restrict__ clear, int n_clear) {
-  if (blockIdx.x == 0 && (int)threadIdx.x < n_clear) clear[threadIdx.x] = 0;
+                                                          const float* __restrict__ add1, float mul_base, CLEAR clear) {
+  clear();
   // the two modulation vectors are the same for every row: the workgroup combines them once into LDS
   // ((base + mul0 + mul1) and (add0 + add1)) while the rows' loads are in flight
   extern __shared__ __attribute__((aligned(16))) float s_tab[];  // [2][D]
@@ -278,7 +291,7 @@ __global__ __launch_bounds__(256) void v_transpose_kernel(const uint16_t* __rest
 // took longer to start than to run (128 tokens of width 256: 3.6 + 3.6 + 2.8 us and two gaps). A wave that did both rows
 // of a token, for one set of angles, held twice the registers (width 5120, 75600 tokens: 957 us against 897 of the three
 // launches) and was the longer chain where the chip is not filled (block of 128 tokens 69.7 us, now 68.9).
-template <int NCH, class TEXT>
+template <int NCH, class TEXT, class CLEAR>
 __global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __restrict__ q, const uint16_t* __restrict__ k,
                                                            const uint16_t* __restrict__ v, long ld,
                                                            const float* __restrict__ gain_q, const float* __restrict__ gain_k,
@@ -286,7 +299,7 @@ __global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __res
                                                            uint16_t* __restrict__ vt, long L, long Lpad, int H, int dh,
                                                            const int* __restrict__ token_idx, int gH, int gW, int rope,
                                                            float q_scale, int row_blocks, int v_tiles, int first2,
-                                                           uint32_t* __restrict__ clear, int n_clear, TEXT text) {
+                                                           CLEAR clear, TEXT text) {
   __shared__ union {
     struct {
       float cos[4][64], sin[4][64];
@@ -294,8 +307,7 @@ __global__ __launch_bounds__(256) void attn_prepare_kernel(const uint16_t* __res
     uint16_t tile[64][64 + 2];
   } sm;
   int block = blockIdx.x;
-  if (block == 0)
-    for (int i = threadIdx.x; i < n_clear; i += 256) clear[i] = 0;
+  clear();
   if constexpr (std::is_same_v<TEXT, PrepareText>) {
     if (block >= first2) {  // the workgroups behind the tokens': the text
       block -= first2;
@@ -344,16 +356,20 @@ int32_t attn_prepare(const uint16_t* q, const uint16_t* k, const uint16_t* v, lo
   const long row_blocks = (Lpad + 3) / 4 * (q ? 2 : 1), v_tiles = Lpad / 64, first2 = row_blocks + v_tiles * (D / 64);
   const long blocks = first2 + (text ? (text->Lpad + 3) / 4 + text->Lpad / 64 * (D / 64) : 0);
   if (blocks > 0x7fffffffL) return CHORUS_E_SHAPE;
-#define PREPARE_AS(NCH, TEXT, text)                                                                                           \
-  hipLaunchKernelGGL((attn_prepare_kernel<NCH, TEXT>), dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, q, k, v, ld,  \
-                     gain_q, gain_k, qh, kh, vt, L, Lpad, H, dh, token_idx, gH, gW, rope, q_scale, (int)row_blocks, (int)v_tiles, \
-                     (int)first2, clear, n_clear, text)
-#define PREPARE(NCH)                           \
-  do {                                         \
-    if (text)                                  \
-      PREPARE_AS(NCH, PrepareText, *text);     \
-    else                                       \
-      PREPARE_AS(NCH, NoText, NoText{});       \
+#define PREPARE_AS(NCH, TEXT, text, CLEAR, clear)                                                                               \
+  hipLaunchKernelGGL((attn_prepare_kernel<NCH, TEXT, CLEAR>), dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, q, k, v, \
+                     ld, gain_q, gain_k, qh, kh, vt, L, Lpad, H, dh, token_idx, gH, gW, rope, q_scale, (int)row_blocks,           \
+                     (int)v_tiles, (int)first2, clear, text)
+#define PREPARE(NCH)                                                          \
+  do {                                                                        \
+    if (text && n_clear)                                                      \
+      PREPARE_AS(NCH, PrepareText, *text, Clear, (Clear{clear, n_clear}));    \
+    else if (text)                                                            \
+      PREPARE_AS(NCH, PrepareText, *text, NoClear, NoClear{});                \
+    else if (n_clear)                                                         \
+      PREPARE_AS(NCH, NoText, NoText{}, Clear, (Clear{clear, n_clear}));      \
+    else                                                                      \
+      PREPARE_AS(NCH, NoText, NoText{}, NoClear, NoClear{});                  \
   } while (0)
   if (D == 1536) PREPARE(3);
   else if (D == 5120) PREPARE(10);
@@ -375,15 +391,23 @@ int32_t ln_modulate(const float* x, uint16_t* out, long L, int D, const float* m
   dim3 grid((unsigned)((L + 3) / 4)), block(256);
   float base = plus_one ? 1.0f : 0.0f;
   const size_t tab_bytes = (size_t)2 * D * sizeof(float);
-  if (tab_bytes > 64 * 1024 || n_clear > 256) return CHORUS_E_SHAPE;
-#define LAUNCH_LN(NV) \
-  hipLaunchKernelGGL((ln_modulate_kernel<NV>), grid, block, tab_bytes, s, x, out, (long)L, D, mul0, mul1, add0, add1, base, clear, \
-                     n_clear)
+  if (tab_bytes > 64 * 1024) return CHORUS_E_SHAPE;
+#define LAUNCH_AS(NV, CLEAR, clear)                                                                                             \
+  hipLaunchKernelGGL((ln_modulate_kernel<NV, CLEAR>), grid, block, tab_bytes, s, x, out, (long)L, D, mul0, mul1, add0, add1, base, \
+                     clear)
+#define LAUNCH_LN(NV)                                    \
+  do {                                                   \
+    if (n_clear)                                         \
+      LAUNCH_AS(NV, Clear, (Clear{clear, n_clear}));     \
+    else                                                 \
+      LAUNCH_AS(NV, NoClear, NoClear{});                 \
+  } while (0)
   if (D == 256) LAUNCH_LN(1);
   else if (D == 1536) LAUNCH_LN(6);
   else if (D == 5120) LAUNCH_LN(20);
   else LAUNCH_LN(0);
 #undef LAUNCH_LN
+#undef LAUNCH_AS
   CHORUS_LAUNCH_CHECK();
   return CHORUS_OK;
 }
