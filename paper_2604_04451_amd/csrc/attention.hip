@@ -756,9 +756,10 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
         for (int c = 0; c < NC; ++c) lacc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[c][rb], lacc[rb], 0, 0, 0);
     }
     if constexpr (KEYS::kRun) {
-      // the next tile's references start at zero
+      // the next tile's references start where the first one's did: plain queries move theirs only past a logit that exceeds it by 8, and
+      // from zero a row of logits below about -126 (in log2 units) would lose all of its keys
 #pragma unroll
-      for (int rb = 0; rb < RB; ++rb) m_run[rb] = last_kt ? 0.f : m_run[rb];
+      for (int rb = 0; rb < RB; ++rb) m_run[rb] = last_kt ? (PRE ? 0.f : -INFINITY) : m_run[rb];
     }
     compute_s(buf ^ 1);
     // issue order: LDS stores, then LDS operand reads kept ahead of the MFMAs (one read feeds two)
