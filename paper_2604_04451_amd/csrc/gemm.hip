@@ -258,14 +258,22 @@ struct Alone {  // no second product
   static constexpr bool kTwo = false, kChain = false;
 };
 // The gated residual in slices of K without scratch: every slice adds its part to the residual itself, in the order of the slices. A
-// slice waits for its tile's count to reach its number; the slices in front of it have lower workgroup numbers, so that they started
-// before it, and the first one waits for nothing: the wait ends. The counts start at zero. Slices of equal length would all end
-// together and then wait for each other's updates: each is a few steps longer than the one in front of it instead (3271 x 1536 x 8960, three
-// slices of 256 x 256 tiles: 100 us with equal ones, 87 with five steps more each).
+// slice waits until its tile's count has reached its number. Workgroups are dealt out by each XCD for itself, so that a workgroup's
+// number says nothing of what has started elsewhere; what a workgroup does is given out by ticket instead. The workgroups
+// whose number leaves the same rest by `groups` (8: they share an XCD and its L2) take tickets of one counter for a range of tiles of their
+// own, all of its tiles of the first slice first. So a slice only ever waits for a lower ticket of its group, whose workgroup
+// has taken it and is running; that one waits for a still lower ticket or for nothing: every wait ends, whatever else runs on the GPU.
+// By workgroup number 3271 x 1536 x 8960 took 84 to 92 us, by ticket 89 to 93; 4500 rows 107 and 107, 2000 70 and 70, 1100 46 and 46.
+// A word a tile, zero at the start: the slices that have been added in its low four bits and, in the word of a group's first
+// tile, the tickets taken in the others.
+// Slices of equal length would all end together and then wait for each other's updates: each is a few steps longer than the one in
+// front of it instead (3271 x 1536 x 8960, three slices of 256 x 256 tiles: 100 us with equal ones, 87 with five steps more each).
 struct Chain {
   uint32_t* count;  // [tiles]
   int stagger;      // steps that a slice is longer than the one in front of it
+  int tiles, groups;
   static constexpr bool kTwo = false, kChain = true;
+  static constexpr uint32_t kTicket = 16, kAdded = 15;  // one ticket; the bits of the slices that have been added
 };
 
 // The 128 x 256 shape takes three quarters of the operand bytes per product of 128 x 128 tiles: for products of about 400 to
@@ -305,8 +313,24 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
       tiles_n = twin.tiles_n;
     }
   }
-  const int nslices = gridDim.y, slice = blockIdx.y;
-  const int tile = xcd_remap(block, ntiles);
+  const int nslices = gridDim.y;
+  int slice = blockIdx.y, tile;
+  if constexpr (SECOND::kChain) {
+    const int g = block % twin.groups, q = twin.tiles / twin.groups, r = twin.tiles % twin.groups;
+    const int of_group = q + (g < r), first_tile = g * q + (g < r ? g : r);
+    if ((slice * (int)gridDim.x + block) / twin.groups >= of_group * nslices) return;  // the grid's x is a multiple of the groups
+    // one of the ring's places that nothing is requested into before every wave has read it
+    uint32_t* const mine = reinterpret_cast<uint32_t*>(smem + (C - 1) * HA);
+    if (threadIdx.x == 0)
+      mine[0] = __hip_atomic_fetch_add(twin.count + first_tile, Chain::kTicket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / Chain::kTicket;
+    __syncthreads();
+    const int ticket = __builtin_amdgcn_readfirstlane((int)mine[0]);
+    slice = ticket / of_group;
+    tile = ticket - slice * of_group;
+    tile = twin.groups == 1 ? xcd_remap(tile, twin.tiles) : first_tile + tile;
+  } else {
+    tile = xcd_remap(block, ntiles);
+  }
   int KTN = K / BK, k_first = 0;
   if (nslices > 1) {
     auto start = [&](int i) {
@@ -522,7 +546,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
     uint32_t* const count = twin.count + tile;
     if (slice > 0) {
       if (tid == 0)
-        while (__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != (uint32_t)slice) __builtin_amdgcn_s_sleep(1);
+        while ((__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & Chain::kAdded) != (uint32_t)slice) __builtin_amdgcn_s_sleep(1);
       __syncthreads();
       asm volatile("" ::: "memory");  // the residual is read behind the count
       ep.bias = nullptr;              // went in with the first slice
@@ -532,7 +556,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
     if (slice + 1 < nslices) {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the wave's stores have completed, past the L2
       __syncthreads();
-      if (tid == 0) __hip_atomic_store(count, (uint32_t)slice + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid == 0) __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     return;
   }
@@ -760,6 +784,10 @@ GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
 
 constexpr int kHalvesDeep = 7, kHalves64 = 9;
 
+// The groups of a chain: an XCD each, or all of the chip in one where an XCD would get more workgroups than it has units that way (three slices
+// of 81 to 85 tiles).
+int chain_groups(int tiles, int slices) { return (tiles + 7) / 8 * 8 * slices <= kChainTiles ? 8 : 1; }
+
 template <int WBM, int WBN, int C>
 int32_t launch_chain(const uint16_t* A, const uint16_t* W, long M, int N, int K, const EpiArgs& ep, int slices, uint32_t* count,
                      int stagger, hipStream_t s) {
@@ -770,8 +798,9 @@ int32_t launch_chain(const uint16_t* A, const uint16_t* W, long M, int N, int K,
   auto kern = gemm_w16_kernel<CHORUS_EPI_RESID, WBM, WBN, C, false, Chain>;
   static DynLdsOnce once;
   CHK_STATUS(once.ensure(reinterpret_cast<const void*>(kern), (int)smem));
-  hipLaunchKernelGGL(kern, dim3((unsigned)(tm * tn), (unsigned)slices), dim3(256), smem, s, A, W, M, N, K, ep, PartPtrs{nullptr, nullptr},
-                     (int)tm, tn, Chain{count, stagger});
+  const int tiles = (int)(tm * tn), groups = chain_groups(tiles, slices);
+  hipLaunchKernelGGL(kern, dim3((unsigned)align_up(tiles, groups), (unsigned)slices), dim3(256), smem, s, A, W, M, N, K, ep,
+                     PartPtrs{nullptr, nullptr}, (int)tm, tn, Chain{count, stagger, tiles, groups});
   CHORUS_LAUNCH_CHECK();
   return CHORUS_OK;
 }

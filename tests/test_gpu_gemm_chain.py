@@ -33,6 +33,35 @@ def test_chain(kernel, steps, slices):
             assert torch.equal(buf[:M], want) and bool((buf[M:] == 7.0).all())
 
 
+def test_chain_in_one_group():
+    """84 tiles in three slices: more workgroups than units on an XCD if each took its tiles' slices, so one counter for all."""
+    M, N, K = 64 * 12, 64 * 7, 64 * 48
+    A, W, out = _ints((M, K), 1), _ints((N, K), 2), _ints((M, N), 4)
+    got = out.clone()
+    B.chorus_gemm_bf16_chain(A.bfloat16(), W.bfloat16(), got, 1, 3, scale=0.5)
+    assert torch.equal(got, out + 0.5 * (A @ W.T))
+
+
+@pytest.mark.parametrize("M,slices", [(3271, 3), (3500, 3), (1500, 4)])
+def test_chains_on_several_streams(M, slices):
+    """Six chains at a time, three in a row on each of six streams: waits that depend on what else runs would show here."""
+    N, K = 1536, 64 * 32
+    A, W, out = _ints((M, K), 1), _ints((N, K), 2), _ints((M, N), 4)
+    print(f"[case] gemm chains on streams M={M} slices={slices}", flush=True)
+    want = out + 3 * (A @ W.T)
+    A, W = A.bfloat16(), W.bfloat16()
+    streams = [torch.cuda.Stream() for _ in range(6)]
+    got = [out.clone() for _ in streams]
+    counts = [torch.full((256,), 77, dtype=torch.int32, device="cuda") for _ in streams]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for st, o, c in zip(streams, got, counts):
+            with torch.cuda.stream(st):
+                B.chorus_gemm_bf16_chain(A, W, o, 3, slices, counts=c)
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, want) for o in got)
+
+
 def test_chain_refuses():
     A, W = torch.zeros(8, 128, dtype=torch.bfloat16, device="cuda"), torch.zeros(64, 128, dtype=torch.bfloat16, device="cuda")
     out, counts = torch.zeros(8, 64, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
@@ -46,6 +75,39 @@ BLOCKS = {(1536, 12, 4096, 300): (False, True), (2048, 16, 4096, 1000): (True, T
           (1024, 8, 8192, 1000): (False, True)}
 
 
+def _weights(rnd, D, F):
+    t = {}
+    for n, o, i in (("qkv", 3 * D, D), ("o", D, D), ("cq", D, D), ("ckv", 2 * D, D), ("co", D, D), ("1", F, D), ("2", D, F)):
+        t["w_" + n], t["b_" + n] = (rnd(o, i) * 0.02).bfloat16(), rnd(o) * 0.05
+    t.update(mod_table=rnd(6, D) * 0.3, g_q=rnd(D), g_k=rnd(D), g_cq=rnd(D), g_ck=rnd(D), ln3_w=rnd(D), ln3_b=rnd(D))
+    return t, B.DeviceBlock(t, B.BlockWeights(**{n: t[n].data_ptr() for n in B._W_FIELDS}))
+
+
+def test_blocks_on_three_streams():
+    """Blocks whose three residual products are all chained, in three streams with a workspace each, against the same calls one by one."""
+    D, H, F, Ls = 2048, 16, 4096, 1000
+    assert BLOCKS[D, H, F, Ls] == (True, True)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)  # noqa: E731
+    _, w = _weights(rnd, D, F)
+    shape = B.make_block_shape(D, H, D // H, F, 40, (1, 32, 32))
+    ctx, t_mod, x = rnd(40, D).bfloat16(), rnd(6, D) * 0.3, [rnd(Ls, D) for _ in range(3)]
+    ws = [torch.full((B.chorus_dit_block_workspace_bytes(shape, Ls),), 255, dtype=torch.uint8, device="cuda") for _ in x]
+    step = lambda y, s: B.chorus_dit_block_step(shape, w, y, Ls, None, ctx, t_mod, None, 1.0, s)  # noqa: E731
+    want = [v.clone() for v in x]
+    for y in want:
+        for _ in range(2):
+            step(y, ws[0])
+    streams = [torch.cuda.Stream() for _ in x]
+    torch.cuda.synchronize()
+    for _ in range(2):
+        for st, y, s in zip(streams, x, ws):
+            with torch.cuda.stream(st):
+                step(y, s)
+    torch.cuda.synchronize()
+    assert all(torch.equal(a, b) for a, b in zip(x, want))
+
+
 @pytest.mark.parametrize("D,H,F,Ls", list(BLOCKS))
 def test_block_with_chained_products(D, H, F, Ls):
     """Three replays of a captured block with other work in between, on a workspace that starts anywhere, against the call outside, and
@@ -55,11 +117,7 @@ def test_block_with_chained_products(D, H, F, Ls):
     print(f"[case] block chained D={D} F={F} Ls={Ls}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(D + F)
     rnd = lambda *s: torch.randn(*s, device="cuda", generator=g)  # noqa: E731
-    t = {}
-    for n, o, i in (("qkv", 3 * D, D), ("o", D, D), ("cq", D, D), ("ckv", 2 * D, D), ("co", D, D), ("1", F, D), ("2", D, F)):
-        t["w_" + n], t["b_" + n] = (rnd(o, i) * 0.02).bfloat16(), rnd(o) * 0.05
-    t.update(mod_table=rnd(6, D) * 0.3, g_q=rnd(D), g_k=rnd(D), g_cq=rnd(D), g_ck=rnd(D), ln3_w=rnd(D), ln3_b=rnd(D))
-    w = B.DeviceBlock(t, B.BlockWeights(**{n: t[n].data_ptr() for n in B._W_FIELDS}))
+    t, w = _weights(rnd, D, F)
     shape = B.make_block_shape(D, H, D // H, F, 40, (1, 32, 32))
     x, ctx, t_mod = rnd(Ls, D), rnd(40, D).bfloat16(), rnd(6, D) * 0.3
     ws = torch.full((B.chorus_dit_block_workspace_bytes(shape, Ls),), 255, dtype=torch.uint8, device="cuda")
