@@ -22,14 +22,17 @@ struct BatchPlan {
   long Npad;             // rows of the partial sums
 };
 
-// Slices along d that the workspace has room for; their partial sums are added in a fixed order afterwards.
+// Slices along d that the workspace has room for; their partial sums are added in a fixed order afterwards. (The workspace's size is
+// what it always was: slices of equal length, as many of them as 1024 workgroups of 64 rows allow, at most 16.)
 inline int max_slices(long N, int d) {
   const long blocks = (N + kBlock - 1) / kBlock;
   const int nchunks = (d + kBK - 1) / kBK;
-  long most = blocks > 0 ? 1024 / blocks : 1;
-  if (most > nchunks) most = nchunks;
-  if (most > 16) most = 16;
-  return most < 1 ? 1 : (int)most;
+  long want = blocks > 0 ? 1024 / blocks : 1;
+  if (want > nchunks) want = nchunks;
+  if (want > 16) want = 16;
+  if (want < 1) want = 1;
+  const int per = (nchunks + (int)want - 1) / (int)want;
+  return (nchunks + per - 1) / per;
 }
 
 // The number of slices and the workgroup's size by an estimate of the two kernels' time in microseconds. What bounds the scan is what a

@@ -218,3 +218,17 @@ def test_mask_hierarchy_plan_refuses():
     for T, H, W, re, rs, want in ((0, 1, 1, (0,) * 3, (0,) * 3, B.E_ARG), (1, 1, 1, (1, 0, 0), (0,) * 3, B.E_ARG),
                                   (1, 1, 1, (0, -1, 0), (0,) * 3, B.E_ARG), (2, 2 ** 15, 2 ** 15, (0,) * 3, (0,) * 3, B.E_SHAPE)):
         assert B.load().chorus_mask_hierarchy_plan(T, H, W, B._Radii(*re), B._Radii(*rs), B.C.byref(B.HierarchyPlan())) == want
+
+
+def test_batch_workspace_is_what_it_was():
+    """A caller may have kept the size: partial sums of as many equal slices of 64-float steps as 1024 workgroups of 64 rows allow (16 at
+    most), then 32 scores a row."""
+    up = lambda v, a: -(-v // a) * a  # noqa: E731
+    for N in (1, 63, 64, 65, 370, 1000, 4096, 7740, 20000, 65537, 300000):
+        for d in (4, 64, 380, 1024, 1096, 2056, 2640, 3420, 4076, 4096, 8192):
+            for Q in (1, 16, 17, 48):
+                blocks, steps = -(-N // 64), -(-d // 64)
+                want = max(1, min(1024 // blocks, steps, 16))
+                slices = -(-steps // -(-steps // want))
+                size = up(slices * blocks * 64 * (32 if Q > 16 else 16) * 4, 256) + up(slices * blocks * 64 * 4, 256) + up(32 * blocks * 64 * 4, 256)
+                assert B.load().chorus_cache_lookup_batch_workspace_bytes(N, d, Q) == size, (N, d, Q)
