@@ -42,25 +42,28 @@ inline int max_slices(long N, int d) {
 // queries: eight waves / four waves, slices), whole call, us: 4096 x 4096, 32: 25.9 (8) / 27.2 (8), 28.8 (16); 20000 x 4096, 32: 87 (3) / 94
 // (3), 113 (1); 20000 x 1024, 32: 41.3 (1) / 38.5 (3), 39.2 (2); 2000 x 4096, 24: 19.3 (16) / 17.5 (8), 19.0 (16); 500 x 4096, 32: 17.7 (16)
 // / 14.5 (16), 17.0 (8); 12000 x 512, 32: 22.6 (2) / 22.5 (1), 22.9 (4).
+// The slices are those of the two query blocks: which of a call's groups a query is in, and how many queries stand beside it, must not
+// change the order in which its sums are added. The workgroup's size may follow the group, it does not change that order.
 inline BatchPlan plan_batch(long N, int d, int QP) {
   const int nchunks = (d + kBK - 1) / kBK, most = max_slices(N, d);
-  BatchPlan best{};
-  double best_time = 0.0;
-  for (int waves = 4; waves <= 8; waves += 4) {
-    const long tiles = (N + 16 * waves - 1) / (16 * waves), slots = waves == 8 ? 256 : 512;
+  auto estimate = [&](int waves, int per, int qp) {
+    const long tiles = (N + 16 * waves - 1) / (16 * waves), slots = waves == 8 ? 256 : 512, KS = (nchunks + per - 1) / per, groups = tiles * KS;
+    const double kb = (double)((groups + 255) / 256) * per * (4.0 * waves + 0.0875 * qp), later = (double)((groups + slots - 1) / slots - 1);
+    return kb / (groups < 230 ? 24.0 : 21.5) + 2.5 + later * (waves == 8 ? 5.0 : 1.5) + 0.15 * KS;
+  };
+  int per = 0;
+  double best = 0.0;
+  for (int waves = 4; waves <= 8; waves += 4)
     for (int want = 1; want <= most; ++want) {
-      const int per = (nchunks + want - 1) / want, KS = (nchunks + per - 1) / per;
-      const long groups = tiles * KS;
-      const double kb = (double)((groups + 255) / 256) * per * (4.0 * waves + 0.0875 * QP), later = (double)((groups + slots - 1) / slots - 1);
-      const double time = kb / (groups < 230 ? 24.0 : 21.5) + 2.5 + later * (waves == 8 ? 5.0 : 1.5) + 0.15 * KS;
-      if (best_time == 0.0 || time < best_time) {
-        best_time = time;
-        best = BatchPlan{waves, (int)tiles, KS, per, 0};
+      const int p = (nchunks + want - 1) / want;
+      const double time = estimate(waves, p, 32);
+      if (per == 0 || time < best) {
+        best = time;
+        per = p;
       }
     }
-  }
-  best.Npad = (N + kBlock - 1) / kBlock * kBlock;
-  return best;
+  const int waves = estimate(8, per, QP) < estimate(4, per, QP) ? 8 : 4;
+  return BatchPlan{waves, (int)((N + 16 * waves - 1) / (16 * waves)), (nchunks + per - 1) / per, per, (N + kBlock - 1) / kBlock * kBlock};
 }
 
 // part_dot [KS][Qp][Npad] (row fastest), part_cc [KS][Npad]; Qp = 16 QB.

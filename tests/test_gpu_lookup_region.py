@@ -335,6 +335,20 @@ def test_lookup_batch_scores_do_not_depend_on_k(N, d, Q):
         assert torch.equal(s, sc[:, :k]) and torch.equal(i, idx[:, :k]) and torch.equal(h, hit), k
 
 
+@pytest.mark.parametrize("N,d", [(4096, 4096), (500, 640), (11001, 2060), (19001, 772), (15003, 1300)])
+def test_lookup_batch_scores_do_not_depend_on_the_place(N, d):
+    """The order of additions depends on (N, d) alone: the same prompts score the same bits whichever of a call's groups of 32 they are
+    in and however many stand beside them."""
+    print(f"[case] lookup_batch scores over places N={N} d={d}", flush=True)
+    g = torch.Generator(device=DEV).manual_seed(N + d)
+    cache, queries = torch.randn(N, d, device=DEV, generator=g), torch.randn(8, d, device=DEV, generator=g)
+    want = P.chorus_cache_lookup_batch(cache, queries, 0.05, 8)
+    for Q in (16, 17, 32, 40, 64):  # the last eight of a group of 16, 17, 32, 8 and 32
+        others = torch.randn(Q - 8, d, device=DEV, generator=g)
+        got = P.chorus_cache_lookup_batch(cache, torch.cat((others, queries)), 0.05, 8)
+        assert all(torch.equal(a[Q - 8:], b) for a, b in zip(got, want)), Q
+
+
 def _graph_us(fn, n=20):
     """Microseconds of one call among n in a graph, the best of seven replays."""
     fn()
