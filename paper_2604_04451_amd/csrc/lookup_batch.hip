@@ -12,7 +12,7 @@ namespace {
 
 constexpr int kBlock = 64;   // rows that partial sums are padded to
 constexpr int kBK = 64;      // floats of every row per step (256 bytes: two full cache lines)
-constexpr int kRing = 3;     // steps of cache rows a wave has in LDS or on their way there
+constexpr int kRing = 2;     // steps of cache rows a wave has in LDS or on their way there
 
 struct BatchPlan {
   int waves;             // of a workgroup: 16 rows each
@@ -36,20 +36,23 @@ inline int max_slices(long N, int d) {
 }
 
 // The number of slices and the workgroup's size by an estimate of the two kernels' time in microseconds. What bounds the scan is what a
-// compute unit takes in: 24 KB a microsecond while it is by itself (its loads in flight over the latency of HBM), 21.5 with all
-// 256 (5.5 TB/s); the queries come from the L2 at about three times that. A workgroup of eight waves has a unit to itself (128 KB of LDS), its
-// successor starts cold; of four waves two share one. Each slice's partial sums cost the selection 0.15 us. Measured (rows x d,
-// queries: eight waves / four waves, slices), whole call, us: 4096 x 4096, 32: 25.9 (8) / 27.2 (8), 28.8 (16); 20000 x 4096, 32: 87 (3) / 94
-// (3), 113 (1); 20000 x 1024, 32: 41.3 (1) / 38.5 (3), 39.2 (2); 2000 x 4096, 24: 19.3 (16) / 17.5 (8), 19.0 (16); 500 x 4096, 32: 17.7 (16)
-// / 14.5 (16), 17.0 (8); 12000 x 512, 32: 22.6 (2) / 22.5 (1), 22.9 (4).
+// compute unit takes in, about 25 KB a microsecond of its busiest share, the queries (from the L2) at a tenth of a row's cost; a second round
+// of workgroups starts cold, and each slice's partial sums cost the selection 0.13 us. With up to 16 queries a unit holds two workgroups of eight
+// waves or three of four, else one or two. Where the rows lie a multiple of 4 KB apart and the slices too, all workgroups read the same
+// 256 bytes of every 4 KB at a time, and take a fifth longer (7700 x 4096, 16 queries: four slices 38.3 us, three 32.5). Fitted to 1434 calls: 0.6 % off
+// the best choice. Measured (rows x d, queries: eight waves / four waves, slices), whole call, us: 4096 x 4096, 32: 25.9 (8) / 26.1 (8);
+// 20000 x 4096, 32: 87 (3) / 91 (3); 20000 x 1024, 32: 40.0 (3) / 39.4 (2); 2000 x 4096, 32: 20.1 (16) / 19.6 (8); 500 x 4096, 32: 16.9
+// (16) / 14.9 (16); 12000 x 512, 32: 22.0 (2) / 22.1 (2); 18061 x 472, 16: 23.5 (1) / 22.9 (2).
 // The slices are those of the two query blocks: which of a call's groups a query is in, and how many queries stand beside it, must not
 // change the order in which its sums are added. The workgroup's size may follow the group, it does not change that order.
 inline BatchPlan plan_batch(long N, int d, int QP) {
   const int nchunks = (d + kBK - 1) / kBK, most = max_slices(N, d);
   auto estimate = [&](int waves, int per, int qp) {
-    const long tiles = (N + 16 * waves - 1) / (16 * waves), slots = waves == 8 ? 256 : 512, KS = (nchunks + per - 1) / per, groups = tiles * KS;
-    const double kb = (double)((groups + 255) / 256) * per * (4.0 * waves + 0.0875 * qp), later = (double)((groups + slots - 1) / slots - 1);
-    return kb / (groups < 230 ? 24.0 : 21.5) + 2.5 + later * (waves == 8 ? 5.0 : 1.5) + 0.15 * KS;
+    const long tiles = (N + 16 * waves - 1) / (16 * waves), slots = 256 * (waves == 8 ? (qp == 16 ? 2 : 1) : (qp == 16 ? 3 : 2));
+    const long KS = (nchunks + per - 1) / per, groups = tiles * KS, later = (groups + slots - 1) / slots - 1;
+    const double intake = (double)((groups + 255) / 256) * per * (4.0 * waves + 0.1 * qp) / 25.0;
+    const bool same_place = KS > 1 && per % 16 == 0 && d % 1024 == 0;  // every slice of every row starts in the same 4 KB
+    return intake * (same_place ? 1.2 : 1.0) + (double)later * (waves == 8 ? 5.5 : 1.7) + 0.13 * (double)KS;
   };
   int per = 0;
   double best = 0.0;
@@ -74,7 +77,7 @@ inline BatchPlan plan_batch(long N, int d, int QP) {
 // A direct load writes the 64 lanes' 16-byte pieces side by side (four rows of 256 bytes, or two of a query's 512); the 16-byte piece c
 // of row r lives at position c ^ (r % 16), which spreads the 16 rows of a fragment read over all banks.
 template <int QB, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void lookup_batch_scores_kernel(const float* __restrict__ cache,
+__global__ __launch_bounds__(64 * NW, 4) void lookup_batch_scores_kernel(const float* __restrict__ cache,
                                                                          const float* __restrict__ queries,
                                                                          float* __restrict__ part_dot,
                                                                          float* __restrict__ part_cc, long N, long Npad, int d,
@@ -152,20 +155,19 @@ __global__ __launch_bounds__(64 * NW, 2) void lookup_batch_scores_kernel(const f
   issue_queries(0);
   issue_rows(0, 0);
   if (1 < n) issue_rows(1, 1);
-  if (2 < n) issue_rows(2, 2);
   int slot = 0;
-  // Loads in flight at step c: rows c .. c + 2, and from an even step on the queries of the next two, requested ahead of the rows of
-  // step c + 3. Loads retire in order: at most as many as were requested behind what the step needs may be left.
+  // Loads in flight at step c: rows c and c + 1, and from an even step on the queries of the next two, requested ahead of the rows of
+  // step c + 2. Loads retire in order: at most as many as were requested behind what the step needs may be left.
   for (int c = 0; c < n; ++c) {
-    const bool more = c + kRing <= n;  // rows c + 1 and c + 2 have been requested
+    const bool more = c + kRing <= n;  // rows c + 1 have been requested
     if ((c & 1) == 0) {
       if (more)
-        asm volatile("s_waitcnt vmcnt(8) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
       else
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
       if (c + 2 < n) issue_queries((c >> 1) + 1);  // into the buffer that everyone has left behind the barrier
     } else if (more) {
-      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(8 + LB) : "memory");
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(4 + LB) : "memory");
     } else {
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
