@@ -21,6 +21,11 @@ struct AttnSlices {
   long whole;
   int sliced, slices;
 };
+// The first of a tile's `units` tiles of keys that slice i of `slices` takes (i == slices: their end): i units / slices, in 32 bits for all
+// that chorus_attention_slices admits (65536 slices), where that product would not fit.
+constexpr int first_of_slice(int i, int units, int slices) {
+  return units / slices * i + (int)((uint32_t)(units % slices) * (uint32_t)i / (uint32_t)slices);
+}
 AttnSlices attention_slices(long L, int H, int dh, int cus, const AttnScratch& scratch);
 // 32-bit words at the start of scratch.first that have to be zero when that launch starts
 inline int attention_slices_words(const AttnSlices& p) { return 2 * p.sliced; }

@@ -393,8 +393,8 @@ __global__ __launch_bounds__(512, 2) void attention_pp16_kernel(
     const KeySlices& keys = keys_arg;
     const int at = tile_id - tile_base, t = at / keys.slices, slice = at - t * keys.slices;
     tile_id = tile_base + t;
-    first_kt = slice * keys.units / keys.slices;
-    const long end = (long)((slice + 1) * keys.units / keys.slices) * KTL;
+    first_kt = first_of_slice(slice, keys.units, keys.slices);
+    const long end = (long)first_of_slice(slice + 1, keys.units, keys.slices) * KTL;
     Lk = (Lk < end ? Lk : end) - (long)first_kt * KTL;
   }
   const int head = tile_id / n_qtiles;

@@ -8,6 +8,7 @@
 #include <limits>
 #include <vector>
 
+#include "attention.h"
 #include "chorus.h"
 #include "chorus_ops.h"
 
@@ -137,6 +138,10 @@ static void sizes_and_validation() {
   EXPECT(chorus_attention_slices_plan(13104, 12, 128, 256, 0, 0, &whole, &slices) == CHORUS_OK && slices == 0);
   EXPECT(chorus_attention_slices_plan(13104, 12, 96, 256, 0, 0, &whole, &slices) == CHORUS_E_SHAPE);
   EXPECT(chorus_attention_slices(nullptr, nullptr, nullptr, nullptr, 1, 128, 1, 64, 0, 2, nullptr, 0, nullptr) == CHORUS_E_ARG);
+  for (int units : {5, 41, 103, 591, 46341, 65536, 1 << 24})  // the shares of the keys, up to the most slices that are admitted
+    for (int slices : {2, 3, 4, 41, 46341, 65536})
+      for (int i = 0; slices <= units && i <= slices; i += 1 + slices / 1000)
+        EXPECT(chorus::first_of_slice(i, units, slices) == (long)i * units / slices);
   EXPECT(chorus_attention_variant(13104, 64, 64, 12, 128, 0, 256) == 3);
   EXPECT(chorus_attention((const uint16_t*)p16, (const uint16_t*)p16, (const uint16_t*)p16, (uint16_t*)p16, nullptr, 8, 8, 64, 64, 2, 96, 0, nullptr) == CHORUS_E_SHAPE);
   EXPECT(chorus_attention((const uint16_t*)p16, (const uint16_t*)p16, (const uint16_t*)p16, (uint16_t*)p16, nullptr, 8, 8, 64, 64, 2, 64, 2, nullptr) == CHORUS_E_ARG);
