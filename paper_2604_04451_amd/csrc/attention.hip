@@ -305,7 +305,7 @@ struct KeySlices {
 struct WholeKeys {
   static constexpr bool kSliced = false, kRun = false;
 };
-// A workgroup a unit that walks over its share of `tiles` tiles. The loop over a tile's keys runs on into the next tile's: the next queries
+// A workgroup that walks over its share of `tiles` tiles. The loop over a tile's keys runs on into the next tile's: the next queries
 // are requested in the last softmax phase, when this tile's are no longer needed, the next first keys in their usual place, and the finished
 // tile leaves in the next first softmax phase, under the other group's MFMAs. A workgroup that ends instead leaves its unit to one
 // that starts cold: about 9 us a tile.
@@ -934,23 +934,37 @@ int32_t launch_attn_pp16_tiles(const uint16_t* Q, const uint16_t* K, const uint1
   return CHORUS_OK;
 }
 
-// More tiles than CUs: workgroups that stay and walk over the tiles (TileRun), over 512 keys and more, where the walk fits the registers
-// (not plain queries with factors). A tile of the text cross-attention, four tiles of keys, takes 15 us so, 22 in a workgroup of its own
-// (32760 x 512, 12 heads 130 -> 106 us, 75600 x 512, 40 heads 1006 -> 820); self-attention gains its start and end (32760 tokens 4655 ->
-// 4640). Its offsets into the values have 32 bits.
+// More tiles than CUs: workgroups that stay and walk over tiles (TileRun), over 512 to 2048 keys, where the walk fits the registers
+// (not plain queries with factors). A tile of the text cross-attention, four tiles of keys, takes 15 us so, 22 in a workgroup of its own.
+// A share is four tiles of queries at most, and 32 tiles of keys in all: what it costs a stream whose neighbour holds a few units is
+// the wait for the last share, which no other unit can take over. us alone / with eight units held by another stream: 32760 x 512, 12 heads
+// without a walk 152 / 179, one share of six tiles a unit 127 / 218, two of three 131 / 178; 75600 x 512, 40 heads 1002 / 1282, one share of
+// 47 866 / 1387, of eight 883 / 1063, of four 905 / 1102, of two 953 / 1174; 32000 x 1536, 12 heads 264 without, 240 with. Over long
+// keys a walk gains nothing that shows: 13104 tokens, 12 heads 844 / 1151 without, 846 / 1285 with; 32760 tokens 4636 / 5600 and 4620 / 5430.
+// Its offsets into the values have 32 bits.
+constexpr int kMostTiles = 4, kMostKeyTiles = 32;
 template <bool PRE, int KIND> constexpr bool kWalks = KIND <= 2 && (PRE || KIND != 2);
+// how many tiles a workgroup walks over on average at most; 1: no walk
 template <bool PRE, int KIND>
-bool walks(long tiles, long LkPad, int cus) { return kWalks<PRE, KIND> && tiles > cus && cus % 8 == 0 && LkPad <= 1 << 23; }
+int walk_share(long tiles, long Lk, long LkPad, int cus) {
+  const long most = kMostKeyTiles / ((Lk + 127) / 128);
+  if (!kWalks<PRE, KIND> || tiles <= cus || cus % 8 || LkPad > 1 << 23 || most < 2) return 1;
+  return (int)(most < kMostTiles ? most : kMostTiles);
+}
 
 // the first `tiles` tiles of 256 rows
 template <int DH, bool PRE, int KIND>
 int32_t launch_attn_full(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* cs, long Lq, long Lk,
                          long LqPad, long LkPad, int H, long tiles, int cus, hipStream_t s) {
   const long nqt = (Lq + 255) / 256;
-  if constexpr (kWalks<PRE, KIND>)
-    if (walks<PRE, KIND>(tiles, LkPad, cus))
-      return launch_attn_pp16_tiles<DH, PRE, 2, KIND, TileRun>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, nqt, 0, cus, s,
-                                                               TileRun{Q, K, Vt, O, Lq, LqPad, LkPad, H, (int)nqt, (int)tiles, cus / 8});
+  if constexpr (kWalks<PRE, KIND>) {
+    const int share = walk_share<PRE, KIND>(tiles, Lk, LkPad, cus);
+    if (share > 1) {
+      const long rounds = (tiles + cus - 1) / cus, groups = cus * ((rounds + share - 1) / share);
+      return launch_attn_pp16_tiles<DH, PRE, 2, KIND, TileRun>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, nqt, 0, groups, s,
+                                                               TileRun{Q, K, Vt, O, Lq, LqPad, LkPad, H, (int)nqt, (int)tiles, (int)(groups / 8)});
+    }
+  }
   return launch_attn_pp16_tiles<DH, PRE, 2, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, nqt, 0, tiles, s);
 }
 
@@ -975,7 +989,7 @@ int32_t launch_attn_pp16_kind(const uint16_t* Q, const uint16_t* K, const uint16
   if (2 * tiles <= cus)
     return launch_attn_pp16_tiles<DH, PRE, 1, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, 2 * nqt, 0, 2 * tiles, s);
   const long tail = cus > 0 ? tiles % cus : 0;
-  const bool halves = tiles > cus && tail > 0 && 2 * tail <= cus && (!walks<PRE, KIND>(tiles, LkPad, cus) || (Lk + 127) / 128 >= kRunKeys);
+  const bool halves = tiles > cus && tail > 0 && 2 * tail <= cus && (walk_share<PRE, KIND>(tiles, Lk, LkPad, cus) == 1 || (Lk + 127) / 128 >= kRunKeys);
   CHK_STATUS((launch_attn_full<DH, PRE, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, halves ? tiles - tail : tiles, cus, s)));
   if (!halves) return CHORUS_OK;
   return launch_attn_pp16_tiles<DH, PRE, 1, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, 2 * nqt, 2 * (tiles - tail), 2 * tail, s);

@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
     (257, 64, 200, 512), (260, 128, 256, 513),   # a tile a head, just over one round
     (40, 64, 1700, 640), (37, 128, 1800, 1000),  # 280 and 296 tiles, five and eight tiles of keys: half tiles behind the walk
     (40, 128, 1700, 512), (66, 64, 2050, 520),   # four and five tiles of keys, 280 and 594 tiles
+    (47, 64, 7000, 512), (60, 64, 5900, 513),    # 1316 and 1440 tiles: two shares a unit
 ])
 @pytest.mark.parametrize("variant", [5, 6])
 @pytest.mark.parametrize("factor", [False, True])
