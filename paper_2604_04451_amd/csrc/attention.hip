@@ -968,16 +968,14 @@ int32_t launch_attn_full(const uint16_t* Q, const uint16_t* K, const uint16_t* V
   return launch_attn_pp16_tiles<DH, PRE, 2, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, nqt, 0, tiles, s);
 }
 
-// Keys from which on a last round of few tiles is worth a launch of its own: with fewer the walk's third tile costs less than
-// another start (13104 x 512 with factors 64.4 us in a launch and one of half tiles, 57 in one; 2000 x 600, 40 heads 42.4 and 43.9).
-constexpr int kRunKeys = 5;
-
 // Launches of at most half as many 256-row tiles as CUs run as workgroups of 128 rows throughout (1200 tokens, 12 heads:
 // 36.2 -> 24.8 us). Else 256 query rows per workgroup. One workgroup fits a CU, so a launch runs in rounds of as many workgroups as the device
 // has CUs. When the last round would be at most half full, its tiles run as workgroups of 128 rows instead (one block
 // of 16 rows per wave: the same K / V stream for half the arithmetic, 0.63-0.67 of a full workgroup's time), twice as
-// many of them, in a second launch behind the first: the partly filled round then takes two thirds of a full one. (With scratch, as a
-// block has it, and long keys the last round runs in slices instead: attention_slices.)
+// many of them, in a second launch behind the first: the partly filled round then takes two thirds of a full one. Also behind a walk,
+// whose next tile costs less than a workgroup's: 512 keys, 12 heads, the tail in the walk / in half tiles, us: 280 tiles (40 heads) 41.7 /
+// 39.6, 320 (40 heads) 38.1 / 36.8, 624 54.3 / 54.1, with factors 56.7 / 56.9; 1536 keys, 624 tiles 120 / 115. (With scratch, as a block
+// has it, and long keys the last round runs in slices instead: attention_slices.)
 template <int DH, bool PRE, int KIND>
 int32_t launch_attn_pp16_kind(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O, const float* cs, long Lq,
                               long Lk, long LqPad, long LkPad, int H, hipStream_t s) {
@@ -989,7 +987,7 @@ int32_t launch_attn_pp16_kind(const uint16_t* Q, const uint16_t* K, const uint16
   if (2 * tiles <= cus)
     return launch_attn_pp16_tiles<DH, PRE, 1, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, 2 * nqt, 0, 2 * tiles, s);
   const long tail = cus > 0 ? tiles % cus : 0;
-  const bool halves = tiles > cus && tail > 0 && 2 * tail <= cus && (walk_share<PRE, KIND>(tiles, Lk, LkPad, cus) == 1 || (Lk + 127) / 128 >= kRunKeys);
+  const bool halves = tiles > cus && tail > 0 && 2 * tail <= cus;
   CHK_STATUS((launch_attn_full<DH, PRE, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, halves ? tiles - tail : tiles, cus, s)));
   if (!halves) return CHORUS_OK;
   return launch_attn_pp16_tiles<DH, PRE, 1, KIND>(Q, K, Vt, O, cs, Lq, Lk, LqPad, LkPad, H, 2 * nqt, 2 * (tiles - tail), 2 * tail, s);

@@ -16,6 +16,7 @@ pytestmark = pytest.mark.gpu
     (257, 64, 200, 512), (260, 128, 256, 513),   # a tile a head, just over one round
     (40, 64, 1700, 640), (37, 128, 1800, 1000),  # 280 and 296 tiles, five and eight tiles of keys: half tiles behind the walk
     (40, 128, 1700, 512), (66, 64, 2050, 520),   # four and five tiles of keys, 280 and 594 tiles
+    (40, 128, 3300, 512), (38, 128, 3000, 512),  # 520 and 456 tiles of four tiles of keys
     (47, 64, 7000, 512), (60, 64, 5900, 513),    # 1316 and 1440 tiles: two shares a unit
 ])
 @pytest.mark.parametrize("variant", [5, 6])
@@ -27,7 +28,8 @@ def test_attention_walk(H, dh, Lq, Lk, variant, factor):
 
 
 @pytest.mark.parametrize("variant", [0, 5, 6])
-@pytest.mark.parametrize("H,dh,Lq,Lk", [(40, 128, 1700, 512), (12, 128, 10000, 640), (66, 64, 2050, 520)])  # 280, 480 and 594 tiles
+@pytest.mark.parametrize("H,dh,Lq,Lk", [(40, 128, 1700, 512), (40, 128, 3300, 512), (12, 128, 10000, 640),
+                                         (66, 64, 2050, 520)])  # 280, 520, 480 and 594 tiles
 def test_attention_walk_low_logits(H, dh, Lq, Lk, variant):
     """A shift of all logits of a row changes nothing, in whichever of a workgroup's tiles the row is: a third of the rows has logits about
     -150 (in natural units, far below what exp2 against a reference of 0 can hold), a third about -85 (at its edge), a third about 0."""
