@@ -1,8 +1,12 @@
 """GPU parity of the gated residual in chained slices of K (each slice adds to the residual behind the one in front of it) and of the
 block's products that take it."""
+import numpy as np
 import pytest
 import torch
 
+import synth
+from gpu_util import check, dev_bf16, dev_f32, errs
+from oracle import chorus_oracle as O
 from paper_2604_04451_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -143,3 +147,43 @@ def test_block_with_chained_products(D, H, F, Ls):
     f = torch.nn.functional.gelu(h @ t["w_1"].double().T + t["b_1"].double(), approximate="tanh") @ t["w_2"].double().T + t["b_2"].double()
     delta = m[5] * f
     assert float(((y.double() - xd) - delta).norm() / delta.norm()) < 5 * 2.0 ** -9 / 3 ** 0.5
+
+
+# (D, H, F, Ls): what the O and cross-O products and self-attention do, by the plan functions: (rows in front, kernel, slices, chained) and
+# (whole tiles, slices of the others)
+BOTH = {(2048, 16, 2048, 1000): ((0, 5, 2, True), (0, 0)), (5120, 40, 2048, 3266): ((3072, 5, 3, True), (512, 4)),
+        (256, 4, 512, 17000): ((0, 0, 0, False), (256, 4))}
+
+
+@pytest.mark.parametrize("D,H,F,Ls", list(BOTH))
+def test_block_with_chains_and_key_slices(D, H, F, Ls):
+    """Blocks whose O and cross-O products are chained, whose self-attention runs its last tiles in key slices, and that do both on scratch
+    that stands side by side, on a workspace that starts anywhere: sampled rows against the oracle, gates near 1 and biases, so that
+    each branch weighs in the result. Tolerances as for the full-size blocks."""
+    chain, slices = BOTH[D, H, F, Ls]
+    plan = B.chorus_gemm_bf16_chain_plan(Ls, D, D)
+    assert (plan == chain if chain[3] else not plan[3]) and B.chorus_attention_slices_plan(Ls, H, D // H, 256, 2 * Ls * D - 1024, 6 * Ls * D) == slices
+    print(f"[case] block chains and key slices D={D} Ls={Ls}", flush=True)
+    bs = synth.BlockShape("chains", D, H, D // H, F, 40, 64, (1, 136, 128))
+    w, inp = synth.block_weights(bs, 1), synth.block_inputs(bs, 1, L=Ls)
+    w["mod_table"][[2, 5]] += 0.8
+    for n in ("b_qkv", "b_o", "b_cq", "b_ckv", "b_co", "b_1", "b_2"):
+        w[n] = synth.normal(2, n, w[n].shape, 0.1)
+    shape = B.make_block_shape(D, H, D // H, F, 40, bs.grid)
+    idx = np.sort(synth.stream(3, "idx").permutation(bs.L)[:Ls])
+    x = dev_f32(inp["x"])
+    ws = torch.full((B.chorus_dit_block_workspace_bytes(shape, Ls),), 255, dtype=torch.uint8, device="cuda")
+    B.chorus_dit_block_step(shape, B.upload_block_weights(w), x, Ls, torch.from_numpy(idx.astype(np.int32)).cuda(), dev_bf16(inp["text_ctx"]),
+                            dev_f32(inp["t_mod"]), None, 0.75, ws)
+    got = x.cpu().numpy()
+    assert np.isfinite(got).all()
+    at = synth.stream(4, "rows").permutation(Ls)
+    rows = np.unique(np.concatenate([at[:24], at[at >= Ls - 170][:12], [0, Ls - 1]]))
+    ref, branch = O.dit_block(inp["x"], w, bs, inp["text_ctx"], inp["t_mod"], token_idx=idx, gamma_o=0.75, rows=rows, return_branches=True)
+    change = ref - inp["x"][rows]
+    for part in (branch["g1"] * branch["y_sa"], 0.75 * branch["y_ca"], branch["g2"] * branch["y_ffn"]):
+        assert np.linalg.norm(part) > 0.05 * np.linalg.norm(change)
+    check(got[rows], ref, "block chains and key slices x")
+    a, r = errs(got[rows] - inp["x"][rows], change)
+    print(f"[parity] block chains and key slices delta: max_abs={a:.3e} rel_l2={r:.3e}", flush=True)
+    assert r <= 2e-2
