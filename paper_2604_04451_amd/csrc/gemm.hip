@@ -263,7 +263,8 @@ struct Alone {  // no second product
 // whose number leaves the same rest by `groups` (8: they share an XCD and its L2) take tickets of one counter for a range of tiles of their
 // own, all of its tiles of the first slice first. So a slice only ever waits for a lower ticket of its group, whose workgroup
 // has taken it and is running; that one waits for a still lower ticket or for nothing: every wait ends, whatever else runs on the GPU.
-// By workgroup number 3271 x 1536 x 8960 took 84 to 92 us, by ticket 89 to 93; 4500 rows 107 and 107, 2000 70 and 70, 1100 46 and 46.
+// The ticket is a round trip to memory ahead of the first load, about 1 us (by workgroup number / by ticket, us: 3271 x 1536 x 8960 84.4 /
+// 86.8, 2000 59.1 / 59.5, 1100 39.3 / 40.7, 300 21.5 / 22.6, 960 x 5120 x 5120 60.3 / 61.2, 200 x 2048 x 4096 13.8 / 15.2, operands warm).
 // A word a tile, zero at the start: the slices that have been added in its low four bits and, in the word of a group's first
 // tile, the tickets taken in the others.
 // Slices of equal length would all end together and then wait for each other's updates: each is a few steps longer than the one in
@@ -327,7 +328,7 @@ __global__ __launch_bounds__(256, 1) void gemm_w16_kernel(const uint16_t* __rest
     const int ticket = __builtin_amdgcn_readfirstlane((int)mine[0]);
     slice = ticket / of_group;
     tile = ticket - slice * of_group;
-    tile = twin.groups == 1 ? xcd_remap(tile, twin.tiles) : first_tile + tile;
+    tile += first_tile;
   } else {
     tile = xcd_remap(block, ntiles);
   }
@@ -784,9 +785,13 @@ GemmPlan plan_gemm(long m, int N, int K, int epi, const GemmParts& parts) {
 
 constexpr int kHalvesDeep = 7, kHalves64 = 9;
 
-// The groups of a chain: an XCD each, or all of the chip in one where an XCD would get more workgroups than it has units that way (three slices
-// of 81 to 85 tiles).
-int chain_groups(int tiles, int slices) { return (tiles + 7) / 8 * 8 * slices <= kChainTiles ? 8 : 1; }
+// The groups of a chain: an XCD each, or two, four or all of them where their units would be fewer than their workgroups that way (three slices
+// of 81 to 84 tiles: four groups; 880 x 1536 x 8960, 84 tiles: in one group a block 200.3 us, so 196.8).
+int chain_groups(int tiles, int slices) {
+  for (int groups = 8; groups > 1; groups /= 2)
+    if ((tiles + groups - 1) / groups * groups * slices <= kChainTiles) return groups;
+  return 1;
+}
 
 template <int WBM, int WBN, int C>
 int32_t launch_chain(const uint16_t* A, const uint16_t* W, long M, int N, int K, const EpiArgs& ep, int slices, uint32_t* count,

@@ -37,9 +37,11 @@ def test_chain(kernel, steps, slices):
             assert torch.equal(buf[:M], want) and bool((buf[M:] == 7.0).all())
 
 
-def test_chain_in_one_group():
-    """84 tiles in three slices: more workgroups than units on an XCD if each took its tiles' slices, so one counter for all."""
-    M, N, K = 64 * 12, 64 * 7, 64 * 48
+@pytest.mark.parametrize("tm,tn", [(12, 7), (27, 3), (5, 17), (17, 5)])
+def test_chain_in_one_group(tm, tn):
+    """81, 84 and 85 tiles in three slices: more workgroups than units on an XCD if each took its tiles' slices, so one counter for two XCDs
+    and for all."""
+    M, N, K = 64 * tm - 1, 64 * tn, 64 * 48
     A, W, out = _ints((M, K), 1), _ints((N, K), 2), _ints((M, N), 4)
     got = out.clone()
     B.chorus_gemm_bf16_chain(A.bfloat16(), W.bfloat16(), got, 1, 3, scale=0.5)
