@@ -34,9 +34,9 @@ HBM_PEAK_GBS = 8000.0
 # launches at 13104 tokens and stage-3 launches at 32760 tokens, weighted 30:60). Hardware
 # counters cannot be read inside this process: the figure is the one the two rocprofv3 --pmc
 # runs (FETCH_SIZE, then WRITE_SIZE) of this same command gave when the summary named below
-# was written (FETCH_SIZE scaled by 1.992, the factor a plain 8.39 MB copy kernel of the same
+# was written (FETCH_SIZE scaled by 2.000, the factor a plain copy kernel of 268 MB in the same
 # run shows; WRITE_SIZE by 1.000); it is reported for that exact workload only, with its source.
-SELF_ATTN_TRAFFIC_BYTES_DEFAULT = 7.75e8
+SELF_ATTN_TRAFFIC_BYTES_DEFAULT = 7.85e8
 SELF_ATTN_TRAFFIC_SOURCE = "profiles/bench_wan1p3b_480p_pmc_traffic.txt"
 
 
@@ -226,7 +226,7 @@ def main():
                      # Q, K, V read once and O written once per launch, averaged over the request's launches
                      # (one per block at the stage-2 token count, two per block at the full count)
                      "algorithmic_bytes": (4 * 2.0 * Ls * D + 2 * 4 * 2.0 * L * D) / 3.0,
-                     "kernel": "attention_pp16_kernel<128,true,2,0> (self-attention; at 13104 tokens its last, partly filled round runs as attention_pp16_kernel<128,true,1,0>)", "launches": attn_n},
+                     "kernel": "attention_pp16_kernel<128,true,2,0,WholeKeys> (self-attention; at 13104 tokens its last, partly filled round runs as attention_pp16_kernel<128,true,2,0,KeySlices>)", "launches": attn_n},
     }
     # what a bare MFMA loop sustains on this device right now (the part is power-managed: the rate depends on the
     # operand values and on the LDS reads and exponentials that accompany the MFMAs); context for roofline.frac
