@@ -139,7 +139,8 @@ int32_t chorus_v_transpose(const uint16_t* in, int64_t ld, uint16_t* out, int64_
 #define CHORUS_ATTENTION_Q_PRESCALE(dh) (1.4426950408889634f / sqrtf((float)(dh)))
 #define CHORUS_ATTENTION_LONG_KEYS(Lk, LkPad) ((LkPad) % 128 == 0 && (Lk) >= 512)
 /* What variant 0 takes on a GPU of `cus` compute units (3, 5 or 7; factor != 0: with col_scale): 7 for at most 128 keys, heads of 64
- * and at most half as many tiles of 256 queries as units, 5 for CHORUS_ATTENTION_LONG_KEYS, and on 65 to 511 keys padded to 128 where it is the faster. Host only. CHORUS_E_ARG,
+ * and at most half as many tiles of 256 queries as units, 5 for CHORUS_ATTENTION_LONG_KEYS, and on 65 to 511 keys padded to 128 where it
+ * is the faster. Host only. CHORUS_E_ARG,
  * CHORUS_E_SHAPE as chorus_attention. */
 int32_t chorus_attention_variant(int64_t Lq, int64_t Lk, int64_t LkPad, int32_t H, int32_t dh, int32_t factor, int32_t cus);
 int32_t chorus_attention(const uint16_t* Q, const uint16_t* K, const uint16_t* Vt, uint16_t* O,

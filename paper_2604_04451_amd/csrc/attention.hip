@@ -308,7 +308,7 @@ struct WholeKeys {
 // A workgroup that walks over its share of `tiles` tiles. The loop over a tile's keys runs on into the next tile's: the next queries
 // are requested in the last softmax phase, when this tile's are no longer needed, the next first keys in their usual place, and the finished
 // tile leaves in the next first softmax phase, under the other group's MFMAs. A workgroup that ends instead leaves its unit to one
-// that starts cold: about 9 us a tile.
+// that starts cold: 3 to 4 us a tile (32760 x 512, 12 heads, six tiles a unit 152 -> 127 us; 75600 x 512, 40 heads, 47 tiles 1002 -> 866).
 struct TileRun {
   const uint16_t *Q, *K, *Vt;
   uint16_t* O;
@@ -935,7 +935,7 @@ int32_t launch_attn_pp16_tiles(const uint16_t* Q, const uint16_t* K, const uint1
 }
 
 // More tiles than CUs: workgroups that stay and walk over tiles (TileRun), over 512 to 2048 keys, where the walk fits the registers
-// (not plain queries with factors). A tile of the text cross-attention, four tiles of keys, takes 15 us so, 22 in a workgroup of its own.
+// (not plain queries with factors).
 // A share is four tiles of queries at most, and 32 tiles of keys in all: what it costs a stream whose neighbour holds a few units is
 // the wait for the last share, which no other unit can take over. us alone / with eight units held by another stream: 32760 x 512, 12 heads
 // without a walk 152 / 179, one share of six tiles a unit 127 / 218, two of three 131 / 178; 75600 x 512, 40 heads 1002 / 1282, one share of
@@ -1008,8 +1008,9 @@ int32_t launch_attn_pp16(const uint16_t* Q, const uint16_t* K, const uint16_t* V
 // Few keys (at most 128) for few queries, heads of 64: nothing to stream, so nothing to stage. A wave takes 16 queries of one head and all
 // keys: it requests its queries, the keys, the values and the factors at once, as MFMA operands straight from memory, and is through after
 // one latency, where the kernels above go through LDS, barriers and two phases (128 queries, 4 heads: 16 keys with factors 7.9 us
-// behind 3.0 of normalisation, here 6.9 with it; 128 keys 6.4 in either). What is left is the wave's own instructions. Operand layout, logits, sums and their order are those of attention_pp16_kernel over one tile of
-// keys on plain queries, so its bits too. Every wave reads all keys: with many queries the L1s would be the bound.
+// behind 3.0 of normalisation, here 6.9 with it; 128 keys 6.4 in either). What is left is the wave's own instructions. Operand layout,
+// logits, sums and their order are those of attention_pp16_kernel over one tile of keys on plain queries, so its bits too. Every wave reads
+// all keys: with many queries the L1s would be the bound.
 // NORM: the queries come as their projection's rows [Lq, H * 64]: the wave normalises its 16 rows itself, as qk_norm_rope_kernel does it (the
 // same order of additions), H * 64 <= 512.
 // ---------------------------------------------------------------------------
@@ -1246,7 +1247,8 @@ int device_cus() {
 // slices) 853 / 786; 8100 (128, two) 329 / 311; 5632 (8, four; 44 key tiles) 216 / 190, in two slices 208; 6000 (32, four) 230 / 202; 40
 // heads: 7168 tokens (96, two) 802 / 793, 3300 (8, four; 26 key tiles) 221 / 212, 2000 (64, three; 16) 91 / 90; 4 heads of 64, 3584 tokens
 // (56, four; 28) 30.6 / 28. Up to two thirds of the chip, three slices a tile in two rounds: 8840 tokens, 12 heads (164; 70 key tiles)
-// whole tiles 410 / slices 392, 3271 (156; 26) 75 / 84. Slower: 2560 tokens, 12 heads (120, two; 20 key tiles) 44 / 43 to 45, 1792, 40 heads (24, four; 14) 82 / 84.
+// whole tiles 410 / slices 392, 3271 (156; 26) 75 / 84. Slower: 2560 tokens, 12 heads (120, two; 20 key tiles) 44 / 43 to 45, 1792, 40 heads
+// (24, four; 14) 82 / 84.
 AttnSlices attention_slices(long L, int H, int dh, int cus, const AttnScratch& scratch) {
   const AttnSlices none{0, 0, 0};
   const long tiles = (L + 255) / 256 * H, units = (L + 127) / 128;

@@ -723,7 +723,7 @@ struct GemmPlan {
 // three slices), 4500 115 / 107 (two), 2352 72 / 71 (128 x 256, two), 2000 78 / 70, 1350 68 / 56 (three), 1100 50 / 46 (128 x 128, two), 480 31
 // / 34; 1200 x 5120 x 13824 179 / 152 (256 x 256, two), 960 173 / 125 (three), 544 101 / 96 (128 x 256, two).
 // 300 x 5120 x 5120 45 / 30 (128 x 128, two), 200 38 / 28 (three), 960 72 / 64 (256 x 256, three). With fewer steps a slice the updates are the
-// larger part: 1200 x 1536 x 1536 14 to 16.5 / 17, 4500 28 / 39.
+// larger part: 1200 x 1536 x 1536 14 to 16.5 / 17, 4500 28 / 39. (With slices by workgroup number; a ticket adds about 1.)
 constexpr int kMaxChain = 4, kChainTiles = 256, kChainSteps = 16;
 constexpr int chain_update(int tile) { return tile == kTile256 || tile == kTileWide ? 5 : 8; }
 int chain_stagger(int tile, int K, int slices) {
@@ -897,8 +897,8 @@ GemmCut plan_rows(long M, int N, int K, int epi, const GemmParts& parts) {
 
 // The tile on which two products with bf16 outputs and the same K run in one launch, kTiles: each in a launch of its own,
 // whichever is the fastest by the estimates for the tiles of both together. 64 x 64 tiles up to one round of two workgroups a
-// unit, the deep 128 x 128 ones up to two rounds of one; beyond that the larger product's own best tile is another one. Measured (tokens and text tokens, QKV and the text's keys and values; 64 x 64 / deep /
-// apart, us): width 256, 128 and 16 4.8 / 5.7 / 7.8; width 1536, 100 and 16 9.9 / 18.2 / 17.9, 480 and 512 29.2 / 19.9 / 33.7, 800
+// unit, the deep 128 x 128 ones up to two rounds of one; beyond that the larger product's own best tile is another one. Measured
+// (tokens and text tokens, QKV and the text's keys and values; 64 x 64 / deep / apart, us): width 256, 128 and 16 4.8 / 5.7 / 7.8; width 1536, 100 and 16 9.9 / 18.2 / 17.9, 480 and 512 29.2 / 19.9 / 33.7, 800
 // and 16 30.2 / 28.1 / 24.5, 900 and 512 40.9 / 33.3 / 39.4; width 5120, 100 and 512 160 / 113 / 129, 200 and 16 99 / 89 / 77, 200 and 512
 // 179 / 152 / 129. Over 91 such pairs the choice is 1.2 % slower than the best (geometric mean), and never slower than apart.
 int plan_two(long M, int N, long M2, int N2, int K) {
