@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
     (40, 128, 1700, 512), (66, 64, 2050, 520),   # four and five tiles of keys, 280 and 594 tiles
     (40, 128, 3300, 512), (38, 128, 3000, 512),  # 520 and 456 tiles of four tiles of keys
     (47, 64, 7000, 512), (60, 64, 5900, 513),    # 1316 and 1440 tiles: two shares a unit
+    (24, 64, 5600, 2048), (24, 64, 5600, 2049),  # the longest keys that are walked, two tiles a share, and one more
 ])
 @pytest.mark.parametrize("variant", [5, 6])
 @pytest.mark.parametrize("factor", [False, True])
